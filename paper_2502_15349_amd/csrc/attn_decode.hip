@@ -1,14 +1,22 @@
-// Decoding shapes with split keys (paper Table 2, the decoding row: one query row per head against thousands of
-// keys; Section 4.1, online row-norm interface: the state of two key blocks is combined by the rule of the online
-// softmax).  One query row has no use for matrix units or for a 256-row tile: the work is reading K and V once, so
-// the kernel is a stream.  A workgroup owns one (batch, q head, key range) and its four wavefronts take the range's
-// keys four at a time; 16 lanes share a key, each holding D / 16 consecutive elements of its row (one 16-byte load
-// per lane for 128 elements, an 8-byte one more for 192), so every load instruction of a wavefront reads four whole
-// rows, contiguous in memory.  The dot product is D / 16 multiply-adds and four data-parallel-primitive adds inside
-// the row of 16 lanes; every group of 16 lanes keeps an online softmax state of its own (reference, sum, D_v / 16
-// output columns), and the 16 states of a workgroup are combined through LDS at the end into one normalised partial
-// row and its log-sum-exp, which attn_merge_kernel combines over the key ranges.  Loads run one block of
-// kDecodeDepth steps ahead of the arithmetic (registers only, no LDS tiles, no barrier inside the loop).
+// Decoding shapes (paper Table 2, the decoding row: one query row per head against thousands of keys; Section 4.1,
+// online row-norm interface: the state of two key blocks is combined by the rule of the online softmax).  One query row
+// has no use for a 256-row tile: the work is reading K and V once, so the kernel is a stream.  A workgroup owns one
+// (batch, k/v head, key range) and up to G of the q heads that share it, and its four wavefronts take the range's keys
+// four at a time; 16 lanes share a key, each holding D / 16 consecutive elements of its row (one 16-byte load per lane
+// for 128 elements, an 8-byte one more for 192), so every load instruction of a wavefront reads four whole rows,
+// contiguous in memory.  The dot product is D / 16 multiply-adds and four data-parallel-primitive adds inside the row of
+// 16 lanes; every group of 16 lanes keeps an online softmax state of its own per q head (reference, sum, D_v / 16 output
+// columns), and the 16 states of a workgroup are combined at the end into one normalised row: the result, where the keys
+// are one range (DIRECT), or else a partial row and its log-sum-exp, which attn_merge_kernel combines over the key
+// ranges.  Loads run one block of kDecodeDepth steps ahead of the arithmetic (registers only, no LDS tiles, no barrier
+// inside the loop).
+//
+// What bounds it: HBM with one q head per k/v head (32 x 16 heads x 4096 keys, 192/128: 6.1 TB/s); with more, the vector
+// arithmetic per key and head, about 30 instructions for 16 lanes (64 x 32/8 heads x 1000 keys, 128/128: 4.8 TB/s).
+// Scoring the heads of a block of keys first and rescaling once per block saves a quarter of them and costs the registers
+// of a second workgroup per compute unit (16 x 32/8 x 5003: 88 -> 99 us).  Keys in one range were the 256-row
+// attention kernel's before, one workgroup per q head: 16 x 32/8 heads x 5003 keys 144 -> 87 us, 64 x 32/8 x 1000
+// 154 -> 54 us, 1 x 16 x 8192 (192/128) 127 -> 93 us, 1 x 12 x 300 (64/64) 8.1 -> 5.0 us.
 #include <hip/hip_runtime.h>
 
 #include "attn_decode.hpp"
@@ -58,28 +66,43 @@ __device__ __forceinline__ float row16_sum(float x) {
 
 constexpr float kNone = -1e30f;  // "no key yet": finite, so that differences of references stay finite
 
-template <int DQK, int DV>
+// G: q heads of the k/v head that one workgroup serves, all from one pass over the keys.
+template <int DQK, int DV, int G, bool DIRECT>
 __global__ __launch_bounds__(256) void attn_decode_kernel(const DecodeParams p) {
   constexpr int NK = DQK / 16, NV = DV / 16;
-  __shared__ float red[16][DV + 2];
+  // one q head: the states of all rows of 16 lanes meet in LDS; more: one per wavefront, folded in registers before
+  constexpr int NS = G == 1 ? 16 : 4;
+  __shared__ float red[NS][G][DV + 2];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, sub = lane & 15;
-  const int c = blockIdx.x % p.n_splits;                 // key range
-  const int64_t row = blockIdx.x / p.n_splits;           // (batch, q head)
-  const int b = (int)(row / p.H_q), hq = (int)(row % p.H_q), hk = hq / p.g;
+  // (key range, batch, k/v head) fastest: the workgroups of one k/v head that serve different q heads are a multiple
+  // of 8 apart where that number is one, and then run on the same XCD
+  // Sets of G q heads slowest: the workgroups that read the same keys for different sets are `units` apart, and run on
+  // the same XCD where that is a multiple of 8 (they take the keys from its L2 then; one q head per workgroup, 32 q
+  // on 8 k/v heads x 4096 keys in 6 ranges: 19.1 us with the sets fastest, 16.5 so).
+  const int set = blockIdx.x / p.units, unit = blockIdx.x % p.units, head = unit / p.n_splits;
+  const int c = unit % p.n_splits;
+  const int b = head / p.H_kv, hk = head % p.H_kv;  // batch entry, k/v head
+  const int h0 = hk * p.g + set * G, n_heads = G == 1 ? 1 : min(G, p.g - set * G);
   const int j_begin = c * p.split_keys, j_end = min(p.L_k, j_begin + p.split_keys);
   const __bf16* Kh = p.K + b * p.ks[0] + hk * p.ks[1];
   const __bf16* Vh = p.V + b * p.vs[0] + hk * p.vs[1];
 
-  // the query row, in log2 units: scale * log2(e) * q, fp32
-  float q[NK];
-  {
-    const RowPiece<NK> qp = load_piece<NK>(p.Q + b * p.qs[0] + hq * p.qs[1], sub);
+  // the query rows, in log2 units: scale * log2(e) * q, fp32 (a head past the group repeats the last one)
+  float q[G][NK];
 #pragma unroll
-    for (int e = 0; e < NK; ++e) q[e] = elem(qp, e) * p.c;
+  for (int h = 0; h < G; ++h) {
+    const RowPiece<NK> qp = load_piece<NK>(p.Q + b * p.qs[0] + (h0 + min(h, n_heads - 1)) * p.qs[1], sub);
+#pragma unroll
+    for (int e = 0; e < NK; ++e) q[h][e] = elem(qp, e) * p.c;
   }
-  float m = kNone, l = 0.f, acc[NV];
+  float m[G], l[G], acc[G][NV];
 #pragma unroll
-  for (int e = 0; e < NV; ++e) acc[e] = 0.f;
+  for (int h = 0; h < G; ++h) {
+    m[h] = kNone;
+    l[h] = 0.f;
+#pragma unroll
+    for (int e = 0; e < NV; ++e) acc[h][e] = 0.f;
+  }
 
   // step s of this wavefront: keys j_begin + (4 s + wave) * 4 + grp
   const int n_steps = (j_end - j_begin + 15) / 16;
@@ -97,19 +120,22 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const DecodeParams p) 
   auto work = [&](int s0, int which) {
 #pragma unroll
     for (int u = 0; u < kDecodeDepth; ++u) {
-      float x = 0.f;
-#pragma unroll
-      for (int e = 0; e < NK; ++e) x = __builtin_fmaf(q[e], elem(kbuf[which][u], e), x);
-      x = row16_sum(x) + p.b2;
       const bool live = key_of(s0 + u) < j_end;
-      x = live ? x : kNone;
-      const float mn = fmaxf(m, x);
-      const float alpha = __builtin_amdgcn_exp2f(m - mn);          // 1 while the reference stands
-      const float w = live ? __builtin_amdgcn_exp2f(x - mn) : 0.f;
-      m = mn;
-      l = l * alpha + w;
 #pragma unroll
-      for (int e = 0; e < NV; ++e) acc[e] = __builtin_fmaf(w, elem(vbuf[which][u], e), acc[e] * alpha);
+      for (int h = 0; h < G; ++h) {
+        float x = 0.f;
+#pragma unroll
+        for (int e = 0; e < NK; ++e) x = __builtin_fmaf(q[h][e], elem(kbuf[which][u], e), x);
+        x = row16_sum(x) + p.b2;
+        x = live ? x : kNone;
+        const float mn = fmaxf(m[h], x);
+        const float alpha = __builtin_amdgcn_exp2f(m[h] - mn);          // 1 while the reference stands
+        const float w = live ? __builtin_amdgcn_exp2f(x - mn) : 0.f;
+        m[h] = mn;
+        l[h] = l[h] * alpha + w;
+#pragma unroll
+        for (int e = 0; e < NV; ++e) acc[h][e] = __builtin_fmaf(w, elem(vbuf[which][u], e), acc[h][e] * alpha);
+      }
     }
   };
   // blocks of kDecodeDepth steps, the loads of block n + 1 in flight while block n is worked on
@@ -124,41 +150,84 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const DecodeParams p) 
     }
   }
 
-  // ---- the 16 states of the workgroup (4 wavefronts x 4 rows of lanes) into one ----
-  {
-    float* mine = red[4 * wave + grp];
+  // ---- the 16 states of the workgroup (4 wavefronts x 4 rows of lanes) into one per q head ----
 #pragma unroll
-    for (int e = 0; e < NV; ++e) mine[NV * sub + e] = acc[e];
-    if (sub == 0) {
-      mine[DV] = m;
-      mine[DV + 1] = l;
+  for (int h = 0; h < G; ++h) {
+    if constexpr (G > 1) {
+      auto fold = [&](int ofs) {
+        const float mo = __shfl_xor(m[h], ofs), mn = fmaxf(m[h], mo);
+        const float fa = __builtin_amdgcn_exp2f(m[h] - mn), fb = __builtin_amdgcn_exp2f(mo - mn);
+        l[h] = l[h] * fa + __shfl_xor(l[h], ofs) * fb;
+#pragma unroll
+        for (int e = 0; e < NV; ++e) acc[h][e] = acc[h][e] * fa + __shfl_xor(acc[h][e], ofs) * fb;
+        m[h] = mn;
+      };
+      fold(16);
+      fold(32);
+    }
+    if (G == 1 || grp == 0) {
+      float* mine = red[G == 1 ? 4 * wave + grp : wave][h];
+#pragma unroll
+      for (int e = 0; e < NV; ++e) mine[NV * sub + e] = acc[h][e];
+      if (sub == 0) {
+        mine[DV] = m[h];
+        mine[DV + 1] = l[h];
+      }
     }
   }
   __syncthreads();
-  if (threadIdx.x < DV) {
-    const int d = threadIdx.x;
+  for (int i = threadIdx.x; i < n_heads * DV; i += 256) {
+    const int h = i / DV, d = i % DV;
     float M = kNone;
 #pragma unroll
-    for (int s = 0; s < 16; ++s) M = fmaxf(M, red[s][DV]);
+    for (int s = 0; s < NS; ++s) M = fmaxf(M, red[s][h][DV]);
     float L = 0.f, o = 0.f;
 #pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      const float f = __builtin_amdgcn_exp2f(red[s][DV] - M);
-      L += f * red[s][DV + 1];
-      o += f * red[s][d];
+    for (int s = 0; s < NS; ++s) {
+      const float f = __builtin_amdgcn_exp2f(red[s][h][DV] - M);
+      L += f * red[s][h][DV + 1];
+      o += f * red[s][h][d];
     }
     const bool any = L > 0.f;
-    p.ws_o[((int64_t)c * p.rows + row) * DV + d] = any ? o / L : 0.f;
-    if (d == 0) p.ws_lse[(int64_t)c * p.rows + row] = any ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f : -INFINITY;
+    o = any ? o / L : 0.f;
+    const float lse = any ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f : -INFINITY;
+    const int64_t row = (int64_t)b * p.H_q + h0 + h;
+    if constexpr (!DIRECT) {
+      p.ws_o[((int64_t)c * p.rows + row) * DV + d] = o;
+      if (d == 0) p.ws_lse[(int64_t)c * p.rows + row] = lse;
+    } else {
+      const int64_t at = b * p.os[0] + (h0 + h) * p.os[1] + d;
+      if (p.out_bf16) static_cast<__bf16*>(p.O)[at] = (__bf16)o;
+      else static_cast<float*>(p.O)[at] = o;
+      if (d == 0 && p.stats != nullptr) p.stats[row] = lse;
+    }
   }
 }
 
+template <int DQK, int DV, int G>
+hipError_t launch_heads(const DecodeParams& p, hipStream_t s) {
+  const int64_t grid = p.rows / p.g * ((p.g + G - 1) / G) * p.n_splits;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  DecodeParams q = p;
+  q.units = (int)(p.rows / p.g * p.n_splits);
+  if (p.n_splits > 1) hipLaunchKernelGGL((attn_decode_kernel<DQK, DV, G, false>), dim3((unsigned)grid), dim3(256), 0, s, q);
+  else hipLaunchKernelGGL((attn_decode_kernel<DQK, DV, G, true>), dim3((unsigned)grid), dim3(256), 0, s, q);
+  return hipGetLastError();
+}
+
+// As many q heads per workgroup as leave a workgroup for every compute unit: sharing the keys saves reads, but a stream
+// needs the whole chip (32 q on 8 k/v heads, in microseconds with 1 / 2 / 4 heads: 16 x 5003 keys -- 128 workgroups with
+// four -- 107 / 87 / 126; 64 x 1000 152 / - / 55; 4 x 5003 in 2 ranges 38 / 47 / 68).  D_qk = 192 with eight needs 318
+// registers and stops at four.
+constexpr int64_t kMinWorkgroups = 256;
 template <int DQK, int DV>
 hipError_t launch(const DecodeParams& p, hipStream_t s) {
-  const int64_t grid = p.rows * p.n_splits;
-  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_decode_kernel<DQK, DV>), dim3((unsigned)grid), dim3(256), 0, s, p);
-  return hipGetLastError();
+  const int64_t units = p.rows / p.g * p.n_splits;
+  if constexpr (DQK <= 128)
+    if (p.g > 4 && units * ((p.g + 7) / 8) >= kMinWorkgroups) return launch_heads<DQK, DV, 8>(p, s);
+  if (p.g > 2 && units * ((p.g + 3) / 4) >= kMinWorkgroups) return launch_heads<DQK, DV, 4>(p, s);
+  if (p.g > 1 && units * ((p.g + 1) / 2) >= kMinWorkgroups) return launch_heads<DQK, DV, 2>(p, s);
+  return launch_heads<DQK, DV, 1>(p, s);
 }
 
 }  // namespace

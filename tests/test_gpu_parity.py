@@ -407,6 +407,39 @@ def test_decoding_rows(A, dims, Lk, splits):
         assert torch.equal(Ob, O.to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("B,H_kv,g,Lk,splits", [(1, 2, 3, 1, 0), (3, 1, 1, 17, 0), (64, 4, 8, 67, 0), (43, 3, 12, 66, 0),
+                                                (52, 5, 5, 131, 0), (65, 2, 3, 63, 0), (129, 1, 2, 16, 0), (22, 4, 4, 257, 3)])
+def test_decoding_rows_shared_keys(A, dims, B, H_kv, g, Lk, splits):
+    """One query row per head, with the keys in one range or (last case) several: the workgroup of the streaming kernel
+    serves one, two, four or eight q heads of a k/v head (as many as still leave 256 workgroups), groups that are no
+    multiple of that among them, on keys and values that are the filled part of a longer cache.  The kernel works in
+    fp32: 1e-4 of the largest |reference| (fp32 sums of at most 257 products, whatever their order)."""
+    from oracle import row_stats_head
+    dev = torch.device("cuda:0")
+    for kw in (dict(), dict(score_mod="bias", bias=-3.0, scale=-0.05)):
+        w = Workload("decode_sets", 23, B, H_kv * g, H_kv, 1, Lk, dims[0], dims[1], mask="causal" if kw else "none", **kw)
+        Q, K, V = make_inputs(w)
+        Kc, Vc = (torch.full((B, H_kv, Lk + 9, t.shape[3]), 1e4, dtype=torch.bfloat16, device=dev) for t in (K, V))
+        Kc[:, :, :Lk], Vc[:, :, :Lk] = K.to(dev), V.to(dev)
+        st = torch.zeros((B, w.H_q, 1), dtype=torch.float32, device=dev)
+        Ob = torch.zeros((B, 1, w.H_q, dims[1]), dtype=torch.bfloat16, device=dev).transpose(1, 2)  # rows of all heads side by side
+        O = A.run_workload(w, Q.to(dev), Kc[:, :, :Lk], Vc[:, :, :Lk], stats=st, kv_splits=splits)
+        A.run_workload(w, Q.to(dev), Kc[:, :, :Lk], Vc[:, :, :Lk], out=Ob, kv_splits=splits)
+        torch.cuda.synchronize()
+        got, ref = O.cpu().double().numpy(), oracle_run(w, Q, K, V)
+        err = np.abs(got - ref).max()
+        print(f"decoding rows {dims} {B}x{H_kv}x{g} L_k {Lk} {kw}: max_abs {err:.3e}", flush=True)
+        assert err <= 1e-4 * np.abs(ref).max()
+        assert torch.equal(Ob, O.to(torch.bfloat16))
+        got = st.cpu().double().numpy()
+        for b in (0, B // 2, B - 1):
+            for h in range(w.H_q):
+                ref = row_stats_head(Q[b, h], K[b, h // g], scale=w.scale_value, score_mod=w.score_mod, bias=w.bias, norm="softmax",
+                                     mask=w.oracle_mask())
+                assert np.abs(got[b, h] - ref).max() <= 1e-3, (b, h)
+
+
 def test_split_keys_decode_full_size(A):
     """The paper's decoding row (Table 2: one query row, 16 heads, 192/128) at 8k keys, batch 8."""
     w = Workload("decode", 20, 8, 16, 16, 1, 8192, 192, 128, mask="causal")
