@@ -498,17 +498,32 @@ hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
 }
 
 // ---- segments: from the final states of the segments (each from a zero start) to the states in front of them ----
+// One thread per state element walks the segments; what it waits for is memory, so the states and decays of kAhead
+// segments are requested together instead of one at a time, each behind the store of the one before (whole calls:
+// 1 x 80 heads x 8192 tokens in 7 segments 210 -> 206 us, 2 x 32 x 4096 in 32 segments 245 -> 233 us).
 __global__ __launch_bounds__(256) void gated_combine_segments_kernel(float* buf, const float* seg_decay, const float* h_in, int nseg,
                                                                       int state_elems) {
+  constexpr int kAhead = 8;
   const int64_t bh = blockIdx.y;
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= state_elems) return;
   float x = h_in ? h_in[bh * state_elems + e] : 0.f;
-  for (int s = 0; s < nseg; ++s) {
-    float* slot = buf + (bh * nseg + s) * state_elems + e;
-    const float local = *slot;
-    *slot = x;
-    x = __expf(seg_decay[bh * nseg + s]) * x + local;
+  float* slot = buf + bh * nseg * state_elems + e;
+  const float* dec = seg_decay + bh * nseg;
+  for (int s0 = 0; s0 < nseg; s0 += kAhead) {
+    float local[kAhead], d[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int s = min(s0 + u, nseg - 1);
+      local[u] = slot[(int64_t)s * state_elems];
+      d[u] = dec[s];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (s0 + u >= nseg) break;
+      slot[(int64_t)(s0 + u) * state_elems] = x;
+      x = __expf(d[u]) * x + local[u];
+    }
   }
 }
 
