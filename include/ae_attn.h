@@ -325,7 +325,7 @@ int32_t ae_attn_version(void);
  * leaves the state in front of each (bf16, [D_qk x D_v]); the parallel-pattern
  * kernel then starts every chunk's rows from the read-out of that state and
  * walks the chunk's own keys on top of it.  The work grows linearly with L.
- * Where B x H is at least 192 the call runs instead as ONE kernel that walks the
+ * Where B x H is more than 128 the call runs instead as ONE kernel that walks the
  * chunks of a (batch, head) in order with the state on chip (the kernel behind
  * ae_gated_forward, with the head's constant decay): same result up to rounding
  * order, Q, K, V read once; the workspace is then not touched (but must still
@@ -423,7 +423,7 @@ ae_status_t ae_gated_forward(const ae_gated_t *h, const void *Q, const void *K, 
 /* The same call for few (batch, head) pairs and long sequences.  One workgroup
  * walks a (batch, head) from the first token to the last, so B x H of them keep
  * B x H compute units busy, however long L is.  Where that leaves most of the
- * chip idle (create decides: fewer than 192 workgroups and L >= 1024) this entry
+ * chip idle (create decides: at most 128 workgroups and L >= 512) this entry
  * point cuts every walk into segments (Section 4.2: parallelism over chunks of
  * the sequence): all segments are walked side by side for their final states from
  * a zero start, a small kernel chains those into the state in front of every

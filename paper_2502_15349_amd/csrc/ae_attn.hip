@@ -723,15 +723,20 @@ int32_t ae_attn_version(void) { return 1; }
 // chunks as if they were batch entries: batch' = chunk index (stride chunk * D), heads' = `fold` batch entries x H
 // heads (stride L * D, which is uniform over (batch, head) in a contiguous [B, H, L, D] tensor).  The decay table
 // of that kernel holds 256 heads, so larger B * H take one launch per batch entry.
-// Segments for a walk of L tokens by `workgroups` workgroups of the single-pass recurrent kernel: enough of them to
-// give every compute unit one, none shorter than 512 tokens (each segment is walked twice, the first time for its
-// state only).  nseg = 1: not cut.
+// Segments for a walk of L tokens by `workgroups` workgroups of the single-pass recurrent kernel (each segment is walked
+// twice, the first time for its state only, a third of the time): as many as one workgroup per compute unit allows --
+// one more and the last few workgroups take a second round as long as the first -- and none shorter than two chunks.
+// Measured (us, segments: time): 40 workgroups x 8192 tokens (Mamba2, 1 x 80 heads) 1: 473, 5: 163, 6: 142, 7: 206;
+// 64 x 4096 (128/128) 3: 141, 4: 118, 5: 168; 96 x 8192 1: 478, 2: 394, 3: 535; 160 x 8192 1: 494, 2: 775; 16 x 2048 4: 60,
+// 8: 40, 16: 34; 8 x 2000 (64/64) 3: 47, 8: 25, 16: 22; 32 x 520 1: 38, 4: 36, 8: 31; 16 x 300 1: 15, 3: 22.  Two segments pay
+// for the two further launches from about 2048 tokens on (64 x 768 1: 37, 2: 40).  nseg = 1: not cut.
+constexpr int64_t kSegmentedBelow = 129;  // workgroups: from here on a second segment is a second round
 static void gated_segments(int64_t workgroups, int L, int* nseg, int* seg_len) {
   *nseg = 1;
   *seg_len = 0;
-  if (workgroups >= 192 || L < 1024) return;
-  int64_t n = std::min<int64_t>((256 + workgroups - 1) / workgroups, L / 512);
-  if (n < 2) return;
+  if (workgroups >= kSegmentedBelow || L < 512) return;
+  int64_t n = std::min<int64_t>(256 / workgroups, L / 128);
+  if (n < 2 || (n == 2 && L < 2048)) return;
   const int len = (int)(((L + n - 1) / n + 63) / 64 * 64);
   *seg_len = len;
   *nseg = (L + len - 1) / len;
@@ -851,9 +856,9 @@ ae_status_t ae_recurrent_create(const ae_recurrent_desc_t* d, ae_recurrent_t** o
   }
   h->ws_bytes = (size_t)d->B * d->H * h->n_chunks * d->D_qk * d->D_v * 2;  // one bf16 state per chunk
   // Measured (8 x 32 heads x 8192 tokens, 128/128): one workgroup per (batch, head) walking the whole sequence with
-  // the state on chip beats the two-kernel form once there is about a workgroup per compute unit; with few pairs
-  // (batch 1) the sequential walk leaves the device idle and the chunk-parallel form wins.
-  h->single_pass = ae::gated_supported(d->D_qk, d->D_v) && (int64_t)d->B * d->H >= 192;
+  // the state on chip beats the two-kernel form once there is about a workgroup per compute unit; with fewer pairs
+  // the walk is cut into segments, and only short sequences of few heads keep the chunk-parallel form.
+  h->single_pass = ae::gated_supported(d->D_qk, d->D_v) && (int64_t)d->B * d->H >= kSegmentedBelow;
   h->nseg = 1;
   h->seg_len = 0;
   if (!h->single_pass && ae::gated_supported(d->D_qk, d->D_v)) {
@@ -994,8 +999,8 @@ ae_status_t ae_recurrent_destroy(ae_recurrent_t* h) {
 struct ae_gated {
   ae_gated_desc_t desc;
   // ae_gated_forward_segmented: the walk of a (batch, head) cut into nseg segments of seg_len tokens where the
-  // (batch, head) pairs alone would leave most compute units idle; 1: not cut
-  int nseg, seg_len;
+  // (batch, head) pairs alone would leave most compute units idle; 1: not cut.  bwd_: the same for ae_gated_backward
+  int nseg, seg_len, bwd_nseg, bwd_seg_len;
 };
 
 extern "C" {
@@ -1019,6 +1024,7 @@ ae_status_t ae_gated_create(const ae_gated_desc_t* d, ae_gated_t** out) {
     // (two heads of a group share a workgroup at 128/64, see launch_gated_recurrent)
     const bool pairs = d->D_qk == 128 && d->D_v == 64 && (d->H / d->H_qk) % 2 == 0;
     gated_segments((int64_t)d->B * d->H / (pairs ? 2 : 1), d->L, &h->nseg, &h->seg_len);
+    gated_segments((int64_t)d->B * d->H, d->L, &h->bwd_nseg, &h->bwd_seg_len);  // (two of its three walks have one head each)
   }
   *out = h;
   return AE_OK;
@@ -1097,15 +1103,15 @@ ae_status_t ae_gated_forward_segmented(const ae_gated_t* h, const void* Q, const
 
 // Workspace of the backward pass: the per-token terms of the decay gradient, fp32 [B, H, L]; and, where value heads
 // share q/k heads, the gradients of q and of the gated key per value head, fp32 [B, H, L, D_qk] each.
-// Where the forward pass would cut the walks into segments, so do the three walks of the backward pass: the segments'
-// states (one set, used by the walks in turn) follow.
+// Where the three walks of the backward pass are cut into segments, the segments' states (one set, used by the walks in
+// turn) follow.
 static size_t gated_backward_ws(const ae_gated* h, size_t* per_head_off, size_t* seg_off) {
   const ae_gated_desc_t& d = h->desc;
   const size_t rows = ((size_t)d.B * d.H * d.L * 4 + 255) & ~(size_t)255;
   const size_t per_head = d.H != d.H_qk ? 2 * (size_t)d.B * d.H * d.L * d.D_qk * 4 : 0;
   if (per_head_off) *per_head_off = rows;
   if (seg_off) *seg_off = rows + per_head;
-  return rows + per_head + gated_segments_ws(d.B, d.H, h->nseg, d.D_qk, d.D_v);
+  return rows + per_head + gated_segments_ws(d.B, d.H, h->bwd_nseg, d.D_qk, d.D_v);
 }
 
 ae_status_t ae_gated_backward_workspace_bytes(const ae_gated_t* h, size_t* bytes) {
@@ -1132,8 +1138,8 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
   void* seg_ws = static_cast<char*>(workspace) + seg_off;
   auto walk = [&](const ae::GatedParams& g, int dqk, int dv) {
     static const ae::DecayTable none = {};
-    return h->nseg > 1 ? launch_gated_segmented(g, none, dqk, dv, h->nseg, h->seg_len, seg_ws, stream)
-                       : ae::launch_gated_recurrent(g, none, dqk, dv, stream);
+    return h->bwd_nseg > 1 ? launch_gated_segmented(g, none, dqk, dv, h->bwd_nseg, h->bwd_seg_len, seg_ws, stream)
+                           : ae::launch_gated_recurrent(g, none, dqk, dv, stream);
   };
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need)
     return fail(AE_ERR_INVALID_ARG, "ae_gated_backward: workspace missing, not 256-byte aligned, or smaller than %zu bytes", need);

@@ -442,3 +442,16 @@ def test_gated_backward_entry_point_checks():
     finally:
         A.ae_gated_destroy(h)
         A.ae_gated_destroy(hu)
+
+
+@pytest.mark.parametrize("H,L,segments", [(1, 511, 1), (1, 512, 4), (128, 2047, 1), (128, 2048, 2), (129, 8192, 1), (85, 512, 3),
+                                          (86, 2047, 1), (16, 1000, 6), (3, 100000, 83)])
+def test_gated_segments_fill_the_chip_once(H, L, segments):
+    """As many segments as keep one workgroup per compute unit (256), none shorter than two chunks of 64 tokens, two only
+    from 2048 tokens on; the workspace holds a state and a decay per (batch, head, segment)."""
+    from paper_2502_15349_amd import ae_attn as A
+    h = A.ae_gated_create(B=1, H=H, L=L, D_qk=128, D_v=128, scale=0.1)
+    slots = H * segments
+    want = 0 if segments == 1 else slots * 128 * 128 * 4 + (slots * 4 + 255) // 256 * 256
+    assert A.ae_gated_workspace_bytes(h) == want
+    A.ae_gated_destroy(h)
