@@ -13,25 +13,24 @@
 //     sign(sum_j S'); the gradient of the raw score is dS' * decay
 //   dQ  = scale * dS' K                   dK = scale * dS'^T Q
 //
-// Two kernels of one shape, no atomics, every output written once:
+// A launch per side, no atomics, every output written once:
 //   * key side (KV_SIDE): a workgroup owns 128 keys of one k/v head and walks the query tiles of
 //     the q heads that share it: dK and dV;
 //   * query side: a workgroup owns 128 query rows of one q head and walks the key tiles: dQ.
-// The key-side kernel holds two accumulators and two resident operands; from D 128/128 on that
-// is more than the 256 registers of a two-waves-per-SIMD kernel, and it then runs one workgroup
-// per CU with up to 512 (a variant squeezed into 256 spilled in its inner loop and was 1.5 x
-// slower; separate dK and dV kernels at two waves per SIMD recompute the scores once more and
-// were 15-25 % slower than the fused one).  Both kernels run against the board's power limit:
-// the clock under load is 1.4-1.7 GHz.
-// In both a wavefront owns 32 rows ("own" side) whose two operand matrices it keeps in
-// registers as MFMA B fragments (K, V | Q, dO), and the tiles of the other side (Q, dO |
-// K, V; 64 rows, double buffered) arrive in LDS by global_load_lds.  Per 32-row sub-tile
+// A wavefront owns 32 rows ("own" side) whose operands it keeps in registers as MFMA B fragments (K, V | Q, dO), and
+// the tiles of the other side (Q, dO | K, V) arrive in LDS by global_load_lds.  Per 32 other rows
 //   S  [other x own] = Y1 X1^T      dP [other x own] = Y2 X2^T        (bf16 MFMA 32x32x16)
 // put a lane's 16 accumulator values in one own column; after the elementwise step they
 // are, packed to bf16 and with no data movement, the B operands of
 //   dQ^T, dK^T [D_qk x own] += Y1^T dS       dV^T [D_v x own] += Y2^T P
 // whose A operands are the same LDS tiles read through the transposing LDS load, in the
 // row order that the accumulator layout dictates.
+//
+// What bounds it is how well a SIMD's vector and matrix work overlap, and that takes two wavefronts per SIMD of at most
+// 256 registers.  Where accumulators, resident operands and score tiles of 32 own rows fit that (64/64; 128/128, query
+// side), a wavefront does all of the above and two workgroups share a CU: attn_bwd_kernel.  Where they do not, the 32
+// rows go to a pair of wavefronts: attn_bwd_pair_kernel.  (One wavefront with 512 registers, alone on its SIMD, kept the
+// matrix units 39 % busy; both kernels then run into the board's power limit.)
 #pragma once
 #include "attn_kernel.hpp"
 
@@ -90,12 +89,9 @@ __device__ __forceinline__ int bswz(int row) {
 constexpr int BWD_NORM_NONE_RELU = 5;
 enum : int { BWD_DQ = 0, BWD_DKV = 1 };  // the query-side kernel (dQ), the key-side kernel (dK and dV)
 
-#ifndef AE_BWD_OCC2_REGS
-#define AE_BWD_OCC2_REGS 176
-#endif
-template <int DQK_, int DV_, int NORM_, bool CAUSAL_, int OUT_, bool BIAS_ = false>
+// ---- one wavefront per 32 own rows, two workgroups per CU ----------------------------------------------------------
+template <int DQK_, int DV_, int NORM_, bool CAUSAL_, int OUT_>
 struct BwdCfg {
-  static constexpr bool BIAS = BIAS_;  // S' = scale * S + bias[b, h_q, i, j]
   static constexpr int DQK = DQK_, DV = DV_, NORM = NORM_, OUT = OUT_;
   static constexpr bool CAUSAL = CAUSAL_, KV_SIDE = OUT_ == BWD_DKV;
   static constexpr int WAVES = 4, THREADS = 256, OWN = 128;  // own rows per workgroup
@@ -103,23 +99,13 @@ struct BwdCfg {
   static constexpr int DB = DQK / 32;  // 32-row blocks of the transposed result dQ^T / dK^T
   static constexpr bool HAS2 = KV_SIDE;               // key side: a second result, dV^T
   static constexpr int DB2 = HAS2 ? DV / 32 : 0;
-  // Two workgroups per CU (two waves per SIMD, 256 registers each) where the accumulators, the
-  // resident operands and the two score tiles leave room for the rest; one (512 registers) otherwise.
-  // bias tensor: per stage the block of it that the tile meets, 16 KB: [128 own queries][64 keys] on the query
-  // side, [64 queries][128 own keys] on the key side
-  static constexpr int BIAS_BYTES = BIAS_ ? 16384 : 0;
-  // (row quantities pass through LDS on the key side only, see ROW_BYTES)
-  static constexpr bool OCC2 = 16 * (DB + DB2) + 4 * T1 + 4 * T2 + 32 + (BIAS_ ? 8 : 0) <= AE_BWD_OCC2_REGS &&
-                               2 * 64 * (DQK + DV) * 2 + (KV_SIDE ? 1024 : 0) + 2 * BIAS_BYTES <= 80 * 1024;
-  // one workgroup per CU: the LDS fragments of a step are read as a batch ahead of its MFMAs
-  static constexpr bool BATCH = !OCC2 && DQK + DV <= 320;  // (beyond that the batches do not fit 512 registers)
   static constexpr int TILE = 64;  // other-side rows per LDS tile (two 32-row sub-tiles)
   static constexpr int RB1 = DQK * 2, RB2 = DV * 2, CPR1 = DQK / 8, CPR2 = DV / 8;
   static constexpr int Y1_BYTES = TILE * RB1, Y2_BYTES = TILE * RB2, STAGE_BYTES = Y1_BYTES + Y2_BYTES;
   // per stage: bias*log2(e) - lse*log2(e) and delta of the tile's rows (key side: they belong to the registers' rows;
   // on the query side they belong to the lane's own row and stay in registers)
   static constexpr int ROW_BYTES = KV_SIDE ? 2 * TILE * 4 : 0;
-  static constexpr int LDS_BYTES = 2 * STAGE_BYTES + 2 * ROW_BYTES + 2 * BIAS_BYTES;
+  static constexpr int LDS_BYTES = 2 * STAGE_BYTES + 2 * ROW_BYTES;
   static_assert(NORM == NORM_SOFTMAX || NORM == NORM_SIGMOID || NORM == NORM_NONE || NORM == BWD_NORM_NONE_RELU ||
                     NORM == NORM_ABSSUM || NORM == NORM_ABS_OF_SUM,
                 "backward: softmax, sigmoid, the abs-sum family, and no normalization with or without ReLU");
@@ -128,7 +114,8 @@ struct BwdCfg {
   // no normalization (without ReLU) is the abs-sum form with the row factors fixed at 1 and 0: P = S', dS' = dP,
   // per-head decay included
   static constexpr bool LIN = ABS || NORM == NORM_NONE;
-  static_assert(LDS_BYTES <= (OCC2 ? 80 : 160) * 1024, "the workgroups of a CU must fit LDS");
+  // the accumulators, the resident operands and the two score tiles leave room for the rest in 256 registers
+  static_assert(16 * (DB + DB2) + 4 * T1 + 4 * T2 + 32 <= 176 && LDS_BYTES <= 80 * 1024, "two workgroups per CU");
   static_assert((TILE * CPR1 / 64) % WAVES == 0 && (TILE * CPR2 / 64) % WAVES == 0, "every wave copies the same number of blocks");
 };
 
@@ -147,11 +134,10 @@ __device__ __forceinline__ bf16x8 pack8(const float (&x)[16], int t) {
 }
 
 template <class C>
-__global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(const BwdParams p, const DecayTable dt) {
+__global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_kernel(const BwdParams p, const DecayTable dt) {
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
   const uint32_t rows0 = lds0 + 2 * C::STAGE_BYTES;
-  const uint32_t bias0 = rows0 + 2 * C::ROW_BYTES;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ln = lane & 31, half = lane >> 5;
   const int off = p.L_k - p.L_q;
@@ -255,26 +241,6 @@ __global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(c
       row = row < L_oth ? row : L_oth - 1;
       const uint32_t goff = (uint32_t)(((int64_t)row * s2 + ((pc ^ bswz<C::CPR2>(r)) * 8)) * 2);
       dma16(y2, goff, base + C::Y1_BYTES + nb * 1024);
-    }
-    if constexpr (C::BIAS) {
-      // The block of the bias tensor that this tile meets, rows = queries.  Query side: 128 rows x 128 bytes
-      // (8 chunks), chunk slot c ^ ((row >> 1) & 7); key side: 64 rows x 256 bytes (16 chunks), slot
-      // c ^ ((row & 3) << 2) (read back transposed, 4 rows x 64 bytes at a time).  Chunks that start beyond the
-      // last key are redirected to the row's last chunk (rows are padded to 8 elements by contract).
-      const __bf16* bb = p.bias + b * p.bs[0] + hq * p.bs[1];
-      constexpr int CPRB = C::KV_SIDE ? 16 : 8;
-      const int q0 = C::KV_SIDE ? r0 : own0, k0 = C::KV_SIDE ? own0 : r0;
-      const int last = ((p.L_k - 1) >> 3) << 3;
-#pragma unroll
-      for (int i = 0; i < 16 / C::WAVES; ++i) {
-        const int nb = wave + i * C::WAVES, pos = nb * 64 + lane;
-        const int r = pos / CPRB, pc = pos % CPRB;
-        const int c = C::KV_SIDE ? pc ^ ((r & 3) << 2) : pc ^ ((r >> 1) & 7);
-        int row = q0 + r, col = k0 + 8 * c;
-        row = row < p.L_q ? row : p.L_q - 1;
-        col = col < p.L_k ? col : last;
-        dma16(bb, (uint32_t)(((int64_t)row * p.bs[2] + col) * 2), bias0 + stage * C::BIAS_BYTES + nb * 1024);
-      }
     }
   };
   // key side: the tile's row quantities, wave 0 -> (bias - lse) * log2(e), wave 1 -> delta.  The
@@ -386,62 +352,13 @@ __global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(c
       }
       return read_tr_frag(atl[k < C::DB ? k : 0] + kT + t * 16 * RBT, ath[k < C::DB ? k : 0] + kT + t * 16 * RBT);
     };
-    bf16x8 tr[2][C::BATCH ? C::DB + C::DB2 : 1];
-    if constexpr (C::BATCH) {
-      // One wave per SIMD: nothing else hides the LDS latency, so all fragments of a step are
-      // requested before its first MFMA, and those of the accumulation step before the elementwise
-      // step (the fences keep the compiler from sinking the reads back to their uses).
-      bf16x8 a1[C::T1], a2[C::T2];
 #pragma unroll
-      for (int t = 0; t < C::T1; ++t) a1[t] = read_k_frag(ar1[t] + kRow1);
+    for (int t = 0; t < C::T1; ++t) s = mfma(read_k_frag(ar1[t] + kRow1), xb1[t], s);
 #pragma unroll
-      for (int t = 0; t < C::T2; ++t) a2[t] = read_k_frag(ar2[t] + kRow2);
-      sched_fence();
-#pragma unroll
-      for (int t = 0; t < C::T1; ++t) s = mfma(a1[t], xb1[t], s);
-#pragma unroll
-      for (int t = 0; t < C::T2; ++t) dp = mfma(a2[t], xb2[t], dp);
-      sched_fence();
-#pragma unroll
-      for (int k = 0; k < C::DB + C::DB2; ++k) tr[0][k] = read_acc(0, k);
-      sched_fence();
-    } else {
-#pragma unroll
-      for (int t = 0; t < C::T1; ++t) s = mfma(read_k_frag(ar1[t] + kRow1), xb1[t], s);
-#pragma unroll
-      for (int t = 0; t < C::T2; ++t) dp = mfma(read_k_frag(ar2[t] + kRow2), xb2[t], dp);
-    }
+    for (int t = 0; t < C::T2; ++t) dp = mfma(read_k_frag(ar2[t] + kRow2), xb2[t], dp);
     float x[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) x[r] = __builtin_fmaf(s[r], p.c2, C::NORM == NORM_SOFTMAX ? nl4[r / 4][r % 4] : p.b2);
-    if constexpr (C::BIAS) {
-      // register r = 4 q4 + e is (query, key) = (own row, key 8 q4 + 4 half + e of the sub-tile) on the query side,
-      // (query 8 q4 + 4 half + e of the sub-tile, own key) on the key side
-      const uint32_t bt = bias0 + STAGE * C::BIAS_BYTES;
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        uint32_t lo, hi;
-        if constexpr (C::KV_SIDE) {
-          const int row = 32 * SUB + 8 * q4 + 4 * half + ((lane & 15) >> 2);   // the row this lane addresses
-          const int cl = 4 * wave + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);  // chunk of its 4 columns
-          const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(
-              bt + row * 256 + ((cl ^ ((row & 3) << 2)) << 4) + (lane & 1) * 8));
-          const u32x2 w2 = __builtin_bit_cast(u32x2, v);
-          lo = w2[0];
-          hi = w2[1];
-        } else {
-          const int row = 32 * wave + ln;
-          const u32x2 w2 = *reinterpret_cast<__attribute__((address_space(3))) const u32x2*>(
-              (lds_char*)(uintptr_t)(bt + row * 128 + (((4 * SUB + q4) ^ ((row >> 1) & 7)) << 4) + 8 * half));
-          lo = w2[0];
-          hi = w2[1];
-        }
-        x[4 * q4 + 0] += __builtin_bit_cast(float, lo << 16) * p.bunit;
-        x[4 * q4 + 1] += __builtin_bit_cast(float, lo & 0xffff0000u) * p.bunit;
-        x[4 * q4 + 2] += __builtin_bit_cast(float, hi << 16) * p.bunit;
-        x[4 * q4 + 3] += __builtin_bit_cast(float, hi & 0xffff0000u) * p.bunit;
-      }
-    }
     // abs-sum family: distance to the diagonal of register 0's entry, for the decay factor
     const float dist0 = (float)(C::KV_SIDE ? o0 + off - own + 4 * half : own + off - o0 - 4 * half);
     if (!full) {  // a hidden entry gets the exponent that makes its weight exactly 0
@@ -488,37 +405,16 @@ __global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(c
       }
       w[r] = pv;
     }
-    if constexpr (C::BIAS && !C::KV_SIDE) {
-      // the bias enters S' with slope 1: its gradient is dS' itself, 4 x 4 consecutive keys of the lane's own row
-      if (p.dbias != nullptr && own < p.L_q) {
-        __bf16* drow = p.dbias + (((int64_t)b * p.H_q + ho) * p.L_q + own) * p.dbias_ld + o0 + 4 * half;
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          if (o0 + 8 * q4 + 4 * half < p.L_k) {  // (a group across the last key writes into the row's padding)
-            bf16x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (__bf16)w[4 * q4 + e];
-            *reinterpret_cast<bf16x4*>(drow + 8 * q4) = v;
-          }
-      }
-    }
     // G^T += Y^T W: per 16-row step t, the DB blocks of Y1^T (dQ^T, dK^T), then (key side) the DB2 blocks of Y2^T
-    if constexpr (C::BATCH) {
-      sched_fence();
-#pragma unroll
-      for (int k = 0; k < C::DB + C::DB2; ++k) tr[1][k] = read_acc(1, k);
-      sched_fence();
-    }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const bf16x8 wb = pack8(w, t);
 #pragma unroll
-      for (int k = 0; k < C::DB; ++k) g[k] = mfma(C::BATCH ? tr[t][C::BATCH ? k : 0] : read_acc(t, k), wb, g[k]);
+      for (int k = 0; k < C::DB; ++k) g[k] = mfma(read_acc(t, k), wb, g[k]);
       if constexpr (C::HAS2) {
         const bf16x8 pb = pack8(w2, t);
 #pragma unroll
-        for (int k = 0; k < C::DB2; ++k)
-          g2[k] = mfma(C::BATCH ? tr[t][C::BATCH ? C::DB + k : 0] : read_acc(t, C::DB + k), pb, g2[k]);
+        for (int k = 0; k < C::DB2; ++k) g2[k] = mfma(read_acc(t, C::DB + k), pb, g2[k]);
       }
     }
   };
@@ -579,6 +475,591 @@ __global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(c
               f32x4{g2[db][4 * q], g2[db][4 * q + 1], g2[db][4 * q + 2], g2[db][4 * q + 3]};
     }
   }
+}
+
+// ---- two wavefronts per 32 own rows -------------------------------------------------------------------------------
+// Role 0 (wavefronts 0..3) keeps X1, computes S and the weights P, writes per entry the factor that turns dP into dS' to
+// LDS (fp32: softmax P, sigmoid P (1 - P), ...) and, on the key side, accumulates dV.  Role 1 (wavefronts 4..7, on the
+// same SIMDs) keeps X2, computes dP, reads the factors and accumulates dK or dQ.  The products split evenly: D_qk + D_v
+// against D_v + D_qk on the key side.  Role 1 is a tile of 32 rows behind, so one barrier per tile hands over the
+// factors, the tiles that have landed and the stages that are free.  Within a tile role 0's order is S, weights, dV and
+// role 1's is dS', dK / dQ, dP of the next tile: one is in its vector work while the other issues matrix products.
+//
+// Measured against one wavefront per 32 rows with 512 registers (us, whole backward pass): 1 x 128 heads x 8192, 192/128,
+// causal 10340 -> 9640; 8 x 16 x 4096 192/128 2786 -> 2600, 128/256 3517 -> 2917, 128/128 (key side) 2106 -> 2013;
+// 1 x 32/8 x 1024 192/128 217 -> 182, 128/256 290 -> 207, 128/128 184 -> 164; 2 x 12 x 1023 x 1201 with a bias tensor, 64/64,
+// 90 -> 88.  The matrix units are busy 48 % of the time at 1.9 GHz (39 % at 2.25 before).  Taking away the copies, the
+// LDS reads or the weights for timing gave 9-10 % each: no one of them bounds it, the hand-over per tile and the board's
+// power do.  Against two workgroups per CU where those fit (64/64 8 x 16 x 4096 1033, 128/128 query side
+// 4 x 32/8 x 2048 210) the pairs take 1212 and 316: the choice in bwd_launch.hpp.
+template <int DQK_, int DV_, int NORM_, bool CAUSAL_, int OUT_, bool BIAS_ = false>
+struct BwdPairCfg {
+  static constexpr bool BIAS = BIAS_;
+  static constexpr int DQK = DQK_, DV = DV_, NORM = NORM_, OUT = OUT_;
+  static constexpr bool CAUSAL = CAUSAL_, KV_SIDE = OUT_ == BWD_DKV;
+  static constexpr int WAVES = 8, THREADS = 512, OWN = 128, TILE = 32;
+  static constexpr int T1 = DQK / 16, T2 = DV / 16, DB = DQK / 32, DB2 = KV_SIDE ? DV / 32 : 0;
+  static constexpr bool ABS = NORM == NORM_ABSSUM || NORM == NORM_ABS_OF_SUM;
+  static constexpr bool ROWS = NORM == NORM_SOFTMAX || ABS;
+  static constexpr bool LIN = ABS || NORM == NORM_NONE;
+  static constexpr bool ROWQ = ROWS && KV_SIDE;
+  static constexpr int RB1 = DQK * 2, RB2 = DV * 2, CPR1 = DQK / 8, CPR2 = DV / 8;
+  static constexpr int Y1_BYTES = TILE * RB1, Y2_BYTES = TILE * RB2, BIAS_BYTES = BIAS_ ? 8192 : 0;
+  static constexpr int STAGE_BYTES = Y1_BYTES + Y2_BYTES + BIAS_BYTES;
+  static constexpr int ROW_BYTES = ROWQ ? 512 : 0;  // per stage: [64] statistic, [64] delta (32 of each are used)
+  static constexpr int STAGES = 5 * (STAGE_BYTES + ROW_BYTES) + 2 * 4 * 4096 <= 160 * 1024 ? 5 : 4, LOOK = STAGES - 2;
+  static constexpr int ROWS0 = STAGES * STAGE_BYTES, E0 = ROWS0 + STAGES * ROW_BYTES, E_BYTES = 4 * 4096;
+  static constexpr int LDS_BYTES = E0 + 2 * E_BYTES;
+  // copies: groups of four 1 KB blocks, group q by the wavefronts of role q % 2
+  static constexpr int G1 = DQK / 64, G2 = DV / 64, GB = BIAS_ ? 2 : 0, GROUPS = G1 + G2 + GB;
+  // swizzle periods of the fragment addresses (in fragments): beyond them an address repeats at a fixed distance
+  static constexpr int PR1 = CPR1 % 16 == 0 ? 8 : 4, PR2 = CPR2 % 16 == 0 ? 8 : 4;
+  static constexpr int PK1 = CPR1 % 16 == 0 ? 4 : 2, PK2 = CPR2 % 16 == 0 ? 4 : 2;
+  static_assert(LDS_BYTES <= 160 * 1024, "the workgroups of a CU must fit LDS");
+};
+
+// 64 lanes x 4 bytes from base + byte_off (per lane) to LDS bytes [lds_addr, lds_addr + 256)
+__device__ __forceinline__ void dma4(const void* base_uniform, uint32_t byte_off, uint32_t lds_addr_uniform) {
+  base_uniform = uniform_ptr(base_uniform);
+  lds_addr_uniform = __builtin_amdgcn_readfirstlane(lds_addr_uniform);
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %1, %2"
+      :
+      : "s"(lds_addr_uniform), "v"(byte_off), "s"(base_uniform)
+      : "memory", "m0");
+}
+__device__ __forceinline__ float lds_read4(uint32_t addr) {
+  return *reinterpret_cast<__attribute__((address_space(3))) const float*>((lds_char*)(uintptr_t)addr);
+}
+__device__ __forceinline__ void lds_store4(uint32_t addr, float v) {
+  *reinterpret_cast<__attribute__((address_space(3))) float*>((lds_char*)(uintptr_t)addr) = v;
+}
+__device__ __forceinline__ void lds_store16(uint32_t addr, f32x4 v) {
+  *reinterpret_cast<__attribute__((address_space(3))) f32x4*>((lds_char*)(uintptr_t)addr) = v;
+}
+
+template <class C>
+__global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdParams p, const DecayTable dt) {
+  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w4 = wave & 3;
+  const int ln = lane & 31, half = lane >> 5;
+  const int off = p.L_k - p.L_q;
+  const int L_own = C::KV_SIDE ? p.L_k : p.L_q, L_oth = C::KV_SIDE ? p.L_q : p.L_k;
+
+  const int n_own_tiles = (L_own + C::OWN - 1) / C::OWN;
+  const int n_groups = p.B * p.H_kv;
+  const int per_group = C::KV_SIDE ? n_own_tiles : n_own_tiles * p.g;
+  const int tg = p.together[C::KV_SIDE ? 1 : 0];
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int set = slot / (tg * per_group), within = slot % (tg * per_group);
+  const int item = within / tg, group = (set * tg + within % tg) * 8 + xcd;
+  if (group >= n_groups) return;
+  const int b = group / p.H_kv, hk = group % p.H_kv;
+  const int ot = C::KV_SIDE ? item : n_own_tiles - 1 - item / p.g;
+  const int ho = C::KV_SIDE ? hk : hk * p.g + item % p.g;  // ho: k/v head (key side) or q head (query side)
+  const int own0 = ot * C::OWN, ow0 = own0 + w4 * 32;
+  const int own = ow0 + ln;
+  const int own_c = own < L_own ? own : L_own - 1;
+
+  // ---- the walk over the other side, in tiles of 32 rows ----
+  int t_first = 0, t_end = (L_oth + C::TILE - 1) / C::TILE;
+  if constexpr (C::CAUSAL) {
+    if constexpr (C::KV_SIDE) {
+      const int i_first = own0 - off;  // first query that sees key own0
+      t_first = i_first > 0 ? i_first / C::TILE : 0;
+      if (t_first > t_end) t_first = t_end;
+      const int i_last = own0 + C::OWN - 1 - off + p.window - 1;  // last query whose window holds a key here
+      const int e = i_last < 0 ? 0 : i_last / C::TILE + 1;
+      if (e < t_end) t_end = e;
+      if (t_end < t_first) t_end = t_first;
+    } else {
+      const int j_last = own0 + C::OWN - 1 + off;  // last key any row here may see
+      const int e = j_last < 0 ? 0 : j_last / C::TILE + 1;
+      if (e < t_end) t_end = e;
+      const int j_first = own0 + off - p.window + 1;  // first key inside the window of row own0
+      t_first = j_first > 0 ? j_first / C::TILE : 0;
+      if (t_first > t_end) t_first = t_end;
+    }
+  }
+  const int N = (t_end - t_first) * (C::KV_SIDE ? p.g : 1);
+  struct Pos {  // a position of the walk: tile t of q head h
+    int t, h;
+  };
+  auto advance = [&](Pos& q) {
+    if (++q.t == t_end) {
+      q.t = t_first;
+      ++q.h;
+    }
+  };
+  const int h_first = C::KV_SIDE ? hk * p.g : ho;
+
+  const int li = lane & 15, blk = (lane >> 4) & 1;
+  const int trow = 4 * half + (li >> 2), tcl = 2 * blk + ((li & 3) >> 1);
+
+  auto walk = [&](auto rolec) {
+    constexpr int ROLE = decltype(rolec)::value;  // 0: scores and weights (and dV on the key side), 1: dP, dS and dK / dQ
+    constexpr int NC = (C::GROUPS - ROLE + 1) / 2;
+    constexpr int T = ROLE == 0 ? C::T1 : C::T2, CPRX = ROLE == 0 ? C::CPR1 : C::CPR2;
+    constexpr int DBX = ROLE == 0 ? C::DB2 : C::DB, CPRT = ROLE == 0 ? C::CPR2 : C::CPR1;  // accumulated blocks, and the tile they read
+    constexpr int PR = ROLE == 0 ? C::PR1 : C::PR2, PK = ROLE == 0 ? C::PK2 : C::PK1;
+    constexpr int RBX = CPRX * 16, RBT = CPRT * 16;
+    constexpr int OFFX = ROLE == 0 ? 0 : C::Y1_BYTES, OFFT = ROLE == 0 ? C::Y1_BYTES : 0;
+    // ---- own operand: B fragments, straight from global memory ----
+    const __bf16* x;
+    if constexpr (ROLE == 0) {
+      x = C::KV_SIDE ? p.K + b * p.ks[0] + hk * p.ks[1] + (int64_t)own_c * p.ks[2] : p.Q + b * p.qs[0] + ho * p.qs[1] + (int64_t)own_c * p.qs[2];
+    } else {
+      x = C::KV_SIDE ? p.V + b * p.vs[0] + hk * p.vs[1] + (int64_t)own_c * p.vs[2]
+                     : p.dO + (((int64_t)b * p.H_q + ho) * p.L_q + own_c) * C::DV;
+    }
+    bf16x8 xb[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) xb[t] = *reinterpret_cast<const bf16x8*>(x + (2 * t + half) * 8);
+    float rq_own = ROLE == 0 ? (C::LIN ? 1.f : -INFINITY) : 0.f;  // query side: the row quantity of the lane's own row
+    if constexpr (!C::KV_SIDE && C::ROWS) {
+      if (own < p.L_q) {
+        const int64_t r = ((int64_t)b * p.H_q + ho) * p.L_q + own;
+        if constexpr (ROLE == 0) {
+          const float st = p.lse[r];
+          if constexpr (C::ABS) rq_own = fast_rcp(fmaxf(fabsf(st), 1.f));
+          else rq_own = st == -INFINITY ? -INFINITY : p.b2 - st * 1.4426950408889634f;
+        } else {
+          rq_own = p.delta[r];
+        }
+      }
+    }
+    auto convert_stat = [&](float v) {
+      return C::ABS ? fast_rcp(fmaxf(fabsf(v), 1.f)) : v == -INFINITY ? -INFINITY : p.b2 - v * 1.4426950408889634f;
+    };
+
+    // ---- copies ----
+    const int64_t s1 = C::KV_SIDE ? p.qs[2] : p.ks[2], s2 = C::KV_SIDE ? (int64_t)C::DV : p.vs[2];
+    uint32_t co[NC], co_tail[NC];  // the lane's byte offset from the tile's first row; the same for a short last tile
+    const int tail = (L_oth - 1) % C::TILE;  // the last tile's last row: rows past it repeat it
+    static_for<0, NC>([&](auto kc) {
+      constexpr int k = decltype(kc)::value, q = 2 * k + ROLE;
+      constexpr bool FIRST = q < C::G1;
+      constexpr int CPR = FIRST ? C::CPR1 : C::CPR2, Q = FIRST ? q : q - C::G1;
+      if constexpr (q < C::G1 + C::G2) {
+        const int pos = (4 * Q + w4) * 64 + lane, r = pos / CPR, c = (pos % CPR) ^ bswz<CPR>(r);
+        co[k] = (uint32_t)((r * (FIRST ? s1 : s2) + c * 8) * 2);
+        co_tail[k] = (uint32_t)((min(r, tail) * (FIRST ? s1 : s2) + c * 8) * 2);
+      }
+    });
+    // the copies' own position in the walk, with the addresses of its tile's first rows
+    Pos ahead{t_first, h_first};
+    const __bf16 *y1, *y2;
+    auto head_start = [&]() {
+      y1 = (C::KV_SIDE ? p.Q + b * p.qs[0] + ahead.h * p.qs[1] : p.K + b * p.ks[0] + hk * p.ks[1]) + (int64_t)t_first * C::TILE * s1;
+      y2 = (C::KV_SIDE ? p.dO + ((int64_t)b * p.H_q + ahead.h) * p.L_q * C::DV : p.V + b * p.vs[0] + hk * p.vs[1]) + (int64_t)t_first * C::TILE * s2;
+    };
+    head_start();
+    const int h_last = h_first + (C::KV_SIDE ? p.g : 1) - 1;
+    auto advance_copies = [&]() {  // (past the end of the walk the last tile is copied again, to stages that nobody reads)
+      if (ahead.t + 1 < t_end) {
+        y1 += C::TILE * s1;
+        y2 += C::TILE * s2;
+        ++ahead.t;
+      } else if (ahead.h < h_last) {
+        ahead.t = t_first;
+        ++ahead.h;
+        head_start();
+      }
+    };
+    // copy instruction k of this wavefront for the tile that the copies stand at
+    auto issue = [&](auto stagec, auto kc) {
+      constexpr int ST = decltype(stagec)::value, k = decltype(kc)::value, q = 2 * k + ROLE;
+      const int r0 = ahead.t * C::TILE;
+      const uint32_t base = lds0 + ST * C::STAGE_BYTES;
+      if constexpr (q < C::G1 + C::G2) {
+        constexpr bool FIRST = q < C::G1;
+        constexpr int Q = FIRST ? q : q - C::G1;
+        const uint32_t o = r0 + C::TILE > L_oth ? co_tail[k] : co[k];
+        dma16(FIRST ? y1 : y2, o, base + (FIRST ? 0 : C::Y1_BYTES) + (4 * Q + w4) * 1024);
+      } else {
+        // The block of the bias tensor that this tile meets, rows = queries.  Query side: 128 rows x 64 bytes
+        // (4 chunks), chunk slot c ^ ((row >> 2) & 3); key side: 32 rows x 256 bytes (16 chunks), slot
+        // c ^ ((row & 3) << 2) (read back transposed, 4 rows x 64 bytes at a time).  Chunks that start beyond the
+        // last key are redirected to the row's last chunk (rows are padded to 8 elements by contract).
+        constexpr int CPRB = C::KV_SIDE ? 16 : 4;
+        const __bf16* bb = p.bias + b * p.bs[0] + ahead.h * p.bs[1];
+        const int nb = 4 * (q - C::G1 - C::G2) + w4, pos = nb * 64 + lane, r = pos / CPRB, pc = pos % CPRB;
+        const int c = C::KV_SIDE ? pc ^ ((r & 3) << 2) : pc ^ ((r >> 2) & 3);
+        int row = (C::KV_SIDE ? r0 : own0) + r, col = (C::KV_SIDE ? own0 : r0) + 8 * c;
+        row = row < p.L_q ? row : p.L_q - 1;
+        col = col < p.L_k ? col : ((p.L_k - 1) >> 3) << 3;
+        dma16(bb, (uint32_t)(((int64_t)row * p.bs[2] + col) * 2), base + C::Y1_BYTES + C::Y2_BYTES + nb * 1024);
+      }
+    };
+    // key side: 32 row quantities of a tile (lanes 32..63 repeat the last row of the query head)
+    auto issue_rows = [&](auto stagec) {
+      if constexpr (C::ROWQ) {
+        constexpr int ST = decltype(stagec)::value;
+        if (w4 == 0) {
+          const int i = min(ahead.t * C::TILE + lane, p.L_q - 1);
+          dma4((ROLE == 0 ? p.lse : p.delta) + ((int64_t)b * p.H_q + ahead.h) * p.L_q, (uint32_t)i * 4u,
+                    lds0 + C::ROWS0 + ST * C::ROW_BYTES + (ROLE == 0 ? 0 : 256));
+        }
+      }
+    };
+
+    // ---- accumulators and fragment addresses (stage 0) ----
+    f32x16 acc[DBX > 0 ? DBX : 1];
+#pragma unroll
+    for (int d = 0; d < DBX; ++d) acc[d] = zero16();
+    constexpr int NR = T < PR ? T : PR, NK = DBX < PK ? DBX : PK;
+    uint32_t ar[NR], atl[NK > 0 ? NK : 1], ath[NK > 0 ? NK : 1];
+#pragma unroll
+    for (int t = 0; t < NR; ++t) ar[t] = lds0 + OFFX + ln * RBX + (((2 * t + half) ^ bswz<CPRX>(ln)) << 4);
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const uint32_t tb = lds0 + OFFT + (li & 1) * 8 + trow * RBT;
+      atl[k] = tb + (((4 * k + tcl) ^ bswz<CPRT>(trow)) << 4);
+      ath[k] = tb + 8 * RBT + (((4 * k + tcl) ^ bswz<CPRT>(trow + 8)) << 4);
+    }
+    auto row_frag = [&](auto stagec, int t) {
+      return read_k_frag(ar[t % PR] + decltype(stagec)::value * C::STAGE_BYTES + (t / PR) * (PR * 32));
+    };
+    // fragment n of the accumulation: 16-row step n / DBX, block n % DBX
+    auto acc_frag = [&](auto stagec, int n) {
+      const int t = n / (DBX > 0 ? DBX : 1), k = n % (DBX > 0 ? DBX : 1);
+      const uint32_t o = decltype(stagec)::value * C::STAGE_BYTES + t * 16 * RBT + (k / PK) * (PK * 64);
+      return read_tr_frag(atl[k % PK] + o, ath[k % PK] + o);
+    };
+    uint32_t e_lane = lds0 + C::E0 + w4 * 4096 + lane * 16, e_flip = C::E_BYTES;  // (the two buffers in turn)
+
+    // anything of the tile visible to this wave's rows?  everything?
+    auto visibility = [&](int o0, bool& any, bool& full) {
+      any = o0 < L_oth, full = o0 + 31 < L_oth;
+      if constexpr (C::CAUSAL) {
+        const int wd = p.window;
+        if constexpr (C::KV_SIDE) {  // own = keys j, other = queries i: visible iff i + off - window < j <= i + off
+          any = any && ow0 <= o0 + 31 + off && o0 + off - wd < ow0 + 31;
+          full = full && ow0 + 31 <= o0 + off && o0 + 31 + off - wd < ow0;
+        } else {                     // own = queries i, other = keys j
+          any = any && o0 <= ow0 + 31 + off && ow0 + off - wd < o0 + 31;
+          full = full && o0 + 31 <= ow0 + off && ow0 + 31 + off - wd < o0;
+        }
+      }
+    };
+
+    // Fragment ring: RF LDS reads in flight ahead of their MFMAs.
+    constexpr int RING = 4, RF = T < RING ? T : RING, NF = 2 * DBX, RA = NF < RING ? NF : RING;
+    bf16x8 fr[RF];  // role 0: the next tile's first row fragments, carried from one iteration to the next
+    f32x16 dp;      // role 1: dP of the next tile, carried likewise
+    auto prefetch = [&](auto stagec) {
+#pragma unroll
+      for (int n = 0; n < RF; ++n) fr[n] = row_frag(stagec, n);
+    };
+    float lg = 0.f;
+    Pos here{t_first, h_first};  // the tile this role works on
+    if constexpr (ROLE == 0 && C::LIN) lg = p.has_decay ? dt.log2_gamma[h_first] : 0.f;
+
+    // The copies of tile i + LOOK go out one instruction at a time between the MFMAs of a product: queued together
+    // they would hold up every wavefront at the compute unit's memory pipe (64 bytes per clock).
+    auto copies = [&](auto copyc, auto tc) {
+      constexpr int t = decltype(tc)::value, GAP = T / (NC + 1) > 0 ? T / (NC + 1) : 1;
+      if constexpr (t % GAP == 0 && t / GAP < NC) issue(copyc, std::integral_constant<int, t / GAP>{});
+    };
+    auto all_copies = [&](auto copyc) {
+      static_for<0, NC>([&](auto kc) { issue(copyc, kc); });
+    };
+
+    auto scores = [&](auto stagec, int o0) {
+      constexpr int ST = decltype(stagec)::value;
+      constexpr std::integral_constant<int, (ST + C::LOOK) % C::STAGES> copyc{};
+      bool any, full;
+      visibility(o0, any, full);
+      if (!any) {
+        all_copies(copyc);
+        return;
+      }
+      // (with 128 accumulator registers the row quantities are read behind the scores: 16 registers less meanwhile)
+      constexpr bool LATE = C::DB2 >= 8;
+      f32x4 nl4[4];
+      auto read_rows = [&]() {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          nl4[q] = f32x4{rq_own, rq_own, rq_own, rq_own};
+          if constexpr (C::ROWQ) nl4[q] = lds_read16(lds0 + C::ROWS0 + ST * C::ROW_BYTES + (8 * q + 4 * half) * 4);
+        }
+      };
+      if constexpr (!LATE) read_rows();
+      sched_fence();
+      f32x16 s = zero16();
+      static_for<0, T>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        s = mfma(fr[t % RF], xb[t], s);
+        if constexpr (t + RF < T) fr[t % RF] = row_frag(stagec, t + RF);
+        sched_fence();
+        copies(copyc, tc);
+      });
+      if constexpr (LATE) read_rows();
+      bf16x8 fa[RA > 0 ? RA : 1];
+#pragma unroll
+      for (int n = 0; n < RA; ++n) fa[n] = acc_frag(stagec, n);
+      sched_fence();
+      float x[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[r] = __builtin_fmaf(s[r], p.c2, C::NORM == NORM_SOFTMAX ? nl4[r / 4][r % 4] : p.b2);
+      if constexpr (C::BIAS) {
+        // register r = 4 q4 + e is (query, key) = (own row, key 8 q4 + 4 half + e of the tile) on the query side,
+        // (query 8 q4 + 4 half + e of the tile, own key) on the key side
+        const uint32_t bt = lds0 + ST * C::STAGE_BYTES + C::Y1_BYTES + C::Y2_BYTES;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          uint32_t lo, hi;
+          if constexpr (C::KV_SIDE) {
+            const int row = 8 * q4 + 4 * half + ((lane & 15) >> 2);               // the row this lane addresses
+            const int cl = 4 * w4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);    // chunk of its 4 columns
+            const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(
+                bt + row * 256 + ((cl ^ ((row & 3) << 2)) << 4) + (lane & 1) * 8));
+            const u32x2 w2 = __builtin_bit_cast(u32x2, v);
+            lo = w2[0];
+            hi = w2[1];
+          } else {
+            const int row = 32 * w4 + ln;
+            const u32x2 w2 = *reinterpret_cast<__attribute__((address_space(3))) const u32x2*>(
+                (lds_char*)(uintptr_t)(bt + row * 64 + ((q4 ^ ((row >> 2) & 3)) << 4) + 8 * half));
+            lo = w2[0];
+            hi = w2[1];
+          }
+          x[4 * q4 + 0] += __builtin_bit_cast(float, lo << 16) * p.bunit;
+          x[4 * q4 + 1] += __builtin_bit_cast(float, lo & 0xffff0000u) * p.bunit;
+          x[4 * q4 + 2] += __builtin_bit_cast(float, hi << 16) * p.bunit;
+          x[4 * q4 + 3] += __builtin_bit_cast(float, hi & 0xffff0000u) * p.bunit;
+        }
+      }
+      if (!full) {  // a hidden entry gets the exponent that makes its weight exactly 0
+        sched_fence();  // (keeps this a branch: most tiles skip it)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int oth = o0 + key_offset(r) + 4 * half;
+          bool vis = oth < L_oth;
+          if constexpr (C::CAUSAL)
+            vis = vis && (C::KV_SIDE ? own <= oth + off && oth + off - p.window < own : oth <= own + off && own + off - p.window < oth);
+          x[r] = vis ? x[r] : -INFINITY;
+        }
+        sched_fence();
+      }
+      // the weight w2 (dV), and the factor e that the partner turns dP into dS' with
+      const float dist0 = (float)(C::KV_SIDE ? o0 + off - own + 4 * half : own + off - o0 - 4 * half);
+      float w2[16], e[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if constexpr (C::NORM == NORM_SOFTMAX) {
+          w2[r] = e[r] = fast_exp2(x[r]);
+        } else if constexpr (C::NORM == NORM_SIGMOID) {
+          w2[r] = fast_rcp(1.f + fast_exp2(-x[r]));
+          e[r] = w2[r] * (1.f - w2[r]);
+        } else if constexpr (C::LIN) {  // a hidden entry has x = -inf: weight and factor 0
+          const bool vis = x[r] != -INFINITY;
+          const float dist = dist0 + (C::KV_SIDE ? 1.f : -1.f) * (float)key_offset(r);
+          const float dec = fast_exp2(lg * fmaxf(dist, 0.f));  // (visible entries have dist >= 0; <= 1 keeps 0 * dec finite)
+          const float sp = (vis ? x[r] : 0.f) * dec;           // S'
+          const float inv = nl4[r / 4][r % 4];
+          w2[r] = sp * inv;
+          e[r] = vis ? inv * dec : 0.f;
+          // abs-sum: the sign of S' travels in the (otherwise unused) sign of the factor
+          if constexpr (C::NORM == NORM_ABSSUM)
+            e[r] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, e[r]) | (__builtin_bit_cast(uint32_t, sp) & 0x80000000u));
+        } else {  // no normalization with ReLU: P = max(x, 0)
+          w2[r] = fmaxf(x[r], 0.f);
+          e[r] = x[r] > 0.f ? 1.f : 0.f;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        lds_store16(e_lane + q * 1024, f32x4{e[4 * q], e[4 * q + 1], e[4 * q + 2], e[4 * q + 3]});
+      if constexpr (C::KV_SIDE) {
+        bf16x8 wb[2] = {pack8(w2, 0), pack8(w2, 1)};
+        sched_fence();
+#pragma unroll
+        for (int n = 0; n < NF; ++n) {
+          acc[n % DBX] = mfma(fa[n % RA], wb[n / DBX], acc[n % DBX]);
+          if (n + RA < NF) fa[n % RA] = acc_frag(stagec, n + RA);
+          sched_fence();
+        }
+      }
+    };
+
+    // role 1: dP of the walk's tile in stage nextc, from row fragments through the ring f that holds the first of them
+    auto upstream = [&](auto nextc, bf16x8 (&f)[RING]) {
+      dp = zero16();
+      static_for<0, T>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        dp = mfma(f[(NF + t) % RING], xb[t], dp);
+        if constexpr (t + RING < T) f[(NF + t) % RING] = row_frag(nextc, t + RING);
+        sched_fence();
+      });
+    };
+    // role 1: dS' and the accumulation of tile n (stage stagec), then dP of the tile behind it (stage nextc)
+    auto gradients = [&](auto stagec, auto nextc, int o0) {
+      constexpr int ST = decltype(stagec)::value;
+      constexpr std::integral_constant<int, (ST + 1 + C::LOOK) % C::STAGES> copyc{};
+      bool any, full;
+      visibility(o0, any, full);
+      bf16x8 f[RING];
+      if (!any) {
+#pragma unroll
+        for (int t = 0; t < RING && t < T; ++t) f[(NF + t) % RING] = row_frag(nextc, t);
+        all_copies(copyc);
+        upstream(nextc, f);
+        return;
+      }
+      f32x4 e4[4], dl4[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) e4[q] = lds_read16(e_lane + q * 1024);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        dl4[q] = f32x4{rq_own, rq_own, rq_own, rq_own};
+        if constexpr (C::ROWQ) dl4[q] = lds_read16(lds0 + C::ROWS0 + ST * C::ROW_BYTES + 256 + (8 * q + 4 * half) * 4);
+      }
+#pragma unroll
+      for (int n = 0; n < RING; ++n) f[n] = n < NF ? acc_frag(stagec, n) : row_frag(nextc, n - NF);
+      sched_fence();
+      float w[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float e = e4[r / 4][r % 4], dl = dl4[r / 4][r % 4];
+        if constexpr (C::NORM == NORM_SOFTMAX) {
+          w[r] = e * (dp[r] - dl);
+        } else if constexpr (C::ABS) {
+          // g * delta: delta with its sign flipped where S' < 0 (abs-sum), or delta already signed by the row sum
+          const float corr = C::NORM == NORM_ABSSUM
+                                 ? __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, dl) ^ (__builtin_bit_cast(uint32_t, e) & 0x80000000u))
+                                 : dl;
+          w[r] = (dp[r] - corr) * fabsf(e);
+        } else {
+          w[r] = dp[r] * e;
+        }
+      }
+      if constexpr (C::BIAS && !C::KV_SIDE) {
+        // the bias enters S' with slope 1: its gradient is dS' itself, 4 x 4 consecutive keys of the lane's own row
+        if (p.dbias != nullptr && own < p.L_q) {
+          __bf16* drow = p.dbias + (((int64_t)b * p.H_q + ho) * p.L_q + own) * p.dbias_ld + o0 + 4 * half;
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            if (o0 + 8 * q4 + 4 * half < p.L_k) {  // (a group across the last key writes into the row's padding)
+              bf16x4 v;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = (__bf16)w[4 * q4 + e];
+              *reinterpret_cast<bf16x4*>(drow + 8 * q4) = v;
+            }
+        }
+      }
+      bf16x8 wb[2] = {pack8(w, 0), pack8(w, 1)};
+      sched_fence();
+      static_for<0, NF>([&](auto nc) {
+        constexpr int n = decltype(nc)::value, m = n + RING, GAP = NF / (NC + 1) > 0 ? NF / (NC + 1) : 1;
+        acc[n % DBX] = mfma(f[n % RING], wb[n / DBX], acc[n % DBX]);
+        if constexpr (m < NF) f[n % RING] = acc_frag(stagec, m);
+        else if constexpr (m < NF + T) f[n % RING] = row_frag(nextc, m - NF);
+        sched_fence();
+        if constexpr (n % GAP == 0 && n / GAP < NC) issue(copyc, std::integral_constant<int, n / GAP>{});
+      });
+      upstream(nextc, f);
+    };
+
+    // Everything loaded so far is consumed here once (see the copies' waits below: the compiler must not wait inside the loop).
+#pragma unroll
+    for (int t = 0; t < T; ++t) pin(xb[t]);
+    pin(rq_own);
+    auto convert_rows = [&](auto stagec) {  // the tile's statistics in LDS, as they arrived, into what the weights need
+      if constexpr (C::ROWQ && ROLE == 0) {
+        if (w4 == 0) {
+          const uint32_t a = lds0 + C::ROWS0 + decltype(stagec)::value * C::ROW_BYTES + lane * 4;
+          lds_store4(a, convert_stat(lds_read4(a)));
+        }
+      }
+    };
+    // Iteration i of the walk: tiles i and i + 1 have landed (of this wave's copies only the youngest LOOK - 2 tiles'
+    // may be in flight), the factors of tile i - 1 are written (of role 0's LDS operations only the reads of
+    // prefetch() may be in flight), and every wave is done with tile i - 2, whose stage takes tile i + LOOK.  Role 0
+    // works on tile i, role 1 on tile i - 1.
+    auto enter = [&](auto stagec, int i) {
+      constexpr int ST = decltype(stagec)::value;
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::LOOK - 2) * NC) : "memory");
+      if constexpr (ROLE == 0) asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(RF) : "memory");
+      else asm volatile("s_barrier" ::: "memory");
+      convert_rows(std::integral_constant<int, (ST + 1) % C::STAGES>{});
+      issue_rows(std::integral_constant<int, (ST + C::LOOK) % C::STAGES>{});
+    };
+    // role 0: iteration i on tile i = n; role 1: iteration n + 1 on tile n
+    auto step = [&](auto stagec, int n) {
+      constexpr int ST = decltype(stagec)::value;
+      constexpr std::integral_constant<int, (ST + 1) % C::STAGES> nextc{};
+      const int i = ROLE == 0 ? n : n + 1;
+      if constexpr (ROLE == 0) {
+        enter(stagec, i);
+        scores(stagec, here.t * C::TILE);
+      } else {
+        enter(nextc, i);
+        gradients(stagec, nextc, here.t * C::TILE);
+      }
+      advance_copies();
+      advance(here);
+      e_lane += e_flip;
+      e_flip = 0u - e_flip;
+      if constexpr (ROLE == 0) {
+        sched_fence();
+        prefetch(nextc);
+        sched_fence();
+      }
+      if constexpr (ROLE == 0 && C::LIN && C::KV_SIDE)
+        if (here.t == t_first && n + 1 < N) lg = p.has_decay ? dt.log2_gamma[here.h] : 0.f;
+    };
+    if (N > 0) {
+      static_for<0, C::LOOK>([&](auto nc) {
+        issue_rows(nc);
+        all_copies(nc);
+        advance_copies();
+      });
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      constexpr std::integral_constant<int, 0> first{};
+      convert_rows(first);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if constexpr (ROLE == 0) {
+        prefetch(first);
+        sched_fence();
+      } else {  // iteration 0
+        enter(first, 0);
+        bf16x8 f[RING];
+#pragma unroll
+        for (int t = 0; t < RING && t < T; ++t) f[(NF + t) % RING] = row_frag(first, t);
+        all_copies(std::integral_constant<int, C::LOOK>{});
+        advance_copies();
+        upstream(first, f);
+      }
+#pragma clang loop unroll(disable)
+      for (int n = 0; n < N; n += C::STAGES)
+        static_for<0, C::STAGES>([&](auto uc) {
+          if (n + decltype(uc)::value < N) step(uc, n + decltype(uc)::value);
+        });
+      if constexpr (ROLE == 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // iteration N
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no copy outlives the workgroup's LDS)
+    }
+
+    // ---- results: register r of block db is column own, row d = 32 db + 8 (r/4) + 4 half + r%4 ----
+    if (own < L_own) {
+      constexpr int D = ROLE == 0 ? C::DV : C::DQK;
+      float* o = nullptr;
+      if constexpr (ROLE == 0) o = p.dV + (((int64_t)b * p.H_kv + hk) * p.L_k + own) * D;
+      else o = (C::KV_SIDE ? p.dK + ((int64_t)b * p.H_kv + hk) * p.L_k * D : p.dQ + ((int64_t)b * p.H_q + ho) * p.L_q * D) + (int64_t)own * D;
+      const float f = ROLE == 0 ? 1.f : p.scale;
+#pragma unroll
+      for (int db = 0; db < DBX; ++db)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4*>(o + 32 * db + 8 * q + 4 * half) =
+              f32x4{acc[db][4 * q] * f, acc[db][4 * q + 1] * f, acc[db][4 * q + 2] * f, acc[db][4 * q + 3] * f};
+    }
+  };
+  if (wave < 4) walk(std::integral_constant<int, 0>{});
+  else walk(std::integral_constant<int, 1>{});
 }
 
 }  // namespace ae

@@ -6,16 +6,29 @@
 namespace ae {
 namespace {
 
+// One wavefront per 32 own rows where two workgroups of it share a CU (without a bias tensor: 64/64, and the query side
+// of 128/128), a pair of wavefronts elsewhere (the measurements stand at attn_bwd_pair_kernel).
+template <int DQK, int DV, int NORM, bool CAUSAL, int OUT, bool BIAS>
+struct Choice {
+  static constexpr bool PAIR = BIAS || !(DQK == 64 || (DQK == 128 && DV == 128 && OUT == BWD_DQ));
+  typedef BwdPairCfg<DQK, DV, NORM, CAUSAL, OUT, BIAS> C;
+  static void launch(unsigned grid, const BwdParams& p, const DecayTable& dt, hipStream_t s) {
+    if constexpr (PAIR) hipLaunchKernelGGL(attn_bwd_pair_kernel<C>, dim3(grid), dim3(C::THREADS), 0, s, p, dt);
+    else hipLaunchKernelGGL((attn_bwd_kernel<BwdCfg<DQK, DV, NORM, CAUSAL, OUT>>), dim3(grid), dim3(256), 0, s, p, dt);
+  }
+};
+
 template <int DQK, int DV, int NORM, bool CAUSAL, int OUT, bool BIAS>
 hipError_t launch_one(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
-  typedef BwdCfg<DQK, DV, NORM, CAUSAL, OUT, BIAS> C;
+  typedef Choice<DQK, DV, NORM, CAUSAL, OUT, BIAS> K;
+  typedef typename K::C C;  // (both kernels own 128 rows per workgroup)
   // whole sets of `together` groups per XCD (the kernel's mapping): sets x together x 8 XCDs x workgroups per group
   const int L = C::KV_SIDE ? p.L_k : p.L_q;
   const int64_t per_group = (int64_t)((L + C::OWN - 1) / C::OWN) * (C::KV_SIDE ? 1 : p.g);
   const int64_t rounds = ((int64_t)p.B * p.H_kv + 7) / 8, tg = p.together[C::KV_SIDE ? 1 : 0];
   const int64_t grid = ((rounds + tg - 1) / tg) * tg * 8 * per_group;
   if (tg < 1 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attn_bwd_kernel<C>, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p, dt);
+  K::launch((unsigned)grid, p, dt, s);
   return hipGetLastError();
 }
 

@@ -39,7 +39,7 @@
 // see GatedParams::reverse) and walks cut into segments (GatedParams::nseg).
 #include <hip/hip_runtime.h>
 
-#include "attn_bwd_kernel.hpp"  // bswz, read_tr_frag
+#include "attn_bwd_kernel.hpp"  // bswz, read_tr_frag, dma4, lds_store4
 #include "gated.hpp"
 
 #ifndef AE_GATED_QS_128
@@ -73,23 +73,6 @@ struct GCfg {
 __device__ __forceinline__ u32x2 lds_read8(uint32_t addr) {
   return *reinterpret_cast<__attribute__((address_space(3))) const u32x2*>((lds_char*)(uintptr_t)addr);
 }
-__device__ __forceinline__ void lds_write4(uint32_t addr, float v) {
-  *reinterpret_cast<__attribute__((address_space(3))) float*>((lds_char*)(uintptr_t)addr) = v;
-}
-
-// 64 lanes x 4 bytes from base + byte_off (per lane) to LDS bytes [lds_addr, lds_addr + 256)
-__device__ __forceinline__ void dma4(const void* base_uniform, uint32_t byte_off, uint32_t lds_addr_uniform) {
-  base_uniform = uniform_ptr(base_uniform);
-  lds_addr_uniform = __builtin_amdgcn_readfirstlane(lds_addr_uniform);
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dword %1, %2"
-      :
-      : "s"(lds_addr_uniform), "v"(byte_off), "s"(base_uniform)
-      : "memory", "m0");
-}
-
 // x of the lane that the control word selects, 0 where it selects none or the masks switch the lane off
 template <int CTRL, int ROW_MASK, int BANK_MASK>
 __device__ __forceinline__ float dpp_f(float x) {
@@ -318,9 +301,9 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
     // one per score.  ref_j - b_j is at most four log-decays: with the bound of 20 above u_j stays finite.
     {
       const float ref = dpp_f<0x00, 0xf, 0xf>(bcum - la);  // the sum in front of lane (lane & ~3): quad broadcast of the exclusive sum
-      lds_write4(gate0 + lane * 4, ref);
-      lds_write4(gate0 + 256 + lane * 4, g * __expf(ref - bcum));
-      lds_write4(gate0 + 512 + lane * 4, g * __expf(b_last - bcum));
+      lds_store4(gate0 + lane * 4, ref);
+      lds_store4(gate0 + 256 + lane * 4, g * __expf(ref - bcum));
+      lds_store4(gate0 + 512 + lane * 4, g * __expf(b_last - bcum));
     }
     if (more && turn == 1) issue_chunk(c + 2);
     float bi0, bi1;  // b of tokens ln and 32 + ln

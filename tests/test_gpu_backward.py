@@ -126,6 +126,18 @@ def test_backward_lengths(A, Lq, Lk, mask):
     run_case(A, Workload(f"len{Lq}x{Lk}{mask}relu", 45, 1, 2, 1, Lq, Lk, 64, 64, mask=mask, norm="none", score_mod="relu", scale=0.02))
 
 
+@pytest.mark.parametrize("dims", [(128, 128), (128, 256), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("Lq,Lk", [(32, 129), (33, 32), (65, 160), (95, 96), (161, 97), (192, 127)])
+def test_backward_pairs_of_wavefronts(A, dims, Lq, Lk):
+    """The kernels with a pair of wavefronts per 32 own rows walk tiles of 32 rows through a ring of five stages: walks
+    of one to six tiles per query head, three query heads one after the other (the copies run three tiles ahead, over
+    the seam between heads), last tiles of 1, 31 and 32 rows, own rows that fill one to four of the pairs; with a row
+    statistic and without, the factor of the abs-sum form carrying the sign of the score."""
+    for kw in (dict(), dict(norm="sigmoid", score_mod="bias", bias=-3.0, mask="causal"),
+               dict(score_mod="head_decay", norm="abssum", mask="causal", decay=True)):
+        run_case(A, Workload("bwd_pairs", 46, 1, 3, 1, Lq, Lk, dims[0], dims[1], **kw))
+
+
 @pytest.mark.parametrize("window", [1, 7, 64, 100, 333, 5000])
 @pytest.mark.parametrize("Lq,Lk", [(300, 333), (333, 300), (700, 700)])
 def test_backward_sliding_window(A, window, Lq, Lk):
