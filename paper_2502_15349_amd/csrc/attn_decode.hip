@@ -1,12 +1,12 @@
 // Decoding shapes (paper Table 2, the decoding row: one query row per head against thousands of keys; Section 4.1,
 // online row-norm interface: the state of two key blocks is combined by the rule of the online softmax).  One query row
 // has no use for a 256-row tile: the work is reading K and V once, so the kernel is a stream.  A workgroup owns one
-// (batch, k/v head, key range) and up to G of the q heads that share it, and its four wavefronts take the range's keys
+// (batch, k/v head, key range) and up to G of the q heads that share it, and its W wavefronts take the range's keys
 // four at a time; 16 lanes share a key, each holding D / 16 consecutive elements of its row (one 16-byte load per lane
 // for 128 elements, an 8-byte one more for 192), so every load instruction of a wavefront reads four whole rows,
 // contiguous in memory.  The dot product is D / 16 multiply-adds and four data-parallel-primitive adds inside the row of
 // 16 lanes; every group of 16 lanes keeps an online softmax state of its own per q head (reference, sum, D_v / 16 output
-// columns), and the 16 states of a workgroup are combined at the end into one normalised row: the result, where the keys
+// columns), and the 4 W states of a workgroup are combined at the end into one normalised row: the result, where the keys
 // are one range (DIRECT), or else a partial row and its log-sum-exp, which attn_merge_kernel combines over the key
 // ranges.  Loads run one block of kDecodeDepth steps ahead of the arithmetic (registers only, no LDS tiles, no barrier
 // inside the loop).
@@ -15,8 +15,8 @@
 // arithmetic per key and head, about 30 instructions for 16 lanes (64 x 32/8 heads x 1000 keys, 128/128: 4.8 TB/s).
 // Scoring the heads of a block of keys first and rescaling once per block saves a quarter of them and costs the registers
 // of a second workgroup per compute unit (16 x 32/8 x 5003: 88 -> 99 us).  Keys in one range were the 256-row
-// attention kernel's before, one workgroup per q head: 16 x 32/8 heads x 5003 keys 144 -> 87 us, 64 x 32/8 x 1000
-// 154 -> 54 us, 1 x 16 x 8192 (192/128) 127 -> 93 us, 1 x 12 x 300 (64/64) 8.1 -> 5.0 us.
+// attention kernel's before, one workgroup per q head: 16 x 32/8 heads x 5003 keys 144 -> 75 us, 64 x 32/8 x 1000
+// 154 -> 54 us, 1 x 16 x 8192 (192/128) 127 -> 73 us, 1 x 12 x 300 (64/64) 8.1 -> 5.0 us.
 #include <hip/hip_runtime.h>
 
 #include "attn_decode.hpp"
@@ -67,11 +67,11 @@ __device__ __forceinline__ float row16_sum(float x) {
 constexpr float kNone = -1e30f;  // "no key yet": finite, so that differences of references stay finite
 
 // G: q heads of the k/v head that one workgroup serves, all from one pass over the keys.
-template <int DQK, int DV, int G, bool DIRECT>
-__global__ __launch_bounds__(256) void attn_decode_kernel(const DecodeParams p) {
+template <int DQK, int DV, int G, bool DIRECT, int W>
+__global__ __launch_bounds__(64 * W) void attn_decode_kernel(const DecodeParams p) {
   constexpr int NK = DQK / 16, NV = DV / 16;
   // one q head: the states of all rows of 16 lanes meet in LDS; more: one per wavefront, folded in registers before
-  constexpr int NS = G == 1 ? 16 : 4;
+  constexpr int NS = G == 1 ? 4 * W : W;
   __shared__ float red[NS][G][DV + 2];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, sub = lane & 15;
   // (key range, batch, k/v head) fastest: the workgroups of one k/v head that serve different q heads are a multiple
@@ -104,9 +104,9 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const DecodeParams p) 
     for (int e = 0; e < NV; ++e) acc[h][e] = 0.f;
   }
 
-  // step s of this wavefront: keys j_begin + (4 s + wave) * 4 + grp
-  const int n_steps = (j_end - j_begin + 15) / 16;
-  auto key_of = [&](int s) { return j_begin + (4 * s + wave) * 4 + grp; };
+  // step s of this wavefront: keys j_begin + (W s + wave) * 4 + grp
+  const int n_steps = (j_end - j_begin + 4 * W - 1) / (4 * W);
+  auto key_of = [&](int s) { return j_begin + (W * s + wave) * 4 + grp; };
   RowPiece<NK> kbuf[2][kDecodeDepth];
   RowPiece<NV> vbuf[2][kDecodeDepth];
   auto issue = [&](int s0, int which) {
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const DecodeParams p) 
     }
   }
 
-  // ---- the 16 states of the workgroup (4 wavefronts x 4 rows of lanes) into one per q head ----
+  // ---- the states of the workgroup (W wavefronts x 4 rows of lanes) into one per q head ----
 #pragma unroll
   for (int h = 0; h < G; ++h) {
     if constexpr (G > 1) {
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const DecodeParams p) 
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < n_heads * DV; i += 256) {
+  for (int i = threadIdx.x; i < n_heads * DV; i += 64 * W) {
     const int h = i / DV, d = i % DV;
     float M = kNone;
 #pragma unroll
@@ -204,15 +204,27 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const DecodeParams p) 
   }
 }
 
+template <int DQK, int DV, int G, int W>
+hipError_t launch_waves(const DecodeParams& p, unsigned grid, hipStream_t s) {
+  if (p.n_splits > 1) hipLaunchKernelGGL((attn_decode_kernel<DQK, DV, G, false, W>), dim3(grid), dim3(64 * W), 0, s, p);
+  else hipLaunchKernelGGL((attn_decode_kernel<DQK, DV, G, true, W>), dim3(grid), dim3(64 * W), 0, s, p);
+  return hipGetLastError();
+}
+
 template <int DQK, int DV, int G>
 hipError_t launch_heads(const DecodeParams& p, hipStream_t s) {
   const int64_t grid = p.rows / p.g * ((p.g + G - 1) / G) * p.n_splits;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   DecodeParams q = p;
   q.units = (int)(p.rows / p.g * p.n_splits);
-  if (p.n_splits > 1) hipLaunchKernelGGL((attn_decode_kernel<DQK, DV, G, false>), dim3((unsigned)grid), dim3(256), 0, s, q);
-  else hipLaunchKernelGGL((attn_decode_kernel<DQK, DV, G, true>), dim3((unsigned)grid), dim3(256), 0, s, q);
-  return hipGetLastError();
+  // Eight wavefronts instead of four keep more loads in flight and halve a workgroup's walk; taken where all workgroups
+  // are resident at once either way (two of eight wavefronts per compute unit with one q head, one with more) and a
+  // range has at least two blocks of steps for each.  Measured (us, 4 / 8 / 16 wavefronts): 16 x 32/8 heads x 5003 keys
+  // 87 / 75 / 76, 32 x 32/8 x 8192 214 / 198 / 530, 1 x 32/8 x 32768 (6 ranges) 75 / 59 / 58, 1 x 16 x 8192 (192/128, one
+  // range) 94 / 73 / 69; against it 64 x 32/8 x 1000 (512 workgroups of four heads) 55 / 60, 1 x 12 x 300 (64/64) 5.0 / 5.2,
+  // and 192-element keys read from HBM by three quarters of the chip (1 x 16 x 8192, 12 ranges) 18.9 / 19.9.
+  const bool wide = grid <= (G == 1 ? 512 : 256) && p.split_keys >= 320 && !(G == 1 && DQK == 192 && grid >= 128);
+  return wide ? launch_waves<DQK, DV, G, 8>(q, (unsigned)grid, s) : launch_waves<DQK, DV, G, 4>(q, (unsigned)grid, s);
 }
 
 // As many q heads per workgroup as leave a workgroup for every compute unit: sharing the keys saves reads, but a stream
