@@ -79,7 +79,12 @@ __device__ __forceinline__ float dpp_f(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROW_MASK, BANK_MASK, false));
 }
 
-template <class C>
+// STATE_ONLY: no outputs, only the state update is walked (see GatedParams::state_only): no queries are fetched, the state is
+// not packed for the read-out.  As a run-time flag of the one kernel the walk fetched and packed them all the same: the segmented
+// call of 1 x 80 heads x 8192 tokens, 128/64 (both walks and the combination), took 144 us then and takes 138 us now.  The full
+// form keeps its (there never set) flag around the outputs: without these branches the compiler moves the state update's loads
+// in between the query blocks, and 8 x 32 heads x 8192 tokens, 128/128, take 588 us for 585.
+template <class C, bool STATE_ONLY>
 __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt) {
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
@@ -160,7 +165,7 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
     for (int i = 0; i < NQ; ++i) {
       const int nb = wave + i * C::WAVES;
       const uint32_t off = whole ? qoff[i] : qoff_t[i];  // (only the last chunk can be short)
-      dma16(qc, off, base + nb * 1024);
+      if constexpr (!STATE_ONLY) dma16(qc, off, base + nb * 1024);
       dma16(kc, off, base + C::Q_BYTES + nb * 1024);
     }
 #pragma unroll
@@ -209,6 +214,7 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
 #pragma unroll
   for (int j = 0; j < 2; ++j) vt0[j] = 2 * C::Q_BYTES + hw * C::V_BYTES + tr_lane(std::integral_constant<int, C::CPRV>{}, vblk, j);
 
+  constexpr int NDMA = STATE_ONLY ? C::NDMA - NQ : C::NDMA;
   float seg_b = 0.f;  // sum of the log-decays walked so far
   issue_chunk(0);
   if (n_chunks > 1) issue_chunk(1);
@@ -253,9 +259,9 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
     // landed and every wave is done with chunk c - 1, whose stage chunk c + 2 may now overwrite.
     {
       const bool nxt = c + 1 < n_chunks, prv = c > 0;
-      const bool st = prv && !p.state_only;  // (a walk that only updates the state stores nothing)
-      if (nxt && st) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::NDMA + C::NST) : "memory");
-      else if (nxt) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::NDMA) : "memory");
+      const bool st = prv && !STATE_ONLY && !p.state_only;  // (a walk that only updates the state stores nothing)
+      if (nxt && st) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NDMA + C::NST) : "memory");
+      else if (nxt) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NDMA) : "memory");
       else if (st) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::NST) : "memory");
       else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       asm volatile("s_barrier" ::: "memory");
@@ -301,8 +307,10 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
     // one per score.  ref_j - b_j is at most four log-decays: with the bound of 20 above u_j stays finite.
     {
       const float ref = dpp_f<0x00, 0xf, 0xf>(bcum - la);  // the sum in front of lane (lane & ~3): quad broadcast of the exclusive sum
-      lds_store4(gate0 + lane * 4, ref);
-      lds_store4(gate0 + 256 + lane * 4, g * __expf(ref - bcum));
+      if constexpr (!STATE_ONLY) {
+        lds_store4(gate0 + lane * 4, ref);
+        lds_store4(gate0 + 256 + lane * 4, g * __expf(ref - bcum));
+      }
       lds_store4(gate0 + 512 + lane * 4, g * __expf(b_last - bcum));
     }
     if (more && turn == 1) issue_chunk(c + 2);
@@ -319,7 +327,7 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float x = H[db][r];
-          hp[db][r / 8][r % 8] = (__bf16)x;
+          if constexpr (!STATE_ONLY) hp[db][r / 8][r % 8] = (__bf16)x;
           H[db][r] = x * dec;
         }
     }
@@ -428,7 +436,7 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
     }
 
     };
-    if (!p.state_only) {
+    if (!STATE_ONLY && !p.state_only) {
       if (C::QS == 1 || ib == 0) query_block(std::integral_constant<int, 0>{});
       if (more && turn == 2) issue_chunk(c + 2);
       if (C::QS == 1 || ib == 1) query_block(std::integral_constant<int, 1>{});
@@ -476,7 +484,9 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
 template <int DQK, int DV, int HPW = 1, int QS = 2>
 hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
   typedef GCfg<DQK, DV, HPW, QS> C;
-  hipLaunchKernelGGL(gated_recurrent_kernel<C>, dim3((unsigned)(p.B * p.H / HPW * p.nseg)), dim3(C::THREADS), 0, s, p, dt);
+  const dim3 grid((unsigned)(p.B * p.H / HPW * p.nseg));
+  if (p.state_only) hipLaunchKernelGGL((gated_recurrent_kernel<C, true>), grid, dim3(C::THREADS), 0, s, p, dt);
+  else hipLaunchKernelGGL((gated_recurrent_kernel<C, false>), grid, dim3(C::THREADS), 0, s, p, dt);
   return hipGetLastError();
 }
 
