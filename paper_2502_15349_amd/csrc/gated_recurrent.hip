@@ -82,8 +82,8 @@ __device__ __forceinline__ float dpp_f(float x) {
 // STATE_ONLY: no outputs, only the state update is walked (see GatedParams::state_only): no queries are fetched, the state is
 // not packed for the read-out.  As a run-time flag of the one kernel the walk fetched and packed them all the same: the segmented
 // call of 1 x 80 heads x 8192 tokens, 128/64 (both walks and the combination), took 144 us then and takes 138 us now.  The full
-// form keeps its (there never set) flag around the outputs: without these branches the compiler moves the state update's loads
-// in between the query blocks, and 8 x 32 heads x 8192 tokens, 128/128, take 588 us for 585.
+// form keeps its (there never set) flag around the outputs: without these branches the compiler orders the chunk differently,
+// and 8 x 32 heads x 8192 tokens, 128/128, take 588 us for 585 (cause not looked into further).
 template <class C, bool STATE_ONLY>
 __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt) {
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
