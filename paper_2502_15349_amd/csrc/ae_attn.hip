@@ -83,6 +83,8 @@ struct MergeParams {
 // nothing else, so the first kBatch partial rows are requested together with the log-sum-exps that weigh them.  With the
 // rows requested behind the weights, and one column per lane after the other, a decoding step of 16 q heads on 8192 keys
 // (192/128, 12 ranges) took 22.8 us for its two kernels; so it takes 18.6.
+// A range without keys has the log-sum-exp -inf and weight 0, a NaN one makes the row and its statistic NaN; told apart by their
+// bits, since device code is compiled under the assumption that no NaN occurs, which a comparison of floats may use.
 template <int VEC>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeParams p) {
   typedef float vec __attribute__((ext_vector_type(VEC)));
@@ -105,6 +107,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeParams p) {
   vec first[kBatch];
 #pragma unroll
   for (int u = 0; u < kBatch; ++u) first[u] = load(u);
+  auto empty = [](float x) { return __builtin_bit_cast(uint32_t, x) == 0xff800000u; };  // -inf
   float mx = -INFINITY;
 #pragma unroll
   for (int k = 0; k < kSlots; ++k) mx = fmaxf(mx, lc[k]);
@@ -112,15 +115,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeParams p) {
   for (int s = 32; s >= 1; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s));
   float tot = 0.f;
 #pragma unroll
-  for (int k = 0; k < kSlots; ++k) tot += lc[k] == -INFINITY ? 0.f : __expf(lc[k] - mx);
+  for (int k = 0; k < kSlots; ++k) tot += empty(lc[k]) ? 0.f : __expf(lc[k] - mx);
 #pragma unroll
   for (int s = 32; s >= 1; s >>= 1) tot += __shfl_xor(tot, s);
-  const float lse = mx == -INFINITY ? -INFINITY : mx + __logf(tot);
+  const float lse = __builtin_bit_cast(uint32_t, tot) == 0 ? -INFINITY : mx + __logf(tot);  // (0: every range is empty)
   vec acc = 0.f;
 #pragma unroll
   for (int k = 0; k < kSlots; ++k) {
     if (64 * k >= p.n_splits) break;
-    const float w = lc[k] == -INFINITY ? 0.f : __expf(lc[k] - lse);  // the weights of this slot's ranges
+    const float w = empty(lc[k]) ? 0.f : __expf(lc[k] - lse);  // the weights of this slot's ranges
     for (int c0 = 64 * k; c0 < 64 * (k + 1) && c0 < p.n_splits; c0 += kBatch) {
       vec part[kBatch];
 #pragma unroll

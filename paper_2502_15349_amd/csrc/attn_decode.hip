@@ -188,7 +188,9 @@ __global__ __launch_bounds__(64 * W) void attn_decode_kernel(const DecodeParams 
       L += f * red[s][h][DV + 1];
       o += f * red[s][h][d];
     }
-    const bool any = L > 0.f;
+    // no visible key leaves the sum at +0; a NaN sum (a NaN or infinite score) makes the row NaN.  The two are told apart by
+    // their bits: device code is compiled under the assumption that no NaN occurs, which a comparison of floats may use
+    const bool any = __builtin_bit_cast(uint32_t, L) != 0;
     o = any ? o / L : 0.f;
     const float lse = any ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f : -INFINITY;
     const int64_t row = (int64_t)b * p.H_q + h0 + h;

@@ -442,6 +442,51 @@ def test_decoding_rows_shared_keys(A, dims, B, H_kv, g, Lk, splits):
                 assert np.abs(got[b, h] - ref).max() <= 1e-3, (b, h)
 
 
+def decode_run(A, w, Q, K, V, splits):
+    """Output and row statistic on the host."""
+    dev = torch.device("cuda:0")
+    st = torch.zeros((w.B, w.H_q, 1), dtype=torch.float32, device=dev)
+    O = A.run_workload(w, Q.to(dev), K.to(dev), V.to(dev), stats=st, kv_splits=splits)
+    torch.cuda.synchronize()
+    return O.cpu(), st.cpu()
+
+
+@pytest.mark.parametrize("splits", [0, 3])
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+def test_decoding_rows_that_are_not_finite(A, dims, splits):
+    """A score that is NaN or +inf makes its row NaN, output and statistic, and no other row; a score of -inf has weight
+    0.  (64 groups of four q heads unsplit: a workgroup serves two of them, the other half of the group another one.)"""
+    w = Workload("decode_nan", 24, 64, 8, 2, 1, 700, dims[0], dims[1])
+    Q, K, V = make_inputs(w)
+    O0, st0 = decode_run(A, w, Q, K, V, splits)
+    Kn = K.clone()
+    Kn[3, 1, 655, 5] = float("nan")
+    O, st = decode_run(A, w, Q, Kn, V, splits)
+    hit = torch.zeros((64, 8), dtype=torch.bool)
+    hit[3, 4:] = True
+    assert torch.isnan(O[hit]).all() and torch.isnan(st[hit]).all()
+    assert torch.equal(O[~hit], O0[~hit]) and torch.equal(st[~hit], st0[~hit])
+    Kn = K.clone()
+    Kn[7, 0, 300, 2] = float("inf")  # the score has the sign of the q head's element
+    O, st = decode_run(A, w, Q, Kn, V, splits)
+    pos = Q[7, :4, 0, 2].float() > 0
+    assert 0 < int(pos.sum()) < 4
+    hit = torch.zeros((64, 8), dtype=torch.bool)
+    hit[7, :4] = pos
+    assert torch.isnan(O[hit]).all() and torch.isnan(st[hit]).all()
+    keep = [j for j in range(700) if j != 300]
+    ref = oracle_run(Workload("decode_nan", 24, 1, 8, 2, 1, 699, dims[0], dims[1]), Q[7:8], K[7:8][:, :, keep], V[7:8][:, :, keep])
+    err = np.abs(O[7, :4][~pos].double().numpy() - ref[0, :4][~pos.numpy()]).max()
+    assert err <= 1e-4 * np.abs(ref).max()
+    Qn = Q.clone()
+    Qn[9, 2, 0, 0] = float("nan")
+    O, st = decode_run(A, w, Qn, K, V, splits)
+    hit = torch.zeros((64, 8), dtype=torch.bool)
+    hit[9, 2] = True
+    assert torch.isnan(O[hit]).all() and torch.isnan(st[hit]).all()
+    assert torch.equal(O[~hit], O0[~hit]) and torch.equal(st[~hit], st0[~hit])
+
+
 def test_split_keys_decode_full_size(A):
     """The paper's decoding row (Table 2: one query row, 16 heads, 192/128) at 8k keys, batch 8."""
     w = Workload("decode", 20, 8, 16, 16, 1, 8192, 192, 128, mask="causal")
