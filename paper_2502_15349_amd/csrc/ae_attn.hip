@@ -76,6 +76,7 @@ struct MergeParams {
   const float* ws_lse;  // [n_splits, rows]
   void* O;              // fp32 or bf16, strides os[] in elements
   float* stats;         // optional [rows]
+  float bias;           // constant bias that the ranges' log-sum-exps leave out
   int n_splits, B, H_q, L_q, D_v, out_bf16;
   int64_t os[3];
 };
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeParams p) {
     if (p.out_bf16) static_cast<__bf16*>(p.O)[obase + e] = (__bf16)acc[e];
     else static_cast<float*>(p.O)[obase + e] = acc[e];
   }
-  if (p.stats != nullptr && lane == 0) p.stats[r] = lse;
+  if (p.stats != nullptr && lane == 0) p.stats[r] = lse + p.bias;
 }
 
 constexpr int kMaxDevices = 64;
@@ -464,7 +465,7 @@ static ae_status_t forward_impl(const ae_attn_t* h, const void* Q, const void* K
     q.n_splits = p.n_splits;
     q.split_keys = p.n_splits > 1 ? p.split_tiles * h->kernel->block_n : p.L_k;
     q.c = h->desc.scale * 1.4426950408889634f;
-    q.b2 = (h->desc.score_mod == AE_MOD_BIAS ? h->desc.bias : 0.f) * 1.4426950408889634f;
+    q.bias = h->desc.score_mod == AE_MOD_BIAS ? h->desc.bias : 0.f;
     e = ae::launch_decode(q, h->desc.D_qk, h->desc.D_v, static_cast<hipStream_t>(stream));
   }
   for (int sl = 0; sl < h->v_slices && e == hipSuccess && !decode; ++sl) {
@@ -487,6 +488,7 @@ static ae_status_t forward_impl(const ae_attn_t* h, const void* Q, const void* K
     m.L_q = p.L_q;
     m.D_v = h->desc.D_v;
     m.out_bf16 = p.out_bf16;
+    m.bias = decode && h->desc.score_mod == AE_MOD_BIAS ? h->desc.bias : 0.f;
     for (int a = 0; a < 3; ++a) m.os[a] = p.os[a];
     const int64_t rows = (int64_t)p.B * p.H_q * p.L_q;
     const dim3 grid((unsigned)((rows + 3) / 4));

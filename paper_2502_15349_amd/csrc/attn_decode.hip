@@ -126,8 +126,7 @@ __global__ __launch_bounds__(64 * W) void attn_decode_kernel(const DecodeParams 
         float x = 0.f;
 #pragma unroll
         for (int e = 0; e < NK; ++e) x = __builtin_fmaf(q[h][e], elem(kbuf[which][u], e), x);
-        x = row16_sum(x) + p.b2;
-        x = live ? x : kNone;
+        x = live ? row16_sum(x) : kNone;
         const float mn = fmaxf(m[h], x);
         const float alpha = __builtin_amdgcn_exp2f(m[h] - mn);          // 1 while the reference stands
         const float w = live ? __builtin_amdgcn_exp2f(x - mn) : 0.f;
@@ -192,7 +191,10 @@ __global__ __launch_bounds__(64 * W) void attn_decode_kernel(const DecodeParams 
     // their bits: device code is compiled under the assumption that no NaN occurs, which a comparison of floats may use
     const bool any = __builtin_bit_cast(uint32_t, L) != 0;
     o = any ? o / L : 0.f;
-    const float lse = any ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f : -INFINITY;
+    // (a constant bias is in every weight of the row and leaves the output alone: only the statistic sees it, here where the
+    // keys are one range, in the merge kernel where they are several.  Added to the scores instead, a bias of 1e6 costs their
+    // fraction and one beyond -7e29 the whole row)
+    const float lse = any ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f + (DIRECT ? p.bias : 0.f) : -INFINITY;
     const int64_t row = (int64_t)b * p.H_q + h0 + h;
     if constexpr (!DIRECT) {
       p.ws_o[((int64_t)c * p.rows + row) * DV + d] = o;

@@ -487,6 +487,20 @@ def test_decoding_rows_that_are_not_finite(A, dims, splits):
     assert torch.equal(O[~hit], O0[~hit]) and torch.equal(st[~hit], st0[~hit])
 
 
+@pytest.mark.parametrize("bias", [1e6, -1e30, 3e38])
+@pytest.mark.parametrize("splits", [0, 3])
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+def test_decoding_rows_constant_bias_cancels(A, dims, splits, bias):
+    """A constant bias is in every weight of a row alike: the output is that without it, bit for bit, whatever its size, and the
+    statistic that without it plus the bias."""
+    base = Workload("decode_bias", 25, 2, 8, 2, 1, 700, dims[0], dims[1], mask="causal")
+    Q, K, V = make_inputs(base)
+    O0, st0 = decode_run(A, base, Q, K, V, splits)
+    O, st = decode_run(A, Workload("decode_bias", 25, 2, 8, 2, 1, 700, dims[0], dims[1], mask="causal", score_mod="bias", bias=bias), Q, K, V, splits)
+    assert torch.equal(O, O0)
+    assert torch.equal(st, st0 + np.float32(bias))
+
+
 def test_split_keys_decode_full_size(A):
     """The paper's decoding row (Table 2: one query row, 16 heads, 192/128) at 8k keys, batch 8."""
     w = Workload("decode", 20, 8, 16, 16, 1, 8192, 192, 128, mask="causal")
