@@ -126,7 +126,9 @@ __global__ __launch_bounds__(64 * W) void attn_decode_kernel(const DecodeParams 
         float x = 0.f;
 #pragma unroll
         for (int e = 0; e < NK; ++e) x = __builtin_fmaf(q[h][e], elem(kbuf[which][u], e), x);
-        x = live ? row16_sum(x) : kNone;
+        x = row16_sum(x);
+        asm volatile("" : "+v"(x));  // (or the compiler makes a branch of the selection, with the multiply-adds inside)
+        x = live ? x : kNone;
         const float mn = fmaxf(m[h], x);
         const float alpha = __builtin_amdgcn_exp2f(m[h] - mn);          // 1 while the reference stands
         const float w = live ? __builtin_amdgcn_exp2f(x - mn) : 0.f;
