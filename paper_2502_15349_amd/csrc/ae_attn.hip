@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeParams p) {
   const int lane = threadIdx.x & 63;
   const float* wo = p.ws_o + r * p.D_v + VEC * lane;
   const int64_t range_stride = rows * p.D_v;
-  // (ranges past the last one repeat it: their weight is 0)
+  // (ranges past the last one repeat its address, and count as zeros: weight 0 alone would turn an infinite value into NaN)
   auto load = [&](int c) { return *reinterpret_cast<const vec*>(wo + min(c, p.n_splits - 1) * range_stride); };
   // the ranges' log-sum-exp: range c in lane c % 64, slot c / 64 (at most kMaxSplits ranges), all loads at once
   float lc[kSlots];
@@ -108,6 +108,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeParams p) {
   vec first[kBatch];
 #pragma unroll
   for (int u = 0; u < kBatch; ++u) first[u] = load(u);
+  __builtin_amdgcn_sched_barrier(0);  // (the compiler moves them behind the reductions of the log-sum-exps otherwise)
   auto empty = [](float x) { return __builtin_bit_cast(uint32_t, x) == 0xff800000u; };  // -inf
   float mx = -INFINITY;
 #pragma unroll
@@ -121,16 +122,22 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeParams p) {
   for (int s = 32; s >= 1; s >>= 1) tot += __shfl_xor(tot, s);
   const float lse = __builtin_bit_cast(uint32_t, tot) == 0 ? -INFINITY : mx + __logf(tot);  // (0: every range is empty)
   vec acc = 0.f;
+  auto add = [&](const vec (&part)[kBatch], float w, int c0) {
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) acc += __shfl(w, (c0 + u) & 63) * (c0 + u < p.n_splits ? part[u] : 0.f);
+  };
+  // the weights of slot k's ranges
+  auto weight = [&](int k) { return empty(lc[k]) ? 0.f : __expf(lc[k] - lse); };
+  add(first, weight(0), 0);
 #pragma unroll
   for (int k = 0; k < kSlots; ++k) {
     if (64 * k >= p.n_splits) break;
-    const float w = empty(lc[k]) ? 0.f : __expf(lc[k] - lse);  // the weights of this slot's ranges
-    for (int c0 = 64 * k; c0 < 64 * (k + 1) && c0 < p.n_splits; c0 += kBatch) {
+    const float w = weight(k);
+    for (int c0 = k == 0 ? kBatch : 64 * k; c0 < 64 * (k + 1) && c0 < p.n_splits; c0 += kBatch) {
       vec part[kBatch];
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) part[u] = c0 == 0 ? first[u] : load(c0 + u);
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) acc += __shfl(w, (c0 + u) & 63) * part[u];
+      for (int u = 0; u < kBatch; ++u) part[u] = load(c0 + u);
+      add(part, w, c0);
     }
   }
   const int i = (int)(r % p.L_q), hq = (int)((r / p.L_q) % p.H_q), b = (int)(r / ((int64_t)p.L_q * p.H_q));

@@ -501,6 +501,21 @@ def test_decoding_rows_constant_bias_cancels(A, dims, splits, bias):
     assert torch.equal(st, st0 + np.float32(bias))
 
 
+@pytest.mark.parametrize("j", [0, 600])
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+def test_merge_keeps_an_infinite_value(A, dims, j):
+    """An infinite value in the first or the last of three key ranges makes its column infinite, not NaN (the merge kernel takes
+    eight ranges at a time, five of them past the last one), and no other column."""
+    w = Workload("merge_inf", 26, 1, 4, 2, 1, 700, dims[0], dims[1])
+    Q, K, V = make_inputs(w)
+    O0, st0 = decode_run(A, w, Q, K, V, 3)
+    V[0, 1, j, 9] = float("inf")
+    O, st = decode_run(A, w, Q, K, V, 3)
+    assert (O[0, 2:, 0, 9] == float("inf")).all()
+    O[0, 2:, 0, 9] = O0[0, 2:, 0, 9]
+    assert torch.equal(O, O0) and torch.equal(st, st0)
+
+
 def test_split_keys_decode_full_size(A):
     """The paper's decoding row (Table 2: one query row, 16 heads, 192/128) at 8k keys, batch 8."""
     w = Workload("decode", 20, 8, 16, 16, 1, 8192, 192, 128, mask="causal")
