@@ -536,8 +536,11 @@ __device__ __forceinline__ float lds_read4(uint32_t addr) {
 __device__ __forceinline__ void lds_store4(uint32_t addr, float v) {
   *reinterpret_cast<__attribute__((address_space(3))) float*>((lds_char*)(uintptr_t)addr) = v;
 }
-__device__ __forceinline__ void lds_store16(uint32_t addr, f32x4 v) {
-  *reinterpret_cast<__attribute__((address_space(3))) f32x4*>((lds_char*)(uintptr_t)addr) = v;
+__device__ __forceinline__ void lds_store16(uint32_t addr, u32x4 v) {
+  *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((lds_char*)(uintptr_t)addr) = v;
+}
+__device__ __forceinline__ u32x4 lds_read16u(uint32_t addr) {
+  return *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>((lds_char*)(uintptr_t)addr);
 }
 
 template <class C>
@@ -847,14 +850,16 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
       }
       // the weight w2 (dV), and the factor e that the partner turns dP into dS' with
       const float dist0 = (float)(C::KV_SIDE ? o0 + off - own + 4 * half : own + off - o0 - 4 * half);
-      float w2[16], e[16];
+      float w2[16];
+      uint32_t e[16];  // (as bits: with ReLU it is a mask)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         if constexpr (C::NORM == NORM_SOFTMAX) {
-          w2[r] = e[r] = fast_exp2(x[r]);
+          w2[r] = fast_exp2(x[r]);
+          e[r] = __builtin_bit_cast(uint32_t, w2[r]);
         } else if constexpr (C::NORM == NORM_SIGMOID) {
           w2[r] = fast_rcp(1.f + fast_exp2(-x[r]));
-          e[r] = w2[r] * (1.f - w2[r]);
+          e[r] = __builtin_bit_cast(uint32_t, w2[r] * (1.f - w2[r]));
         } else if constexpr (C::LIN) {  // a hidden entry has x = -inf: weight and factor 0
           const bool vis = x[r] != -INFINITY;
           const float dist = dist0 + (C::KV_SIDE ? 1.f : -1.f) * (float)key_offset(r);
@@ -862,18 +867,18 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
           const float sp = (vis ? x[r] : 0.f) * dec;           // S'
           const float inv = nl4[r / 4][r % 4];
           w2[r] = sp * inv;
-          e[r] = vis ? inv * dec : 0.f;
+          e[r] = __builtin_bit_cast(uint32_t, vis ? inv * dec : 0.f);
           // abs-sum: the sign of S' travels in the (otherwise unused) sign of the factor
           if constexpr (C::NORM == NORM_ABSSUM)
-            e[r] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, e[r]) | (__builtin_bit_cast(uint32_t, sp) & 0x80000000u));
+            e[r] |= __builtin_bit_cast(uint32_t, sp) & 0x80000000u;
         } else {  // no normalization with ReLU: P = max(x, 0)
           w2[r] = fmaxf(x[r], 0.f);
-          e[r] = x[r] > 0.f ? 1.f : 0.f;
+          e[r] = x[r] > 0.f ? 0xffffffffu : 0u;  // dS' = dP or 0
         }
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        lds_store16(e_lane + q * 1024, f32x4{e[4 * q], e[4 * q + 1], e[4 * q + 2], e[4 * q + 3]});
+        lds_store16(e_lane + q * 1024, u32x4{e[4 * q], e[4 * q + 1], e[4 * q + 2], e[4 * q + 3]});
       if constexpr (C::KV_SIDE) {
         bf16x8 wb[2] = {pack8(w2, 0), pack8(w2, 1)};
         sched_fence();
@@ -910,9 +915,10 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
         upstream(nextc, f);
         return;
       }
-      f32x4 e4[4], dl4[4];
+      u32x4 e4[4];
+      f32x4 dl4[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) e4[q] = lds_read16(e_lane + q * 1024);
+      for (int q = 0; q < 4; ++q) e4[q] = lds_read16u(e_lane + q * 1024);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         dl4[q] = f32x4{rq_own, rq_own, rq_own, rq_own};
@@ -924,19 +930,31 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
       float w[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float e = e4[r / 4][r % 4], dl = dl4[r / 4][r % 4];
+        const uint32_t ebits = e4[r / 4][r % 4];
+        const float e = __builtin_bit_cast(float, ebits), dl = dl4[r / 4][r % 4];
         if constexpr (C::NORM == NORM_SOFTMAX) {
           w[r] = e * (dp[r] - dl);
         } else if constexpr (C::ABS) {
           // g * delta: delta with its sign flipped where S' < 0 (abs-sum), or delta already signed by the row sum
           const float corr = C::NORM == NORM_ABSSUM
-                                 ? __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, dl) ^ (__builtin_bit_cast(uint32_t, e) & 0x80000000u))
+                                 ? __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, dl) ^ (ebits & 0x80000000u))
                                  : dl;
           w[r] = (dp[r] - corr) * fabsf(e);
+        } else if constexpr (C::NORM == BWD_NORM_NONE_RELU) {
+          const float d = dp[r];  // (a scalar first: the bit cast of a vector element came out as an undefined register)
+          w[r] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, d) & ebits);
         } else {
           w[r] = dp[r] * e;
         }
       }
+      if constexpr (C::LIN)
+        if (!full) {  // the factor of a hidden entry is 0: its gradient is 0 whatever dP is, where the product with an infinite one is NaN
+          sched_fence();
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            w[r] = __builtin_bit_cast(float, (e4[r / 4][r % 4] & 0x7fffffffu) != 0 ? __builtin_bit_cast(uint32_t, w[r]) : 0u);
+          sched_fence();
+        }
       if constexpr (C::BIAS && !C::KV_SIDE) {
         // the bias enters S' with slope 1: its gradient is dS' itself, 4 x 4 consecutive keys of the lane's own row
         if (p.dbias != nullptr && own < p.L_q) {

@@ -297,3 +297,63 @@ def test_backward_bias_tensor(A, dims, norm, mask):
         errB = np.abs(gB - rB) / np.maximum(np.abs(rB).max(axis=-1, keepdims=True), 1.0)
         print(f"{w.name} {tuple(bt.shape)} dBias: max_abs {errB.max():.3e} mean_abs {errB.mean():.3e}", flush=True)
         assert np.isfinite(gB).all() and errB.max() <= 3e-2 and errB.mean() <= MEAN_ABS
+
+
+SELECTING = {
+    "retention": dict(score_mod="head_decay", norm="abssum", mask="causal", decay=True),
+    "abs_of_sum": dict(norm="abs_of_sum", score_mod="bias", bias=3.0, mask="causal"),
+    "decay_nonorm": dict(score_mod="head_decay", norm="none", mask="causal", decay=True, scale=0.01),
+    "none_window": dict(norm="none", mask="sliding_window", window=40, scale=0.01),
+    "none_bias_tensor": dict(norm="none", score_mod="bias_tensor", mask="causal", scale=0.01),
+    "relu": dict(score_mod="relu", norm="none", scale=0.01),
+    "relu_causal": dict(score_mod="relu", norm="none", mask="causal", scale=0.01),
+}
+
+
+@pytest.mark.parametrize("dims", DIMS, ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("form", sorted(SELECTING))
+def test_backward_hidden_entries_stay_zero(A, dims, form):
+    """The retention, no-normalization and ReLU forms select the score gradient 0 of a hidden (or clipped) entry: an
+    infinite value row changes dQ of no query that does not see it (or clips it), an infinite row of dO changes dK of no
+    key hidden from that query, not by a bit."""
+    if form == "none_bias_tensor" and dims == (128, 256):
+        pytest.skip("the bias tensor does not come with head dims 128/256")
+    dev = torch.device("cuda:0")
+    w = Workload("bwd_select", 47, 1, 4, 2, 150, 163, dims[0], dims[1], **SELECTING[form])
+    Q, K, V = (t.to(dev) for t in make_inputs(w))
+    dO = make_grad(w).to(dev)
+    bt = torch.zeros((1, 1, 150, 168), dtype=torch.bfloat16, device=dev)[..., :163] if form == "none_bias_tensor" else None
+    stats = torch.empty((1, 4, 150), dtype=torch.float32, device=dev) if w.norm in ("abssum", "abs_of_sum") else None
+    O = A.run_workload(w, Q, K, V, stats=stats, bias_tensor=bt)
+
+    def grads(V, dO):
+        out = A.attention_backward(Q, K, V, O if stats is not None else None, dO, stats, scale=w.scale_value, score_mod=w.score_mod,
+                                   bias=w.bias, gamma=w.gamma(), norm=w.norm, mask=w.mask, window=w.window, bias_tensor=bt,
+                                   want_dbias=bt is not None)
+        torch.cuda.synchronize()
+        return out
+
+    i = torch.arange(150, device=dev).view(-1, 1) + 13
+    j = torch.arange(163, device=dev).view(1, -1)
+    zero = torch.zeros((1, 4, 150, 163), dtype=torch.bool, device=dev)
+    if w.mask != "none":
+        zero |= j > i
+    if w.mask == "sliding_window":
+        zero |= j <= i - w.window
+    if w.score_mod == "relu":
+        zero |= (Q.double() @ K.double().repeat_interleave(2, 1).transpose(2, 3)) < 0
+    clean = grads(V, dO)
+    Vx = V.clone()
+    Vx[0, :, 100, 3] = float("inf")
+    got = grads(Vx, dO)
+    free = zero[:, :, :, 100]
+    assert free.any() and torch.equal(got[0][free], clean[0][free])
+    assert not torch.isfinite(got[0][~free]).all()
+    if bt is not None:
+        assert torch.equal(got[3][free], clean[3][free])
+    dOx = dO.clone()
+    dOx[0, ::2, 60, 3] = float("inf")  # one q head of each group
+    got = grads(V, dOx)
+    free = zero[:, ::2, 60, :]
+    assert free.any() and torch.equal(got[1][free], clean[1][free])
+    assert not torch.isfinite(got[1][~free]).all()
