@@ -6,29 +6,37 @@
 namespace ae {
 namespace {
 
-// One wavefront per 32 own rows where two workgroups of it share a CU (without a bias tensor: 64/64, and the query side
-// of 128/128), a pair of wavefronts elsewhere (the measurements stand at attn_bwd_pair_kernel).
-template <int DQK, int DV, int NORM, bool CAUSAL, int OUT, bool BIAS>
-struct Choice {
-  static constexpr bool PAIR = BIAS || !(DQK == 64 || (DQK == 128 && DV == 128 && OUT == BWD_DQ));
-  typedef BwdPairCfg<DQK, DV, NORM, CAUSAL, OUT, BIAS> C;
-  static void launch(unsigned grid, const BwdParams& p, const DecayTable& dt, hipStream_t s) {
-    if constexpr (PAIR) hipLaunchKernelGGL(attn_bwd_pair_kernel<C>, dim3(grid), dim3(C::THREADS), 0, s, p, dt);
-    else hipLaunchKernelGGL((attn_bwd_kernel<BwdCfg<DQK, DV, NORM, CAUSAL, OUT>>), dim3(grid), dim3(256), 0, s, p, dt);
-  }
-};
+// One wavefront per 32 own rows where two workgroups of it fit a CU (64/64, and the query side of 128/128 without a bias
+// tensor), a pair of wavefronts elsewhere (the measurements stand at attn_bwd_pair_kernel).  64/64 with a bias tensor has
+// both: what two workgroups per CU give needs more of them than one for every CU of an XCD.  Whole backward pass, one
+// wavefront / pair, us: 1 x 6 heads x 1023 x 1060 (8 and 9 workgroups per XCD) 73 / 68, 2 x 12 x 1023 x 1060 (24 and 27) 83 / 80;
+// 1 x 6 x 4096 x 4133 (32 and 33) 342 / 398, 8 x 16 x 512 x 549 (64 and 80) 96 / 113, 8 x 16 x 2048 causal (256) 744 / 919,
+// without the bias's gradient 364 / 514.
+constexpr int64_t kUnitsPerXcd = 32;
 
 template <int DQK, int DV, int NORM, bool CAUSAL, int OUT, bool BIAS>
 hipError_t launch_one(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
-  typedef Choice<DQK, DV, NORM, CAUSAL, OUT, BIAS> K;
-  typedef typename K::C C;  // (both kernels own 128 rows per workgroup)
+  constexpr bool kKvSide = OUT == BWD_DKV;
+  constexpr int kOwn = 128;  // (both kernels own 128 rows per workgroup)
   // whole sets of `together` groups per XCD (the kernel's mapping): sets x together x 8 XCDs x workgroups per group
-  const int L = C::KV_SIDE ? p.L_k : p.L_q;
-  const int64_t per_group = (int64_t)((L + C::OWN - 1) / C::OWN) * (C::KV_SIDE ? 1 : p.g);
-  const int64_t rounds = ((int64_t)p.B * p.H_kv + 7) / 8, tg = p.together[C::KV_SIDE ? 1 : 0];
+  const int L = kKvSide ? p.L_k : p.L_q;
+  const int64_t per_group = (int64_t)((L + kOwn - 1) / kOwn) * (kKvSide ? 1 : p.g);
+  const int64_t rounds = ((int64_t)p.B * p.H_kv + 7) / 8, tg = p.together[kKvSide ? 1 : 0];
   const int64_t grid = ((rounds + tg - 1) / tg) * tg * 8 * per_group;
   if (tg < 1 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  K::launch((unsigned)grid, p, dt, s);
+  constexpr bool kOneFits = DQK == 64 || (DQK == 128 && DV == 128 && !kKvSide && !BIAS);
+  bool pair = !kOneFits;
+  if constexpr (kOneFits && BIAS) pair = rounds * per_group <= kUnitsPerXcd;
+  if constexpr (kOneFits) {
+    typedef BwdCfg<DQK, DV, NORM, CAUSAL, OUT, BIAS> C;
+    static_assert(C::OWN == kOwn, "");
+    if (!pair) hipLaunchKernelGGL(attn_bwd_kernel<C>, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p, dt);
+  }
+  if constexpr (!kOneFits || BIAS) {
+    typedef BwdPairCfg<DQK, DV, NORM, CAUSAL, OUT, BIAS> C;
+    static_assert(C::OWN == kOwn, "");
+    if (pair) hipLaunchKernelGGL(attn_bwd_pair_kernel<C>, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p, dt);
+  }
   return hipGetLastError();
 }
 

@@ -299,6 +299,44 @@ def test_backward_bias_tensor(A, dims, norm, mask):
         assert np.isfinite(gB).all() and errB.max() <= 3e-2 and errB.mean() <= MEAN_ABS
 
 
+@pytest.mark.parametrize("B,H,H_kv,Lq,Lk", [(4, 64, 64, 90, 129), (5, 52, 52, 129, 90), (4, 128, 64, 128, 70), (4, 240, 60, 33, 500)])
+@pytest.mark.parametrize("norm", ["softmax", "sigmoid", "none"])
+def test_backward_bias_tensor_by_number_of_workgroups(A, B, H, H_kv, Lq, Lk, norm):
+    """64/64 with a bias tensor: a side of at most 32 workgroups per XCD runs on pairs of wavefronts, a larger one on single
+    ones.  Workgroups per XCD on the query / key side of the four shapes: 32 and 64, 66 and 33, 64 and 32, 120 and 120; of one
+    batch entry alone at most 32 (the form that the oracle's test above covers).  The two forms sum in one order: the whole
+    batch gives the bits of its entries alone, but for sigmoid, whose factors dP P (1 - P) are multiplied in another order:
+    2^-23 relative, which turns one bf16 rounding of dS' (2^-9) in 2^13; the root of the mean square over all is
+    2^-9 2^-6.5 = 2e-5, held to ten times that."""
+    from paper_2502_15349_amd.workloads import make_bias_tensor
+    dev = torch.device("cuda:0")
+    w = Workload("bwd_bias_many", 64, B, H, H_kv, Lq, Lk, 64, 64, score_mod="bias_tensor", norm=norm, mask="causal" if Lk >= Lq else "none",
+                 scale=(0.01 if norm == "none" else None))
+    print(f"case {w}", flush=True)
+    Q, K, V = (t.to(dev) for t in make_inputs(w))
+    dO = make_grad(w).to(dev)
+    bt = make_bias_tensor(w, False, True)
+    btd = torch.zeros(bt.shape[:3] + ((Lk + 7) // 8 * 8,), dtype=torch.bfloat16, device=dev)
+    btd[..., :Lk] = bt.to(dev)
+    btv = btd[..., :Lk]
+    stats = torch.empty((B, H, Lq), dtype=torch.float32, device=dev) if norm == "softmax" else None
+    O = A.run_workload(w, Q, K, V, stats=stats, bias_tensor=btv)
+
+    def grads(sl):
+        out = A.attention_backward(Q[sl], K[sl], V[sl], O[sl], dO[sl], None if stats is None else stats[sl], scale=w.scale_value,
+                                   score_mod="bias_tensor", norm=norm, mask=w.mask, bias_tensor=btv, want_dbias=True)
+        torch.cuda.synchronize()
+        return [g.float() for g in out]
+    whole, parts = grads(slice(0, B)), [grads(slice(b, b + 1)) for b in range(B)]
+    for n, name in enumerate(("dQ", "dK", "dV", "dBias")):
+        ref = torch.cat([q[n] for q in parts])
+        assert torch.isfinite(ref).all()
+        if norm == "sigmoid":
+            assert (whole[n] - ref).norm() <= 2e-4 * ref.norm(), name
+        else:
+            assert torch.equal(whole[n], ref), name
+
+
 SELECTING = {
     "retention": dict(score_mod="head_decay", norm="abssum", mask="causal", decay=True),
     "abs_of_sum": dict(norm="abs_of_sum", score_mod="bias", bias=3.0, mask="causal"),
