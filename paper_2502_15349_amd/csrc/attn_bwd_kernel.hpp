@@ -688,18 +688,11 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
     bf16x8 xb[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) xb[t] = *reinterpret_cast<const bf16x8*>(x + (2 * t + half) * 8);
-    float rq_own = ROLE == 0 ? (C::LIN ? 1.f : -INFINITY) : 0.f;  // query side: the row quantity of the lane's own row
-    if constexpr (!C::KV_SIDE && C::ROWS) {
-      if (own < p.L_q) {
-        const int64_t r = ((int64_t)b * p.H_q + ho) * p.L_q + own;
-        if constexpr (ROLE == 0) {
-          const float st = p.lse[r];
-          if constexpr (C::ABS) rq_own = fast_rcp(fmaxf(fabsf(st), 1.f));
-          else rq_own = st == -INFINITY ? -INFINITY : p.b2 - st * 1.4426950408889634f;
-        } else {
-          rq_own = p.delta[r];
-        }
-      }
+    // query side: the row quantity of the lane's own row (role 0: converted behind the first copies)
+    constexpr bool OWN_ROW = !C::KV_SIDE && C::ROWS;
+    float rq_own = ROLE == 0 ? (OWN_ROW ? (C::ABS ? 0.f : -INFINITY) : C::LIN ? 1.f : -INFINITY) : 0.f;
+    if constexpr (OWN_ROW) {
+      if (own < p.L_q) rq_own = (ROLE == 0 ? p.lse : p.delta)[((int64_t)b * p.H_q + ho) * p.L_q + own];
     }
     auto convert_stat = [&](float v) {
       return C::ABS ? fast_rcp(fmaxf(fabsf(v), 1.f)) : v == -INFINITY ? -INFINITY : p.b2 - v * 1.4426950408889634f;
@@ -1049,10 +1042,6 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
       upstream(nextc, f);
     };
 
-    // Everything loaded so far is consumed here once (see the copies' waits below: the compiler must not wait inside the loop).
-#pragma unroll
-    for (int t = 0; t < T; ++t) pin(xb[t]);
-    pin(rq_own);
     auto convert_rows = [&](auto stagec) {  // the tile's statistics in LDS, as they arrived, into what the weights need
       if constexpr (C::ROWQ && ROLE == 0) {
         if (w4 == 0) {
@@ -1103,6 +1092,16 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
         all_copies(nc);
         advance_copies();
       });
+    }
+    // The own operand, requested in front of the first copies, is consumed here once: the compiler must not wait for it inside
+    // the loop, where its count would wait for the copies too.  (In front of the copies the two latencies added up: 0.2 us of a
+    // pass of one to four tiles; and the abs-sum kernels of 128/256 spilled 25 to 30 registers instead of 9: 2 x 64/8 x 1024 causal
+    // 593 -> 544 us.)
+#pragma unroll
+    for (int t = 0; t < T; ++t) pin(xb[t]);
+    pin(rq_own);
+    if constexpr (OWN_ROW && ROLE == 0) rq_own = convert_stat(rq_own);
+    if (N > 0) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       constexpr std::integral_constant<int, 0> first{};
       convert_rows(first);
