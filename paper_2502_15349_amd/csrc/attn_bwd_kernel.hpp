@@ -89,7 +89,7 @@ __device__ __forceinline__ int bswz(int row) {
 constexpr int BWD_NORM_NONE_RELU = 5;
 enum : int { BWD_DQ = 0, BWD_DKV = 1 };  // the query-side kernel (dQ), the key-side kernel (dK and dV)
 
-// ---- one wavefront per 32 own rows, two workgroups per CU ----------------------------------------------------------
+// ---- one wavefront per 32 own rows ---------------------------------------------------------------------------------
 template <int DQK_, int DV_, int NORM_, bool CAUSAL_, int OUT_, bool BIAS_ = false>
 struct BwdCfg {
   static constexpr bool BIAS = BIAS_;  // S' = scale * S + bias[b, h_q, i, j]
@@ -118,8 +118,12 @@ struct BwdCfg {
   // no normalization (without ReLU) is the abs-sum form with the row factors fixed at 1 and 0: P = S', dS' = dP,
   // per-head decay included
   static constexpr bool LIN = ABS || NORM == NORM_NONE;
-  // the accumulators, the resident operands and the two score tiles leave room for the rest in 256 registers
-  static_assert(16 * (DB + DB2) + 4 * T1 + 4 * T2 + 32 + (BIAS_ ? 8 : 0) <= 176 && LDS_BYTES <= 80 * 1024, "two workgroups per CU");
+  // Two workgroups per CU (two waves per SIMD, 256 registers each) where the accumulators, the resident operands and the
+  // two score tiles leave room for the rest; one (512 registers) otherwise.
+  static constexpr bool OCC2 = 16 * (DB + DB2) + 4 * T1 + 4 * T2 + 32 + (BIAS_ ? 8 : 0) <= 176 && LDS_BYTES <= 80 * 1024;
+  // one workgroup per CU: the LDS fragments of a step are read as a batch ahead of its MFMAs
+  static constexpr bool BATCH = !OCC2 && DQK + DV <= 320;  // (beyond that the batches do not fit 512 registers)
+  static_assert(LDS_BYTES <= 160 * 1024, "a workgroup must fit LDS");
   static_assert((TILE * CPR1 / 64) % WAVES == 0 && (TILE * CPR2 / 64) % WAVES == 0, "every wave copies the same number of blocks");
 };
 
@@ -138,7 +142,7 @@ __device__ __forceinline__ bf16x8 pack8(const float (&x)[16], int t) {
 }
 
 template <class C>
-__global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_kernel(const BwdParams p, const DecayTable dt) {
+__global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(const BwdParams p, const DecayTable dt) {
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
   const uint32_t rows0 = lds0 + 2 * C::STAGE_BYTES;
@@ -377,10 +381,31 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_kernel(const BwdParams
       }
       return read_tr_frag(atl[k < C::DB ? k : 0] + kT + t * 16 * RBT, ath[k < C::DB ? k : 0] + kT + t * 16 * RBT);
     };
+    bf16x8 tr[2][C::BATCH ? C::DB + C::DB2 : 1];
+    if constexpr (C::BATCH) {
+      // One wave per SIMD: nothing else hides the LDS latency, so all fragments of a step are
+      // requested before its first MFMA, and those of the accumulation step before the elementwise
+      // step (the fences keep the compiler from sinking the reads back to their uses).
+      bf16x8 a1[C::T1], a2[C::T2];
 #pragma unroll
-    for (int t = 0; t < C::T1; ++t) s = mfma(read_k_frag(ar1[t] + kRow1), xb1[t], s);
+      for (int t = 0; t < C::T1; ++t) a1[t] = read_k_frag(ar1[t] + kRow1);
 #pragma unroll
-    for (int t = 0; t < C::T2; ++t) dp = mfma(read_k_frag(ar2[t] + kRow2), xb2[t], dp);
+      for (int t = 0; t < C::T2; ++t) a2[t] = read_k_frag(ar2[t] + kRow2);
+      sched_fence();
+#pragma unroll
+      for (int t = 0; t < C::T1; ++t) s = mfma(a1[t], xb1[t], s);
+#pragma unroll
+      for (int t = 0; t < C::T2; ++t) dp = mfma(a2[t], xb2[t], dp);
+      sched_fence();
+#pragma unroll
+      for (int k = 0; k < C::DB + C::DB2; ++k) tr[0][k] = read_acc(0, k);
+      sched_fence();
+    } else {
+#pragma unroll
+      for (int t = 0; t < C::T1; ++t) s = mfma(read_k_frag(ar1[t] + kRow1), xb1[t], s);
+#pragma unroll
+      for (int t = 0; t < C::T2; ++t) dp = mfma(read_k_frag(ar2[t] + kRow2), xb2[t], dp);
+    }
     float x[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) x[r] = __builtin_fmaf(s[r], p.c2, C::NORM == NORM_SOFTMAX ? nl4[r / 4][r % 4] : p.b2);
@@ -472,16 +497,22 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_kernel(const BwdParams
           }
       }
     }
+    if constexpr (C::BATCH) {
+      sched_fence();
+#pragma unroll
+      for (int k = 0; k < C::DB + C::DB2; ++k) tr[1][k] = read_acc(1, k);
+      sched_fence();
+    }
     // G^T += Y^T W: per 16-row step t, the DB blocks of Y1^T (dQ^T, dK^T), then (key side) the DB2 blocks of Y2^T
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const bf16x8 wb = pack8(w, t);
 #pragma unroll
-      for (int k = 0; k < C::DB; ++k) g[k] = mfma(read_acc(t, k), wb, g[k]);
+      for (int k = 0; k < C::DB; ++k) g[k] = mfma(C::BATCH ? tr[t][C::BATCH ? k : 0] : read_acc(t, k), wb, g[k]);
       if constexpr (C::HAS2) {
         const bf16x8 pb = pack8(w2, t);
 #pragma unroll
-        for (int k = 0; k < C::DB2; ++k) g2[k] = mfma(read_acc(t, C::DB + k), pb, g2[k]);
+        for (int k = 0; k < C::DB2; ++k) g2[k] = mfma(C::BATCH ? tr[t][C::BATCH ? C::DB + k : 0] : read_acc(t, C::DB + k), pb, g2[k]);
       }
     }
   };

@@ -138,6 +138,18 @@ def test_backward_pairs_of_wavefronts(A, dims, Lq, Lk):
         run_case(A, Workload("bwd_pairs", 46, 1, 3, 1, Lq, Lk, dims[0], dims[1], **kw))
 
 
+@pytest.mark.parametrize("dims", [(128, 128), (128, 256), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("Lq,Lk,window,g", [(64, 65, 500, 1), (65, 64, 500, 1), (128, 128, 500, 1), (129, 128, 500, 1), (128, 129, 500, 1), (400, 333, 7, 1), (333, 400, 33, 2),
+                                            (400, 420, 96, 1), (420, 400, 97, 1), (520, 540, 256, 1), (540, 520, 257, 1), (300, 333, 128, 2),
+                                            (333, 300, 129, 2), (300, 310, 299, 1)])
+def test_backward_short_walks(A, dims, Lq, Lk, window, g):
+    """Head dims whose registers leave room for one workgroup per CU: windows of up to 256 rows (128/256: 96), times the q
+    heads of a group on the key side, and causal walks of up to 128 (64) rows run on single wavefronts, longer ones on pairs.  Both
+    sides of each limit, windows that hide whole tiles from some waves and not from others, L_q and L_k either way."""
+    for kw in (dict(), dict(norm="sigmoid", score_mod="bias", bias=-3.0), dict(norm="none", scale=0.01)):
+        run_case(A, Workload(f"short{window}", 48, 1, g, 1, Lq, Lk, dims[0], dims[1], mask="sliding_window", window=window, **kw))
+
+
 @pytest.mark.parametrize("window", [1, 7, 64, 100, 333, 5000])
 @pytest.mark.parametrize("Lq,Lk", [(300, 333), (333, 300), (700, 700)])
 def test_backward_sliding_window(A, window, Lq, Lk):
@@ -299,23 +311,26 @@ def test_backward_bias_tensor(A, dims, norm, mask):
         assert np.isfinite(gB).all() and errB.max() <= 3e-2 and errB.mean() <= MEAN_ABS
 
 
-@pytest.mark.parametrize("B,H,H_kv,Lq,Lk", [(4, 64, 64, 90, 129), (5, 52, 52, 129, 90), (4, 128, 64, 128, 70), (4, 240, 60, 33, 500)])
+@pytest.mark.parametrize("B,H,H_kv,Lq,Lk", [(2, 64, 64, 400, 385), (3, 40, 40, 385, 520), (2, 96, 24, 260, 500), (4, 12, 12, 767, 800)])
 @pytest.mark.parametrize("norm", ["softmax", "sigmoid", "none"])
 def test_backward_bias_tensor_by_number_of_workgroups(A, B, H, H_kv, Lq, Lk, norm):
-    """64/64 with a bias tensor: a side of at most 32 workgroups per XCD runs on pairs of wavefronts, a larger one on single
-    ones.  Workgroups per XCD on the query / key side of the four shapes: 32 and 64, 66 and 33, 64 and 32, 120 and 120; of one
-    batch entry alone at most 32 (the form that the oracle's test above covers).  The two forms sum in one order: the whole
-    batch gives the bits of its entries alone, but for sigmoid, whose factors dP P (1 - P) are multiplied in another order:
-    2^-23 relative, which turns one bf16 rounding of dS' (2^-9) in 2^13; the root of the mean square over all is
-    2^-9 2^-6.5 = 2e-5, held to ten times that."""
+    """64/64 with a bias tensor: a side whose walks are 384 rows or longer (half of them with the causal mask) runs on pairs of
+    wavefronts while it has at most 32 workgroups per XCD, on single ones beyond.  Workgroups per XCD of the four shapes,
+    query side / key side: 64 / 64, 60 / 75, 72 / 24, 36 / 42; of one batch entry alone 32 / 32, 20 / 25, 36 / 12, 12 / 14.  The two
+    forms sum in one order: the whole batch gives the bits of its entries alone, but for sigmoid, whose factors
+    dP P (1 - P) are multiplied in another order: 2^-23 relative, which turns one bf16 rounding of dS' (2^-9) in 2^13; the
+    root of the mean square over all is 2^-9 2^-6.5 = 2e-5, held to ten times that.  The entries alone are held to the
+    oracle on the first group of heads."""
     from paper_2502_15349_amd.workloads import make_bias_tensor
     dev = torch.device("cuda:0")
-    w = Workload("bwd_bias_many", 64, B, H, H_kv, Lq, Lk, 64, 64, score_mod="bias_tensor", norm=norm, mask="causal" if Lk >= Lq else "none",
+    w = Workload("bwd_bias_many", 64, B, H, H_kv, Lq, Lk, 64, 64, score_mod="bias_tensor", norm=norm, mask="causal" if B == 4 else "none",
                  scale=(0.01 if norm == "none" else None))
     print(f"case {w}", flush=True)
     Q, K, V = (t.to(dev) for t in make_inputs(w))
     dO = make_grad(w).to(dev)
     bt = make_bias_tensor(w, False, True)
+    if norm == "none":
+        bt = (bt.float() * 0.01).to(torch.bfloat16)
     btd = torch.zeros(bt.shape[:3] + ((Lk + 7) // 8 * 8,), dtype=torch.bfloat16, device=dev)
     btd[..., :Lk] = bt.to(dev)
     btv = btd[..., :Lk]
@@ -335,6 +350,11 @@ def test_backward_bias_tensor_by_number_of_workgroups(A, B, H, H_kv, Lq, Lk, nor
             assert (whole[n] - ref).norm() <= 2e-4 * ref.norm(), name
         else:
             assert torch.equal(whole[n], ref), name
+    n = H // H_kv
+    ref = attention_backward(Q[:1, :n].cpu(), K[:1, :1].cpu(), V[:1, :1].cpu(), dO[:1, :n].cpu(), scale=w.scale_value, score_mod="bias_tensor",
+                             norm=norm, mask=w.mask, bias_tensor=bt[:, :n])
+    for name, g, r in zip(("dQ", "dK", "dV"), (whole[0][:1, :n], whole[1][:1, :1], whole[2][:1, :1]), ref):
+        check(g.cpu().double().numpy(), r, f"{w.name} {name}")
 
 
 SELECTING = {
