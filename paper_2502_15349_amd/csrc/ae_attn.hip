@@ -737,21 +737,29 @@ int32_t ae_attn_version(void) { return 1; }
 // of that kernel holds 256 heads, so larger B * H take one launch per batch entry.
 // Segments for a walk of L tokens by `workgroups` workgroups of the single-pass recurrent kernel (each segment is walked
 // twice, the first time for its state only, a third of the time): as many as one workgroup per compute unit allows --
-// one more and the last few workgroups take a second round as long as the first -- and none shorter than two chunks.
+// one more and the last few workgroups take a second round as long as the first -- and of at least two chunks of 64 tokens,
+// but for the last one, which may be shorter.
 // Measured (us, segments: time): 40 workgroups x 8192 tokens (Mamba2, 1 x 80 heads) 1: 473, 5: 163, 6: 142, 7: 206;
 // 64 x 4096 (128/128) 3: 141, 4: 118, 5: 168; 96 x 8192 1: 478, 2: 394, 3: 535; 160 x 8192 1: 494, 2: 775; 16 x 2048 4: 60,
-// 8: 40, 16: 34; 8 x 2000 (64/64) 3: 47, 8: 25, 16: 22; 32 x 520 1: 38, 4: 36, 8: 31; 16 x 300 1: 15, 3: 22.  Two segments pay
-// for the two further launches from about 2048 tokens on (64 x 768 1: 37, 2: 40).  nseg = 1: not cut.
+// 8: 40, 16: 34; 8 x 2000 (64/64) 3: 47, 8: 25, 16: 22.
 constexpr int64_t kSegmentedBelow = 129;  // workgroups: from here on a second segment is a second round
-static void gated_segments(int64_t workgroups, int L, int* nseg, int* seg_len) {
+static int64_t most_segments(int64_t workgroups, int L) {
+  return workgroups < kSegmentedBelow ? std::min<int64_t>(256 / workgroups, L / 128) : 1;
+}
+static void cut_segments(int64_t n, int L, int* nseg, int* seg_len) {  // nseg = 1: not cut
   *nseg = 1;
   *seg_len = 0;
-  if (workgroups >= kSegmentedBelow || L < 512) return;
-  int64_t n = std::min<int64_t>(256 / workgroups, L / 128);
-  if (n < 2 || (n == 2 && L < 2048)) return;
-  const int len = (int)(((L + n - 1) / n + 63) / 64 * 64);
-  *seg_len = len;
-  *nseg = (L + len - 1) / len;
+  if (n < 2) return;
+  *seg_len = (int)(((L + n - 1) / n + 63) / 64 * 64);
+  *nseg = (L + *seg_len - 1) / *seg_len;
+}
+// From which length on the two further launches pay against the uncut walk; the fewer segments the chip has room for, the later
+// (us, cut / uncut): 32 workgroups x 512 tokens 30 / 33; 64 x 512 34.9 / 33.6, 64 x 700 41.3 / 44.0; 85 x 700 48.0 / 44.2, 85 x 900
+// 53.6 / 58.1; 86 x 1152 68.3 / 69.0, 128 x 1024 68.9 / 62.6, 128 x 1408 85.4 / 84.1 (128/128; 64/64 and Mamba2 alike).
+static void gated_segments(int64_t workgroups, int L, int* nseg, int* seg_len) {
+  const int64_t n = most_segments(workgroups, L), room = 256 / workgroups;
+  const int from = room >= 8 ? 512 : room >= 4 ? 640 : room == 3 ? 832 : 1152;
+  cut_segments(L >= from ? n : 1, L, nseg, seg_len);
 }
 
 static size_t gated_segments_ws(int B, int H, int nseg, int dqk, int dv) {
@@ -867,16 +875,22 @@ ae_status_t ae_recurrent_create(const ae_recurrent_desc_t* d, ae_recurrent_t** o
     return st;  // the message of the inner call stands
   }
   h->ws_bytes = (size_t)d->B * d->H * h->n_chunks * d->D_qk * d->D_v * 2;  // one bf16 state per chunk
-  // Measured (8 x 32 heads x 8192 tokens, 128/128): one workgroup per (batch, head) walking the whole sequence with
-  // the state on chip beats the two-kernel form once there is about a workgroup per compute unit; with fewer pairs
-  // the walk is cut into segments, and only short sequences of few heads keep the chunk-parallel form.
-  h->single_pass = ae::gated_supported(d->D_qk, d->D_v) && (int64_t)d->B * d->H >= kSegmentedBelow;
-  h->nseg = 1;
-  h->seg_len = 0;
-  if (!h->single_pass && ae::gated_supported(d->D_qk, d->D_v)) {
-    gated_segments((int64_t)d->B * d->H, d->L, &h->nseg, &h->seg_len);
-    h->ws_bytes = std::max(h->ws_bytes, gated_segments_ws(d->B, d->H, h->nseg, d->D_qk, d->D_v));
-  }
+  // Three forms.  One workgroup per (batch, head) walking the whole sequence with the state on chip, once a second segment
+  // would be a second round of workgroups (8 x 32 heads x 8192 tokens, 128/128: 0.59 ms against 0.98 in two kernels); below 192
+  // pairs not for a sequence of one chunk, which is a single launch of the attention kernel (160 pairs x 100 tokens 9.5 us, the
+  // walk 12.1).  Fewer pairs: the walk cut into segments, or the chunk-parallel kernels.  These are three launches where the
+  // last chunk is short and two where it is not; so below 1024 tokens the segments take the former (64 pairs x 700 tokens in chunks
+  // of 256 41 against 56 us) and not the latter (64 x 768 41 against 32), from there on both (85 x 1024 58 / 62) -- but where the
+  // chip has room for two segments only, not up to five whole chunks (128 x 1024 in chunks of 256 69 against 60 us, x 1536 90 / 89,
+  // in chunks of 64 70 / 133).
+  const int64_t pairs = (int64_t)d->B * d->H;
+  const bool walks = ae::gated_supported(d->D_qk, d->D_v);
+  h->single_pass = walks && (pairs >= 192 || (pairs >= kSegmentedBelow && h->n_chunks > 1));
+  const int64_t n = walks ? most_segments(pairs, d->L) : 1;
+  const bool whole = h->tail_len == 0;
+  const int from = n == 2 ? (whole && h->n_chunks <= 5 ? 1536 : 1024) : whole ? 1024 : 513;
+  cut_segments(d->L >= from ? n : 1, d->L, &h->nseg, &h->seg_len);
+  h->ws_bytes = std::max(h->ws_bytes, gated_segments_ws(d->B, d->H, h->nseg, d->D_qk, d->D_v));
   *out = h;
   return AE_OK;
 }

@@ -114,8 +114,8 @@ def test_strong_decay_and_no_decay(A):
 @pytest.mark.parametrize("kind", ["gated_retention", "mamba2"])
 @pytest.mark.parametrize("L", [1061, 2560])
 def test_segmented_walk(A, dqk, dv, H, H_qk, kind, L):
-    # few heads, a long sequence: ae_gated_forward_segmented cuts the walks into segments (2 and 5 here; a ragged
-    # last one), with a state handed in and the final state handed back; against the oracle's single walk
+    # few heads, a long sequence: ae_gated_forward_segmented cuts the walks into segments (6 and 20 here, the
+    # last one short), with a state handed in and the final state handed back; against the oracle's single walk
     Q, K, V, la, kg = inputs(820 + L % 5, 1, H, H_qk, L, dqk, dv, kind)
     g = torch.Generator().manual_seed(77)
     h0 = torch.randn((1, H, dqk, dv), generator=g, dtype=torch.float32)

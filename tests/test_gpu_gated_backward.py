@@ -158,7 +158,7 @@ def test_grouped_query_key_heads(A, dqk, dv):
 @pytest.mark.parametrize("kind", ["gated_retention", "mamba2"])
 @pytest.mark.parametrize("L", [1061, 2560])
 def test_few_heads_long_sequence(A, dqk, dv, H, H_qk, kind, L):
-    # shapes whose walks the library cuts into segments (2 and 5 here, a ragged last one), forwards and backwards
+    # shapes whose walks the library cuts into segments (6 and 20 here, the last one short), forwards and backwards
     Q, K, V, la, kg, dO = inputs(920 + L % 5, 1, H, H_qk, L, dqk, dv, kind)
     scale = 1.0 / math.sqrt(dqk)
     got = run(A, Q, K, V, la, kg, dO, scale)

@@ -60,8 +60,17 @@ def test_recurrent_matches_oracle(A, D, L, chunk):
     _check(O.cpu().double().numpy(), ref, w.name)
 
 
-def test_many_heads_take_one_launch_per_batch_entry(A):
-    # B * H beyond the decay table of the intra-chunk kernel: the batch entries are launched one by one
+def form(A, B, H, L, D, chunk):
+    """What the workspace tells of the form that a call takes: "segments" (their states in fp32), or "uncut" (a bf16 state per
+    chunk: the chunk-parallel form, or, with many (batch, head) pairs, the whole walk, which leaves it untouched)."""
+    h = A.ae_recurrent_create(B=B, H=H, L=L, D_qk=D, D_v=D, chunk=chunk, scale=0.1, gamma=[0.9] * H)
+    need = A.ae_recurrent_workspace_bytes(h)
+    A.ae_recurrent_destroy(h)
+    return "segments" if need > B * H * ((L + chunk - 1) // chunk) * D * D * 2 else "uncut"
+
+
+def test_many_heads(A):
+    # B * H beyond the 256 entries of the decay table of the intra-chunk kernel: one workgroup per (batch, head) walks it whole
     w = _workload("rec_many_heads", 791, 5, 64, 200, 64)
     Q, K, V = make_inputs(w)
     gam = _gammas(64)
@@ -73,20 +82,56 @@ def test_many_heads_take_one_launch_per_batch_entry(A):
         _check(O[b, h], ref, f"{w.name} b{b} h{h}")
 
 
-def test_chunk_sizes_agree_and_workspace_is_reusable(A):
-    # the same inputs through every chunk size (different cuts of the same sum), the workspace handed in and reused
-    w = _workload("rec_chunks", 792, 1, 4, 1000, 128)
+@pytest.mark.parametrize("B,H,L,D", [(1, 4, 500, 128), (2, 48, 1000, 64)])
+def test_chunk_sizes_agree_and_workspace_is_reusable(A, B, H, L, D):
+    # the same inputs through every chunk size (different cuts of the same sum), the workspace handed in and reused, on
+    # shapes that every chunk size takes in the chunk-parallel form
+    w = _workload("rec_chunks", 792, B, H, L, D)
     Q, K, V = make_inputs(w)
     dev = torch.device("cuda:0")
     Qd, Kd, Vd = Q.to(dev), K.to(dev), V.to(dev)
-    gam = _gammas(4)
-    ref = oracle_recurrent(Q.float().numpy(), K.float().numpy(), V.float().numpy(), scale=0.09, gamma=gam)
-    ws = torch.empty(1 << 24, dtype=torch.uint8, device=dev)
+    gam = _gammas(H)
+    heads = [(b, h) for b in range(B) for h in range(H)][::max(1, B * H // 6)]
+    ref = [retention_recurrent_head(Q[b, h].float().numpy(), K[b, h].float().numpy(), V[b, h].float().numpy(), scale=0.09, gamma_h=gam[h])
+           for b, h in heads]
+    ws = torch.empty(1 << 26, dtype=torch.uint8, device=dev)
+    outs = []
     for chunk in (64, 128, 256, 64):
+        assert form(A, B, H, L, D, chunk) == "uncut"
         print(f"case {w.name} chunk {chunk}", flush=True)
         O = A.retention_recurrent(Qd, Kd, Vd, scale=0.09, gamma=gam, chunk=chunk, workspace=ws)
         torch.cuda.synchronize()
-        _check(O.cpu().double().numpy(), ref, f"{w.name} chunk {chunk}")
+        for (b, h), r in zip(heads, ref):
+            _check(O[b, h].cpu().double().numpy(), r, f"{w.name} chunk {chunk} b{b} h{h}")
+        outs.append(O)
+    assert torch.equal(outs[0], outs[3]) and not torch.equal(outs[0], outs[1]) and not torch.equal(outs[1], outs[2])
+
+
+# Both sides of the lines between the forms: one chunk or two with 129 to 191 (batch, head) pairs, a whole or a short last
+# chunk, two segments or chunks
+@pytest.mark.parametrize("B,H,L,D,chunk,takes", [(1, 129, 64, 64, 64, "uncut"), (1, 129, 65, 128, 64, "uncut"), (3, 50, 256, 128, 256, "uncut"),
+                                                 (3, 50, 257, 64, 256, "uncut"), (1, 8, 512, 128, 256, "uncut"), (1, 8, 513, 64, 256, "segments"),
+                                                 (1, 16, 768, 128, 256, "uncut"), (1, 85, 800, 64, 256, "segments"),
+                                                 (1, 86, 1024, 64, 256, "uncut"), (1, 86, 1024, 64, 128, None),
+                                                 (2, 64, 1280, 64, 256, "uncut"), (2, 64, 1536, 64, 256, None)])
+def test_lines_between_the_forms(A, B, H, L, D, chunk, takes):
+    assert takes in (None, form(A, B, H, L, D, chunk))  # (None: two segments, whose states need less than those of the chunks)
+    w = _workload("rec_forms", 796, B, H, L, D)
+    Q, K, V = make_inputs(w)
+    gam = _gammas(H)
+    dev = torch.device("cuda:0")
+    g = torch.Generator().manual_seed(796)
+    h0 = torch.randn((B, H, D, D), generator=g, dtype=torch.float32)
+    for h_in in (None, h0):
+        print(f"case {w.name} {takes} {B}x{H}x{L} state {h_in is not None}", flush=True)
+        O, hN = A.retention_recurrent(Q.to(dev), K.to(dev), V.to(dev), scale=0.09, gamma=gam, chunk=chunk,
+                                      h_in=None if h_in is None else h_in.to(dev), return_state=True)
+        torch.cuda.synchronize()
+        for b, h in {(0, 0), (B - 1, H // 2), (0, H - 1), (B - 1, 7)}:
+            ref, hs = retention_recurrent_head(Q[b, h].float().numpy(), K[b, h].float().numpy(), V[b, h].float().numpy(), scale=0.09,
+                                               gamma_h=gam[h], return_state=True, **({} if h_in is None else dict(h0=h0[b, h].double().numpy())))
+            _check(O[b, h].cpu().double().numpy(), ref, f"{w.name} b{b} h{h}")
+            _check(hN[b, h].cpu().double().numpy(), hs, f"{w.name} state b{b} h{h}")
 
 
 def test_sampled_rows_at_benchmark_size(A):
@@ -105,13 +150,15 @@ def test_sampled_rows_at_benchmark_size(A):
         _check(O[b, h].cpu().double().numpy(), ref, f"{w.name} b{b} h{h}")
 
 
-def test_hip_graph_replays(A):
+@pytest.mark.parametrize("L,takes", [(500, "uncut"), (600, "segments")])
+def test_hip_graph_replays(A, L, takes):
     """ae_recurrent_forward allocates nothing and clears nothing (the states are overwritten whole), so its
     launches can be captured into a HIP graph: replayed four times with new K values and eager work between
     the replays, every replay must equal the eager call on the same inputs bit for bit; the first one is also
     held against the oracle."""
     dev = torch.device("cuda:0")
-    w = _workload("rec_graph", 794, 2, 4, 600, 128)
+    assert form(A, 2, 4, L, 128, 256) == takes
+    w = _workload("rec_graph", 794, 2, 4, L, 128)
     Qc, Kc, Vc = make_inputs(w)
     Q, K, V = Qc.to(dev), Kc.to(dev), Vc.to(dev)
     gam = _gammas(4)
