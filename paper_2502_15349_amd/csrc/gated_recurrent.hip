@@ -507,9 +507,9 @@ __global__ __launch_bounds__(256) void gated_combine_segments_kernel(float* buf,
     float local[kAhead], d[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
-      const int s = min(s0 + u, nseg - 1);
-      local[u] = slot[(int64_t)s * state_elems];
-      d[u] = dec[s];
+      if (s0 + u >= nseg) break;
+      local[u] = slot[(int64_t)(s0 + u) * state_elems];
+      d[u] = dec[s0 + u];
     }
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
