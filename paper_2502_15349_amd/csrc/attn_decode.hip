@@ -217,34 +217,49 @@ hipError_t launch_waves(const DecodeParams& p, unsigned grid, hipStream_t s) {
   return hipGetLastError();
 }
 
+constexpr int64_t kUnits = 256;  // compute units
+
 template <int DQK, int DV, int G>
 hipError_t launch_heads(const DecodeParams& p, hipStream_t s) {
   const int64_t grid = p.rows / p.g * ((p.g + G - 1) / G) * p.n_splits;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   DecodeParams q = p;
   q.units = (int)(p.rows / p.g * p.n_splits);
-  // Eight wavefronts instead of four keep more loads in flight and halve a workgroup's walk; taken where all workgroups
-  // are resident at once either way (two of eight wavefronts per compute unit with one q head, one with more) and a
-  // range has at least two blocks of steps for each.  Measured (us, 4 / 8 / 16 wavefronts): 16 x 32/8 heads x 5003 keys
-  // 87 / 75 / 76, 32 x 32/8 x 8192 214 / 198 / 530, 1 x 32/8 x 32768 (6 ranges) 75 / 59 / 58, 1 x 16 x 8192 (192/128, one
-  // range) 94 / 73 / 69; against it 64 x 32/8 x 1000 (512 workgroups of four heads) 55 / 60, 1 x 12 x 300 (64/64) 5.0 / 5.2,
-  // and 192-element keys read from HBM by three quarters of the chip (1 x 16 x 8192, 12 ranges) 18.9 / 19.9.
-  const bool wide = grid <= (G == 1 ? 512 : 256) && p.split_keys >= 320 && !(G == 1 && DQK == 192 && grid >= 128);
+  // Eight wavefronts instead of four keep more loads in flight and halve a workgroup's walk; taken where no compute unit has a
+  // second workgroup to do that, from 320 keys on.  128/128, us, 4 / 8 wavefronts: 4 x 16 heads x 4096 keys (64 workgroups) 46 / 37,
+  // 16 x 32/8 x 4096 (256 of two heads) 64 / 55, 16 x 64/8 x 4096 (256 of four) 98 / 89; against it 17 x 16 x 4096 (272 workgroups,
+  // 64/64) 61 / 67, 33 x 64/8 x 300 (264 of eight) 32 / 42.  Not for 192-element keys that no other workgroup of the XCD reads,
+  // once 128 workgroups pull them from HBM: 12 x 16 x 1000 25.8 / 26.9, 2 x 16 x 8192 in 8 ranges 30.4 / 32.9, 12 x 16 x 8192
+  // 172 / 186, 17 x 8/1 x 16384 200 / 222 (shared ones: 4 x 32/8 x 8192 in 2 ranges 55 / 45).
+  const bool from_hbm = DQK == 192 && G == 1 && (p.g == 1 || q.units % 8 != 0) && grid >= 128;
+  const bool wide = grid <= kUnits && p.split_keys >= 320 && !from_hbm;
   return wide ? launch_waves<DQK, DV, G, 8>(q, (unsigned)grid, s) : launch_waves<DQK, DV, G, 4>(q, (unsigned)grid, s);
 }
 
-// As many q heads per workgroup as leave a workgroup for every compute unit: sharing the keys saves reads, but a stream
-// needs the whole chip (32 q on 8 k/v heads, in microseconds with 1 / 2 / 4 heads: 16 x 5003 keys -- 128 workgroups with
-// four -- 107 / 87 / 126; 64 x 1000 152 / - / 55; 4 x 5003 in 2 ranges 38 / 47 / 68).  D_qk = 192 with eight needs 318
-// registers and stops at four.
-constexpr int64_t kMinWorkgroups = 256;
+// How many of the q heads of a k/v head one workgroup serves.  A key costs a workgroup its loads and, per head, its arithmetic,
+// about as 5 to 2, a head its place in the combination at the end, about what the loads of 128 keys cost, and the fullest compute
+// unit decides: the G that makes rounds of 256 workgroups x (keys (5 + 2 G) + 640 G) least.  Over batch 1 to 64, 300 to 32k keys, 1
+// to 32 ranges, 1, 3, 4 and 8 q heads per k/v head and the three head dims (2112 shapes) the times are 0.7 % above the best G and
+// number of wavefronts on the average; with the most heads that leave 256 workgroups it was 4.1 %.
+// 128/128, 32/8 heads x 4096 keys, us with 1 / 2 / 4 heads: batch 12 65 / 52 / 87, 15 73 / 54 / 88, 16 77 / 55 / 89, 17 114 / 100 / 91.
+// D_qk = 192 with eight needs 318 registers and stops at four.
 template <int DQK, int DV>
 hipError_t launch(const DecodeParams& p, hipStream_t s) {
   const int64_t units = p.rows / p.g * p.n_splits;
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int G = 1; G <= (DQK <= 128 ? 8 : 4) && G < 2 * p.g; G *= 2) {
+    const int64_t rounds = (units * ((p.g + G - 1) / G) + kUnits - 1) / kUnits;
+    const int64_t cost = rounds * ((int64_t)p.split_keys * (5 + 2 * G) + 640 * G);
+    if (cost < least) {
+      least = cost;
+      best = G;
+    }
+  }
   if constexpr (DQK <= 128)
-    if (p.g > 4 && units * ((p.g + 7) / 8) >= kMinWorkgroups) return launch_heads<DQK, DV, 8>(p, s);
-  if (p.g > 2 && units * ((p.g + 3) / 4) >= kMinWorkgroups) return launch_heads<DQK, DV, 4>(p, s);
-  if (p.g > 1 && units * ((p.g + 1) / 2) >= kMinWorkgroups) return launch_heads<DQK, DV, 2>(p, s);
+    if (best == 8) return launch_heads<DQK, DV, 8>(p, s);
+  if (best == 4) return launch_heads<DQK, DV, 4>(p, s);
+  if (best == 2) return launch_heads<DQK, DV, 2>(p, s);
   return launch_heads<DQK, DV, 1>(p, s);
 }
 

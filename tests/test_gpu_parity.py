@@ -410,13 +410,18 @@ def test_decoding_rows(A, dims, Lk, splits):
 @pytest.mark.parametrize("dims", [(64, 64), (128, 128), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
 @pytest.mark.parametrize("B,H_kv,g,Lk,splits", [(1, 2, 3, 1, 0), (3, 1, 1, 17, 0), (64, 4, 8, 67, 0), (43, 3, 12, 66, 0),
                                                 (52, 5, 5, 131, 0), (65, 2, 3, 63, 0), (129, 1, 2, 16, 0), (22, 4, 4, 257, 3),
-                                                (2, 2, 3, 320, 0), (64, 4, 4, 353, 0), (3, 2, 2, 700, 2)])
+                                                (2, 2, 3, 320, 0), (64, 4, 4, 353, 0), (3, 2, 2, 700, 2),
+                                                (64, 2, 4, 353, 0), (64, 2, 4, 131, 0), (32, 2, 4, 1000, 2), (32, 2, 4, 400, 2),
+                                                (32, 4, 4, 1000, 2), (64, 4, 8, 353, 0), (32, 4, 8, 1000, 2), (32, 4, 8, 400, 2),
+                                                (32, 4, 4, 400, 2), (32, 4, 5, 353, 0), (32, 4, 9, 353, 0), (65, 4, 4, 353, 0), (43, 3, 2, 321, 0)])
 def test_decoding_rows_shared_keys(A, dims, B, H_kv, g, Lk, splits):
     """One query row per head, with the keys in one range or several: the workgroup of the streaming kernel
-    serves one, two, four or eight q heads of a k/v head (as many as still leave 256 workgroups), groups that are no
-    multiple of that among them, on keys and values that are the filled part of a longer cache; from 320 keys on eight
-    wavefronts share a range.  The kernel works in fp32: 1e-4 of the largest |reference| (fp32 sums of at most 700
-    products, whatever their order)."""
+    serves one, two, four or eight q heads of a k/v head (whatever loads the fullest of 256 compute units least), groups that
+    are no multiple of that among them, on keys and values that are the filled part of a longer cache; from 320 keys per range
+    on eight wavefronts share a range where there are at most 256 workgroups.  The second half of the list: two, four and
+    eight heads with four and with eight wavefronts, direct and in ranges (320 keys and more, and fewer), and one workgroup more
+    than 256.  The kernel works in fp32: 1e-4 of the largest |reference| (fp32 sums of at most 1000 products, whatever their
+    order)."""
     from oracle import row_stats_head
     dev = torch.device("cuda:0")
     for kw in (dict(), dict(score_mod="bias", bias=-3.0, scale=-0.05)):
