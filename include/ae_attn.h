@@ -325,11 +325,13 @@ int32_t ae_attn_version(void);
  * leaves the state in front of each (bf16, [D_qk x D_v]); the parallel-pattern
  * kernel then starts every chunk's rows from the read-out of that state and
  * walks the chunk's own keys on top of it.  The work grows linearly with L.
- * Where B x H is more than 128 the call runs instead as ONE kernel that walks the
- * chunks of a (batch, head) in order with the state on chip (the kernel behind
- * ae_gated_forward, with the head's constant decay): same result up to rounding
- * order, Q, K, V read once; the workspace is then not touched (but must still
- * be passed: the choice is the library's).
+ * Where B x H is more than 128 (192 for a sequence of one chunk) the call runs
+ * instead as ONE kernel that walks the chunks of a (batch, head) in order with the
+ * state on chip (the kernel behind ae_gated_forward, with the head's constant
+ * decay): same result up to rounding order, Q, K, V read once; the workspace is
+ * then not touched (but must still be passed: the choice is the library's).  Fewer
+ * pairs and more than 512 tokens (1024 where the last chunk is a whole one): that
+ * kernel on segments of the sequence, as ae_gated_forward_segmented.
  *
  * Layouts: Q, K [B, H, L, D_qk] and V [B, H, L, D_v] bf16, O [B, H, L, D_v]
  * fp32 (or bf16, desc.out_dtype), all contiguous, device memory, 16-byte aligned; the caller owns them.
@@ -337,8 +339,9 @@ int32_t ae_attn_version(void);
  * or 256 tokens (256 fills the parallel kernel's 256-row tile).  Head dims
  * 64/64 and 128/128; H <= AE_MAX_DECAY_HEADS.
  * The workspace (device memory, 256-byte aligned, owned by the caller, size
- * from ae_recurrent_workspace_bytes) holds the state in front of every chunk:
- * 2 bytes x B x H x chunks x D_qk x D_v.
+ * from ae_recurrent_workspace_bytes) holds the state in front of every chunk,
+ * 2 bytes x B x H x chunks x D_qk x D_v, or the segments' fp32 states if they
+ * need more.
  * ae_recurrent_forward_state also takes the state in front of the first token
  * (h_in, fp32 [B, H, D_qk, D_v], device memory, 16-byte aligned; NULL: zero)
  * and hands back the one after the last token (h_out, same layout; NULL: not
@@ -423,8 +426,8 @@ ae_status_t ae_gated_forward(const ae_gated_t *h, const void *Q, const void *K, 
 /* The same call for few (batch, head) pairs and long sequences.  One workgroup
  * walks a (batch, head) from the first token to the last, so B x H of them keep
  * B x H compute units busy, however long L is.  Where that leaves most of the
- * chip idle (create decides: at most 128 workgroups and L >= 512) this entry
- * point cuts every walk into segments (Section 4.2: parallelism over chunks of
+ * chip idle (create decides: at most 128 workgroups, and at least 512 tokens where
+ * there is room for eight segments, 1152 where for two) this entry point cuts every walk into segments (Section 4.2: parallelism over chunks of
  * the sequence): all segments are walked side by side for their final states from
  * a zero start, a small kernel chains those into the state in front of every
  * segment (h_s+1 = exp(sum of the segment's log-decays) h_s + the segment's own

@@ -186,8 +186,9 @@ struct ae_attn {
   // kernel, each over 128 columns of V and O (the scores and the row normalizer are the same in every launch)
   int v_slices;
   // One query row per head, softmax, every key visible (a decoding step): the keys, split or not, are walked by the
-  // streaming kernel of attn_decode.hip instead of the 256-row attention kernel (unsplit it is the faster one on every
-  // shape measured, 300 to 32k keys, 12 to 2048 q heads: 1.02 to 2.8 times, see there)
+  // streaming kernel of attn_decode.hip instead of the 256-row attention kernel (unsplit 1.9 times as fast on the average of 238
+  // shapes of 17 to 16k keys and 1 to 4096 q heads; of these 17 x 16 heads x 16384, 64/64, and 17 x 8/1 x 16384, 128/128, were slower,
+  // 0.90 and 0.95 times: there the last few workgroups are a second round)
   bool decode;
 };
 

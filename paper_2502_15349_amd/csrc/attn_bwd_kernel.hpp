@@ -29,8 +29,9 @@
 // What bounds it is how well a SIMD's vector and matrix work overlap, and that takes two wavefronts per SIMD of at most
 // 256 registers.  Where accumulators, resident operands and score tiles of 32 own rows fit that (64/64; 128/128, query
 // side), a wavefront does all of the above and two workgroups share a CU: attn_bwd_kernel.  Where they do not, the 32
-// rows go to a pair of wavefronts: attn_bwd_pair_kernel.  (One wavefront with 512 registers, alone on its SIMD, kept the
-// matrix units 39 % busy; both kernels then run into the board's power limit.)
+// rows go to a pair of wavefronts: attn_bwd_pair_kernel (its key side at 128/256 still spills up to 9 registers), but for
+// short walks, which the first form takes with one workgroup per CU and up to 472 registers.  The lines between the two
+// stand in bwd_launch.hpp.
 #pragma once
 #include "attn_kernel.hpp"
 
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(c
   auto a_tl = [&](int k) { return tbl + (((4 * k + tcl) ^ flo) << 4); };
   auto a_th = [&](int k) { return tbh + (((4 * k + tcl) ^ fhi) << 4); };
   uint32_t ar1[C::T1], ar2[C::T2], atl[C::DB], ath[C::DB];
-  uint32_t atl2[C::HAS2 ? C::DB2 : 1], ath2[C::HAS2 ? C::DB2 : 1];  // fused kernel: the same for the Y2 tile
+  uint32_t atl2[C::HAS2 ? C::DB2 : 1], ath2[C::HAS2 ? C::DB2 : 1];  // key side: the same for the Y2 tile
   if constexpr (C::HAS2) {
     const int glo = bswz<C::CPR2>(trow), ghi = bswz<C::CPR2>(trow + 8);
     const uint32_t t2 = lds0 + C::Y1_BYTES + (li & 1) * 8 + trow * C::RB2;
@@ -451,7 +452,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(c
       }
       sched_fence();
     }
-    float w[16], w2[C::HAS2 ? 16 : 1];  // the weight (dV) or the score gradient (dQ, dK); fused: both
+    float w[16], w2[C::HAS2 ? 16 : 1];  // the weight (dV) or the score gradient (dQ, dK); key side: both
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       if constexpr (ROWQ)
@@ -583,10 +584,9 @@ __global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(c
 // factors, the tiles that have landed and the stages that are free.  Within a tile role 0's order is S, weights, dV and
 // role 1's is dS', dK / dQ, dP of the next tile: one is in its vector work while the other issues matrix products.
 //
-// Measured against one wavefront per 32 rows with 512 registers (us, whole backward pass): 1 x 128 heads x 8192, 192/128,
-// causal 10340 -> 9640; 8 x 16 x 4096 192/128 2786 -> 2600, 128/256 3517 -> 2917, 128/128 (key side) 2106 -> 2013;
-// 1 x 32/8 x 1024 192/128 217 -> 182, 128/256 290 -> 207, 128/128 184 -> 164; 2 x 12 x 1023 x 1201 with a bias tensor, 64/64,
-// 90 -> 88.  The matrix units are busy 48 % of the time at 1.9 GHz (39 % at 2.25 before).  Taking away the copies, the
+// Measured against one wavefront per 32 rows with 512 registers (us, whole backward pass, causal): 1 x 128 heads x 8192,
+// 192/128, 10340 -> 9640; 8 x 16 x 4096 192/128 2786 -> 2600, 128/256 3517 -> 2917, 128/128 (key side) 2106 -> 2013;
+// 1 x 32/8 x 1024 192/128 217 -> 182, 128/256 290 -> 207, 128/128 184 -> 164; 4 x 32/8 x 2048 128/128 579 -> 580.  Taking away the copies, the
 // LDS reads or the weights for timing gave 9-10 % each: no one of them bounds it, the hand-over per tile and the board's
 // power do.  Against two workgroups per CU where those fit (64/64 8 x 16 x 4096 1033, 128/128 query side
 // 4 x 32/8 x 2048 210) the pairs take 1212 and 316: the choice in bwd_launch.hpp.
