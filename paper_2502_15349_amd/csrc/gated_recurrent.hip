@@ -491,9 +491,10 @@ hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
 }
 
 // ---- segments: from the final states of the segments (each from a zero start) to the states in front of them ----
-// One thread per state element walks the segments; what it waits for is memory, so the states and decays of kAhead
-// segments are requested together instead of one at a time, each behind the store of the one before (whole calls:
-// 1 x 80 heads x 8192 tokens in 7 segments 210 -> 206 us, 2 x 32 x 4096 in 32 segments 245 -> 233 us).
+// One thread per state element walks the segments; what it waits for is memory, so the states and decays of up to kAhead
+// segments are requested together instead of one at a time, each behind the store of the one before (whole calls with walks cut
+// in 7 and in 32 segments 210 -> 206 and 245 -> 233 us), and no more than there are (1 x 128 heads x 1152 tokens, two segments,
+// 75.9 us with eight requests, 73.3 so).
 __global__ __launch_bounds__(256) void gated_combine_segments_kernel(float* buf, const float* seg_decay, const float* h_in, int nseg,
                                                                       int state_elems) {
   constexpr int kAhead = 8;

@@ -127,13 +127,15 @@ def test_backward_lengths(A, Lq, Lk, mask):
 
 
 @pytest.mark.parametrize("dims", [(128, 128), (128, 256), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
-@pytest.mark.parametrize("Lq,Lk", [(32, 129), (33, 32), (65, 160), (95, 96), (161, 97), (192, 127)])
+@pytest.mark.parametrize("Lq,Lk", [(32, 129), (33, 32), (65, 160), (95, 96), (161, 97), (192, 127), (129, 161)])
 def test_backward_pairs_of_wavefronts(A, dims, Lq, Lk):
     """The kernels with a pair of wavefronts per 32 own rows walk tiles of 32 rows through a ring of five stages: walks
     of one to six tiles per query head, three query heads one after the other (the copies run three tiles ahead, over
     the seam between heads), last tiles of 1, 31 and 32 rows, own rows that fill one to four of the pairs; with a row
-    statistic and without, the factor of the abs-sum form carrying the sign of the score."""
-    for kw in (dict(), dict(norm="sigmoid", score_mod="bias", bias=-3.0, mask="causal"),
+    statistic and without, the factor of the abs-sum form carrying the sign of the score, ReLU's a mask.  (Without a mask every
+    length runs on pairs; the causal ones of up to 128 rows on single wavefronts, see test_backward_short_walks.)"""
+    for kw in (dict(), dict(norm="sigmoid", score_mod="bias", bias=-3.0), dict(norm="abssum"), dict(score_mod="relu", norm="none", scale=0.01),
+               dict(norm="sigmoid", score_mod="bias", bias=-3.0, mask="causal"),
                dict(score_mod="head_decay", norm="abssum", mask="causal", decay=True)):
         run_case(A, Workload("bwd_pairs", 46, 1, 3, 1, Lq, Lk, dims[0], dims[1], **kw))
 
