@@ -18,7 +18,8 @@ constexpr int64_t kUnitsPerXcd = 32, kLongBiasWalk = 384;
 // q heads that a key-side workgroup walks one after the other.  4 x 24 heads x 4096, one wavefront / pair, us: 128/128 window
 // 64 429 / 461, 256 533 / 548, 512 671 / 672; 192/128 64 529 / 572, 256 677 / 686, 512 844 / 827; 128/256 64 635 / 665, 128
 // 698 / 705, 256 807 / 778.  Causal without a window: 128/128 64 rows 18.0 / 18.9, 128 28.3 / 28.7, 150 31.3 / 30.4; 192/128
-// 21.0 / 21.8, 33.0 / 33.7, 36.4 / 35.8; 128/256 64 rows 23.7 / 24.6, 100 35.0 / 33.8.
+// 21.0 / 21.8, 33.0 / 33.7, 36.4 / 35.8; 128/256 64 rows 23.7 / 24.6, 100 35.0 / 33.8; 128/128 with a bias tensor 64 rows 19.1 / 20.6,
+// 100 28.2 / 29.3 (192/128 with one 21.9 / 22.3, 32.8 / 32.3: always pairs).
 constexpr int64_t short_window(int dv) { return dv == 256 ? 96 : 256; }
 constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
 
@@ -33,7 +34,7 @@ hipError_t launch_one(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
   const int64_t grid = ((rounds + tg - 1) / tg) * tg * 8 * per_group;
   if (tg < 1 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
   constexpr bool kTwoPerCu = DQK == 64 || (DQK == 128 && DV == 128 && !kKvSide && !BIAS);
-  constexpr bool kShort = !kTwoPerCu && CAUSAL && !BIAS;
+  constexpr bool kShort = !kTwoPerCu && CAUSAL && (!BIAS || DQK == 128);
   const int64_t walk = (kKvSide ? (int64_t)p.L_q * p.g : p.L_k), window = p.window < (kKvSide ? p.L_q : p.L_k) ? p.window : 0;
   bool pair = !kTwoPerCu;
   if constexpr (kTwoPerCu && BIAS) pair = rounds * per_group <= kUnitsPerXcd && walk / (CAUSAL ? 2 : 1) >= kLongBiasWalk;

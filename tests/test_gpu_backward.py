@@ -313,6 +313,38 @@ def test_backward_bias_tensor(A, dims, norm, mask):
         assert np.isfinite(gB).all() and errB.max() <= 3e-2 and errB.mean() <= MEAN_ABS
 
 
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("norm", ["softmax", "sigmoid", "none"])
+@pytest.mark.parametrize("Lq,Lk", [(64, 64), (64, 65), (65, 64), (61, 128), (64, 129)])
+def test_backward_bias_tensor_short_walks(A, dims, norm, Lq, Lk):
+    """Causal walks of up to 128 rows (keys; queries times the two q heads of a group) with a bias tensor run on single
+    wavefronts at 128/128 (64/64 likewise, 192/128 on pairs); both sides of the limit."""
+    from paper_2502_15349_amd.workloads import make_bias_tensor
+    dev = torch.device("cuda:0")
+    w = Workload(f"bwd_bias_short_{norm}", 65, 2, 4, 2, Lq, Lk, dims[0], dims[1], score_mod="bias_tensor", norm=norm, mask="causal",
+                 scale=(0.01 if norm == "none" else None))
+    print(f"case {w}", flush=True)
+    Q, K, V = make_inputs(w)
+    dO = make_grad(w)
+    bt = make_bias_tensor(w, True, True)
+    if norm == "none":
+        bt = (bt.float() * 0.01).to(torch.bfloat16)
+    btd = torch.zeros(bt.shape[:3] + ((Lk + 7) // 8 * 8,), dtype=torch.bfloat16, device=dev)
+    btd[..., :Lk] = bt.to(dev)
+    Qd, Kd, Vd, dOd = (t.to(dev) for t in (Q, K, V, dO))
+    stats = torch.empty((2, 4, Lq), dtype=torch.float32, device=dev) if norm == "softmax" else None
+    O = A.run_workload(w, Qd, Kd, Vd, stats=stats, bias_tensor=btd[..., :Lk])
+    got = A.attention_backward(Qd, Kd, Vd, O, dOd, stats, scale=w.scale_value, score_mod="bias_tensor", norm=norm, mask="causal",
+                               bias_tensor=btd[..., :Lk], want_dbias=True)
+    torch.cuda.synchronize()
+    ref = attention_backward(Q, K, V, dO, scale=w.scale_value, score_mod="bias_tensor", norm=norm, mask="causal", bias_tensor=bt, with_dbias=True)
+    for name, g, r in zip(("dQ", "dK", "dV"), got, ref):
+        check(g.cpu().double().numpy(), r, f"{w.name} {name}")
+    gB, rB = got[3].float().cpu().double().numpy(), ref[3]  # (the bars of test_backward_bias_tensor)
+    errB = np.abs(gB - rB) / np.maximum(np.abs(rB).max(axis=-1, keepdims=True), 1.0)
+    assert np.isfinite(gB).all() and errB.max() <= 3e-2 and errB.mean() <= MEAN_ABS
+
+
 @pytest.mark.parametrize("B,H,H_kv,Lq,Lk", [(2, 64, 64, 400, 385), (3, 40, 40, 385, 520), (2, 96, 24, 260, 500), (4, 12, 12, 767, 800)])
 @pytest.mark.parametrize("norm", ["softmax", "sigmoid", "none"])
 def test_backward_bias_tensor_by_number_of_workgroups(A, B, H, H_kv, Lq, Lk, norm):
