@@ -330,8 +330,9 @@ int32_t ae_attn_version(void);
  * state on chip (the kernel behind ae_gated_forward, with the head's constant
  * decay): same result up to rounding order, Q, K, V read once; the workspace is
  * then not touched (but must still be passed: the choice is the library's).  Fewer
- * pairs and more than 512 tokens (1024 where the last chunk is a whole one): that
- * kernel on segments of the sequence, as ae_gated_forward_segmented.
+ * pairs and more than 512 tokens (1024 where the last chunk is a whole one and
+ * there are more than 8 pairs): that kernel on segments of the sequence, as
+ * ae_gated_forward_segmented.
  *
  * Layouts: Q, K [B, H, L, D_qk] and V [B, H, L, D_v] bf16, O [B, H, L, D_v]
  * fp32 (or bf16, desc.out_dtype), all contiguous, device memory, 16-byte aligned; the caller owns them.
@@ -427,7 +428,7 @@ ae_status_t ae_gated_forward(const ae_gated_t *h, const void *Q, const void *K, 
  * walks a (batch, head) from the first token to the last, so B x H of them keep
  * B x H compute units busy, however long L is.  Where that leaves most of the
  * chip idle (create decides: at most 128 workgroups, and at least 512 tokens where
- * there is room for eight segments, 1152 where for two) this entry point cuts every walk into segments (Section 4.2: parallelism over chunks of
+ * there is room for six segments, 1152 where for two) this entry point cuts every walk into segments (Section 4.2: parallelism over chunks of
  * the sequence): all segments are walked side by side for their final states from
  * a zero start, a small kernel chains those into the state in front of every
  * segment (h_s+1 = exp(sum of the segment's log-decays) h_s + the segment's own

@@ -755,11 +755,12 @@ static void cut_segments(int64_t n, int L, int* nseg, int* seg_len) {  // nseg =
   *nseg = (L + *seg_len - 1) / *seg_len;
 }
 // From which length on the two further launches pay against the uncut walk; the fewer segments the chip has room for, the later
-// (us, cut / uncut): 32 workgroups x 512 tokens 30 / 33; 64 x 512 34.9 / 33.6, 64 x 700 41.3 / 44.0; 85 x 700 48.0 / 44.2, 85 x 900
-// 53.6 / 58.1; 86 x 1152 68.3 / 69.0, 128 x 1024 68.9 / 62.6, 128 x 1408 85.4 / 84.1 (128/128; 64/64 and Mamba2 alike).
+// (us, cut / uncut): 40 workgroups x 512 tokens 30.4 / 33.2; 64 x 512 34.9 / 33.6, 64 x 600 40.8 / 40.5 (64/64 22.9 / 24.9); 85 x 700
+// 48.0 / 44.2, 85 x 900 53.6 / 58.1; 86 x 1152 68.3 / 69.0, 110 x 1152 71.6 / 69.5, 128 x 1280 79.7 / 76.7, 128 x 1408 85.4 / 84.1
+// (128/128; 64/64 and Mamba2 alike, 128 workgroups of Mamba2 x 1280 78.3 / 79.4).
 static void gated_segments(int64_t workgroups, int L, int* nseg, int* seg_len) {
   const int64_t n = most_segments(workgroups, L), room = 256 / workgroups;
-  const int from = room >= 8 ? 512 : room >= 4 ? 640 : room == 3 ? 832 : 1152;
+  const int from = room >= 6 ? 512 : room >= 4 ? 576 : room == 3 ? 832 : workgroups <= 100 ? 1152 : 1280;
   cut_segments(L >= from ? n : 1, L, nseg, seg_len);
 }
 
@@ -888,8 +889,10 @@ ae_status_t ae_recurrent_create(const ae_recurrent_desc_t* d, ae_recurrent_t** o
   const bool walks = ae::gated_supported(d->D_qk, d->D_v);
   h->single_pass = walks && (pairs >= 192 || (pairs >= kSegmentedBelow && h->n_chunks > 1));
   const int64_t n = walks ? most_segments(pairs, d->L) : 1;
-  const bool whole = h->tail_len == 0;
-  const int from = n == 2 ? (whole && h->n_chunks <= 5 ? 1536 : 1024) : whole ? 1024 : 513;
+  // (a handful of pairs, and a length that makes segments of two chunks each: 4 x 512 in chunks of 256 22 against 24 us)
+  const bool few = pairs <= 8 && d->L % 128 == 0 && d->L >= (d->chunk == 256 ? 512 : 640);
+  const bool whole = h->tail_len == 0 && !few;
+  const int from = n == 2 ? (whole && h->n_chunks <= 5 ? 1536 : 1024) : whole ? 1024 : few ? 512 : 513;
   cut_segments(d->L >= from ? n : 1, d->L, &h->nseg, &h->seg_len);
   h->ws_bytes = std::max(h->ws_bytes, gated_segments_ws(d->B, d->H, h->nseg, d->D_qk, d->D_v));
   *out = h;

@@ -12,7 +12,9 @@ namespace {
 // pair, us: 1 x 6 heads x 1023 x 1060 (8 and 9 workgroups per XCD) 73 / 68, 2 x 12 x 1023 x 1060 (24 and 27) 83 / 80;
 // 1 x 6 x 4096 x 4133 (32 and 33) 342 / 398, 8 x 16 x 512 x 549 (64 and 80) 96 / 113, 8 x 16 x 2048 causal (256) 744 / 919,
 // without the bias's gradient 364 / 514; 4 x 24 x 100 causal 20.0 / 22.4, 2 x 12 x 512 causal 39.3 / 40.5, unmasked 38.9 / 38.1.
-constexpr int64_t kUnitsPerXcd = 32, kLongBiasWalk = 384;
+// Causal workgroups are half as long on the average: up to 48 of them (2 x 12 x 2048, 48 and 48, 116 / 109; 4096, 96, 262 / 368).
+constexpr int64_t units_per_xcd(bool causal) { return causal ? 48 : 32; }
+constexpr int64_t kLongBiasWalk = 384;
 // Where only one workgroup fits a CU, short walks stay with one wavefront too: the pair is a tile behind itself, has three tiles
 // to wait for at its start, and of a narrow window most waves skip most tiles.  Keys (queries) that a row may see, times the
 // q heads that a key-side workgroup walks one after the other.  4 x 24 heads x 4096, one wavefront / pair, us: 128/128 window
@@ -37,7 +39,7 @@ hipError_t launch_one(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
   constexpr bool kShort = !kTwoPerCu && CAUSAL && (!BIAS || DQK == 128);
   const int64_t walk = (kKvSide ? (int64_t)p.L_q * p.g : p.L_k), window = p.window < (kKvSide ? p.L_q : p.L_k) ? p.window : 0;
   bool pair = !kTwoPerCu;
-  if constexpr (kTwoPerCu && BIAS) pair = rounds * per_group <= kUnitsPerXcd && walk / (CAUSAL ? 2 : 1) >= kLongBiasWalk;
+  if constexpr (kTwoPerCu && BIAS) pair = rounds * per_group <= units_per_xcd(CAUSAL) && walk / (CAUSAL ? 2 : 1) >= kLongBiasWalk;
   if constexpr (kShort) pair = window ? window * (kKvSide ? p.g : 1) > short_window(DV) : walk > short_walk(DV);
   if constexpr (kTwoPerCu || kShort) {
     typedef BwdCfg<DQK, DV, NORM, CAUSAL, OUT, BIAS> C;

@@ -444,11 +444,12 @@ def test_gated_backward_entry_point_checks():
         A.ae_gated_destroy(hu)
 
 
-@pytest.mark.parametrize("H,L,segments", [(1, 511, 1), (1, 512, 4), (32, 512, 4), (33, 639, 1), (64, 640, 4), (65, 831, 1), (85, 832, 3),
-                                          (86, 1151, 1), (86, 1500, 2), (128, 1152, 2), (129, 8192, 1), (16, 1000, 6), (3, 100000, 83)])
+@pytest.mark.parametrize("H,L,segments", [(1, 511, 1), (1, 512, 4), (42, 512, 4), (43, 575, 1), (64, 640, 4), (65, 831, 1), (85, 832, 3),
+                                          (86, 1151, 1), (100, 1152, 2), (101, 1279, 1), (128, 1280, 2), (129, 8192, 1), (16, 1000, 6), (3, 100000, 83)])
 def test_gated_segments_fill_the_chip_once(H, L, segments):
     """As many segments as keep one workgroup per compute unit (256), of at least two chunks of 64 tokens (the last one may be
-    shorter), from 512 tokens on where there is room for eight, from 640, 832 and 1152 on with room for four, three and two;
+    shorter), from 512 tokens on where there is room for six, from 576, 832 and 1152 (above 100 walks 1280) on with room for four, three and
+    two;
     the workspace holds a state and a decay per (batch, head, segment)."""
     from paper_2502_15349_amd import ae_attn as A
     h = A.ae_gated_create(B=1, H=H, L=L, D_qk=128, D_v=128, scale=0.1)
@@ -458,12 +459,13 @@ def test_gated_segments_fill_the_chip_once(H, L, segments):
     A.ae_gated_destroy(h)
 
 
-@pytest.mark.parametrize("H,L,chunk,segments", [(4, 500, 256, 1), (4, 513, 256, 3), (64, 700, 256, 4), (85, 1000, 256, 3), (64, 768, 256, 1),
+@pytest.mark.parametrize("H,L,chunk,segments", [(4, 500, 256, 1), (4, 512, 256, 4), (8, 512, 128, 1), (8, 640, 128, 5), (9, 640, 128, 1), (4, 704, 64, 1), (4, 513, 256, 3), (64, 700, 256, 4), (85, 1000, 256, 3), (64, 768, 256, 1),
                                                 (16, 896, 64, 1), (16, 1024, 64, 8), (85, 1024, 128, 3), (86, 1023, 256, 1),
                                                 (100, 1024, 256, 1), (100, 1024, 128, 2), (100, 1100, 256, 2), (128, 1280, 256, 1),
                                                 (128, 1536, 256, 2), (128, 2047, 256, 2), (129, 2048, 64, 1)])
 def test_recurrent_segments(H, L, chunk, segments):
-    """ae_recurrent: the chunk-parallel form below 513 tokens, below 1024 where the last chunk is whole, and, with room for two
+    """ae_recurrent: the chunk-parallel form below 513 tokens, below 1024 where the last chunk is whole (up to eight pairs below
+    640, or 512 in chunks of 256, where segments of 128 tokens come out even), and, with room for two
     segments only, up to five whole chunks; segments of the walk elsewhere (their states are fp32, a chunk's bf16)."""
     from paper_2502_15349_amd import ae_attn as A
     h = A.ae_recurrent_create(B=1, H=H, L=L, D_qk=128, D_v=128, chunk=chunk, scale=0.1, gamma=[0.97] * H)

@@ -110,7 +110,7 @@ def test_chunk_sizes_agree_and_workspace_is_reusable(A, B, H, L, D):
 # Both sides of the lines between the forms: one chunk or two with 129 to 191 (batch, head) pairs, a whole or a short last
 # chunk, two segments or chunks
 @pytest.mark.parametrize("B,H,L,D,chunk,takes", [(1, 129, 64, 64, 64, "uncut"), (1, 129, 65, 128, 64, "uncut"), (3, 50, 256, 128, 256, "uncut"),
-                                                 (3, 50, 257, 64, 256, "uncut"), (1, 8, 512, 128, 256, "uncut"), (1, 8, 513, 64, 256, "segments"),
+                                                 (3, 50, 257, 64, 256, "uncut"), (1, 9, 512, 128, 256, "uncut"), (1, 8, 512, 128, 256, "segments"), (1, 8, 513, 64, 256, "segments"),
                                                  (1, 16, 768, 128, 256, "uncut"), (1, 85, 800, 64, 256, "segments"),
                                                  (1, 86, 1024, 64, 256, "uncut"), (1, 86, 1024, 64, 128, None),
                                                  (2, 64, 1280, 64, 256, "uncut"), (2, 64, 1536, 64, 256, None)])
