@@ -12,367 +12,439 @@
 //     H_new = e^{b_last} H + sum_j (e^{b_last - b_j} g_j) k_j^T v_j
 // Every exponent is <= 0: nothing overflows, nothing is divided by a decay.
 //
-// A wavefront owns 32 of the D_v output columns and keeps, for its columns, the state slab [D_qk x 32] as D_qk / 32
-// accumulator tiles.  It takes both of the chunk's two blocks of 32 queries (QS = 1: D_v / 32 wavefronts per head,
-// each alone on its SIMD with the whole register file) or one of them (QS = 2: two wavefronts per column block that
-// both hold the slab and both apply every update to it -- the same instructions on the same operands, so the copies
-// stay bit-identical -- where the registers allow two wavefronts per SIMD: 64 / 128).  The path is bound by memory
-// and by the latency chain of a chunk, not by MFMAs.
+// What bounds a walk is the latency chain of its chunks, and most of a chunk does not depend on the state: the weights of its
+// 64 x 64 pairs and the gates.  So the work is split between two kinds of wavefronts, one of each on a SIMD, whose matrix and
+// vector instructions overlap:
+//   * state wavefronts, one per 32 value columns of a head: they keep the state slab [D_qk x 32] as D_qk / 32 accumulator tiles;
+//     per chunk they read the state out for the 64 queries, add the weighted values, store the outputs and update the state;
+//   * four helpers: three of them form the three 32 x 32 blocks of the chunk's weights that the causal order leaves (once
+//     per chunk, not once per 32 value columns) and copy the tiles, the fourth makes the gates' sums and factors.  The scores
+//     of a chunk are formed while the state wavefronts work on the chunk before, the weights while they read the state out.
+// Two barriers per chunk: in front of the first one the state is read out and the weights are written, behind it the weights
+// are used, the state is updated, and the next chunk's scores and gates are formed.
 // All products are transposed so that a lane owns one column -- a
 // query in S^T and O^T, a value column in H -- and the registers run over the contracted index:
-//     S^T [keys x queries]   = K Q^T          A: K rows, B: Q rows (16-byte row pieces in the d order below)
+//     S^T [keys x queries]   = K Q^T          A: K rows, B: Q rows (16-byte row pieces)
 //     R^T [v x queries]      = H^T Q^T        A: the state accumulators themselves, packed to bf16 (lane = value
 //                                                column, registers = d: an accumulator tile IS an A operand whose
-//                                                contraction runs over its rows), B: the same Q fragments
+//                                                contraction runs over its rows), B: Q rows, read like those of S^T
 //     O^T += V^T P^T                          A: V through the transposing LDS read, B: the S^T accumulators,
-//                                                weighted and packed (no data movement)
+//                                                weighted and packed (through LDS in the registers' own order)
 //     H   += K^T (w . V)                      A: K through the transposing read, B: the same V fragments times
 //                                                the per-token weights w_j = e^{b_last - b_j} g_j
-// The contraction order over d is free, so Q and K rows are read in the order the accumulator layout of H
-// dictates (register r of a tile is row 8 (r / 4) + 4 (lane / 32) + r % 4): two 8-byte pieces per fragment.
-// Of the three 32 x 32 blocks of S^T that the causal order inside a chunk leaves, a wavefront computes those of
-// its query block itself (cheaper than an exchange through LDS and a barrier).
-// Q, K, V tiles and the chunk's gates arrive by LDS-DMA into a ring of three stages (chunk c is worked on while
-// c + 1 and c + 2 are in flight), one barrier per chunk, the wavefronts issuing their shares of the copies at
-// different points of the iteration.  The output of a chunk is stored before the state update, whose MFMAs cover
-// the stores.  The same kernel serves the backward pass (other operands, a walk from the last token to the first,
+// Row m of an accumulator tile of H is the column of K that lane m of the A operand reads.  The transposing read takes pieces
+// of four columns from any address: pieces 1 and 2 of every 16 columns are exchanged, so that the eight registers a lane
+// packs for the read-out are eight consecutive d, and a query fragment is one 16-byte read.
+// The outputs of a chunk (32 queries x 32 columns per state wavefront and block) are turned around in LDS, where the chunk's
+// queries were, and stored in whole 128-byte lines: as they stand, a store instruction would touch 32 rows of 32 bytes, and the
+// compute unit's memory pipe takes about 60 clocks for each of those (16 for a kilobyte of whole lines).
+// Q, K, V tiles arrive by LDS-DMA into a ring of three stages (chunk c is worked on, c + 1 is needed half a chunk later, c + 2
+// is in flight).  Measured against the form without helpers, where every state wavefront formed the gates and, for its own 32
+// columns, the weights (us, one box): 8 x 32 heads x 8192 tokens, 128/128, 592 -> 535 (5.0 TB/s: the memory's rate), 8 x 16 x 4096
+// 64/64 119 -> 92, 1 x 4 x 300 128/128 21.0 -> 14.8, Mamba2 1 x 80 x 8192 (three launches) 137 -> 113, 8 x 80 x 2048 259 -> 180.
+// The same kernel serves the backward pass (other operands, a walk from the last token to the first,
 // see GatedParams::reverse) and walks cut into segments (GatedParams::nseg).
 #include <hip/hip_runtime.h>
 
-#include "attn_bwd_kernel.hpp"  // bswz, read_tr_frag, dma4, lds_store4
+#include "attn_bwd_kernel.hpp"  // bswz, read_tr_frag, lds_store4
 #include "gated.hpp"
-
-#ifndef AE_GATED_QS_128
-#define AE_GATED_QS_128 1  // wavefronts per block of 32 value columns at 128/128 (build-time knob of the sweeps)
-#endif
 
 namespace ae {
 namespace {
 
 // HPW_: value heads per workgroup.  Heads of one q/k group (Mamba2: every head of a group reads the same B and C)
-// can share the Q and K tiles of a workgroup: HPW_ consecutive heads, each with its own V tile, gates and state.
-// QS_: wavefronts per block of 32 value columns: 2 (one per query block of the chunk, see above) or 1 (both query
-// blocks in one wavefront: half the wavefronts, each with the whole register file where 2 would spill).
-template <int DQK_, int DV_, int HPW_ = 1, int QS_ = 2>
+// can share the Q and K tiles, and the scores, of a workgroup: HPW_ consecutive heads, each with its own V tile, gates and state.
+template <int DQK_, int DV_, int HPW_ = 1>
 struct GCfg {
-  static constexpr int DQK = DQK_, DV = DV_, HPW = HPW_, QS = QS_, WPH = QS_ * (DV_ / 32), WAVES = HPW_ * WPH, THREADS = 64 * WAVES, CH = 64;
+  static constexpr int DQK = DQK_, DV = DV_, HPW = HPW_, CH = 64;
+  static constexpr int NB = DV / 32, SW = HPW * NB;  // state wavefronts: one per 32 value columns of a head
+  static constexpr int WAVES = SW + 4, THREADS = 64 * WAVES;
   static constexpr int RBQ = DQK * 2, RBV = DV * 2, CPRQ = DQK / 8, CPRV = DV / 8;
-  static constexpr int Q_BYTES = CH * RBQ, V_BYTES = CH * RBV, STAGE_BYTES = 2 * Q_BYTES + HPW * V_BYTES;
-  static constexpr int STAGES = 3;                // chunk c is worked on while c + 1 and c + 2 are arriving
-  static constexpr int GATE_BYTES = 3 * CH * 4;   // per wavefront: b, g, w of the chunk's tokens
-  static constexpr int RAW_BYTES = 2 * CH * 4;    // per head and stage: the chunk's log-decays and key gates as they arrive
-  static constexpr int LDS_BYTES = STAGES * (STAGE_BYTES + HPW * RAW_BYTES) + WAVES * GATE_BYTES + 256;  // (+ a row nobody reads)
-  // copy instructions per wavefront and chunk: its shares of the Q, K and V tiles and one of the two gate rows
-  static constexpr int NDMA = 2 * (CPRQ / WAVES) + CPRV / WPH + 1;
-  static constexpr int NST = 4 * (3 - QS);        // store instructions per wavefront and (whole) chunk
+  static constexpr int Q_BYTES = CH * RBQ, V_BYTES = CH * RBV;
   static constexpr int T = DQK / 16, DBQ = DQK / 32;
-  static_assert(CPRQ % WAVES == 0 && CPRV % WPH == 0, "every wave copies the same number of 1 KB blocks");
-  static_assert(LDS_BYTES <= 160 * 1024, "tiles do not fit LDS");
+  // the gates' values of a head's chunk, in floats: b, u, s (see put_gates), two sets of w, the groups' references, two decays
+  static constexpr int kB = 0, kU = 64, kS = 128, kW = 192, kRef = 320, kDec = 336, GATE_BYTES = 352 * 4;
+  static constexpr int P_BYTES = 3 * 2048;  // per head: the chunk's weights, three blocks of 32 x 32 in bf16
+  // 64/64: two workgroups per compute unit (three wavefronts per SIMD)
+  static constexpr int WAVES_PER_SIMD = DQK == 64 && DV == 64 ? 3 : 2;
 };
 
-__device__ __forceinline__ u32x2 lds_read8(uint32_t addr) {
-  return *reinterpret_cast<__attribute__((address_space(3))) const u32x2*>((lds_char*)(uintptr_t)addr);
-}
+// LDS layout: a stage holds the tiles Q (full walks only), K, V of every head
+template <class C, bool STATE_ONLY>
+struct GLayout {
+  static constexpr int kK = STATE_ONLY ? 0 : C::Q_BYTES, kV = kK + C::Q_BYTES, STAGE_BYTES = kV + C::HPW * C::V_BYTES;
+  // a state walk needs a chunk only when it updates with it and has the room: one more chunk in flight
+  static constexpr int STAGES = STATE_ONLY ? 4 : 3;
+  static constexpr int kP = STAGES * STAGE_BYTES, kGates = kP + (STATE_ONLY ? 0 : C::HPW * C::P_BYTES);
+  // 4 KB per state wavefront to turn an output block around: the stage's queries, where they are large enough
+  static constexpr bool kOutInQ = C::Q_BYTES >= C::SW * 4096;
+  static constexpr int kOut = kGates + C::HPW * C::GATE_BYTES;
+  static constexpr int LDS_BYTES = kOut + (STATE_ONLY || kOutInQ ? 0 : C::SW * 4096);
+  static_assert(LDS_BYTES <= 160 * 1024 / (C::WAVES_PER_SIMD == 3 ? 2 : 1), "tiles do not fit LDS");
+};
+
 // x of the lane that the control word selects, 0 where it selects none or the masks switch the lane off
 template <int CTRL, int ROW_MASK, int BANK_MASK>
 __device__ __forceinline__ float dpp_f(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROW_MASK, BANK_MASK, false));
 }
+__device__ __forceinline__ float lds_read4(uint32_t addr) {
+  return *reinterpret_cast<__attribute__((address_space(3))) const float*>((lds_char*)(uintptr_t)addr);
+}
+// Workgroup barrier: this wavefront's LDS reads and writes are done (its copies in flight are not waited for).
+__device__ __forceinline__ void chunk_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// STATE_ONLY: no outputs, only the state update is walked (see GatedParams::state_only): no queries are fetched, the state is
-// not packed for the read-out.  As a run-time flag of the one kernel the walk fetched and packed them all the same: the segmented
-// call of 1 x 80 heads x 8192 tokens, 128/64 (both walks and the combination), took 144 us then and takes 138 us now.  The full
-// form keeps its (there never set) flag around the outputs: without these branches the compiler orders the chunk differently,
-// and 8 x 32 heads x 8192 tokens, 128/128, take 588 us for 585 (cause not looked into further).
+// The copies of one helper: the tile of a chunk (64 rows of 16 CPR bytes) of each of TILES tensors.  A copy instruction moves
+// 1 KB; per instruction of a tile the lane's byte offset inside a chunk is fixed (row r of the tile, 16-byte chunk with the
+// tile's swizzle) and the chunk's first row moves the wave-uniform base pointer.  The last chunk, if short, takes the rows past
+// its end from the last token (their gates are zero).
+template <int CPR, int TILES>
+struct TileCopy {
+  static constexpr int N = CPR * TILES, CH = 64;  // instructions per chunk
+  const __bf16* base;
+  int64_t tile_step;
+  uint32_t lds_off;
+  int lane, L;
+  bool rev;
+  uint32_t off[CPR];
+  __device__ __forceinline__ TileCopy(const __bf16* base_, int64_t tile_step_, uint32_t lds_off_, int lane_, int L_, bool rev_)
+      : base(base_), tile_step(tile_step_), lds_off(lds_off_), lane(lane_), L(L_), rev(rev_) {
+#pragma unroll
+    for (int i = 0; i < CPR; ++i) off[i] = lane_off(i, CH);
+  }
+  __device__ __forceinline__ uint32_t lane_off(int nb, int rows) const {
+    const int pos = nb * 64 + lane, r = pos / CPR, pc = pos % CPR;
+    // walking backwards, tile row r is the token r in front of the chunk's first one, and the base pointer stands at
+    // the chunk's lowest address: its last row (row 63 of a whole chunk, token 0 of a short one)
+    int row = min(r, rows - 1);
+    if (rev) row = rows - 1 - row;
+    return (uint32_t)(row * (CPR * 16) + ((pc ^ bswz<CPR>(r)) << 4));
+  }
+  __device__ __forceinline__ void issue(int c, uint32_t stage) const {
+    const int t0 = c * CH, rows = min(L - t0, CH);
+    const int64_t r0 = rev ? max(L - CH - t0, 0) : t0;  // the chunk's row with the lowest address
+    static_for<0, TILES>([&](auto tc) {
+      const __bf16* src = base + decltype(tc)::value * tile_step + r0 * (CPR * 8);
+      const uint32_t dst = stage + lds_off + decltype(tc)::value * (CPR * 1024);
+      if (rows == CH) {
+        static_for<0, CPR>([&](auto nb) { dma16_at<decltype(nb)::value * 1024>(src, off[decltype(nb)::value], dst); });
+      } else {
+        static_for<0, CPR>([&](auto nb) { dma16_at<decltype(nb)::value * 1024>(src, lane_off(decltype(nb)::value, rows), dst); });
+      }
+    });
+  }
+};
+
+// STATE_ONLY: no outputs, only the state update is walked (see GatedParams::state_only): no queries, no weights, one barrier
+// per chunk.
 template <class C, bool STATE_ONLY>
-__global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt) {
-  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
+__global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt) {
+  using Y = GLayout<C, STATE_ONLY>;
+  __shared__ __attribute__((aligned(1024))) char smem[Y::LDS_BYTES];
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ln = lane & 31, half = lane >> 5;
-  // workgroup -> batch entry and HPW consecutive value heads of one q/k group; wave -> (head, 32 value columns,
-  // query block of the chunk)
-  const int hw = wave / C::WPH, wh = wave % C::WPH, vblk = wh / C::QS, ib = wh % C::QS;
+  // workgroup -> batch entry and HPW consecutive value heads of one q/k group, and the segment of the walk
   const int seg = blockIdx.x % p.nseg;
-  const int bh0 = (blockIdx.x / p.nseg) * C::HPW, b = bh0 / p.H, h = bh0 % p.H + hw, bh = bh0 + hw;
-  const int hqk = h / (p.H / p.H_qk);
+  const int bh0 = (blockIdx.x / p.nseg) * C::HPW, b = bh0 / p.H, h0 = bh0 % p.H;
+  const int hqk = h0 / (p.H / p.H_qk);
   const bool rev = p.reverse != 0;
   // the tokens this workgroup walks: L of them from position `first` of the walk (the whole sequence unless it is
   // cut into segments); row_lo: the one with the lowest address, where all base pointers below stand
   const int64_t Lt = p.L, first = (int64_t)seg * p.seg_len;
-  const int64_t L = p.nseg > 1 ? min(Lt - first, (int64_t)p.seg_len) : Lt;
+  const int L = (int)(p.nseg > 1 ? min(Lt - first, (int64_t)p.seg_len) : Lt);
   const int64_t row_lo = rev ? Lt - first - L : first;
-  const __bf16* Qh = p.Q + (((int64_t)b * p.H_qk + hqk) * Lt + row_lo) * C::DQK;
-  const __bf16* Kh = p.K + (((int64_t)b * p.H_qk + hqk) * Lt + row_lo) * C::DQK;
-  const __bf16* Vh = p.V + (((int64_t)b * p.H_v + h / (p.H / p.H_v)) * Lt + row_lo) * C::DV;
-  const float* lah = p.log_decay ? p.log_decay + (int64_t)bh * Lt + row_lo : nullptr;
-  const float la_const = lah ? 0.f : dt.log2_gamma[h] * 0.6931471805599453f;  // constant decay per head: ln gamma
-  const float* gh = p.key_gate ? p.key_gate + (int64_t)bh * Lt + row_lo : nullptr;
-  const int64_t slot = (int64_t)bh * p.nseg + seg;  // of this segment's states
-  const uint32_t raw0 = lds0 + C::STAGES * C::STAGE_BYTES + hw * C::RAW_BYTES;  // the head's raw gates, stage 0
-  const uint32_t gate0 = lds0 + C::STAGES * (C::STAGE_BYTES + C::HPW * C::RAW_BYTES) + wave * C::GATE_BYTES;  // this wave's b[64], g[64], w[64]
-  const uint32_t scrap0 = lds0 + C::LDS_BYTES - 256;
+  const int n_chunks = (L + C::CH - 1) / C::CH;
+  auto stage_of = [&](int c) { return lds0 + (uint32_t)(c % Y::STAGES) * Y::STAGE_BYTES; };
+  auto gates_of = [&](int hh) { return lds0 + Y::kGates + hh * C::GATE_BYTES; };
 
-  // ---- the state slab of this wavefront: rows d, columns 32 * wave .. + 31 ----
-  f32x16 H[C::DBQ];
-#pragma unroll
-  for (int db = 0; db < C::DBQ; ++db) {
-    if (p.h_in) {
-      const float* src = p.h_in + slot * C::DQK * C::DV + 32 * vblk + ln;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) H[db][r] = src[(int64_t)(32 * db + key_offset(r) + 4 * half) * C::DV];
-    } else {
-      H[db] = zero16();
-    }
-    pin(H[db]);  // (the loads of the initial state are awaited here, not by a wait inside the loop)
-  }
-
-  // ---- copies: chunk c -> stage c % 3 ----
-  // Per copy instruction of this wave the lane's byte offset inside a chunk is fixed (row r of the tile, chunk slot
-  // with the tile's swizzle); the chunk's first row moves the wave-uniform base pointer.  The last chunk, if short,
-  // takes the offsets with its rows clamped to the last token (their gates are zero).
-  constexpr int NQ = C::CPRQ / C::WAVES, NV = C::CPRV / C::WPH;
-  uint32_t qoff[NQ], voff[NV];  // whole chunks: the lane's byte offsets from the chunk's first row (Q and K tiles alike)
-  auto lane_off = [&](auto cprc, int nb, int t0, bool whole) {
-    constexpr int CPR = decltype(cprc)::value;
-    const int pos = nb * 64 + lane, r = pos / CPR, pc = pos % CPR;
-    int row = whole ? r : min(r, (int)L - 1 - t0);
-    // walking backwards, tile row r is the token r in front of the chunk's first one, and the base pointer stands at
-    // the chunk's lowest address: its last row (row 63 of a whole chunk, token 0 of a short one)
-    if (rev) row = (whole ? C::CH - 1 : (int)L - 1 - t0) - row;
-    return (uint32_t)((row * (CPR * 8) + ((pc ^ bswz<CPR>(r)) * 8)) * 2);
-  };
-  uint32_t qoff_t[NQ], voff_t[NV];  // the same for the last chunk, if it is short
-  const int n_chunks = (int)((L + C::CH - 1) / C::CH);
-  const int t0_last = (n_chunks - 1) * C::CH;
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    qoff[i] = lane_off(std::integral_constant<int, C::CPRQ>{}, wave + i * C::WAVES, 0, true);
-    qoff_t[i] = lane_off(std::integral_constant<int, C::CPRQ>{}, wave + i * C::WAVES, t0_last, false);
-  }
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    voff[i] = lane_off(std::integral_constant<int, C::CPRV>{}, wh + i * C::WPH, 0, true);
-    voff_t[i] = lane_off(std::integral_constant<int, C::CPRV>{}, wh + i * C::WPH, t0_last, false);
-  }
-  auto issue_chunk = [&](int c) {
-    const int t0 = c * C::CH;
-    const bool whole = t0 + C::CH <= L;
-    const uint32_t base = lds0 + (c % C::STAGES) * C::STAGE_BYTES;
-    const int64_t r0 = rev ? max((int)L - C::CH - t0, 0) : t0;  // the chunk's row with the lowest address
-    const __bf16 *qc = Qh + r0 * C::DQK, *kc = Kh + r0 * C::DQK, *vc = Vh + r0 * C::DV;
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) {
-      const int nb = wave + i * C::WAVES;
-      const uint32_t off = whole ? qoff[i] : qoff_t[i];  // (only the last chunk can be short)
-      if constexpr (!STATE_ONLY) dma16(qc, off, base + nb * 1024);
-      dma16(kc, off, base + C::Q_BYTES + nb * 1024);
-    }
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int nb = wh + i * C::WPH;
-      const uint32_t off = whole ? voff[i] : voff_t[i];
-      dma16(vc, off, base + 2 * C::Q_BYTES + hw * C::V_BYTES + nb * 1024);
-    }
-    // the head's gates, one token per lane: its first wave fetches the log-decays, its second the key gates; the
-    // others (and a row that does not exist: constant decay, no key gate) fetch a word they never look at, so that
-    // every wave issues the same number of copies
-    const float* grow = wh == 0 && lah ? lah : wh == 1 && gh ? gh : nullptr;
-    const uint32_t gdst = raw0 + (c % C::STAGES) * (C::HPW * C::RAW_BYTES) + (wh == 1 ? 256 : 0);
-    // walking backwards: the decay of the token one later in the sequence (the walk's first token has none: its
-    // word is replaced by 0 where it is read), the gate of the token itself
-    // (cut into segments, the first token of a later segment does have a successor: the word behind the segment)
-    int gi = min(t0 + lane, (int)L - 1);
-    if (rev) gi = wh == 0 ? min((int)L - gi, first > 0 ? (int)L : (int)L - 1) : (int)L - 1 - gi;
-    const uint32_t goff = grow ? (uint32_t)gi * 4u : 0u;
-    dma4(grow ? (const void*)grow : (const void*)Qh, goff, grow ? gdst : scrap0);
-  };
-
-  // Per-lane parts of the fragment addresses, relative to a stage (see attn_bwd_kernel.hpp for the two read patterns
-  // of a tile).  Whatever depends on the lane sits in these registers; the stage adds one uniform offset per chunk
-  // (below), and tile, row block and token step are compile-time offsets that the LDS instructions carry themselves.
-  const int li = lane & 15, blk = (lane >> 4) & 1;
-  const int trow = 4 * half + (li >> 2), tcl = 2 * blk + ((li & 3) >> 1);
-  // row fragment of Q or K for d-step t (d = 16 t + 4 half + {0..3} and + 8), row ln of a 32-row block: two 8-byte pieces
-  uint32_t rq0[C::T][2];
-#pragma unroll
-  for (int t = 0; t < C::T; ++t)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) rq0[t][j] = ln * C::RBQ + 8 * half + (((2 * t + j) ^ bswz<C::CPRQ>(ln)) << 4);
-  // transposed fragment: 32 columns of block k, rows trow and trow + 8 of a 16-token step (lane = column, registers =
-  // rows in accumulator order)
-  auto tr_lane = [&](auto cprc, int k, int j) {
+  // transposed fragment: 32 columns of a tile, rows trow and trow + 8 of a 16-token step (lane = column, registers =
+  // rows in accumulator order); `piece` of four columns of every 16
+  const int li = lane & 15, blk = (lane >> 4) & 1, trow = 4 * half + (li >> 2);
+  auto tr_lane = [&](auto cprc, int k, int j, int piece) {
     constexpr int CPR = decltype(cprc)::value, RB = CPR * 16;
     const int r = trow + 8 * j;
-    return (uint32_t)((li & 1) * 8 + r * RB + (((4 * k + tcl) ^ bswz<CPR>(r)) << 4));
+    return (uint32_t)((piece & 1) * 8 + r * RB + (((4 * k + 2 * blk + (piece >> 1)) ^ bswz<CPR>(r)) << 4));
   };
-  uint32_t kt0[C::DBQ][2], vt0[2];
-#pragma unroll
-  for (int k = 0; k < C::DBQ; ++k)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) kt0[k][j] = C::Q_BYTES + tr_lane(std::integral_constant<int, C::CPRQ>{}, k, j);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) vt0[j] = 2 * C::Q_BYTES + hw * C::V_BYTES + tr_lane(std::integral_constant<int, C::CPRV>{}, vblk, j);
+  // row fragment of Q or K for d-step t (d = 16 t + 8 half + {0..7}), row ln of a 32-row block
+  auto row_lane = [&](int t) { return (uint32_t)(ln * C::RBQ + (((2 * t + half) ^ bswz<C::CPRQ>(ln)) << 4)); };
 
-  constexpr int NDMA = STATE_ONLY ? C::NDMA - NQ : C::NDMA;
-  float seg_b = 0.f;  // sum of the log-decays walked so far
-  issue_chunk(0);
-  if (n_chunks > 1) issue_chunk(1);
-
-  for (int c = 0; c < n_chunks; ++c) {
-    const int t0 = c * C::CH;
-    // this chunk's fragment addresses: the lane parts plus the stage
-    uint32_t rq[C::T][2], kt[C::DBQ][2], vt[2];
-    {
-      const uint32_t sb = lds0 + (c % C::STAGES) * C::STAGE_BYTES;
+  if (wave < C::SW) {
+    // ================= state wavefront: 32 value columns of one head =================
+    const int hw = wave / C::NB, vblk = wave % C::NB, bh = bh0 + hw;
+    const int64_t slot = (int64_t)bh * p.nseg + seg;  // of this segment's states
+    const uint32_t gate = gates_of(hw);
+    f32x16 H[C::DBQ];  // register r of tile db: row d = 32 db + 16 (r / 8) + 8 half + r % 8 of the slab, column ln
+    auto h_row = [&](int db, int r) { return (int64_t)(32 * db + 16 * (r >> 3) + 8 * half + (r & 7)) * C::DV; };
 #pragma unroll
-      for (int t = 0; t < C::T; ++t)
+    for (int db = 0; db < C::DBQ; ++db) {
+      if (p.h_in) {
+        const float* src = p.h_in + slot * C::DQK * C::DV + 32 * vblk + ln;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          rq[t][j] = rq0[t][j] + sb;
-          pin(rq[t][j]);
-        }
-#pragma unroll
-      for (int k = 0; k < C::DBQ; ++k)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          kt[k][j] = kt0[k][j] + sb;
-          pin(kt[k][j]);
-        }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        vt[j] = vt0[j] + sb;
-        pin(vt[j]);
+        for (int r = 0; r < 16; ++r) H[db][r] = src[h_row(db, r)];
+      } else {
+        H[db] = zero16();
       }
+      pin(H[db]);
     }
-    // rows row0 + ln of the Q tile (tile 0) or the K tile (tile 1), d-step t
-    auto row_frag = [&](int tile, int row0, int t) {
-      const uint32_t o = tile * C::Q_BYTES + row0 * C::RBQ;
-      const u32x2 lo = lds_read8(rq[t][0] + o), hi = lds_read8(rq[t][1] + o);
-      return __builtin_bit_cast(bf16x8, (u32x4){lo[0], lo[1], hi[0], hi[1]});
+    uint32_t rq0[C::T], kt0[C::DBQ][2], vt0[2];
+#pragma unroll
+    for (int t = 0; t < C::T; ++t) rq0[t] = row_lane(t);
+#pragma unroll
+    for (int k = 0; k < C::DBQ; ++k)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        kt0[k][j] = Y::kK + tr_lane(std::integral_constant<int, C::CPRQ>{}, k, j, 2 * (li & 1) + ((li >> 1) & 1));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) vt0[j] = Y::kV + hw * C::V_BYTES + tr_lane(std::integral_constant<int, C::CPRV>{}, vblk, j, li & 3);
+
+    // The chunk's V fragments times the tokens' weights (element e of fragment s: token 16 s + 8 (e / 4) + 4 half + e % 4),
+    // then H += K^T (w . V)
+    auto update = [&](int c, const bf16x8 (&vf)[4]) {
+      const uint32_t sb = stage_of(c), w = gate + (C::kW + (c & 1) * 64 + 4 * half) * 4;
+      f32x4 wv[8];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) wv[s] = lds_read16(w + 32 * s);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        bf16x8 vw;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          vw[e] = (__bf16)((float)vf[s][e] * wv[2 * s][e]);
+          vw[4 + e] = (__bf16)((float)vf[s][4 + e] * wv[2 * s + 1][e]);
+        }
+#pragma unroll
+        for (int db = 0; db < C::DBQ; ++db)
+          H[db] = mfma(read_tr_frag(sb + kt0[db][0] + 16 * s * C::RBQ, sb + kt0[db][1] + 16 * s * C::RBQ), vw, H[db]);
+      }
     };
-    auto k_tr_frag = [&](int k, int s) { return read_tr_frag(kt[k][0] + 16 * s * C::RBQ, kt[k][1] + 16 * s * C::RBQ); };
-    auto v_tr_frag = [&](int s) { return read_tr_frag(vt[0] + 16 * s * C::RBV, vt[1] + 16 * s * C::RBV); };
-    // Chunk c has landed: of this wave's memory operations only those issued after its copies may still be in
-    // flight -- the copies of chunk c + 1 (if there is one) and the stores of chunk c - 1 (if there was one; it was
-    // a whole chunk: four stores).  The counter runs in issue order.  Then the barrier: everybody's copies have
-    // landed and every wave is done with chunk c - 1, whose stage chunk c + 2 may now overwrite.
-    {
-      const bool nxt = c + 1 < n_chunks, prv = c > 0;
-      const bool st = prv && !STATE_ONLY && !p.state_only;  // (a walk that only updates the state stores nothing)
-      if (nxt && st) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NDMA + C::NST) : "memory");
-      else if (nxt) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NDMA) : "memory");
-      else if (st) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::NST) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      asm volatile("s_barrier" ::: "memory");
-    }
-    // The copies of chunk c + 2 (its stage is free from the barrier on).  The compute unit's memory pipe takes 64
-    // bytes per clock, a chunk's tiles are 48 KB: if all wavefronts queued their copies here, they would wait for the
-    // pipe and for each other.  Each issues its share at a different point of the iteration instead (the counts
-    // in the waits above do not care in which order a wavefront's copies and stores were issued: both are younger
-    // than the copies it waits for).
-    const bool more = c + 2 < n_chunks;
-    const int turn = wave & 3;
-    if (more && turn == 0) issue_chunk(c + 2);
-    // gates of this lane's token: log-decay (0 past the end: the state is carried unchanged; at least -20: a token
-    // that lets less than e^-20 through lets nothing through at the precision of the path, and the bound keeps the
-    // factorised weights below in range) and key gate (0 past the end)
-    float la = 0.f, g = 0.f;
-    if (t0 + lane < L) {
-      const uint32_t raw = raw0 + (c % C::STAGES) * (C::HPW * C::RAW_BYTES) + lane * 4;
-      la = lah ? fmaxf(*reinterpret_cast<__attribute__((address_space(3))) const float*>((lds_char*)(uintptr_t)raw), -20.f) : la_const;
-      g = gh ? *reinterpret_cast<__attribute__((address_space(3))) const float*>((lds_char*)(uintptr_t)(raw + 256)) : 1.f;
-      if (rev && t0 + lane == 0 && first == 0) la = lah ? 0.f : la;  // (a constant decay is the same for every token: nothing to shift)
-    }
-    // the gate as a factor on the output rows instead of the keys: the two query tokens of this lane
-    float og0 = 1.f, og1 = 1.f;
-    if (p.gate_on_output) {
-      swap_halves(g, og0, og1);
-      g = t0 + lane < L ? 1.f : 0.f;
-    }
+    auto v_frags = [&](int c, bf16x8 (&vf)[4]) {
+      const uint32_t sb = stage_of(c);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) vf[s] = read_tr_frag(sb + vt0[0] + 16 * s * C::RBV, sb + vt0[1] + 16 * s * C::RBV);
+    };
 
-    // ---- gates: b = inclusive prefix sum of the log-decays over the chunk's 64 tokens (lane = token) ----
-    // (data-parallel-primitive steps: within rows of 16 lanes by shifts of 1, 2, 4, 8, then the row totals onward)
-    float bcum = la;
-    bcum += dpp_f<0x111, 0xf, 0xf>(bcum);
-    bcum += dpp_f<0x112, 0xf, 0xf>(bcum);
-    bcum += dpp_f<0x114, 0xf, 0xe>(bcum);
-    bcum += dpp_f<0x118, 0xf, 0xc>(bcum);
-    bcum += dpp_f<0x142, 0xa, 0xf>(bcum);
-    bcum += dpp_f<0x143, 0xc, 0xf>(bcum);
-    const float b_last = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, bcum), 63));
-    // Weights inside the chunk, factorised per group of four tokens: with ref_j the sum in front of token j's group
-    // (ref_j >= b_i for every i in or behind the group),  e^{b_i - b_j} g_j = e^{b_i - ref_j} * u_j,
-    // u_j = g_j e^{ref_j - b_j}: one exponential per token here and four per lane and block of keys below instead of
-    // one per score.  ref_j - b_j is at most four log-decays: with the bound of 20 above u_j stays finite.
-    {
-      const float ref = dpp_f<0x00, 0xf, 0xf>(bcum - la);  // the sum in front of lane (lane & ~3): quad broadcast of the exclusive sum
-      if constexpr (!STATE_ONLY) {
-        lds_store4(gate0 + lane * 4, ref);
-        lds_store4(gate0 + 256 + lane * 4, g * __expf(ref - bcum));
+    if constexpr (STATE_ONLY) {
+      chunk_barrier();
+      for (int c = 0; c < n_chunks; ++c) {
+        const float dec = lds_read4(gate + (C::kDec + (c & 1)) * 4);
+        bf16x8 vf[4];
+        v_frags(c, vf);
+#pragma unroll
+        for (int db = 0; db < C::DBQ; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) H[db][r] *= dec;
+        update(c, vf);
+        chunk_barrier();
       }
-      lds_store4(gate0 + 512 + lane * 4, g * __expf(b_last - bcum));
+    } else {
+      chunk_barrier();
+      chunk_barrier();
+      // where this wavefront turns an output block of 32 queries x 32 columns around: 16-byte chunk k of row r at k ^ (r % 8)
+      const uint32_t wr0 = ln * 128, rd_row = lane >> 3, rd_pc = lane & 7;
+      const int64_t o_head = (int64_t)bh * Lt + row_lo;
+      for (int c = 0; c < n_chunks; ++c) {
+        const uint32_t sb = stage_of(c);
+        const int t0 = c * C::CH;
+        // ---- read-out of the state in front of the chunk: O^T = H^T Q^T, times s_i e^{b_i} ----
+        const float dec = lds_read4(gate + (C::kDec + (c & 1)) * 4);
+        const float f0 = lds_read4(gate + (C::kS + ln) * 4) * __expf(lds_read4(gate + (C::kB + ln) * 4));
+        const float f1 = lds_read4(gate + (C::kS + 32 + ln) * 4) * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
+        f32x16 o0 = zero16(), o1 = zero16();
+#pragma unroll
+        for (int db = 0; db < C::DBQ; ++db) {
+          // the state rounded to bf16; in the same pass over the accumulators it takes the chunk's whole decay
+          bf16x8 hp[2];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float x = H[db][r];
+            hp[r / 8][r % 8] = (__bf16)x;
+            H[db][r] = x * dec;
+          }
+#pragma unroll
+          for (int tt = 0; tt < 2; ++tt) {
+            const uint32_t a = sb + rq0[2 * db + tt];
+            o0 = mfma(hp[tt], read_k_frag(a), o0);
+            o1 = mfma(hp[tt], read_k_frag(a + 32 * C::RBQ), o1);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          o0[r] *= f0;
+          o1[r] *= f1;
+        }
+        chunk_barrier();
+        // ---- the chunk's own tokens: O^T += V^T P^T; block 0: queries 0-31 x keys 0-31, 1: 32-63 x 32-63, 2: 32-63 x 0-31 ----
+        bf16x8 vf[4];
+        v_frags(c, vf);
+        {
+          const uint32_t pb = lds0 + Y::kP + hw * C::P_BYTES + lane * 16;
+          o0 = mfma(vf[0], read_k_frag(pb), o0);
+          o0 = mfma(vf[1], read_k_frag(pb + 1024), o0);
+          o1 = mfma(vf[0], read_k_frag(pb + 4096), o1);
+          o1 = mfma(vf[1], read_k_frag(pb + 5120), o1);
+          o1 = mfma(vf[2], read_k_frag(pb + 2048), o1);
+          o1 = mfma(vf[3], read_k_frag(pb + 3072), o1);
+        }
+        // ---- store ----
+        const uint32_t out = Y::kOutInQ ? sb + wave * 4096 : lds0 + Y::kOut + wave * 4096;
+        auto store_block = [&](auto ibc, const f32x16& o) {
+          constexpr int IB = decltype(ibc)::value;
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+            lds_write16(out + wr0 + (((2 * a + half) ^ (ln & 7)) << 4), (f32x4){o[4 * a], o[4 * a + 1], o[4 * a + 2], o[4 * a + 3]});
+          f32x4 v[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v[k] = lds_read16(out + (8 * k + rd_row) * 128 + ((rd_pc ^ rd_row) << 4));
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int i = t0 + 32 * IB + 8 * k + (int)rd_row;
+            if (i < L) {
+              const int64_t e0 = (o_head + (rev ? L - 1 - i : i)) * C::DV + 32 * vblk + 4 * rd_pc;
+              if (p.out_bf16) {
+                bf16x4 hv;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) hv[e] = (__bf16)v[k][e];
+                *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.O) + e0) = hv;
+              } else {
+                *reinterpret_cast<f32x4*>(static_cast<float*>(p.O) + e0) = v[k];
+              }
+            }
+          }
+        };
+        store_block(std::integral_constant<int, 0>{}, o0);
+        store_block(std::integral_constant<int, 1>{}, o1);
+        update(c, vf);
+        chunk_barrier();
+      }
     }
-    if (more && turn == 1) issue_chunk(c + 2);
-    float bi0, bi1;  // b of tokens ln and 32 + ln
-    swap_halves(bcum, bi0, bi1);
-    // The state in front of the chunk, rounded to bf16: the A operands of the read-out (an accumulator tile is an A
-    // operand whose contraction runs over its rows).  In the same pass over the accumulators the state takes the
-    // chunk's whole decay, as the update at the end of the iteration needs it.
-    bf16x8 hp[C::DBQ][2];
-    {
-      const float dec = __expf(b_last);
+    if (p.h_out && (!p.h_out_last_only || seg == p.nseg - 1)) {
+      float* dst = p.h_out + (p.h_out_last_only ? (int64_t)bh : slot) * C::DQK * C::DV + 32 * vblk + ln;
 #pragma unroll
       for (int db = 0; db < C::DBQ; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float x = H[db][r];
-          if constexpr (!STATE_ONLY) hp[db][r / 8][r % 8] = (__bf16)x;
-          H[db][r] = x * dec;
+        for (int r = 0; r < 16; ++r) dst[h_row(db, r)] = H[db][r];
+    }
+    return;
+  }
+
+  const int role = wave - C::SW;
+  if (role == 3) {
+    // ================= the gates: lane = token of the chunk =================
+    float la[C::HPW], g[C::HPW], seg_b[C::HPW];
+    auto load_gates = [&](int c) {
+      const int t = c * C::CH + lane, gi = min(t, L - 1);
+      // walking backwards: the decay of the token one later in the sequence (the walk's first token has none: its
+      // value is replaced by 0; cut into segments, the first token of a later segment does have a successor: the
+      // word behind the segment), the gate of the token itself
+      const int gl = rev ? min(L - gi, first > 0 ? L : L - 1) : gi, gg = rev ? L - 1 - gi : gi;
+#pragma unroll
+      for (int hh = 0; hh < C::HPW; ++hh) {
+        const int64_t row = (int64_t)(bh0 + hh) * Lt + row_lo;
+        la[hh] = p.log_decay ? p.log_decay[row + gl] : dt.log2_gamma[h0 + hh] * 0.6931471805599453f;  // constant: ln gamma
+        g[hh] = p.key_gate ? p.key_gate[row + gg] : 1.f;
+      }
+    };
+    auto put_gates = [&](int c) {
+      const int t = c * C::CH + lane;
+#pragma unroll
+      for (int hh = 0; hh < C::HPW; ++hh) {
+        const uint32_t gate = gates_of(hh);
+        // log-decay (0 past the end: the state is carried unchanged; at least -20: a token that lets less than e^-20
+        // through lets nothing through at the precision of the path, and the bound keeps the factorised weights below in
+        // range) and key gate (0 past the end); a constant decay is the same for every token: nothing to shift or to bound
+        float a = la[hh], k = g[hh], s = p.scale;
+        if (p.log_decay) a = rev && t == 0 && first == 0 ? 0.f : fmaxf(a, -20.f);
+        if (p.gate_on_output) {  // the gate as a factor on the output rows instead of the keys
+          s *= k;
+          k = 1.f;
         }
+        if (t >= L) a = k = 0.f;
+        // b: inclusive prefix sum over the 64 tokens (data-parallel-primitive steps: within rows of 16 lanes by shifts of
+        // 1, 2, 4, 8, then the row totals onward)
+        float bcum = a;
+        bcum += dpp_f<0x111, 0xf, 0xf>(bcum);
+        bcum += dpp_f<0x112, 0xf, 0xf>(bcum);
+        bcum += dpp_f<0x114, 0xf, 0xe>(bcum);
+        bcum += dpp_f<0x118, 0xf, 0xc>(bcum);
+        bcum += dpp_f<0x142, 0xa, 0xf>(bcum);
+        bcum += dpp_f<0x143, 0xc, 0xf>(bcum);
+        const float b_last = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, bcum), 63));
+        seg_b[hh] += b_last;
+        lds_store4(gate + (C::kW + (c & 1) * 64 + lane) * 4, k * __expf(b_last - bcum));
+        lds_store4(gate + (C::kDec + (c & 1)) * 4, __expf(b_last));
+        if constexpr (!STATE_ONLY) {
+          // Weights inside the chunk, factorised per group of four tokens: with ref_j the sum in front of token j's group
+          // (ref_j >= b_i for every i in or behind the group),  e^{b_i - b_j} g_j = e^{b_i - ref_j} * u_j,
+          // u_j = g_j e^{ref_j - b_j}: one exponential per token here and four per lane and block of weights instead of
+          // one per weight.  ref_j - b_j is at most four log-decays: with the bound of 20 above u_j stays finite.
+          const float ref = dpp_f<0x00, 0xf, 0xf>(bcum - a);  // the sum in front of lane (lane & ~3): quad broadcast of the exclusive sum
+          lds_store4(gate + (C::kB + lane) * 4, bcum);
+          lds_store4(gate + (C::kU + lane) * 4, k * __expf(ref - bcum));
+          lds_store4(gate + (C::kS + lane) * 4, s);
+          lds_store4(gate + (C::kRef + (lane >> 2)) * 4, ref);
+        }
+      }
+    };
+#pragma unroll
+    for (int hh = 0; hh < C::HPW; ++hh) seg_b[hh] = 0.f;
+    load_gates(0);
+    if constexpr (!STATE_ONLY) chunk_barrier();
+    put_gates(0);
+    if (n_chunks > 1) load_gates(1);
+    chunk_barrier();
+    for (int c = 0; c < n_chunks; ++c) {
+      if constexpr (!STATE_ONLY) chunk_barrier();
+      if (c + 1 < n_chunks) {
+        put_gates(c + 1);
+        if (c + 2 < n_chunks) load_gates(c + 2);
+      }
+      chunk_barrier();
     }
-    bf16x8 vf[4];  // the V fragments of the chunk's four 16-token steps (this wave's 32 value columns)
-    // The wave's query block as a compile-time constant (register arrays indexed by it stay in registers).
-    auto query_block = [&](auto ibc) {
-    constexpr int IB = decltype(ibc)::value;
-    const float bi = IB ? bi1 : bi0;  // of this lane's query: token 32 IB + ln of the chunk
-    const float og = IB ? og1 : og0;
-    // ---- Q fragments of the wave's query block (B operands of S^T and of the read-out) ----
-    bf16x8 qf[C::T];
+    if (p.seg_decay && lane == 0) {
 #pragma unroll
-    for (int t = 0; t < C::T; ++t) qf[t] = row_frag(0, 32 * IB, t);
-
-    // ---- read-out of the state in front of the chunk: O^T = H^T Q^T, times scale e^{b_i} ----
-    f32x16 o = zero16();
-#pragma unroll
-    for (int db = 0; db < C::DBQ; ++db)
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt) o = mfma(hp[db][tt], qf[2 * db + tt], o);
-    {
-      const float f = p.scale * __expf(bi);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[r] *= f;
+      for (int hh = 0; hh < C::HPW; ++hh) p.seg_decay[(int64_t)(bh0 + hh) * p.nseg + seg] = seg_b[hh];
     }
+    return;
+  }
 
-    // weights of one S^T block: scale e^{b_i - b_j} g_j s for key j <= query i (positions inside the chunk), else 0
-    auto weigh = [&](const f32x16& s, int kblk, bool diag, u32x4 (&pk)[2]) {
+  // ================= copies (helper 0: Q, 1: K, 2: V of every head) and weights =================
+  // scores of this helper's block in front of the weights: role 0: keys 0-31 x queries 0-31, 1: 32-63 x 32-63, 2: 0-31 x 32-63
+  const int kb = role == 1 ? 1 : 0, qb = role == 0 ? 0 : 1;
+  const int last_key = role == 2 ? C::CH : ln;  // inside a diagonal block keys behind the lane's query get weight 0
+  uint32_t rq0[C::T];
+#pragma unroll
+  for (int t = 0; t < C::T; ++t) rq0[t] = row_lane(t);
+  auto scores = [&](int c) {
+    const uint32_t kt = stage_of(c) + Y::kK + 32 * kb * C::RBQ, qt = stage_of(c) + 32 * qb * C::RBQ;
+    f32x16 s = zero16();
+#pragma unroll
+    for (int t = 0; t < C::T; ++t) s = mfma(read_k_frag(kt + rq0[t]), read_k_frag(qt + rq0[t]), s);
+    return s;
+  };
+  // weights of the block: s_i e^{b_i - b_j} g_j (q_i . k_j) for key j <= query i (positions inside the chunk), else 0
+  auto weigh = [&](const f32x16& sc) {
+#pragma unroll
+    for (int hh = 0; hh < C::HPW; ++hh) {
+      const uint32_t gate = gates_of(hh);
+      const float bi = lds_read4(gate + (C::kB + 32 * qb + ln) * 4), si = lds_read4(gate + (C::kS + 32 * qb + ln) * 4);
       float ref[4];
       f32x4 uj[4];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {  // (all eight reads first: one LDS latency for the block, not four)
-        const uint32_t off = (32 * kblk + 8 * a + 4 * half) * 4;
-        ref[a] = *reinterpret_cast<__attribute__((address_space(3))) const float*>((lds_char*)(uintptr_t)(gate0 + off));
-        uj[a] = lds_read16(gate0 + 256 + off);
+      for (int a = 0; a < 4; ++a) {
+        ref[a] = lds_read4(gate + (C::kRef + 8 * kb + 2 * a + half) * 4);
+        uj[a] = lds_read16(gate + (C::kU + 32 * kb + 8 * a + 4 * half) * 4);
       }
+      u32x4 pk[2];
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         // (groups past the lane's query have bi > ref: whatever the factor becomes there, the mask below discards it)
-        const float qfac = p.scale * __expf(bi - ref[a]);
+        const float qfac = si * __expf(bi - ref[a]);
         float x[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          x[e] = s[4 * a + e] * (qfac * uj[a][e]);
-          if (diag && 8 * a + 4 * half + e > ln) x[e] = 0.f;
+          x[e] = sc[4 * a + e] * (qfac * uj[a][e]);
+          if (8 * a + 4 * half + e > last_key) x[e] = 0.f;
         }
         bf16x2 lo, hi;
         lo[0] = (__bf16)x[0];
@@ -382,108 +454,66 @@ __global__ __launch_bounds__(C::THREADS) void gated_recurrent_kernel(const Gated
         pk[a / 2][2 * (a % 2)] = __builtin_bit_cast(uint32_t, lo);
         pk[a / 2][2 * (a % 2) + 1] = __builtin_bit_cast(uint32_t, hi);
       }
-    };
-    // ---- scores and aggregation inside the chunk: the diagonal block of the wave's queries, and for the second
-    //      query block also the block below the diagonal (keys 0-31) ----
-    {
-      f32x16 sd = zero16();
-#pragma unroll
-      for (int t = 0; t < C::T; ++t) sd = mfma(row_frag(1, 32 * IB, t), qf[t], sd);
-      u32x4 pd[2];
-      weigh(sd, IB, true, pd);
-      // the V fragments of the chunk's four 16-token steps (this wave's 32 value columns): A operands of the
-      // aggregation and, weighted, B operands of the state update
-      if constexpr (IB == 0 || C::QS == 2) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) vf[s] = v_tr_frag(s);
+      const uint32_t pb = lds0 + Y::kP + hh * C::P_BYTES + role * 2048 + lane * 16;
+      lds_write16(pb, __builtin_bit_cast(f32x4, pk[0]));
+      lds_write16(pb + 1024, __builtin_bit_cast(f32x4, pk[1]));
+    }
+  };
+  auto help = [&](const auto& cp) {
+    constexpr int N = std::decay_t<decltype(cp)>::N;
+    if constexpr (STATE_ONLY) {
+      // this wavefront's share of chunk c has landed: all of its copies but those of the chunks behind it (at most two)
+      auto landed = [&](int c) {
+        const int behind = min(n_chunks - 1 - c, 2);
+        if (behind == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * N) : "memory");
+        else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      };
+      for (int c = 0; c < min(n_chunks, 3); ++c) cp.issue(c, stage_of(c));
+      landed(0);
+      chunk_barrier();
+      for (int c = 0; c < n_chunks; ++c) {
+        if (c + 3 < n_chunks) cp.issue(c + 3, stage_of(c + 3));
+        if (c + 1 < n_chunks) landed(c + 1);
+        chunk_barrier();
       }
-      o = mfma(vf[2 * IB], __builtin_bit_cast(bf16x8, pd[0]), o);
-      o = mfma(vf[2 * IB + 1], __builtin_bit_cast(bf16x8, pd[1]), o);
-    }
-    if constexpr (IB == 1) {
-      f32x16 sl = zero16();
-#pragma unroll
-      for (int t = 0; t < C::T; ++t) sl = mfma(row_frag(1, 0, t), qf[t], sl);
-      u32x4 pl[2];
-      weigh(sl, 0, false, pl);
-      o = mfma(vf[0], __builtin_bit_cast(bf16x8, pl[0]), o);
-      o = mfma(vf[1], __builtin_bit_cast(bf16x8, pl[1]), o);
-    }
-
-    // ---- store: lane = query row, four 16-byte pieces of the wave's 32 columns ----
-    {
-      const int64_t i = t0 + 32 * IB + ln;
-      if (i < L) {
-        if (p.gate_on_output) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[r] *= og;
-        }
-        const int64_t e0 = ((int64_t)bh * Lt + row_lo + (rev ? L - 1 - i : i)) * C::DV + 32 * vblk + 4 * half;
-        if (p.out_bf16) {
-#pragma unroll
-          for (int a = 0; a < 4; ++a) {
-            bf16x4 hv;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) hv[e] = (__bf16)o[4 * a + e];
-            *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.O) + e0 + 8 * a) = hv;
-          }
-        } else {
-#pragma unroll
-          for (int a = 0; a < 4; ++a)
-            *reinterpret_cast<f32x4*>(static_cast<float*>(p.O) + e0 + 8 * a) = (f32x4){o[4 * a], o[4 * a + 1], o[4 * a + 2], o[4 * a + 3]};
-        }
-      }
-    }
-
-    };
-    if (!STATE_ONLY && !p.state_only) {
-      if (C::QS == 1 || ib == 0) query_block(std::integral_constant<int, 0>{});
-      if (more && turn == 2) issue_chunk(c + 2);
-      if (C::QS == 1 || ib == 1) query_block(std::integral_constant<int, 1>{});
     } else {
-      if (more && turn == 2) issue_chunk(c + 2);
-      // (the V fragments that a query block would have left behind for the update)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) vf[s] = v_tr_frag(s);
-    }
-    seg_b += b_last;
-    if (more && turn == 3) issue_chunk(c + 2);
-
-    // ---- state update: H (already e^{b_last} times the old state) += K^T (w . V) ----
-    f32x4 wv[8];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      wv[2 * s] = lds_read16(gate0 + 512 + (16 * s + 4 * half) * 4);
-      wv[2 * s + 1] = lds_read16(gate0 + 512 + (16 * s + 8 + 4 * half) * 4);
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      // the V fragment of token step s times the tokens' weights (element e of the fragment: token 16 s + 8 (e / 4) + 4 half + e % 4)
-      bf16x8 vw;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        vw[e] = (__bf16)((float)vf[s][e] * wv[2 * s][e]);
-        vw[4 + e] = (__bf16)((float)vf[s][4 + e] * wv[2 * s + 1][e]);
+      auto landed = [&](bool one_behind) {
+        if (one_behind) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      };
+      cp.issue(0, stage_of(0));
+      if (n_chunks > 1) cp.issue(1, stage_of(1));
+      landed(n_chunks > 1);
+      chunk_barrier();
+      f32x16 s = scores(0);
+      chunk_barrier();
+      for (int c = 0; c < n_chunks; ++c) {
+        const bool more = c + 2 < n_chunks;
+        if (more) cp.issue(c + 2, stage_of(c + 2));
+        weigh(s);
+        if (c + 1 < n_chunks) landed(more);
+        chunk_barrier();
+        if (c + 1 < n_chunks) s = scores(c + 1);
+        chunk_barrier();
       }
-#pragma unroll
-      for (int db = 0; db < C::DBQ; ++db)
-        H[db] = mfma(k_tr_frag(db, s), vw, H[db]);
     }
-  }
-
-  if (p.seg_decay && wh == 0 && lane == 0) p.seg_decay[slot] = seg_b;
-  if (p.h_out && ib == 0 && (!p.h_out_last_only || seg == p.nseg - 1)) {  // (the slab's other copy is identical)
-    float* dst = p.h_out + (p.h_out_last_only ? (int64_t)bh : slot) * C::DQK * C::DV + 32 * vblk + ln;
-#pragma unroll
-    for (int db = 0; db < C::DBQ; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dst[(int64_t)(32 * db + key_offset(r) + 4 * half) * C::DV] = H[db][r];
+  };
+  const int64_t qk_row = ((int64_t)b * p.H_qk + hqk) * Lt + row_lo;
+  if (role == 2) {
+    // (HPW > 1: the heads' V are consecutive, see launch_gated_recurrent)
+    const int64_t v_row = ((int64_t)b * p.H_v + h0 / (p.H / p.H_v)) * Lt + row_lo;
+    help(TileCopy<C::CPRV, C::HPW>(p.V + v_row * C::DV, Lt * C::DV, Y::kV, lane, L, rev));
+  } else if (role == 1 || !STATE_ONLY) {
+    help(TileCopy<C::CPRQ, 1>((role == 1 ? p.K : p.Q) + qk_row * C::DQK, 0, role == 1 ? Y::kK : 0, lane, L, rev));
+  } else {
+    for (int c = 0; c <= n_chunks; ++c) chunk_barrier();
   }
 }
 
-template <int DQK, int DV, int HPW = 1, int QS = 2>
+template <int DQK, int DV, int HPW = 1>
 hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
-  typedef GCfg<DQK, DV, HPW, QS> C;
+  typedef GCfg<DQK, DV, HPW> C;
   const dim3 grid((unsigned)(p.B * p.H / HPW * p.nseg));
   if (p.state_only) hipLaunchKernelGGL((gated_recurrent_kernel<C, true>), grid, dim3(C::THREADS), 0, s, p, dt);
   else hipLaunchKernelGGL((gated_recurrent_kernel<C, false>), grid, dim3(C::THREADS), 0, s, p, dt);
@@ -634,11 +664,11 @@ hipError_t launch_gated_recurrent(const GatedParams& p_in, const DecayTable& dt,
   if (dqk == 128 && dv == 64) {
     // value heads that share their q/k head (Mamba2's groups) share the Q and K tiles of a workgroup, two at a time
     const int grp = p.H / p.H_qk;
-    if (grp % 2 == 0 && p.H_v == p.H) return launch<128, 64, 2, 1>(p, dt, s);
+    if (grp % 2 == 0 && p.H_v == p.H) return launch<128, 64, 2>(p, dt, s);
     return launch<128, 64>(p, dt, s);
   }
   if (dqk == 64 && dv == 128) return launch<64, 128>(p, dt, s);
-  if (dqk == 128 && dv == 128) return launch<128, 128, 1, AE_GATED_QS_128>(p, dt, s);
+  if (dqk == 128 && dv == 128) return launch<128, 128>(p, dt, s);
   return hipErrorInvalidValue;
 }
 

@@ -60,6 +60,22 @@ def test_matches_oracle(A, dqk, dv, kind, L):
     check(got.cpu().double().numpy(), ref, f"{kind} {dqk}/{dv} L={L}")
 
 
+@pytest.mark.parametrize("dqk,dv,H,H_qk", [(64, 64, 3, 3), (64, 128, 2, 2), (128, 64, 3, 3), (128, 64, 4, 1), (128, 128, 2, 2)])
+@pytest.mark.parametrize("L", [127, 128, 129, 192, 257])
+def test_chunk_counts_and_bf16_rows(A, dqk, dv, H, H_qk, L):
+    # two to five chunks (the copies run up to three chunks ahead), whole and short last ones, every workgroup shape; bf16 rows
+    # are the fp32 rows rounded to nearest even
+    Q, K, V, la, kg = inputs(840 + L % 7, 1, H, H_qk, L, dqk, dv, "mamba2")
+    dev = torch.device("cuda:0")
+    args = (Q.to(dev), K.to(dev), V.to(dev), la.to(dev), kg.to(dev))
+    got = A.gated_recurrent(*args, scale=0.1)
+    rounded = A.gated_recurrent(*args, scale=0.1, out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    assert torch.equal(rounded, got.to(torch.bfloat16))
+    ref = oracle_gated(Q.float().numpy(), K.float().numpy(), V.float().numpy(), la.numpy(), kg.numpy(), scale=0.1)
+    check(got.cpu().double().numpy(), ref, f"{dqk}/{dv} H {H}/{H_qk} L={L}")
+
+
 def test_grouped_query_key_heads_mamba2_shape(A):
     # Mamba2's structure at a reduced head count: B and C shared by the value heads of a group, D_qk 128, D_v 64
     Q, K, V, la, kg = inputs(810, 1, 8, 2, 300, 128, 64, "mamba2")
