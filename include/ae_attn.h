@@ -470,10 +470,11 @@ ae_status_t ae_gated_forward_segmented(const ae_gated_t *h, const void *Q, const
  *   dlog_decay device, fp32 [B, H, L];  dkey_gate the same, required exactly when
  *              key_gate is given, else NULL;
  *   workspace  device, 256-byte aligned, ae_gated_backward_workspace_bytes: 4 B per
- *              (batch, head, token), plus 8 D_qk B per (batch, head, token) when
- *              H_qk < H (the gradients of q and of the gated key per value head,
- *              which a small kernel sums over each group), plus the segments'
- *              states where the walks are cut (see ae_gated_forward_segmented).
+ *              (batch, head, token), plus at most 8 D_qk B per (batch, head,
+ *              token) when H_qk < H (the gradients of q and of the gated key per
+ *              value head, or summed over two or three of them, which a small
+ *              kernel sums over each group), plus the segments' states where the
+ *              walks are cut (see ae_gated_forward_segmented).
  *              Owned by the caller; calls sharing it must not overlap.
  * Tensors 16-byte aligned, gates and their gradients 4-byte; outputs must alias
  * neither inputs nor each other.  Uses B, H, H_qk, L, the head dims and scale of

@@ -1026,11 +1026,34 @@ ae_status_t ae_recurrent_destroy(ae_recurrent_t* h) {
 }  // extern "C"
 
 // ---- recurrent pattern with per-token gates: one kernel, state on chip ------------------------------------
+// Value heads of a group that a workgroup of the backward pass takes in turn, its gradients of q and k summed on chip; 0: one
+// head per workgroup and the sums in a kernel of their own.  Two walks take rounds of 256 workgroups x heads each, and a round
+// has a start and an end that cost about as much as a head: the heads with the least rounds x (heads + 1) are taken (us for 1 /
+// 2 / 3 heads, Mamba2 128/64: 2 x 80 heads x 768 tokens 122 / 145 / 174, 4 x 80 228 / 157 / 183, 8 x 64 301 / 206 / 202, 8 x 80
+// 401 / 332 / 257, 16 x 80 694 / 538 / 476; 6 x 80 x 500 193 / 120 / 134; 8 x 64 x 768 at 64/64 219 / 159 / 187).  With one head
+// the kernel of the sums pays where it has workgroups enough: it takes a group's heads one after the other (8 x 24 x 768 120
+// against 129, 8 x 32/8 x 600 129 against 134, but 3 x 80 x 700 146 against 131, 1 x 80 x 300 100 against 63).
+static int gated_group_heads(const ae_gated_desc_t* d, int bwd_nseg) {
+  const int64_t groups = (int64_t)d->B * d->H_qk, size = d->H / d->H_qk;
+  if (size < 2 || bwd_nseg > 1 || !ae::gated_group_supported(d->D_qk, d->D_v)) return 0;
+  int64_t heads = 1, least = INT64_MAX;
+  for (int64_t n = 1; n <= std::min<int64_t>(size, ae::kGatedGroupHeads); ++n) {
+    const int64_t cost = (groups * ((size + n - 1) / n) + 255) / 256 * (n + 1);
+    if (cost < least) {
+      least = cost;
+      heads = n;
+    }
+  }
+  const int64_t sum_workgroups = groups * d->L * d->D_qk / 1024;
+  return heads == 1 && sum_workgroups >= 512 ? 0 : (int)heads;
+}
+
 struct ae_gated {
   ae_gated_desc_t desc;
   // ae_gated_forward_segmented: the walk of a (batch, head) cut into nseg segments of seg_len tokens where the
   // (batch, head) pairs alone would leave most compute units idle; 1: not cut.  bwd_: the same for ae_gated_backward
   int nseg, seg_len, bwd_nseg, bwd_seg_len;
+  int group_heads;  // ae_gated_backward: value heads of a q/k head whose gradients of q and k a workgroup sums (0: one each, see gated_group_heads)
 };
 
 extern "C" {
@@ -1055,6 +1078,7 @@ ae_status_t ae_gated_create(const ae_gated_desc_t* d, ae_gated_t** out) {
     const bool pairs = d->D_qk == 128 && d->D_v == 64 && (d->H / d->H_qk) % 2 == 0;
     gated_segments((int64_t)d->B * d->H / (pairs ? 2 : 1), d->L, &h->nseg, &h->seg_len);
     gated_segments((int64_t)d->B * d->H, d->L, &h->bwd_nseg, &h->bwd_seg_len);  // (two of its three walks have one head each)
+    h->group_heads = gated_group_heads(d, h->bwd_nseg);
   }
   *out = h;
   return AE_OK;
@@ -1135,10 +1159,14 @@ ae_status_t ae_gated_forward_segmented(const ae_gated_t* h, const void* Q, const
 // share q/k heads, the gradients of q and of the gated key per value head, fp32 [B, H, L, D_qk] each.
 // Where the three walks of the backward pass are cut into segments, the segments' states (one set, used by the walks in
 // turn) follow.
+static int gated_parts(const ae_gated* h) {  // workgroups that share a q/k head
+  return (h->desc.H / h->desc.H_qk + h->group_heads - 1) / h->group_heads;
+}
 static size_t gated_backward_ws(const ae_gated* h, size_t* per_head_off, size_t* seg_off) {
   const ae_gated_desc_t& d = h->desc;
   const size_t rows = ((size_t)d.B * d.H * d.L * 4 + 255) & ~(size_t)255;
-  const size_t per_head = d.H != d.H_qk ? 2 * (size_t)d.B * d.H * d.L * d.D_qk * 4 : 0;
+  const size_t slabs = h->group_heads ? (size_t)d.H_qk * gated_parts(h) : (size_t)d.H;  // (a part's or a head's gradients)
+  const size_t per_head = d.H != d.H_qk ? 2 * (size_t)d.B * slabs * d.L * d.D_qk * 4 : 0;
   if (per_head_off) *per_head_off = rows;
   if (seg_off) *seg_off = rows + per_head;
   return rows + per_head + gated_segments_ws(d.B, d.H, h->bwd_nseg, d.D_qk, d.D_v);
@@ -1207,7 +1235,27 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
   p.gate_on_output = 0;
   p.reverse = 0;
   p.O = dQu;
-  hipError_t e = walk(p, d.D_v, d.D_qk);
+  // (where a workgroup takes several heads of a group, (1) and (2) leave sums over these and dB and dkey_gate)
+  ae::GatedGroupParams gp;
+  gp.Q = static_cast<const __bf16*>(dO);
+  gp.K = static_cast<const __bf16*>(V);
+  gp.V = static_cast<const __bf16*>(K);
+  gp.R = static_cast<const __bf16*>(Q);
+  gp.log_decay = p.log_decay;
+  gp.key_gate = p.key_gate;
+  gp.out = dQu;
+  gp.dB = dB;
+  gp.dkey_gate = static_cast<float*>(dkey_gate);
+  gp.B = d.B;
+  gp.H = d.H;
+  gp.H_qk = d.H_qk;
+  gp.L = d.L;
+  gp.scale = d.scale;
+  gp.reverse = 0;
+  gp.heads = h->group_heads;
+  gp.parts = h->group_heads ? gated_parts(h) : 0;
+  float* dk_parts = dQu + (size_t)d.B * d.H_qk * gp.parts * d.L * d.D_qk;
+  hipError_t e = gp.heads ? ae::launch_gated_group(gp, d.D_qk, d.D_v, stream) : walk(p, d.D_v, d.D_qk);
   // (2) x_j = scale sum_{i >= j} A_ij (v_j . dO_i) q_i, walking backwards: queries V, keys dO, values Q, no gate
   if (e == hipSuccess) {
     p.Q = static_cast<const __bf16*>(V);
@@ -1216,7 +1264,11 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
     p.key_gate = nullptr;
     p.reverse = 1;
     p.O = X;
-    e = walk(p, d.D_v, d.D_qk);
+    std::swap(gp.Q, gp.K);
+    std::swap(gp.V, gp.R);
+    gp.out = dk_parts;
+    gp.reverse = 1;
+    e = gp.heads ? ae::launch_gated_group(gp, d.D_qk, d.D_v, stream) : walk(p, d.D_v, d.D_qk);
   }
   // (3) dv_j = g_j scale sum_{i >= j} A_ij (k_j . q_i) dO_i, walking backwards: queries K, keys Q, values dO
   if (e == hipSuccess) {
@@ -1230,7 +1282,11 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
     p.O = dV;
     e = walk(p, d.D_qk, d.D_v);
   }
-  if (e == hipSuccess) {
+  if (e == hipSuccess && gp.heads) {
+    e = ae::launch_gated_group_sum(dQu, dk_parts, static_cast<float*>(dQ), static_cast<float*>(dK), gp.parts, (int64_t)d.L * d.D_qk,
+                                   (int64_t)d.B * d.H_qk * d.L * d.D_qk, stream);
+    if (e == hipSuccess) e = ae::launch_gated_suffix_sum(dB, static_cast<float*>(dlog_decay), d.B * d.H, d.L, stream);
+  } else if (e == hipSuccess) {
     ae::GatedBwdEpilogueParams q;
     q.Q = static_cast<const __bf16*>(Q);
     q.K = static_cast<const __bf16*>(K);

@@ -60,6 +60,33 @@ struct GatedBwdEpilogueParams {
   int B, H, H_qk, L;
 };
 hipError_t launch_gated_backward_epilogue(const GatedBwdEpilogueParams& p, int dqk, hipStream_t stream);
+// The same gradients where value heads share q/k heads, summed over `heads` of them (at most kGatedGroupHeads; the last part of
+// a group may have fewer) inside the walks: part `i` of a q/k head takes heads [i * heads, (i + 1) * heads) of its group and
+// leaves its sum in out [B, H_qk, parts, L, D_qk].  Forwards (reverse = 0; Q = dO, K = V, V = K, R = Q): the gradient of q, the
+// key gate on the keys, dB[h, t] = q_t . (gradient of q by head h).  Backwards (Q = V, K = dO, V = Q, R = K): the gradient of
+// k, x_h being that of head h in front of its gate: the sum of g x_h, dkey_gate[h, t] = k_t . x_h, dB[h, t] -= g k_t . x_h.
+constexpr int kGatedGroupHeads = 3;
+struct GatedGroupParams {
+  const __bf16* Q;         // [B, H, L, D_v]
+  const __bf16* K;         // [B, H, L, D_v]
+  const __bf16* V;         // [B, H_qk, L, D_qk]
+  const __bf16* R;         // [B, H_qk, L, D_qk]
+  const float* log_decay;  // [B, H, L]
+  const float* key_gate;   // [B, H, L] or null
+  float* out;
+  float* dB;               // [B, H, L]
+  float* dkey_gate;        // [B, H, L] or null
+  int B, H, H_qk, L;
+  float scale;
+  int reverse, heads, parts;
+};
+bool gated_group_supported(int dqk, int dv);
+hipError_t launch_gated_group(const GatedGroupParams& p, int dqk, int dv, hipStream_t stream);
+// dQ, dK [B, H_qk, L, D_qk]: the sums of the parts; head_elems = L * D_qk, elems = B * H_qk * L * D_qk
+hipError_t launch_gated_group_sum(const float* dq_parts, const float* dk_parts, float* dQ, float* dK, int parts, int64_t head_elems,
+                                  int64_t elems, hipStream_t stream);
+// dlog_decay[h, t] = sum_{i >= t} dB[h, i] (what launch_gated_backward_epilogue ends with)
+hipError_t launch_gated_suffix_sum(const float* dB, float* dlog_decay, int BH, int L, hipStream_t stream);
 bool gated_supported(int dqk, int dv);
 // dt: log2 of the per-head decay, read only where p.log_decay is null
 hipError_t launch_gated_recurrent(const GatedParams& p, const DecayTable& dt, int dqk, int dv, hipStream_t stream);

@@ -94,6 +94,160 @@ __device__ __forceinline__ float lds_read4(uint32_t addr) {
 // Workgroup barrier: this wavefront's LDS reads and writes are done (its copies in flight are not waited for).
 __device__ __forceinline__ void chunk_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// ---- fragments: the lane's part of their LDS addresses ----
+// Transposed fragment: 32 columns (block k) of a tile of CPR chunks per row, rows 4 half + li / 4 (+ 8 for j = 1) of a 16-token
+// step (lane = column, registers = rows in accumulator order); `piece`: which four columns of every 16.
+template <int CPR>
+__device__ __forceinline__ uint32_t tr_lane(int lane, int k, int j, int piece) {
+  const int r = 4 * (lane >> 5) + ((lane & 15) >> 2) + 8 * j;
+  return (uint32_t)((piece & 1) * 8 + r * (CPR * 16) + (((4 * k + 2 * ((lane >> 4) & 1) + (piece >> 1)) ^ bswz<CPR>(r)) << 4));
+}
+// pieces 1 and 2 of every 16 columns exchanged: the order that makes a lane's eight packed state registers consecutive rows d
+__device__ __forceinline__ int swapped_piece(int lane) { return 2 * (lane & 1) + ((lane >> 1) & 1); }
+// row fragment of Q or K for d-step t (d = 16 t + 8 half + {0..7}), row lane % 32 of a 32-row block
+template <class C>
+__device__ __forceinline__ uint32_t row_lane(int lane, int t) {
+  return (uint32_t)((lane & 31) * C::RBQ + (((2 * t + (lane >> 5)) ^ bswz<C::CPRQ>(lane & 31)) << 4));
+}
+
+// ---- a state wavefront's share of a chunk ----
+// O^T = H^T Q^T for both blocks of 32 queries (H rounded to bf16); in the same pass over the accumulators H takes the chunk's
+// whole decay.  q: the lane's fragment addresses rq plus the queries' tile.
+template <class C>
+__device__ __forceinline__ void read_out(f32x16 (&H)[C::DBQ], float dec, const uint32_t (&rq)[C::T], uint32_t q, f32x16& o0, f32x16& o1) {
+  o0 = zero16();
+  o1 = zero16();
+#pragma unroll
+  for (int db = 0; db < C::DBQ; ++db) {
+    bf16x8 hp[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float x = H[db][r];
+      hp[r / 8][r % 8] = (__bf16)x;
+      H[db][r] = x * dec;
+    }
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt) {
+      const uint32_t a = q + rq[2 * db + tt];
+      o0 = mfma(hp[tt], read_k_frag(a), o0);
+      o1 = mfma(hp[tt], read_k_frag(a + 32 * C::RBQ), o1);
+    }
+  }
+}
+// O^T += V^T P^T; weights at pb: block 0: queries 0-31 x keys 0-31, 1: 32-63 x 32-63, 2: queries 32-63 x keys 0-31
+__device__ __forceinline__ void add_pairs(const bf16x8 (&vf)[4], uint32_t pb, f32x16& o0, f32x16& o1) {
+  o0 = mfma(vf[0], read_k_frag(pb), o0);
+  o0 = mfma(vf[1], read_k_frag(pb + 1024), o0);
+  o1 = mfma(vf[0], read_k_frag(pb + 4096), o1);
+  o1 = mfma(vf[1], read_k_frag(pb + 5120), o1);
+  o1 = mfma(vf[2], read_k_frag(pb + 2048), o1);
+  o1 = mfma(vf[3], read_k_frag(pb + 3072), o1);
+}
+// H += K^T (w . V): the chunk's V fragments times the tokens' weights at w (element e of fragment s: token
+// 16 s + 8 (e / 4) + 4 half + e % 4); k: the K tile
+template <class C>
+__device__ __forceinline__ void update_state(f32x16 (&H)[C::DBQ], const bf16x8 (&vf)[4], uint32_t w, uint32_t k, const uint32_t (&kt)[C::DBQ][2]) {
+  f32x4 wv[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) wv[s] = lds_read16(w + 32 * s);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    bf16x8 vw;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      vw[e] = (__bf16)((float)vf[s][e] * wv[2 * s][e]);
+      vw[4 + e] = (__bf16)((float)vf[s][4 + e] * wv[2 * s + 1][e]);
+    }
+#pragma unroll
+    for (int db = 0; db < C::DBQ; ++db)
+      H[db] = mfma(read_tr_frag(k + kt[db][0] + 16 * s * C::RBQ, k + kt[db][1] + 16 * s * C::RBQ), vw, H[db]);
+  }
+}
+// One block of 32 queries x 32 columns, turned around in the wavefront's 4 KB of LDS (16-byte chunk k of row r at k ^ (r % 8)):
+// afterwards v[k] holds columns 4 (lane % 8) .. + 3 of row 8 k + lane / 8.
+__device__ __forceinline__ void turn_around(uint32_t out, int lane, const f32x16& o, f32x4 (&v)[4]) {
+  const int ln = lane & 31, half = lane >> 5, row = lane >> 3;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+    lds_write16(out + ln * 128 + (((2 * a + half) ^ (ln & 7)) << 4), (f32x4){o[4 * a], o[4 * a + 1], o[4 * a + 2], o[4 * a + 3]});
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = lds_read16(out + (8 * k + row) * 128 + (((lane & 7) ^ row) << 4));
+}
+
+// ---- the helpers' shares ----
+// The gates' values of a chunk (lane = token): a: log-decay, k: key gate (both 0 past the end), s: the factor on the output row.
+// Returns the sum of the chunk's log-decays.
+template <class C, bool STATE_ONLY>
+__device__ __forceinline__ float put_factors(uint32_t gate, int lane, int odd, float a, float k, float s) {
+  // b: inclusive prefix sum over the 64 tokens (data-parallel-primitive steps: within rows of 16 lanes by shifts of
+  // 1, 2, 4, 8, then the row totals onward)
+  float bcum = a;
+  bcum += dpp_f<0x111, 0xf, 0xf>(bcum);
+  bcum += dpp_f<0x112, 0xf, 0xf>(bcum);
+  bcum += dpp_f<0x114, 0xf, 0xe>(bcum);
+  bcum += dpp_f<0x118, 0xf, 0xc>(bcum);
+  bcum += dpp_f<0x142, 0xa, 0xf>(bcum);
+  bcum += dpp_f<0x143, 0xc, 0xf>(bcum);
+  const float b_last = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, bcum), 63));
+  lds_store4(gate + (C::kW + odd * 64 + lane) * 4, k * __expf(b_last - bcum));
+  lds_store4(gate + (C::kDec + odd) * 4, __expf(b_last));
+  if constexpr (!STATE_ONLY) {
+    // Weights inside the chunk, factorised per group of four tokens: with ref_j the sum in front of token j's group
+    // (ref_j >= b_i for every i in or behind the group),  e^{b_i - b_j} g_j = e^{b_i - ref_j} * u_j,
+    // u_j = g_j e^{ref_j - b_j}: one exponential per token here and four per lane and block of weights instead of
+    // one per weight.  ref_j - b_j is at most four log-decays: with the bound of 20 above u_j stays finite.
+    const float ref = dpp_f<0x00, 0xf, 0xf>(bcum - a);  // the sum in front of lane (lane & ~3): quad broadcast of the exclusive sum
+    lds_store4(gate + (C::kB + lane) * 4, bcum);
+    lds_store4(gate + (C::kU + lane) * 4, k * __expf(ref - bcum));
+    lds_store4(gate + (C::kS + lane) * 4, s);
+    lds_store4(gate + (C::kRef + (lane >> 2)) * 4, ref);
+  }
+  return b_last;
+}
+// scores of a 32 x 32 block: K rows at kt, Q rows at qt
+template <class C>
+__device__ __forceinline__ f32x16 block_scores(const uint32_t (&rq)[C::T], uint32_t kt, uint32_t qt) {
+  f32x16 s = zero16();
+#pragma unroll
+  for (int t = 0; t < C::T; ++t) s = mfma(read_k_frag(kt + rq[t]), read_k_frag(qt + rq[t]), s);
+  return s;
+}
+// weights of the block: s_i e^{b_i - b_j} g_j (q_i . k_j) for key j <= query i (positions inside the chunk), else 0; inside a
+// diagonal block keys behind the lane's query (last_key) get weight 0
+template <class C>
+__device__ __forceinline__ void block_weights(const f32x16& sc, uint32_t gate, int lane, int kb, int qb, int last_key, uint32_t dst) {
+  const int ln = lane & 31, half = lane >> 5;
+  const float bi = lds_read4(gate + (C::kB + 32 * qb + ln) * 4), si = lds_read4(gate + (C::kS + 32 * qb + ln) * 4);
+  float ref[4];
+  f32x4 uj[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    ref[a] = lds_read4(gate + (C::kRef + 8 * kb + 2 * a + half) * 4);
+    uj[a] = lds_read16(gate + (C::kU + 32 * kb + 8 * a + 4 * half) * 4);
+  }
+  u32x4 pk[2];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    // (groups past the lane's query have bi > ref: whatever the factor becomes there, the mask below discards it)
+    const float qfac = si * __expf(bi - ref[a]);
+    float x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[e] = sc[4 * a + e] * (qfac * uj[a][e]);
+      if (8 * a + 4 * half + e > last_key) x[e] = 0.f;
+    }
+    bf16x2 lo, hi;
+    lo[0] = (__bf16)x[0];
+    lo[1] = (__bf16)x[1];
+    hi[0] = (__bf16)x[2];
+    hi[1] = (__bf16)x[3];
+    pk[a / 2][2 * (a % 2)] = __builtin_bit_cast(uint32_t, lo);
+    pk[a / 2][2 * (a % 2) + 1] = __builtin_bit_cast(uint32_t, hi);
+  }
+  lds_write16(dst + lane * 16, __builtin_bit_cast(f32x4, pk[0]));
+  lds_write16(dst + lane * 16 + 1024, __builtin_bit_cast(f32x4, pk[1]));
+}
+
 // The copies of one helper: the tile of a chunk (64 rows of 16 CPR bytes) of each of TILES tensors.  A copy instruction moves
 // 1 KB; per instruction of a tile the lane's byte offset inside a chunk is fixed (row r of the tile, 16-byte chunk with the
 // tile's swizzle) and the chunk's first row moves the wave-uniform base pointer.  The last chunk, if short, takes the rows past
@@ -120,11 +274,12 @@ struct TileCopy {
     if (rev) row = rows - 1 - row;
     return (uint32_t)(row * (CPR * 16) + ((pc ^ bswz<CPR>(r)) << 4));
   }
-  __device__ __forceinline__ void issue(int c, uint32_t stage) const {
+  // (shift: elements from `base` to the tensor meant)
+  __device__ __forceinline__ void issue(int c, uint32_t stage, int64_t shift = 0) const {
     const int t0 = c * CH, rows = min(L - t0, CH);
     const int64_t r0 = rev ? max(L - CH - t0, 0) : t0;  // the chunk's row with the lowest address
     static_for<0, TILES>([&](auto tc) {
-      const __bf16* src = base + decltype(tc)::value * tile_step + r0 * (CPR * 8);
+      const __bf16* src = base + shift + decltype(tc)::value * tile_step + r0 * (CPR * 8);
       const uint32_t dst = stage + lds_off + decltype(tc)::value * (CPR * 1024);
       if (rows == CH) {
         static_for<0, CPR>([&](auto nb) { dma16_at<decltype(nb)::value * 1024>(src, off[decltype(nb)::value], dst); });
@@ -158,17 +313,6 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
   auto stage_of = [&](int c) { return lds0 + (uint32_t)(c % Y::STAGES) * Y::STAGE_BYTES; };
   auto gates_of = [&](int hh) { return lds0 + Y::kGates + hh * C::GATE_BYTES; };
 
-  // transposed fragment: 32 columns of a tile, rows trow and trow + 8 of a 16-token step (lane = column, registers =
-  // rows in accumulator order); `piece` of four columns of every 16
-  const int li = lane & 15, blk = (lane >> 4) & 1, trow = 4 * half + (li >> 2);
-  auto tr_lane = [&](auto cprc, int k, int j, int piece) {
-    constexpr int CPR = decltype(cprc)::value, RB = CPR * 16;
-    const int r = trow + 8 * j;
-    return (uint32_t)((piece & 1) * 8 + r * RB + (((4 * k + 2 * blk + (piece >> 1)) ^ bswz<CPR>(r)) << 4));
-  };
-  // row fragment of Q or K for d-step t (d = 16 t + 8 half + {0..7}), row ln of a 32-row block
-  auto row_lane = [&](int t) { return (uint32_t)(ln * C::RBQ + (((2 * t + half) ^ bswz<C::CPRQ>(ln)) << 4)); };
-
   if (wave < C::SW) {
     // ================= state wavefront: 32 value columns of one head =================
     const int hw = wave / C::NB, vblk = wave % C::NB, bh = bh0 + hw;
@@ -189,34 +333,15 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
     }
     uint32_t rq0[C::T], kt0[C::DBQ][2], vt0[2];
 #pragma unroll
-    for (int t = 0; t < C::T; ++t) rq0[t] = row_lane(t);
+    for (int t = 0; t < C::T; ++t) rq0[t] = row_lane<C>(lane, t);
 #pragma unroll
     for (int k = 0; k < C::DBQ; ++k)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        kt0[k][j] = Y::kK + tr_lane(std::integral_constant<int, C::CPRQ>{}, k, j, 2 * (li & 1) + ((li >> 1) & 1));
+      for (int j = 0; j < 2; ++j) kt0[k][j] = tr_lane<C::CPRQ>(lane, k, j, swapped_piece(lane));
 #pragma unroll
-    for (int j = 0; j < 2; ++j) vt0[j] = Y::kV + hw * C::V_BYTES + tr_lane(std::integral_constant<int, C::CPRV>{}, vblk, j, li & 3);
-
-    // The chunk's V fragments times the tokens' weights (element e of fragment s: token 16 s + 8 (e / 4) + 4 half + e % 4),
-    // then H += K^T (w . V)
+    for (int j = 0; j < 2; ++j) vt0[j] = Y::kV + hw * C::V_BYTES + tr_lane<C::CPRV>(lane, vblk, j, lane & 3);
     auto update = [&](int c, const bf16x8 (&vf)[4]) {
-      const uint32_t sb = stage_of(c), w = gate + (C::kW + (c & 1) * 64 + 4 * half) * 4;
-      f32x4 wv[8];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) wv[s] = lds_read16(w + 32 * s);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        bf16x8 vw;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          vw[e] = (__bf16)((float)vf[s][e] * wv[2 * s][e]);
-          vw[4 + e] = (__bf16)((float)vf[s][4 + e] * wv[2 * s + 1][e]);
-        }
-#pragma unroll
-        for (int db = 0; db < C::DBQ; ++db)
-          H[db] = mfma(read_tr_frag(sb + kt0[db][0] + 16 * s * C::RBQ, sb + kt0[db][1] + 16 * s * C::RBQ), vw, H[db]);
-      }
+      update_state<C>(H, vf, gate + (C::kW + (c & 1) * 64 + 4 * half) * 4, stage_of(c) + Y::kK, kt0);
     };
     auto v_frags = [&](int c, bf16x8 (&vf)[4]) {
       const uint32_t sb = stage_of(c);
@@ -240,8 +365,6 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
     } else {
       chunk_barrier();
       chunk_barrier();
-      // where this wavefront turns an output block of 32 queries x 32 columns around: 16-byte chunk k of row r at k ^ (r % 8)
-      const uint32_t wr0 = ln * 128, rd_row = lane >> 3, rd_pc = lane & 7;
       const int64_t o_head = (int64_t)bh * Lt + row_lo;
       for (int c = 0; c < n_chunks; ++c) {
         const uint32_t sb = stage_of(c);
@@ -250,57 +373,29 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
         const float dec = lds_read4(gate + (C::kDec + (c & 1)) * 4);
         const float f0 = lds_read4(gate + (C::kS + ln) * 4) * __expf(lds_read4(gate + (C::kB + ln) * 4));
         const float f1 = lds_read4(gate + (C::kS + 32 + ln) * 4) * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
-        f32x16 o0 = zero16(), o1 = zero16();
-#pragma unroll
-        for (int db = 0; db < C::DBQ; ++db) {
-          // the state rounded to bf16; in the same pass over the accumulators it takes the chunk's whole decay
-          bf16x8 hp[2];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float x = H[db][r];
-            hp[r / 8][r % 8] = (__bf16)x;
-            H[db][r] = x * dec;
-          }
-#pragma unroll
-          for (int tt = 0; tt < 2; ++tt) {
-            const uint32_t a = sb + rq0[2 * db + tt];
-            o0 = mfma(hp[tt], read_k_frag(a), o0);
-            o1 = mfma(hp[tt], read_k_frag(a + 32 * C::RBQ), o1);
-          }
-        }
+        f32x16 o0, o1;
+        read_out<C>(H, dec, rq0, sb, o0, o1);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           o0[r] *= f0;
           o1[r] *= f1;
         }
         chunk_barrier();
-        // ---- the chunk's own tokens: O^T += V^T P^T; block 0: queries 0-31 x keys 0-31, 1: 32-63 x 32-63, 2: 32-63 x 0-31 ----
+        // ---- the chunk's own tokens ----
         bf16x8 vf[4];
         v_frags(c, vf);
-        {
-          const uint32_t pb = lds0 + Y::kP + hw * C::P_BYTES + lane * 16;
-          o0 = mfma(vf[0], read_k_frag(pb), o0);
-          o0 = mfma(vf[1], read_k_frag(pb + 1024), o0);
-          o1 = mfma(vf[0], read_k_frag(pb + 4096), o1);
-          o1 = mfma(vf[1], read_k_frag(pb + 5120), o1);
-          o1 = mfma(vf[2], read_k_frag(pb + 2048), o1);
-          o1 = mfma(vf[3], read_k_frag(pb + 3072), o1);
-        }
+        add_pairs(vf, lds0 + Y::kP + hw * C::P_BYTES + lane * 16, o0, o1);
         // ---- store ----
         const uint32_t out = Y::kOutInQ ? sb + wave * 4096 : lds0 + Y::kOut + wave * 4096;
         auto store_block = [&](auto ibc, const f32x16& o) {
           constexpr int IB = decltype(ibc)::value;
-#pragma unroll
-          for (int a = 0; a < 4; ++a)
-            lds_write16(out + wr0 + (((2 * a + half) ^ (ln & 7)) << 4), (f32x4){o[4 * a], o[4 * a + 1], o[4 * a + 2], o[4 * a + 3]});
           f32x4 v[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) v[k] = lds_read16(out + (8 * k + rd_row) * 128 + ((rd_pc ^ rd_row) << 4));
+          turn_around(out, lane, o, v);
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const int i = t0 + 32 * IB + 8 * k + (int)rd_row;
+            const int i = t0 + 32 * IB + 8 * k + (lane >> 3);
             if (i < L) {
-              const int64_t e0 = (o_head + (rev ? L - 1 - i : i)) * C::DV + 32 * vblk + 4 * rd_pc;
+              const int64_t e0 = (o_head + (rev ? L - 1 - i : i)) * C::DV + 32 * vblk + 4 * (lane & 7);
               if (p.out_bf16) {
                 bf16x4 hv;
 #pragma unroll
@@ -360,30 +455,7 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
           k = 1.f;
         }
         if (t >= L) a = k = 0.f;
-        // b: inclusive prefix sum over the 64 tokens (data-parallel-primitive steps: within rows of 16 lanes by shifts of
-        // 1, 2, 4, 8, then the row totals onward)
-        float bcum = a;
-        bcum += dpp_f<0x111, 0xf, 0xf>(bcum);
-        bcum += dpp_f<0x112, 0xf, 0xf>(bcum);
-        bcum += dpp_f<0x114, 0xf, 0xe>(bcum);
-        bcum += dpp_f<0x118, 0xf, 0xc>(bcum);
-        bcum += dpp_f<0x142, 0xa, 0xf>(bcum);
-        bcum += dpp_f<0x143, 0xc, 0xf>(bcum);
-        const float b_last = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, bcum), 63));
-        seg_b[hh] += b_last;
-        lds_store4(gate + (C::kW + (c & 1) * 64 + lane) * 4, k * __expf(b_last - bcum));
-        lds_store4(gate + (C::kDec + (c & 1)) * 4, __expf(b_last));
-        if constexpr (!STATE_ONLY) {
-          // Weights inside the chunk, factorised per group of four tokens: with ref_j the sum in front of token j's group
-          // (ref_j >= b_i for every i in or behind the group),  e^{b_i - b_j} g_j = e^{b_i - ref_j} * u_j,
-          // u_j = g_j e^{ref_j - b_j}: one exponential per token here and four per lane and block of weights instead of
-          // one per weight.  ref_j - b_j is at most four log-decays: with the bound of 20 above u_j stays finite.
-          const float ref = dpp_f<0x00, 0xf, 0xf>(bcum - a);  // the sum in front of lane (lane & ~3): quad broadcast of the exclusive sum
-          lds_store4(gate + (C::kB + lane) * 4, bcum);
-          lds_store4(gate + (C::kU + lane) * 4, k * __expf(ref - bcum));
-          lds_store4(gate + (C::kS + lane) * 4, s);
-          lds_store4(gate + (C::kRef + (lane >> 2)) * 4, ref);
-        }
+        seg_b[hh] += put_factors<C, STATE_ONLY>(gate, lane, c & 1, a, k, s);
       }
     };
 #pragma unroll
@@ -414,50 +486,11 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
   const int last_key = role == 2 ? C::CH : ln;  // inside a diagonal block keys behind the lane's query get weight 0
   uint32_t rq0[C::T];
 #pragma unroll
-  for (int t = 0; t < C::T; ++t) rq0[t] = row_lane(t);
-  auto scores = [&](int c) {
-    const uint32_t kt = stage_of(c) + Y::kK + 32 * kb * C::RBQ, qt = stage_of(c) + 32 * qb * C::RBQ;
-    f32x16 s = zero16();
-#pragma unroll
-    for (int t = 0; t < C::T; ++t) s = mfma(read_k_frag(kt + rq0[t]), read_k_frag(qt + rq0[t]), s);
-    return s;
-  };
-  // weights of the block: s_i e^{b_i - b_j} g_j (q_i . k_j) for key j <= query i (positions inside the chunk), else 0
+  for (int t = 0; t < C::T; ++t) rq0[t] = row_lane<C>(lane, t);
+  auto scores = [&](int c) { return block_scores<C>(rq0, stage_of(c) + Y::kK + 32 * kb * C::RBQ, stage_of(c) + 32 * qb * C::RBQ); };
   auto weigh = [&](const f32x16& sc) {
 #pragma unroll
-    for (int hh = 0; hh < C::HPW; ++hh) {
-      const uint32_t gate = gates_of(hh);
-      const float bi = lds_read4(gate + (C::kB + 32 * qb + ln) * 4), si = lds_read4(gate + (C::kS + 32 * qb + ln) * 4);
-      float ref[4];
-      f32x4 uj[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        ref[a] = lds_read4(gate + (C::kRef + 8 * kb + 2 * a + half) * 4);
-        uj[a] = lds_read16(gate + (C::kU + 32 * kb + 8 * a + 4 * half) * 4);
-      }
-      u32x4 pk[2];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        // (groups past the lane's query have bi > ref: whatever the factor becomes there, the mask below discards it)
-        const float qfac = si * __expf(bi - ref[a]);
-        float x[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[e] = sc[4 * a + e] * (qfac * uj[a][e]);
-          if (8 * a + 4 * half + e > last_key) x[e] = 0.f;
-        }
-        bf16x2 lo, hi;
-        lo[0] = (__bf16)x[0];
-        lo[1] = (__bf16)x[1];
-        hi[0] = (__bf16)x[2];
-        hi[1] = (__bf16)x[3];
-        pk[a / 2][2 * (a % 2)] = __builtin_bit_cast(uint32_t, lo);
-        pk[a / 2][2 * (a % 2) + 1] = __builtin_bit_cast(uint32_t, hi);
-      }
-      const uint32_t pb = lds0 + Y::kP + hh * C::P_BYTES + role * 2048 + lane * 16;
-      lds_write16(pb, __builtin_bit_cast(f32x4, pk[0]));
-      lds_write16(pb + 1024, __builtin_bit_cast(f32x4, pk[1]));
-    }
+    for (int hh = 0; hh < C::HPW; ++hh) block_weights<C>(sc, gates_of(hh), lane, kb, qb, last_key, lds0 + Y::kP + hh * C::P_BYTES + role * 2048);
   };
   auto help = [&](const auto& cp) {
     constexpr int N = std::decay_t<decltype(cp)>::N;
@@ -509,6 +542,292 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
   } else {
     for (int c = 0; c <= n_chunks; ++c) chunk_barrier();
   }
+}
+
+// ---- backward pass where value heads share a q/k head: the gradients of q and k, summed over heads ----
+// The walk of gated_recurrent_kernel for several value heads of one q/k head in one workgroup, which takes them in turn, chunk
+// by chunk: a unit of work is a (chunk, head).  Queries and keys of the walk (dO and V) are each head's own and arrive per unit,
+// the values (K, or Q in the walk that goes backwards) and the rows of the dot products (Q, or K) once per
+// chunk.  The outputs are summed over the heads in registers, and each head's row products
+// (q . dq, k . dk / g) are formed on the way.  Stored per head, as gated_bwd_rows_kernel takes them, the two walks wrote and that
+// kernel read 2 x 251 MB at 8 x 80 heads x 768 tokens: 379 us for the whole backward pass, 257 this way (three heads each).
+// DQK_, DV_: head dims of the walk, i.e. of dO and V, and of Q and K.
+template <int DQK_, int DV_>
+struct GroupCfg : GCfg<DQK_, DV_> {
+  using G = GCfg<DQK_, DV_>;
+  static constexpr int HEADS = kGatedGroupHeads;  // at most, per workgroup: 32 registers of state each at head dim 64
+  static constexpr int kG = G::GATE_BYTES / 4, GATES = G::GATE_BYTES + 256;  // (behind the gates' values: the factor of the head's rows in the sum)
+  static constexpr int UNIT_BYTES = 2 * G::Q_BYTES, SHARED_BYTES = 2 * G::V_BYTES;
+  static constexpr int kShared = 3 * UNIT_BYTES, kP = kShared + 2 * SHARED_BYTES, kGates = kP + G::P_BYTES;
+  static constexpr int kDots = kGates + GATES, kOut = kDots + G::NB * 256, LDS_BYTES = kOut + G::NB * 4096;
+  static_assert(LDS_BYTES <= 160 * 1024, "tiles do not fit LDS");
+};
+
+template <class C>
+__global__ __launch_bounds__(C::THREADS, 2) void gated_group_kernel(const GatedGroupParams p) {
+  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ln = lane & 31, half = lane >> 5;
+  const int part = blockIdx.x % p.parts, bhq = blockIdx.x / p.parts, group = p.H / p.H_qk;
+  const int nh = min(p.heads, group - part * p.heads);                          // heads of this workgroup
+  const int64_t bh0 = (int64_t)bhq * group + part * p.heads;                    // the first of them, batch included
+  const bool rev = p.reverse != 0;
+  const int L = p.L, n_chunks = (L + C::CH - 1) / C::CH, units = n_chunks * nh;
+  const uint32_t gate = lds0 + C::kGates;
+  auto unit_stage = [&](int st) { return lds0 + (uint32_t)st * C::UNIT_BYTES; };
+  auto shared_stage = [&](int c) { return lds0 + C::kShared + (uint32_t)(c & 1) * C::SHARED_BYTES; };
+  auto next = [](int st) { return st == 2 ? 0 : st + 1; };
+
+  if (wave < C::NB) {
+    // ================= state wavefront: 32 columns of every head =================
+    f32x16 H[C::HEADS][C::DBQ];
+#pragma unroll
+    for (int n = 0; n < C::HEADS; ++n)
+#pragma unroll
+      for (int db = 0; db < C::DBQ; ++db) H[n][db] = zero16();
+    uint32_t rq0[C::T], kt0[C::DBQ][2], vt0[2], rr0[4];
+#pragma unroll
+    for (int t = 0; t < C::T; ++t) rq0[t] = row_lane<C>(lane, t);
+#pragma unroll
+    for (int k = 0; k < C::DBQ; ++k)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) kt0[k][j] = C::Q_BYTES + tr_lane<C::CPRQ>(lane, k, j, swapped_piece(lane));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) vt0[j] = tr_lane<C::CPRV>(lane, wave, j, lane & 3);
+    // the rows of the dot products as the outputs lie in registers: row ln, columns 32 wave + 8 a + 4 half + {0..3}
+#pragma unroll
+    for (int a = 0; a < 4; ++a) rr0[a] = C::V_BYTES + ln * C::RBV + (((4 * wave + a) ^ bswz<C::CPRV>(ln)) << 4) + 8 * half;
+    const uint32_t out = lds0 + C::kOut + wave * 4096, dots = lds0 + C::kDots + wave * 256;
+    chunk_barrier();
+    chunk_barrier();
+    int st = 0, odd = 0;  // unit modulo 3 and 2
+    for (int c = 0; c < n_chunks; ++c) {
+      const uint32_t sh = shared_stage(c);
+      const int t0 = c * C::CH;
+      f32x16 sum0 = zero16(), sum1 = zero16();
+      static_for<0, C::HEADS>([&](auto nc) {
+        constexpr int n = decltype(nc)::value;
+        if (n < nh) {
+          const uint32_t sb = unit_stage(st);
+          const float dec = lds_read4(gate + (C::kDec + odd) * 4);
+          const float f0 = lds_read4(gate + (C::kS + ln) * 4) * __expf(lds_read4(gate + (C::kB + ln) * 4));
+          const float f1 = lds_read4(gate + (C::kS + 32 + ln) * 4) * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
+          const float g0 = lds_read4(gate + (C::kG + ln) * 4), g1 = lds_read4(gate + (C::kG + 32 + ln) * 4);
+          f32x16 o0, o1;
+          read_out<C>(H[n], dec, rq0, sb, o0, o1);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            o0[r] *= f0;
+            o1[r] *= f1;
+          }
+          chunk_barrier();
+          // (read anew for every head, and the fences keep the sums in front of the update: registers)
+          bf16x8 vf[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) vf[s] = read_tr_frag(sh + vt0[0] + 16 * s * C::RBV, sh + vt0[1] + 16 * s * C::RBV);
+          bf16x4 rows[2][4];
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+              rows[q][a] = *reinterpret_cast<__attribute__((address_space(3))) const bf16x4*>((lds_char*)(uintptr_t)(sh + rr0[a] + 32 * q * C::RBV));
+          add_pairs(vf, lds0 + C::kP + lane * 16, o0, o1);
+          sched_fence();
+          float d0 = 0.f, d1 = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            d0 = __builtin_fmaf(o0[r], (float)rows[0][r / 4][r % 4], d0);
+            d1 = __builtin_fmaf(o1[r], (float)rows[1][r / 4][r % 4], d1);
+            sum0[r] = __builtin_fmaf(g0, o0[r], sum0[r]);
+            sum1[r] = __builtin_fmaf(g1, o1[r], sum1[r]);
+          }
+          d0 = sum_halves(d0);
+          d1 = sum_halves(d1);
+          lds_store4(dots + lane * 4, half ? d1 : d0);  // of token `lane` of the chunk
+          sched_fence();
+          if (n == nh - 1) {
+            int lane_now = lane;  // (hidden from the optimiser: the addresses below are formed here, not kept through the loop)
+            pin(lane_now);
+            auto store_block = [&](auto qc, const f32x16& o) {
+              f32x4 v[4];
+              turn_around(out, lane_now, o, v);
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                const int i = t0 + 32 * decltype(qc)::value + 8 * k + (lane_now >> 3);
+                if (i < L)
+                  *reinterpret_cast<f32x4*>(p.out + (((int64_t)bhq * p.parts + part) * L + (rev ? L - 1 - i : i)) * C::DV + 32 * wave + 4 * (lane_now & 7)) = v[k];
+              }
+            };
+            store_block(std::integral_constant<int, 0>{}, sum0);
+            store_block(std::integral_constant<int, 1>{}, sum1);
+          }
+          sched_fence();
+          update_state<C>(H[n], vf, gate + (C::kW + odd * 64 + 4 * half) * 4, sb, kt0);
+          chunk_barrier();
+          st = next(st);
+          odd ^= 1;
+        }
+      });
+    }
+    return;
+  }
+
+  const int role = wave - C::NB;
+  if (role == 3) {
+    // ================= the gates: lane = token of the chunk; and the heads' row products =================
+    float la = 0.f, g = 1.f, old = 0.f;      // of the unit to prepare next
+    float g_put = 1.f, old_put = 0.f, g_done = 1.f, old_done = 0.f;  // of the unit prepared last, of the one whose products are due
+    auto token = [&](int c) {
+      const int i = min(c * C::CH + lane, L - 1);
+      return rev ? L - 1 - i : i;
+    };
+    auto load = [&](int c, int n) {
+      const int64_t row = (bh0 + n) * L;
+      const int t = token(c);
+      // (walking backwards: the decay of the token one later in the sequence; the walk's first token has none)
+      la = p.log_decay[row + (rev ? min(t + 1, L - 1) : t)];
+      g = p.key_gate ? p.key_gate[row + t] : 1.f;
+      if (rev) old = p.dB[row + t];
+    };
+    auto put = [&](int c, int odd) {
+      const int t = c * C::CH + lane;
+      float a = rev && t == 0 ? 0.f : fmaxf(la, -20.f), k = rev ? 1.f : g;
+      if (t >= L) a = k = 0.f;
+      put_factors<C, false>(gate, lane, odd, a, k, p.scale);
+      lds_store4(gate + (C::kG + lane) * 4, rev ? g : 1.f);
+    };
+    auto finish = [&](int c, int n) {
+      float d = 0.f;
+#pragma unroll
+      for (int w = 0; w < C::NB; ++w) d += lds_read4(lds0 + C::kDots + w * 256 + lane * 4);
+      if (c * C::CH + lane < L) {
+        const int64_t e = (bh0 + n) * L + token(c);
+        if (rev) {
+          if (p.dkey_gate) p.dkey_gate[e] = d;
+          d = old_done - g_done * d;
+        }
+        p.dB[e] = d;
+      }
+    };
+    int c = 0, n = 0, cl = 0, nl = 0, cd = 0, nd = 0;  // the unit under way, the next to load, the next to finish
+    auto step = [&](int& cc, int& nn) {
+      if (++nn == nh) {
+        nn = 0;
+        ++cc;
+      }
+    };
+    load(0, 0);
+    step(cl, nl);
+    chunk_barrier();
+    put(0, 0);
+    g_put = g;
+    old_put = old;
+    if (units > 1) load(cl, nl);
+    chunk_barrier();
+    for (int u = 0; u < units; ++u) {
+      if (u > 0) {
+        finish(cd, nd);
+        step(cd, nd);
+      }
+      chunk_barrier();
+      g_done = g_put;
+      old_done = old_put;
+      step(c, n);
+      if (u + 1 < units) {
+        put(c, (u + 1) & 1);
+        g_put = g;
+        old_put = old;
+        step(cl, nl);
+        if (u + 2 < units) load(cl, nl);
+      }
+      chunk_barrier();
+    }
+    finish(cd, nd);
+    return;
+  }
+
+  // ================= copies (helper 0: queries, 1: keys of a unit, 2: values and rows of a chunk) and weights =================
+  const int kb = role == 1 ? 1 : 0, qb = role == 0 ? 0 : 1;
+  const int last_key = role == 2 ? C::CH : ln;
+  uint32_t rq0[C::T];
+#pragma unroll
+  for (int t = 0; t < C::T; ++t) rq0[t] = row_lane<C>(lane, t);
+  auto scores = [&](int st) { return block_scores<C>(rq0, unit_stage(st) + C::Q_BYTES + 32 * kb * C::RBQ, unit_stage(st) + 32 * qb * C::RBQ); };
+  auto help = [&](auto&& start, auto&& copy, auto&& landed) {
+    start();
+    chunk_barrier();
+    int st = 0;
+    f32x16 s = scores(0);
+    chunk_barrier();
+    for (int u = 0; u < units; ++u) {
+      copy(u);
+      block_weights<C>(s, gate, lane, kb, qb, last_key, lds0 + C::kP + role * 2048);
+      landed(u);
+      chunk_barrier();
+      st = next(st);
+      if (u + 1 < units) s = scores(st);
+      chunk_barrier();
+    }
+  };
+  if (role == 2) {
+    const int64_t row = (int64_t)bhq * L * C::DV;
+    TileCopy<C::CPRV, 2> cp(p.V + row, (int64_t)((intptr_t)p.R - (intptr_t)p.V) / 2, 0, lane, L, rev);
+    int c = 0, n = 0;
+    help([&] { cp.issue(0, shared_stage(0)); },
+         [&](int) {
+           if (n == 0) {  // the chunk's tiles have landed (they are used behind the next barrier), the next chunk's follow
+             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+             if (c + 1 < n_chunks) cp.issue(c + 1, shared_stage(c + 1));
+           }
+           if (++n == nh) {
+             n = 0;
+             ++c;
+           }
+         },
+         [](int) {});
+  } else {
+    const int64_t head = (int64_t)L * C::DQK;
+    TileCopy<C::CPRQ, 1> cp((role == 1 ? p.K : p.Q) + bh0 * head, 0, role == 1 ? C::Q_BYTES : 0, lane, L, rev);
+    int c = 0, n = 0, st = 0;  // the unit to copy next
+    auto issue = [&] {
+      cp.issue(c, unit_stage(st), n * head);
+      st = next(st);
+      if (++n == nh) {
+        n = 0;
+        ++c;
+      }
+    };
+    auto wait = [&](bool one_behind) {
+      if (one_behind) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::CPRQ) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    help(
+        [&] {
+          issue();
+          if (units > 1) issue();
+          wait(units > 1);
+        },
+        [&](int u) {
+          if (u + 2 < units) issue();
+        },
+        [&](int u) {
+          if (u + 1 < units) wait(u + 2 < units);
+        });
+  }
+}
+
+// dQ and dK (blockIdx.y) of every q/k head: the sum of its parts, in their order
+__global__ __launch_bounds__(256) void gated_group_sum_kernel(const float* dq_parts, const float* dk_parts, float* dQ, float* dK, int parts,
+                                                              int64_t head_elems, int64_t elems) {
+  const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (e >= elems) return;
+  const int64_t head = e / head_elems, in = e % head_elems;
+  const float* src = (blockIdx.y ? dk_parts : dq_parts) + head * parts * head_elems + in;
+  f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int i = 0; i < parts; ++i) x += *reinterpret_cast<const f32x4*>(src + i * head_elems);
+  *reinterpret_cast<f32x4*>((blockIdx.y ? dK : dQ) + e) = x;
 }
 
 template <int DQK, int DV, int HPW = 1>
@@ -600,17 +919,17 @@ __global__ __launch_bounds__(256) void gated_bwd_rows_kernel(const GatedBwdEpilo
 
 // dlog_decay[t] = sum_{i >= t} dB[i]: one wavefront per (batch, head) walks from the end in blocks of 256 tokens,
 // four per lane; the running total is kept in double (the terms change sign and the sum is long).
-__global__ __launch_bounds__(64) void gated_bwd_suffix_sum_kernel(const GatedBwdEpilogueParams p) {
+__global__ __launch_bounds__(64) void gated_bwd_suffix_sum_kernel(const float* dB, float* dlog_decay, int L) {
   const int lane = threadIdx.x;
-  const float* src = p.dB + (int64_t)blockIdx.x * p.L;
-  float* dst = p.dlog_decay + (int64_t)blockIdx.x * p.L;
+  const float* src = dB + (int64_t)blockIdx.x * L;
+  float* dst = dlog_decay + (int64_t)blockIdx.x * L;
   double carry = 0.0;
-  const int nblk = (p.L + 255) / 256;
+  const int nblk = (L + 255) / 256;
   for (int blk = nblk - 1; blk >= 0; --blk) {
     const int t0 = blk * 256 + 4 * lane;
     float x[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = t0 + e < p.L ? src[t0 + e] : 0.f;
+    for (int e = 0; e < 4; ++e) x[e] = t0 + e < L ? src[t0 + e] : 0.f;
     // suffix sums inside the lane, then over the lanes behind this one
     x[2] += x[3];
     x[1] += x[2];
@@ -624,7 +943,7 @@ __global__ __launch_bounds__(64) void gated_bwd_suffix_sum_kernel(const GatedBwd
     const float behind = tot - x[0];  // the lanes strictly behind
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (t0 + e < p.L) dst[t0 + e] = (float)(carry + (double)(x[e] + behind));
+      if (t0 + e < L) dst[t0 + e] = (float)(carry + (double)(x[e] + behind));
     carry += (double)__shfl(tot, 0);
   }
 }
@@ -639,16 +958,40 @@ hipError_t launch_gated_combine_segments(float* buf, const float* seg_decay, con
   return hipGetLastError();
 }
 
+bool gated_group_supported(int dqk, int dv) { return (dqk == 64 || dqk == 128) && dv == 64; }
+
+hipError_t launch_gated_group(const GatedGroupParams& p, int dqk, int dv, hipStream_t s) {
+  if (!gated_group_supported(dqk, dv) || p.heads < 1 || p.heads > kGatedGroupHeads || p.H_qk < 1 || p.H % p.H_qk != 0 ||
+      (int64_t)p.parts * p.heads < p.H / p.H_qk || (int64_t)(p.parts - 1) * p.heads >= p.H / p.H_qk ||
+      (int64_t)p.B * p.H_qk * p.parts > 0x7fffffffLL)
+    return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(p.B * p.H_qk * p.parts));
+  if (dqk == 128) hipLaunchKernelGGL((gated_group_kernel<GroupCfg<64, 128>>), grid, dim3(GroupCfg<64, 128>::THREADS), 0, s, p);
+  else hipLaunchKernelGGL((gated_group_kernel<GroupCfg<64, 64>>), grid, dim3(GroupCfg<64, 64>::THREADS), 0, s, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_gated_group_sum(const float* dq_parts, const float* dk_parts, float* dQ, float* dK, int parts, int64_t head_elems,
+                                  int64_t elems, hipStream_t s) {
+  const int64_t grid = (elems / 4 + 255) / 256;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gated_group_sum_kernel, dim3((unsigned)grid, 2), dim3(256), 0, s, dq_parts, dk_parts, dQ, dK, parts, head_elems, elems);
+  return hipGetLastError();
+}
+
+hipError_t launch_gated_suffix_sum(const float* dB, float* dlog_decay, int BH, int L, hipStream_t s) {
+  hipLaunchKernelGGL(gated_bwd_suffix_sum_kernel, dim3((unsigned)BH), dim3(64), 0, s, dB, dlog_decay, L);
+  return hipGetLastError();
+}
+
 hipError_t launch_gated_backward_epilogue(const GatedBwdEpilogueParams& p, int dqk, hipStream_t s) {
   const int tpb = 4 * (64 / (dqk / 4));
   const int64_t grid = (int64_t)p.B * p.H_qk * (((int64_t)p.L + tpb - 1) / tpb);
   if (grid > 0x7fffffffLL || (dqk != 64 && dqk != 128)) return hipErrorInvalidValue;
   if (dqk == 64) hipLaunchKernelGGL(gated_bwd_rows_kernel<64>, dim3((unsigned)grid), dim3(256), 0, s, p);
   else hipLaunchKernelGGL(gated_bwd_rows_kernel<128>, dim3((unsigned)grid), dim3(256), 0, s, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(gated_bwd_suffix_sum_kernel, dim3((unsigned)(p.B * p.H)), dim3(64), 0, s, p);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_gated_suffix_sum(p.dB, p.dlog_decay, p.B * p.H, p.L, s);
 }
 
 bool gated_supported(int dqk, int dv) { return (dqk == 64 || dqk == 128) && (dv == 64 || dv == 128); }

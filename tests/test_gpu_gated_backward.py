@@ -154,6 +154,41 @@ def test_grouped_query_key_heads(A, dqk, dv):
     compare(got, ref, f"mamba2 groups {dqk}/{dv}", True, dots)
 
 
+@pytest.mark.parametrize("dqk", [64, 128])
+@pytest.mark.parametrize("H,H_qk,heads", [(256, 128, 2), (384, 128, 3), (320, 64, 3)])
+@pytest.mark.parametrize("kind,L", [("gated_retention", 64), ("mamba2", 130), ("mamba2", 193)])
+def test_several_heads_per_workgroup(A, dqk, H, H_qk, heads, kind, L):
+    # more value heads than compute units: a workgroup takes two or three heads of a group in turn (of five: three, then two)
+    Q, K, V, la, kg, dO = inputs(930 + L % 7, 2, H, H_qk, L, dqk, 64, kind)
+    h = A.ae_gated_create(B=2, H=H, H_qk=H_qk, L=L, D_qk=dqk, D_v=64, scale=0.1)
+    parts = -(-(H // H_qk) // heads)
+    assert A.ae_gated_backward_workspace_bytes(h) == (2 * H * L * 4 + 255) // 256 * 256 + 2 * 2 * H_qk * parts * L * dqk * 4
+    A.ae_gated_destroy(h)
+    dQ, dK, dV, dla, dkg = run(A, Q, K, V, la, kg, dO, 0.1)
+    # The same with every head given its own copy of its q/k head, which is the path of one head per workgroup (held to the oracle
+    # above): the same products from the same operands, so what is left is the order of sums in 32 bits -- 2^-23 of the sum of
+    # the absolute terms for every addition.
+    grp = H // H_qk
+    Qx, Kx = (t.repeat_interleave(grp, dim=1) for t in (Q, K))
+    eQ, eK, eV, ela, ekg = run(A, Qx, Kx, V, la, kg, dO, 0.1)
+    eps = 2.0 ** -23
+
+    def close(got, ref, bound, what):
+        ratio = np.abs(got - ref) / (bound + 1e-30)
+        print(f"{heads} heads per workgroup {kind} {dqk}/64 L={L} {what}: worst error / bound {ratio.max():.3f}", flush=True)
+        assert np.isfinite(got).all() and ratio.max() <= 1.0, (what, ratio.max())
+
+    for name, g, e in (("dQ", dQ, eQ), ("dK", dK, eK)):
+        e = e.reshape(2, H_qk, grp, L, dqk)
+        close(g, e.sum(axis=2), 2 * grp * eps * np.abs(e).sum(axis=2) + 1e-7, name)
+    assert np.array_equal(dV, eV)
+    q, k = Qx.double().numpy(), Kx.double().numpy()
+    rows_q, rows_k = np.abs(q * eQ).sum(axis=-1), np.abs(k * eK).sum(axis=-1)
+    if kg is not None:
+        close(dkg, ekg, 2 * dqk * eps * rows_k / kg.double().numpy() + 1e-7, "dkey_gate")
+    close(dla, ela, (2 * dqk * eps * (rows_q + rows_k) + 1e-7)[..., ::-1].cumsum(axis=-1)[..., ::-1] + 2 * eps * np.abs(ela), "dlog_decay")
+
+
 @pytest.mark.parametrize("dqk,dv,H,H_qk", [(128, 128, 2, 2), (64, 64, 3, 3), (128, 64, 4, 1)])
 @pytest.mark.parametrize("kind", ["gated_retention", "mamba2"])
 @pytest.mark.parametrize("L", [1061, 2560])
