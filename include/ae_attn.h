@@ -478,7 +478,7 @@ ae_status_t ae_gated_forward_segmented(const ae_gated_t *h, const void *Q, const
  *              Owned by the caller; calls sharing it must not overlap.
  * Tensors 16-byte aligned, gates and their gradients 4-byte; outputs must alias
  * neither inputs nor each other.  Uses B, H, H_qk, L, the head dims and scale of
- * the handle (out_dtype plays no part: gradients are fp32).  Five launches on
+ * the handle (out_dtype plays no part: gradients are fp32).  At most five launches on
  * `stream`, no allocation, no wait.  Errors as ae_gated_forward.                */
 ae_status_t ae_gated_backward_workspace_bytes(const ae_gated_t *h, size_t *bytes);
 ae_status_t ae_gated_backward(const ae_gated_t *h, const void *Q, const void *K, const void *V,

@@ -764,9 +764,9 @@ static void gated_segments(int64_t workgroups, int L, int* nseg, int* seg_len) {
   cut_segments(L >= from ? n : 1, L, nseg, seg_len);
 }
 
-static size_t gated_segments_ws(int B, int H, int nseg, int dqk, int dv) {
+static size_t gated_segments_ws(size_t walks, int nseg, int dqk, int dv) {
   if (nseg == 1) return 0;
-  const size_t slots = (size_t)B * H * nseg;
+  const size_t slots = walks * nseg;
   return slots * dqk * dv * 4 + ((slots * 4 + 255) & ~(size_t)255);
 }
 
@@ -796,6 +796,36 @@ static hipError_t launch_gated_segmented(const ae::GatedParams& p, const ae::Dec
   s2.h_in = buf;
   s2.h_out_last_only = 1;
   return ae::launch_gated_recurrent(s2, dt, dqk, dv, stream);
+}
+
+// The same for the three walks of the backward pass: their states (of D_qk x D_v elements each) stand one walk behind the other,
+// so that one launch of each kind does for all three.  nseg = 1: not cut.
+static hipError_t launch_gated_backward_segmented(const ae::GatedParams (&walk)[3], const ae::GatedGroupParams* group, int dqk, int dv,
+                                                  int nseg, int seg_len, void* workspace, hipStream_t stream) {
+  if (nseg == 1) return ae::launch_gated_backward(walk, group, dqk, dv, stream);
+  const size_t slots = (size_t)walk[0].B * walk[0].H * nseg;
+  float* dec = static_cast<float*>(workspace);
+  float* buf = reinterpret_cast<float*>(static_cast<char*>(workspace) + ((3 * slots * 4 + 255) & ~(size_t)255));
+  ae::GatedParams w[3];
+  for (int i = 0; i < 3; ++i) {
+    w[i] = walk[i];
+    w[i].nseg = nseg;
+    w[i].seg_len = seg_len;
+    w[i].state_only = 1;
+    w[i].h_out = buf + i * slots * dqk * dv;
+    w[i].seg_decay = dec + i * slots;
+  }
+  hipError_t e = ae::launch_gated_backward(w, nullptr, dqk, dv, stream);
+  if (e != hipSuccess) return e;
+  e = ae::launch_gated_combine_segments(buf, dec, nullptr, 3 * walk[0].B * walk[0].H, nseg, dqk * dv, stream);
+  if (e != hipSuccess) return e;
+  for (int i = 0; i < 3; ++i) {
+    w[i].state_only = 0;
+    w[i].h_in = w[i].h_out;
+    w[i].h_out = nullptr;
+    w[i].seg_decay = nullptr;
+  }
+  return ae::launch_gated_backward(w, nullptr, dqk, dv, stream);
 }
 
 struct ae_recurrent {
@@ -894,7 +924,7 @@ ae_status_t ae_recurrent_create(const ae_recurrent_desc_t* d, ae_recurrent_t** o
   const bool whole = h->tail_len == 0 && !few;
   const int from = n == 2 ? (whole && h->n_chunks <= 5 ? 1536 : 1024) : whole ? 1024 : few ? 512 : 513;
   cut_segments(d->L >= from ? n : 1, d->L, &h->nseg, &h->seg_len);
-  h->ws_bytes = std::max(h->ws_bytes, gated_segments_ws(d->B, d->H, h->nseg, d->D_qk, d->D_v));
+  h->ws_bytes = std::max(h->ws_bytes, gated_segments_ws((size_t)d->B * d->H, h->nseg, d->D_qk, d->D_v));
   *out = h;
   return AE_OK;
 }
@@ -1027,25 +1057,66 @@ ae_status_t ae_recurrent_destroy(ae_recurrent_t* h) {
 
 // ---- recurrent pattern with per-token gates: one kernel, state on chip ------------------------------------
 // Value heads of a group that a workgroup of the backward pass takes in turn, its gradients of q and k summed on chip; 0: one
-// head per workgroup and the sums in a kernel of their own.  Two walks take rounds of 256 workgroups x heads each, and a round
-// has a start and an end that cost about as much as a head: the heads with the least rounds x (heads + 1) are taken (us for 1 /
-// 2 / 3 heads, Mamba2 128/64: 2 x 80 heads x 768 tokens 122 / 145 / 174, 4 x 80 228 / 157 / 183, 8 x 64 301 / 206 / 202, 8 x 80
-// 401 / 332 / 257, 16 x 80 694 / 538 / 476; 6 x 80 x 500 193 / 120 / 134; 8 x 64 x 768 at 64/64 219 / 159 / 187).  With one head
-// the kernel of the sums pays where it has workgroups enough: it takes a group's heads one after the other (8 x 24 x 768 120
-// against 129, 8 x 32/8 x 600 129 against 134, but 3 x 80 x 700 146 against 131, 1 x 80 x 300 100 against 63).
-static int gated_group_heads(const ae_gated_desc_t* d, int bwd_nseg) {
+// head per workgroup and the sums in a kernel of their own (where that walk is not built or cut into segments).  Few heads fill
+// the device, many leave fewer parts to sum; the time is estimated in units of a walk over one head (16 us at 768 tokens):
+// heads + 1 for a workgroup of the first two walks, 1.6 to 2.4 for one of the third (which takes one head or two), handed to 256
+// compute units in this order, and the sum kernel's bytes.  Measured (us for 1 / 2 / 3 heads, 768 tokens): Mamba2 128/64 1 x 80 heads 52 / 63
+// / 79, 2 x 80 93 / 68 / 81, 4 x 80 208 / 127 / 120, 8 x 64 307 / 205 / 172, 8 x 80 391 / 270 / 224, 8 x 32/8 x 600 129 / 96 / 109;
+// 64/64 4 x 32/8 69 / 59 / 75, 8 x 24 94 / 81 / 74, 8 x 64 223 / 161 / 166.
+static double gated_walks_time(int64_t first_two, double cost, int64_t third, double cost3) {
+  // all compute units are busy until `lo`, `n_hi` of them until `hi`; the third walk's workgroups go where one is free first
+  double lo = (double)(first_two / 256) * cost, hi = lo + cost;
+  int64_t n_hi = first_two % 256, n_lo = 256 - n_hi;
+  if (n_hi == 0) hi = lo;
+  for (;;) {
+    const bool low = lo <= hi || n_hi == 0;
+    const int64_t n = low ? n_lo : n_hi;
+    double& t = low ? lo : hi;
+    if (third < n) return std::max(std::max(lo, hi), third > 0 ? t + cost3 : 0.0);
+    third -= n;
+    t += cost3;
+  }
+}
+static int gated_group_heads(const ae_gated_desc_t* d, int bwd_nseg, int* third) {
   const int64_t groups = (int64_t)d->B * d->H_qk, size = d->H / d->H_qk;
+  *third = 1;
   if (size < 2 || bwd_nseg > 1 || !ae::gated_group_supported(d->D_qk, d->D_v)) return 0;
-  int64_t heads = 1, least = INT64_MAX;
-  for (int64_t n = 1; n <= std::min<int64_t>(size, ae::kGatedGroupHeads); ++n) {
-    const int64_t cost = (groups * ((size + n - 1) / n) + 255) / 256 * (n + 1);
-    if (cost < least) {
-      least = cost;
-      heads = n;
+  int heads = 1;
+  double least = 0;
+  for (int n = 1; n <= std::min<int64_t>(size, ae::kGatedGroupHeads); ++n)
+    for (int m = 1; m <= (size % 2 == 0 ? 2 : 1); ++m) {
+      const int64_t parts = (size + n - 1) / n;
+      const double cost3 = d->D_qk == 128 ? (m == 2 ? 2.4 : 2.1) : (m == 2 ? 2.0 : 1.6);
+      const double t = gated_walks_time(2 * groups * parts, n + 1, groups * size / m, cost3) + 1e-4 * groups * parts * d->D_qk;
+      if ((n == 1 && m == 1) || t < least) {
+        least = t;
+        heads = n;
+        *third = m;
+      }
+    }
+  return heads;
+}
+// Value heads of a q/k head that a workgroup of the forward walk takes, and the segments of its walk if it may be cut.  Two heads
+// share the tiles and the scores; a chunk then takes 1.23 (64/64) or 1.12 times as long as with one, and half the workgroups do.
+// Measured (us, one head / two): Mamba2 64/64, uncut, 8 x 64 heads x 768 48 / 33, 8 x 80 x 3000 246 / 221, but 8 x 32/8 x 2048 (256
+// workgroups of one head) 60 / 75; cut, 1 x 80 x 8192 111 / 79, 1 x 24 x 8192 42 / 37; 128/64 uncut 1 x 24 x 4096 147 / 160.
+static void gated_forward_plan(const ae_gated_desc_t* d, bool may_cut, int* heads, int* nseg, int* seg_len) {
+  const bool pairs = d->D_v == 64 && (d->H / d->H_qk) % 2 == 0;
+  double least = 0;
+  for (int n = 1; n <= (pairs ? 2 : 1); ++n) {
+    const int64_t workgroups = (int64_t)d->B * d->H / n;
+    int ns = 1, len = 0;
+    if (may_cut) gated_segments(workgroups, d->L, &ns, &len);
+    // (cut: the state's walk takes a third of the time, and two more launches cost about 300 tokens)
+    const double tokens = ns > 1 ? 1.4 * len + 300 : (double)((workgroups + 255) / 256) * d->L;
+    const double t = tokens * (n == 1 ? 1.0 : d->D_qk == 64 ? 1.23 : 1.12);
+    if (n == 1 || t < 0.9 * least) {  // (3 x 80 x 4096, 64/64: 0.95 by this estimate, 115 / 126 us)
+      least = t;
+      *heads = n;
+      *nseg = ns;
+      *seg_len = len;
     }
   }
-  const int64_t sum_workgroups = groups * d->L * d->D_qk / 1024;
-  return heads == 1 && sum_workgroups >= 512 ? 0 : (int)heads;
 }
 
 struct ae_gated {
@@ -1053,6 +1124,8 @@ struct ae_gated {
   // ae_gated_forward_segmented: the walk of a (batch, head) cut into nseg segments of seg_len tokens where the
   // (batch, head) pairs alone would leave most compute units idle; 1: not cut.  bwd_: the same for ae_gated_backward
   int nseg, seg_len, bwd_nseg, bwd_seg_len;
+  int fwd_heads, seg_heads;  // value heads per workgroup, see gated_forward_plan: uncut walks, ae_gated_forward_segmented
+  int third_heads;           // ... of the backward pass's walk for the gradient of v
   int group_heads;  // ae_gated_backward: value heads of a q/k head whose gradients of q and k a workgroup sums (0: one each, see gated_group_heads)
 };
 
@@ -1073,13 +1146,11 @@ ae_status_t ae_gated_create(const ae_gated_desc_t* d, ae_gated_t** out) {
   ae_gated* h = new (std::nothrow) ae_gated;
   if (!h) return fail(AE_ERR_NOMEM, "ae_gated_create: out of host memory");
   h->desc = *d;
-  {
-    // (two heads of a group share a workgroup at 128/64, see launch_gated_recurrent)
-    const bool pairs = d->D_qk == 128 && d->D_v == 64 && (d->H / d->H_qk) % 2 == 0;
-    gated_segments((int64_t)d->B * d->H / (pairs ? 2 : 1), d->L, &h->nseg, &h->seg_len);
-    gated_segments((int64_t)d->B * d->H, d->L, &h->bwd_nseg, &h->bwd_seg_len);  // (two of its three walks have one head each)
-    h->group_heads = gated_group_heads(d, h->bwd_nseg);
-  }
+  int uncut_nseg = 1, uncut_len = 0;
+  gated_forward_plan(d, false, &h->fwd_heads, &uncut_nseg, &uncut_len);
+  gated_forward_plan(d, true, &h->seg_heads, &h->nseg, &h->seg_len);
+  gated_segments(3 * (int64_t)d->B * d->H, d->L, &h->bwd_nseg, &h->bwd_seg_len);  // (three walks side by side)
+  h->group_heads = gated_group_heads(d, h->bwd_nseg, &h->third_heads);
   *out = h;
   return AE_OK;
 }
@@ -1087,7 +1158,7 @@ ae_status_t ae_gated_create(const ae_gated_desc_t* d, ae_gated_t** out) {
 }  // extern "C"
 
 static size_t gated_forward_ws(const ae_gated* h) {
-  return gated_segments_ws(h->desc.B, h->desc.H, h->nseg, h->desc.D_qk, h->desc.D_v);
+  return gated_segments_ws((size_t)h->desc.B * h->desc.H, h->nseg, h->desc.D_qk, h->desc.D_v);
 }
 
 static ae_status_t gated_forward_impl(const ae_gated_t* h, const void* Q, const void* K, const void* V, const void* log_decay,
@@ -1128,8 +1199,10 @@ static ae_status_t gated_forward_impl(const ae_gated_t* h, const void* Q, const 
     for (const void* in : ins)
       if (in == workspace) return fail(AE_ERR_INVALID_ARG, "ae_gated_forward_segmented: the workspace aliases an input");
     if (workspace == O || workspace == h_out) return fail(AE_ERR_INVALID_ARG, "ae_gated_forward_segmented: the workspace aliases an output");
+    p.heads_per_workgroup = h->seg_heads;
     e = launch_gated_segmented(p, no_table, d.D_qk, d.D_v, h->nseg, h->seg_len, workspace, stream);
   } else {
+    p.heads_per_workgroup = h->fwd_heads;
     e = ae::launch_gated_recurrent(p, no_table, d.D_qk, d.D_v, stream);
   }
   if (e != hipSuccess) return fail(AE_ERR_HIP, "ae_gated_forward: %s", hipGetErrorString(e));
@@ -1157,8 +1230,7 @@ ae_status_t ae_gated_forward_segmented(const ae_gated_t* h, const void* Q, const
 
 // Workspace of the backward pass: the per-token terms of the decay gradient, fp32 [B, H, L]; and, where value heads
 // share q/k heads, the gradients of q and of the gated key per value head, fp32 [B, H, L, D_qk] each.
-// Where the three walks of the backward pass are cut into segments, the segments' states (one set, used by the walks in
-// turn) follow.
+// Where the three walks of the backward pass are cut into segments, the segments' states (a set for each) follow.
 static int gated_parts(const ae_gated* h) {  // workgroups that share a q/k head
   return (h->desc.H / h->desc.H_qk + h->group_heads - 1) / h->group_heads;
 }
@@ -1169,7 +1241,7 @@ static size_t gated_backward_ws(const ae_gated* h, size_t* per_head_off, size_t*
   const size_t per_head = d.H != d.H_qk ? 2 * (size_t)d.B * slabs * d.L * d.D_qk * 4 : 0;
   if (per_head_off) *per_head_off = rows;
   if (seg_off) *seg_off = rows + per_head;
-  return rows + per_head + gated_segments_ws(d.B, d.H, h->bwd_nseg, d.D_qk, d.D_v);
+  return rows + per_head + gated_segments_ws(3 * (size_t)d.B * d.H, h->bwd_nseg, d.D_qk, d.D_v);
 }
 
 ae_status_t ae_gated_backward_workspace_bytes(const ae_gated_t* h, size_t* bytes) {
@@ -1193,12 +1265,6 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
   const ae_gated_desc_t& d = h->desc;
   size_t per_head_off = 0, seg_off = 0;
   const size_t need = gated_backward_ws(h, &per_head_off, &seg_off);
-  void* seg_ws = static_cast<char*>(workspace) + seg_off;
-  auto walk = [&](const ae::GatedParams& g, int dqk, int dv) {
-    static const ae::DecayTable none = {};
-    return h->bwd_nseg > 1 ? launch_gated_segmented(g, none, dqk, dv, h->bwd_nseg, h->bwd_seg_len, seg_ws, stream)
-                           : ae::launch_gated_recurrent(g, none, dqk, dv, stream);
-  };
   if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < need)
     return fail(AE_ERR_INVALID_ARG, "ae_gated_backward: workspace missing, not 256-byte aligned, or smaller than %zu bytes", need);
   const void* ins[] = {Q, K, V, log_decay, key_gate, dO};
@@ -1214,9 +1280,10 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
   float* dB = static_cast<float*>(workspace);
   float* dQu = grouped ? reinterpret_cast<float*>(static_cast<char*>(workspace) + per_head_off) : static_cast<float*>(dQ);
   float* X = grouped ? dQu + (size_t)d.B * d.H * d.L * d.D_qk : static_cast<float*>(dK);
-  static const ae::DecayTable no_table = {};
-  // The three sums of the backward pass are the forward recurrence itself on other operands (see include/ae_attn.h):
-  ae::GatedParams p;
+  // The three sums of the backward pass are the forward recurrence itself on other operands (see include/ae_attn.h), and none
+  // needs another's result: one launch.
+  ae::GatedParams walk[3];
+  ae::GatedParams& p = walk[0];
   p.h_in = nullptr;
   p.h_out = nullptr;
   p.B = d.B;
@@ -1235,57 +1302,59 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
   p.gate_on_output = 0;
   p.reverse = 0;
   p.O = dQu;
-  // (where a workgroup takes several heads of a group, (1) and (2) leave sums over these and dB and dkey_gate)
-  ae::GatedGroupParams gp;
-  gp.Q = static_cast<const __bf16*>(dO);
-  gp.K = static_cast<const __bf16*>(V);
-  gp.V = static_cast<const __bf16*>(K);
-  gp.R = static_cast<const __bf16*>(Q);
-  gp.log_decay = p.log_decay;
-  gp.key_gate = p.key_gate;
-  gp.out = dQu;
-  gp.dB = dB;
-  gp.dkey_gate = static_cast<float*>(dkey_gate);
-  gp.B = d.B;
-  gp.H = d.H;
-  gp.H_qk = d.H_qk;
-  gp.L = d.L;
-  gp.scale = d.scale;
-  gp.reverse = 0;
-  gp.heads = h->group_heads;
-  gp.parts = h->group_heads ? gated_parts(h) : 0;
-  float* dk_parts = dQu + (size_t)d.B * d.H_qk * gp.parts * d.L * d.D_qk;
-  hipError_t e = gp.heads ? ae::launch_gated_group(gp, d.D_qk, d.D_v, stream) : walk(p, d.D_v, d.D_qk);
   // (2) x_j = scale sum_{i >= j} A_ij (v_j . dO_i) q_i, walking backwards: queries V, keys dO, values Q, no gate
-  if (e == hipSuccess) {
-    p.Q = static_cast<const __bf16*>(V);
-    p.K = static_cast<const __bf16*>(dO);
-    p.V = static_cast<const __bf16*>(Q);
-    p.key_gate = nullptr;
-    p.reverse = 1;
-    p.O = X;
-    std::swap(gp.Q, gp.K);
-    std::swap(gp.V, gp.R);
-    gp.out = dk_parts;
-    gp.reverse = 1;
-    e = gp.heads ? ae::launch_gated_group(gp, d.D_qk, d.D_v, stream) : walk(p, d.D_v, d.D_qk);
-  }
+  ae::GatedParams& px = walk[1] = p;
+  px.Q = static_cast<const __bf16*>(V);
+  px.K = static_cast<const __bf16*>(dO);
+  px.V = static_cast<const __bf16*>(Q);
+  px.key_gate = nullptr;
+  px.reverse = 1;
+  px.O = X;
   // (3) dv_j = g_j scale sum_{i >= j} A_ij (k_j . q_i) dO_i, walking backwards: queries K, keys Q, values dO
-  if (e == hipSuccess) {
-    p.Q = static_cast<const __bf16*>(K);
-    p.K = static_cast<const __bf16*>(Q);
-    p.V = static_cast<const __bf16*>(dO);
-    p.H_qk = d.H_qk;
-    p.H_v = d.H;
-    p.key_gate = static_cast<const float*>(key_gate);
-    p.gate_on_output = key_gate ? 1 : 0;
-    p.O = dV;
-    e = walk(p, d.D_qk, d.D_v);
-  }
-  if (e == hipSuccess && gp.heads) {
-    e = ae::launch_gated_group_sum(dQu, dk_parts, static_cast<float*>(dQ), static_cast<float*>(dK), gp.parts, (int64_t)d.L * d.D_qk,
+  ae::GatedParams& pv = walk[2] = px;
+  pv.Q = static_cast<const __bf16*>(K);
+  pv.K = static_cast<const __bf16*>(Q);
+  pv.V = static_cast<const __bf16*>(dO);
+  pv.H_qk = d.H_qk;
+  pv.H_v = d.H;
+  pv.key_gate = static_cast<const float*>(key_gate);
+  pv.gate_on_output = key_gate ? 1 : 0;
+  pv.heads_per_workgroup = h->third_heads;
+  pv.O = dV;
+  // (where a workgroup takes several heads of a group, (1) and (2) leave sums over these, dkey_gate, and the row products of
+  // every head: those of (1) in dB, those of (2) where the gradient of the log-decays will stand)
+  ae::GatedGroupParams gp[2];
+  gp[0].Q = p.Q;
+  gp[0].K = p.K;
+  gp[0].V = p.V;
+  gp[0].R = static_cast<const __bf16*>(Q);
+  gp[0].log_decay = p.log_decay;
+  gp[0].key_gate = p.key_gate;
+  gp[0].out = dQu;
+  gp[0].dots = dB;
+  gp[0].dkey_gate = static_cast<float*>(dkey_gate);
+  gp[0].B = d.B;
+  gp[0].H = d.H;
+  gp[0].H_qk = d.H_qk;
+  gp[0].L = d.L;
+  gp[0].scale = d.scale;
+  gp[0].reverse = 0;
+  gp[0].heads = h->group_heads;
+  gp[0].parts = h->group_heads ? gated_parts(h) : 0;
+  float* dk_parts = dQu + (size_t)d.B * d.H_qk * gp[0].parts * d.L * d.D_qk;
+  gp[1] = gp[0];
+  std::swap(gp[1].Q, gp[1].K);
+  std::swap(gp[1].V, gp[1].R);
+  gp[1].out = dk_parts;
+  gp[1].dots = static_cast<float*>(dlog_decay);
+  gp[1].reverse = 1;
+  const bool sums_inside = h->group_heads > 0;
+  hipError_t e = launch_gated_backward_segmented(walk, sums_inside ? gp : nullptr, d.D_qk, d.D_v, h->bwd_nseg, h->bwd_seg_len,
+                                                 static_cast<char*>(workspace) + seg_off, stream);
+  if (e == hipSuccess && sums_inside) {
+    e = ae::launch_gated_group_sum(dQu, dk_parts, static_cast<float*>(dQ), static_cast<float*>(dK), gp[0].parts, (int64_t)d.L * d.D_qk,
                                    (int64_t)d.B * d.H_qk * d.L * d.D_qk, stream);
-    if (e == hipSuccess) e = ae::launch_gated_suffix_sum(dB, static_cast<float*>(dlog_decay), d.B * d.H, d.L, stream);
+    if (e == hipSuccess) e = ae::launch_gated_suffix_sum(dB, static_cast<float*>(dlog_decay), static_cast<float*>(dlog_decay), d.B * d.H, d.L, stream);
   } else if (e == hipSuccess) {
     ae::GatedBwdEpilogueParams q;
     q.Q = static_cast<const __bf16*>(Q);

@@ -35,6 +35,9 @@ struct GatedParams {
   // state_only: no outputs -- only the state update is walked (O is not touched); seg_decay, if set, receives the
   // sum of the segment's log-decays, fp32 [B, H, nseg]
   int state_only = 0;
+  // 2: a workgroup walks two consecutive value heads of one q/k head, whose tiles and scores they share (D_v = 64, an even
+  // number of value heads per q/k head, H_v = H; in launch_gated_backward beside several heads of the first two walks only)
+  int heads_per_workgroup = 1;
   float* seg_decay = nullptr;
 };
 // In place on buf [B, H, nseg, D_qk x D_v] (the segments' final states from a zero start, as a state_only walk
@@ -63,8 +66,8 @@ hipError_t launch_gated_backward_epilogue(const GatedBwdEpilogueParams& p, int d
 // The same gradients where value heads share q/k heads, summed over `heads` of them (at most kGatedGroupHeads; the last part of
 // a group may have fewer) inside the walks: part `i` of a q/k head takes heads [i * heads, (i + 1) * heads) of its group and
 // leaves its sum in out [B, H_qk, parts, L, D_qk].  Forwards (reverse = 0; Q = dO, K = V, V = K, R = Q): the gradient of q, the
-// key gate on the keys, dB[h, t] = q_t . (gradient of q by head h).  Backwards (Q = V, K = dO, V = Q, R = K): the gradient of
-// k, x_h being that of head h in front of its gate: the sum of g x_h, dkey_gate[h, t] = k_t . x_h, dB[h, t] -= g k_t . x_h.
+// key gate on the keys, dots[h, t] = q_t . (gradient of q by head h).  Backwards (Q = V, K = dO, V = Q, R = K): the gradient of
+// k, x_h being that of head h in front of its gate: the sum of g x_h, dkey_gate[h, t] = k_t . x_h, dots[h, t] = g k_t . x_h.
 constexpr int kGatedGroupHeads = 3;
 struct GatedGroupParams {
   const __bf16* Q;         // [B, H, L, D_v]
@@ -74,20 +77,22 @@ struct GatedGroupParams {
   const float* log_decay;  // [B, H, L]
   const float* key_gate;   // [B, H, L] or null
   float* out;
-  float* dB;               // [B, H, L]
+  float* dots;             // [B, H, L]
   float* dkey_gate;        // [B, H, L] or null
   int B, H, H_qk, L;
   float scale;
   int reverse, heads, parts;
 };
 bool gated_group_supported(int dqk, int dv);
-hipError_t launch_gated_group(const GatedGroupParams& p, int dqk, int dv, hipStream_t stream);
 // dQ, dK [B, H_qk, L, D_qk]: the sums of the parts; head_elems = L * D_qk, elems = B * H_qk * L * D_qk
 hipError_t launch_gated_group_sum(const float* dq_parts, const float* dk_parts, float* dQ, float* dK, int parts, int64_t head_elems,
                                   int64_t elems, hipStream_t stream);
-// dlog_decay[h, t] = sum_{i >= t} dB[h, i] (what launch_gated_backward_epilogue ends with)
-hipError_t launch_gated_suffix_sum(const float* dB, float* dlog_decay, int BH, int L, hipStream_t stream);
+// dlog_decay[h, t] = sum_{i >= t} dB[h, i] - minus[h, i] (minus: null, or dlog_decay itself); launch_gated_backward_epilogue ends with it
+hipError_t launch_gated_suffix_sum(const float* dB, const float* minus, float* dlog_decay, int BH, int L, hipStream_t stream);
 bool gated_supported(int dqk, int dv);
 // dt: log2 of the per-head decay, read only where p.log_decay is null
 hipError_t launch_gated_recurrent(const GatedParams& p, const DecayTable& dt, int dqk, int dv, hipStream_t stream);
+// The three walks of the backward pass (dims D_v / D_qk, D_v / D_qk, D_qk / D_v, all cut alike) in one launch; group: the first two
+// take these instead, several heads each.  dqk, dv: those of the forward pass.
+hipError_t launch_gated_backward(const GatedParams (&walk)[3], const GatedGroupParams* group, int dqk, int dv, hipStream_t stream);
 }  // namespace ae

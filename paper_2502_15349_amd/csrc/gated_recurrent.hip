@@ -65,8 +65,8 @@ struct GCfg {
   // the gates' values of a head's chunk, in floats: b, u, s (see put_gates), two sets of w, the groups' references, two decays
   static constexpr int kB = 0, kU = 64, kS = 128, kW = 192, kRef = 320, kDec = 336, GATE_BYTES = 352 * 4;
   static constexpr int P_BYTES = 3 * 2048;  // per head: the chunk's weights, three blocks of 32 x 32 in bf16
-  // 64/64: two workgroups per compute unit (three wavefronts per SIMD)
-  static constexpr int WAVES_PER_SIMD = DQK == 64 && DV == 64 ? 3 : 2;
+  // 64/64, one head: two workgroups per compute unit (three wavefronts per SIMD)
+  static constexpr int WAVES_PER_SIMD = DQK == 64 && DV == 64 && HPW == 1 ? 3 : 2;
 };
 
 // LDS layout: a stage holds the tiles Q (full walks only), K, V of every head
@@ -292,16 +292,15 @@ struct TileCopy {
 
 // STATE_ONLY: no outputs, only the state update is walked (see GatedParams::state_only): no queries, no weights, one barrier
 // per chunk.
-template <class C, bool STATE_ONLY>
-__global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt) {
+// block: the workgroup's number among those of this walk; const_decay(h): the log-decay of head h where p.log_decay is null.
+template <class C, bool STATE_ONLY, class F>
+__device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint32_t lds0, F&& const_decay) {
   using Y = GLayout<C, STATE_ONLY>;
-  __shared__ __attribute__((aligned(1024))) char smem[Y::LDS_BYTES];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ln = lane & 31, half = lane >> 5;
   // workgroup -> batch entry and HPW consecutive value heads of one q/k group, and the segment of the walk
-  const int seg = blockIdx.x % p.nseg;
-  const int bh0 = (blockIdx.x / p.nseg) * C::HPW, b = bh0 / p.H, h0 = bh0 % p.H;
+  const int seg = block % p.nseg;
+  const int bh0 = (block / p.nseg) * C::HPW, b = bh0 / p.H, h0 = bh0 % p.H;
   const int hqk = h0 / (p.H / p.H_qk);
   const bool rev = p.reverse != 0;
   // the tokens this workgroup walks: L of them from position `first` of the walk (the whole sequence unless it is
@@ -436,7 +435,7 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
 #pragma unroll
       for (int hh = 0; hh < C::HPW; ++hh) {
         const int64_t row = (int64_t)(bh0 + hh) * Lt + row_lo;
-        la[hh] = p.log_decay ? p.log_decay[row + gl] : dt.log2_gamma[h0 + hh] * 0.6931471805599453f;  // constant: ln gamma
+        la[hh] = p.log_decay ? p.log_decay[row + gl] : const_decay(h0 + hh);
         g[hh] = p.key_gate ? p.key_gate[row + gg] : 1.f;
       }
     };
@@ -544,6 +543,13 @@ __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent
   }
 }
 
+template <class C, bool STATE_ONLY>
+__global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt) {
+  __shared__ __attribute__((aligned(1024))) char smem[GLayout<C, STATE_ONLY>::LDS_BYTES];
+  gated_walk<C, STATE_ONLY>(p, blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
+                            [&](int h) { return dt.log2_gamma[h] * 0.6931471805599453f; });  // ln gamma
+}
+
 // ---- backward pass where value heads share a q/k head: the gradients of q and k, summed over heads ----
 // The walk of gated_recurrent_kernel for several value heads of one q/k head in one workgroup, which takes them in turn, chunk
 // by chunk: a unit of work is a (chunk, head).  Queries and keys of the walk (dO and V) are each head's own and arrive per unit,
@@ -564,12 +570,10 @@ struct GroupCfg : GCfg<DQK_, DV_> {
 };
 
 template <class C>
-__global__ __launch_bounds__(C::THREADS, 2) void gated_group_kernel(const GatedGroupParams p) {
-  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
+__device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int block, uint32_t lds0) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ln = lane & 31, half = lane >> 5;
-  const int part = blockIdx.x % p.parts, bhq = blockIdx.x / p.parts, group = p.H / p.H_qk;
+  const int part = block % p.parts, bhq = block / p.parts, group = p.H / p.H_qk;
   const int nh = min(p.heads, group - part * p.heads);                          // heads of this workgroup
   const int64_t bh0 = (int64_t)bhq * group + part * p.heads;                    // the first of them, batch included
   const bool rev = p.reverse != 0;
@@ -676,8 +680,8 @@ __global__ __launch_bounds__(C::THREADS, 2) void gated_group_kernel(const GatedG
   const int role = wave - C::NB;
   if (role == 3) {
     // ================= the gates: lane = token of the chunk; and the heads' row products =================
-    float la = 0.f, g = 1.f, old = 0.f;      // of the unit to prepare next
-    float g_put = 1.f, old_put = 0.f, g_done = 1.f, old_done = 0.f;  // of the unit prepared last, of the one whose products are due
+    float la = 0.f, g = 1.f;         // of the unit to prepare next
+    float g_put = 1.f, g_done = 1.f;  // of the unit prepared last, of the one whose products are due
     auto token = [&](int c) {
       const int i = min(c * C::CH + lane, L - 1);
       return rev ? L - 1 - i : i;
@@ -688,7 +692,6 @@ __global__ __launch_bounds__(C::THREADS, 2) void gated_group_kernel(const GatedG
       // (walking backwards: the decay of the token one later in the sequence; the walk's first token has none)
       la = p.log_decay[row + (rev ? min(t + 1, L - 1) : t)];
       g = p.key_gate ? p.key_gate[row + t] : 1.f;
-      if (rev) old = p.dB[row + t];
     };
     auto put = [&](int c, int odd) {
       const int t = c * C::CH + lane;
@@ -705,9 +708,9 @@ __global__ __launch_bounds__(C::THREADS, 2) void gated_group_kernel(const GatedG
         const int64_t e = (bh0 + n) * L + token(c);
         if (rev) {
           if (p.dkey_gate) p.dkey_gate[e] = d;
-          d = old_done - g_done * d;
+          d *= g_done;
         }
-        p.dB[e] = d;
+        p.dots[e] = d;
       }
     };
     int c = 0, n = 0, cl = 0, nl = 0, cd = 0, nd = 0;  // the unit under way, the next to load, the next to finish
@@ -722,7 +725,6 @@ __global__ __launch_bounds__(C::THREADS, 2) void gated_group_kernel(const GatedG
     chunk_barrier();
     put(0, 0);
     g_put = g;
-    old_put = old;
     if (units > 1) load(cl, nl);
     chunk_barrier();
     for (int u = 0; u < units; ++u) {
@@ -732,12 +734,10 @@ __global__ __launch_bounds__(C::THREADS, 2) void gated_group_kernel(const GatedG
       }
       chunk_barrier();
       g_done = g_put;
-      old_done = old_put;
       step(c, n);
       if (u + 1 < units) {
         put(c, (u + 1) & 1);
         g_put = g;
-        old_put = old;
         step(cl, nl);
         if (u + 2 < units) load(cl, nl);
       }
@@ -814,6 +814,54 @@ __global__ __launch_bounds__(C::THREADS, 2) void gated_group_kernel(const GatedG
         [&](int u) {
           if (u + 1 < units) wait(u + 2 < units);
         });
+  }
+}
+
+// ---- the three walks of the backward pass in one launch ----
+// They do not depend on each other, each is a chain of chunks as long as the sequence, and with a launch for each the next one
+// waits for the last workgroup of the one before.  Side by side they fill the compute units that one of them leaves idle.
+// Three launches / one (us): 1 x 8 heads x 768, 128/128, 66.6 / 32.3, 2 x 32 x 768 120 / 57, 4 x 32 x 768 131 / 103,
+// 8 x 32 x 768 203 / 195, 4 x 8 x 500 64/64 58 / 28, Mamba2 8 x 80 x 768 256 / 224, 1 x 80 x 300 61 / 31.
+// A: head dims of the walks for the gradients of q and k (D_v, D_qk), E: of the one for that of v (D_qk, D_v).  The longest
+// workgroups come first: GROUP: those that take several heads; otherwise all are alike and the gradient of v, which no
+// later kernel reads, goes first (the others are still in the caches then: 8 x 32 x 768 202 against 192).
+struct GatedBackwardWalks {
+  GatedParams walk[3];
+  GatedGroupParams group[2];
+  int first[2];  // number of the first workgroup of walks 1 and 2
+};
+template <class A, class E, bool STATE_ONLY, bool GROUP>
+struct BackwardCfg {
+  static constexpr int THREADS = A::THREADS > E::THREADS ? A::THREADS : E::THREADS;
+  static constexpr int WAVES_PER_SIMD = A::WAVES_PER_SIMD < E::WAVES_PER_SIMD || GROUP ? 2 : E::WAVES_PER_SIMD;
+  static constexpr int first_two() {
+    if constexpr (GROUP) return A::LDS_BYTES;
+    else return GLayout<A, STATE_ONLY>::LDS_BYTES;
+  }
+  static constexpr int THIRD = GLayout<E, STATE_ONLY>::LDS_BYTES;
+  static constexpr int LDS_BYTES = first_two() > THIRD ? first_two() : THIRD;
+};
+template <class A, class E, bool STATE_ONLY, bool GROUP>
+__global__ __launch_bounds__((BackwardCfg<A, E, STATE_ONLY, GROUP>::THREADS), (BackwardCfg<A, E, STATE_ONLY, GROUP>::WAVES_PER_SIMD))
+void gated_backward_kernel(const GatedBackwardWalks w) {
+  typedef BackwardCfg<A, E, STATE_ONLY, GROUP> C;
+  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
+  const int n = (int)blockIdx.x, which = (n >= w.first[0] ? 1 : 0) + (n >= w.first[1] ? 1 : 0);
+  const int block = n - (which == 0 ? 0 : w.first[which - 1]);
+  const auto no_const = [](int) { return 0.f; };
+  constexpr int kE = GROUP ? 2 : 0;  // place of the walk for the gradient of v
+  if constexpr (std::is_same<A, E>::value) {
+    gated_walk<E, STATE_ONLY>(w.walk[which], block, lds0, no_const);
+  } else {
+    // (wavefronts beyond those of the walk end here: a barrier counts those that are left)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (which == kE) {
+      if (wave < E::WAVES) gated_walk<E, STATE_ONLY>(w.walk[kE], block, lds0, no_const);
+    } else if (wave < A::WAVES) {
+      if constexpr (GROUP) gated_group_walk<A>(w.group[which], block, lds0);
+      else gated_walk<A, STATE_ONLY>(w.walk[which], block, lds0, no_const);
+    }
   }
 }
 
@@ -917,11 +965,12 @@ __global__ __launch_bounds__(256) void gated_bwd_rows_kernel(const GatedBwdEpilo
   }
 }
 
-// dlog_decay[t] = sum_{i >= t} dB[i]: one wavefront per (batch, head) walks from the end in blocks of 256 tokens,
+// dlog_decay[t] = sum_{i >= t} dB[i] - minus[i] (minus: null or dlog_decay itself, read in front of the writes): one wavefront per (batch, head) walks from the end in blocks of 256 tokens,
 // four per lane; the running total is kept in double (the terms change sign and the sum is long).
-__global__ __launch_bounds__(64) void gated_bwd_suffix_sum_kernel(const float* dB, float* dlog_decay, int L) {
+__global__ __launch_bounds__(64) void gated_bwd_suffix_sum_kernel(const float* dB, const float* minus, float* dlog_decay, int L) {
   const int lane = threadIdx.x;
   const float* src = dB + (int64_t)blockIdx.x * L;
+  const float* sub = minus ? minus + (int64_t)blockIdx.x * L : nullptr;
   float* dst = dlog_decay + (int64_t)blockIdx.x * L;
   double carry = 0.0;
   const int nblk = (L + 255) / 256;
@@ -929,7 +978,7 @@ __global__ __launch_bounds__(64) void gated_bwd_suffix_sum_kernel(const float* d
     const int t0 = blk * 256 + 4 * lane;
     float x[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = t0 + e < L ? src[t0 + e] : 0.f;
+    for (int e = 0; e < 4; ++e) x[e] = t0 + e < L ? src[t0 + e] - (sub ? sub[t0 + e] : 0.f) : 0.f;
     // suffix sums inside the lane, then over the lanes behind this one
     x[2] += x[3];
     x[1] += x[2];
@@ -960,17 +1009,6 @@ hipError_t launch_gated_combine_segments(float* buf, const float* seg_decay, con
 
 bool gated_group_supported(int dqk, int dv) { return (dqk == 64 || dqk == 128) && dv == 64; }
 
-hipError_t launch_gated_group(const GatedGroupParams& p, int dqk, int dv, hipStream_t s) {
-  if (!gated_group_supported(dqk, dv) || p.heads < 1 || p.heads > kGatedGroupHeads || p.H_qk < 1 || p.H % p.H_qk != 0 ||
-      (int64_t)p.parts * p.heads < p.H / p.H_qk || (int64_t)(p.parts - 1) * p.heads >= p.H / p.H_qk ||
-      (int64_t)p.B * p.H_qk * p.parts > 0x7fffffffLL)
-    return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(p.B * p.H_qk * p.parts));
-  if (dqk == 128) hipLaunchKernelGGL((gated_group_kernel<GroupCfg<64, 128>>), grid, dim3(GroupCfg<64, 128>::THREADS), 0, s, p);
-  else hipLaunchKernelGGL((gated_group_kernel<GroupCfg<64, 64>>), grid, dim3(GroupCfg<64, 64>::THREADS), 0, s, p);
-  return hipGetLastError();
-}
-
 hipError_t launch_gated_group_sum(const float* dq_parts, const float* dk_parts, float* dQ, float* dK, int parts, int64_t head_elems,
                                   int64_t elems, hipStream_t s) {
   const int64_t grid = (elems / 4 + 255) / 256;
@@ -979,8 +1017,8 @@ hipError_t launch_gated_group_sum(const float* dq_parts, const float* dk_parts, 
   return hipGetLastError();
 }
 
-hipError_t launch_gated_suffix_sum(const float* dB, float* dlog_decay, int BH, int L, hipStream_t s) {
-  hipLaunchKernelGGL(gated_bwd_suffix_sum_kernel, dim3((unsigned)BH), dim3(64), 0, s, dB, dlog_decay, L);
+hipError_t launch_gated_suffix_sum(const float* dB, const float* minus, float* dlog_decay, int BH, int L, hipStream_t s) {
+  hipLaunchKernelGGL(gated_bwd_suffix_sum_kernel, dim3((unsigned)BH), dim3(64), 0, s, dB, minus, dlog_decay, L);
   return hipGetLastError();
 }
 
@@ -991,27 +1029,90 @@ hipError_t launch_gated_backward_epilogue(const GatedBwdEpilogueParams& p, int d
   if (dqk == 64) hipLaunchKernelGGL(gated_bwd_rows_kernel<64>, dim3((unsigned)grid), dim3(256), 0, s, p);
   else hipLaunchKernelGGL(gated_bwd_rows_kernel<128>, dim3((unsigned)grid), dim3(256), 0, s, p);
   const hipError_t e = hipGetLastError();
-  return e != hipSuccess ? e : launch_gated_suffix_sum(p.dB, p.dlog_decay, p.B * p.H, p.L, s);
+  return e != hipSuccess ? e : launch_gated_suffix_sum(p.dB, nullptr, p.dlog_decay, p.B * p.H, p.L, s);
 }
 
 bool gated_supported(int dqk, int dv) { return (dqk == 64 || dqk == 128) && (dv == 64 || dv == 128); }
 
-hipError_t launch_gated_recurrent(const GatedParams& p_in, const DecayTable& dt, int dqk, int dv, hipStream_t s) {
-  GatedParams p = p_in;
+static hipError_t check_walk(GatedParams& p) {
   if (p.H_v == 0) p.H_v = p.H;
   if (p.H_qk < 1 || p.H % p.H_qk != 0 || p.H % p.H_v != 0) return hipErrorInvalidValue;
   if (p.nseg < 1 || (p.nseg > 1 && (p.seg_len < 64 || p.seg_len % 64 != 0 || (int64_t)(p.nseg - 1) * p.seg_len >= p.L)))
     return hipErrorInvalidValue;
-  if ((int64_t)p.B * p.H * p.nseg > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (dqk == 64 && dv == 64) return launch<64, 64>(p, dt, s);
-  if (dqk == 128 && dv == 64) {
-    // value heads that share their q/k head (Mamba2's groups) share the Q and K tiles of a workgroup, two at a time
-    const int grp = p.H / p.H_qk;
-    if (grp % 2 == 0 && p.H_v == p.H) return launch<128, 64, 2>(p, dt, s);
-    return launch<128, 64>(p, dt, s);
-  }
+  // value heads that share their q/k head (Mamba2's groups) can share the Q and K tiles of a workgroup, two at a time
+  if (p.heads_per_workgroup != 1 && (p.heads_per_workgroup != 2 || p.H / p.H_qk % 2 != 0 || p.H_v != p.H)) return hipErrorInvalidValue;
+  return (int64_t)p.B * p.H * p.nseg > 0x7fffffffLL ? hipErrorInvalidValue : hipSuccess;
+}
+
+hipError_t launch_gated_recurrent(const GatedParams& p_in, const DecayTable& dt, int dqk, int dv, hipStream_t s) {
+  GatedParams p = p_in;
+  const hipError_t e = check_walk(p);
+  if (e != hipSuccess) return e;
+  const bool pairs = p.heads_per_workgroup == 2;
+  if (pairs && dv != 64) return hipErrorInvalidValue;
+  if (dqk == 64 && dv == 64) return pairs ? launch<64, 64, 2>(p, dt, s) : launch<64, 64>(p, dt, s);
+  if (dqk == 128 && dv == 64) return pairs ? launch<128, 64, 2>(p, dt, s) : launch<128, 64>(p, dt, s);
   if (dqk == 64 && dv == 128) return launch<64, 128>(p, dt, s);
   if (dqk == 128 && dv == 128) return launch<128, 128>(p, dt, s);
+  return hipErrorInvalidValue;
+}
+
+template <class A, class E, bool GROUP = false>
+static hipError_t launch_walks(const GatedBackwardWalks& w, int64_t blocks, hipStream_t s) {
+  const dim3 grid((unsigned)blocks);
+  if constexpr (!GROUP) {
+    if (w.walk[0].state_only) {
+      hipLaunchKernelGGL((gated_backward_kernel<A, E, true, false>), grid, dim3(BackwardCfg<A, E, true, false>::THREADS), 0, s, w);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP>), grid, dim3(BackwardCfg<A, E, false, GROUP>::THREADS), 0, s, w);
+  return hipGetLastError();
+}
+
+hipError_t launch_gated_backward(const GatedParams (&walk)[3], const GatedGroupParams* group, int dqk, int dv, hipStream_t s) {
+  GatedBackwardWalks w = {};
+  const bool pairs = walk[2].heads_per_workgroup == 2;
+  if ((pairs && (dv != 64 || walk[0].nseg != 1)) || walk[0].heads_per_workgroup != 1 || walk[1].heads_per_workgroup != 1) return hipErrorInvalidValue;
+  int64_t blocks = 0;
+  for (int i = 0; i < 3; ++i) {
+    const int from = group ? i : (i + 2) % 3;
+    GatedParams& p = w.walk[i] = walk[from];
+    const hipError_t e = check_walk(p);
+    if (e != hipSuccess) return e;
+    if (p.nseg != walk[0].nseg || p.state_only != walk[0].state_only) return hipErrorInvalidValue;
+    if (i > 0) w.first[i - 1] = (int)blocks;
+    if (group && i < 2) {
+      const GatedGroupParams& g = w.group[i] = group[i];
+      if (!gated_group_supported(dqk, dv) || p.nseg != 1 || p.state_only || g.heads < 1 || g.heads > kGatedGroupHeads || g.H_qk < 1 ||
+          g.H % g.H_qk != 0 || (int64_t)g.parts * g.heads < g.H / g.H_qk || (int64_t)(g.parts - 1) * g.heads >= g.H / g.H_qk)
+        return hipErrorInvalidValue;
+      blocks += (int64_t)g.B * g.H_qk * g.parts;
+    } else {
+      blocks += (int64_t)p.B * p.H * p.nseg / p.heads_per_workgroup;
+    }
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  }
+  if (group) {
+    if (dqk == 64) return pairs ? launch_walks<GroupCfg<64, 64>, GCfg<64, 64, 2>, true>(w, blocks, s) : launch_walks<GroupCfg<64, 64>, GCfg<64, 64>, true>(w, blocks, s);
+    return pairs ? launch_walks<GroupCfg<64, 128>, GCfg<128, 64, 2>, true>(w, blocks, s) : launch_walks<GroupCfg<64, 128>, GCfg<128, 64>, true>(w, blocks, s);
+  }
+  if (pairs) return hipErrorInvalidValue;
+  if (dqk == 64 && dv == 64) {
+    // Two workgroups share a compute unit here, each the slower for it: where a walk by itself gives every compute unit one and
+    // its chunks outweigh two more launches, one behind the other (us, one launch / three: 8 x 32 heads x 768 109.6 / 105.4, 6 x 32 x
+    // 2000 258 / 247; but 8 x 32 x 200 43.2 / 44.3, 5 x 32 x 768 75 / 95, 9 x 32 x 768 136 / 173).
+    if (!w.walk[0].state_only && blocks > 3 * 160 && blocks <= 3 * 256 && w.walk[0].L >= 320) {
+      static const DecayTable none = {};
+      hipError_t e = hipSuccess;
+      for (int i = 0; i < 3 && e == hipSuccess; ++i) e = launch<64, 64>(w.walk[i], none, s);
+      return e;
+    }
+    return launch_walks<GCfg<64, 64>, GCfg<64, 64>>(w, blocks, s);
+  }
+  if (dqk == 128 && dv == 128) return launch_walks<GCfg<128, 128>, GCfg<128, 128>>(w, blocks, s);
+  if (dqk == 64 && dv == 128) return launch_walks<GCfg<128, 64>, GCfg<64, 128>>(w, blocks, s);
+  if (dqk == 128 && dv == 64) return launch_walks<GCfg<64, 128>, GCfg<128, 64>>(w, blocks, s);
   return hipErrorInvalidValue;
 }
 

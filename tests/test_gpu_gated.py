@@ -76,6 +76,19 @@ def test_chunk_counts_and_bf16_rows(A, dqk, dv, H, H_qk, L):
     check(got.cpu().double().numpy(), ref, f"{dqk}/{dv} H {H}/{H_qk} L={L}")
 
 
+@pytest.mark.parametrize("dqk", [64, 128])
+@pytest.mark.parametrize("L", [1, 64, 129, 200])
+def test_two_heads_per_workgroup(A, dqk, L):
+    # more (batch, head) pairs than compute units and an even group: a workgroup walks two heads; the same values as with a
+    # copy of its q/k head for every head, where it walks one (the same products, summed in the same order)
+    Q, K, V, la, kg = inputs(860 + L % 7, 2, 132, 22, L, dqk, 64, "mamba2")
+    h0 = torch.randn(2, 132, dqk, 64, generator=torch.Generator().manual_seed(7))
+    got, state = run(A, Q, K, V, la, kg, 0.1, h_in=h0, want_state=True)
+    Qx, Kx = (t.repeat_interleave(6, dim=1) for t in (Q, K))
+    ref, ref_state = run(A, Qx, Kx, V, la, kg, 0.1, h_in=h0, want_state=True)
+    assert torch.equal(got, ref) and torch.equal(state, ref_state)
+
+
 def test_grouped_query_key_heads_mamba2_shape(A):
     # Mamba2's structure at a reduced head count: B and C shared by the value heads of a group, D_qk 128, D_v 64
     Q, K, V, la, kg = inputs(810, 1, 8, 2, 300, 128, 64, "mamba2")
@@ -126,7 +139,7 @@ def test_strong_decay_and_no_decay(A):
     check(got.cpu().double().numpy(), ref, "decay e^-8 / none / resets")
 
 
-@pytest.mark.parametrize("dqk,dv,H,H_qk", [(128, 128, 2, 2), (64, 64, 3, 3), (128, 64, 4, 1), (64, 128, 2, 2)])
+@pytest.mark.parametrize("dqk,dv,H,H_qk", [(128, 128, 2, 2), (64, 64, 3, 3), (128, 64, 4, 1), (64, 64, 4, 1), (64, 128, 2, 2)])
 @pytest.mark.parametrize("kind", ["gated_retention", "mamba2"])
 @pytest.mark.parametrize("L", [1061, 2560])
 def test_segmented_walk(A, dqk, dv, H, H_qk, kind, L):

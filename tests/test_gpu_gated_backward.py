@@ -189,6 +189,17 @@ def test_several_heads_per_workgroup(A, dqk, H, H_qk, heads, kind, L):
     close(dla, ela, (2 * dqk * eps * (rows_q + rows_k) + 1e-7)[..., ::-1].cumsum(axis=-1)[..., ::-1] + 2 * eps * np.abs(ela), "dlog_decay")
 
 
+@pytest.mark.parametrize("dqk,dv", [(64, 64), (128, 64), (64, 128), (128, 128)])
+def test_batch_entries_do_not_depend_on_the_launches(A, dqk, dv):
+    # 180 (batch, head) pairs: one launch for the three walks or (64/64) one each; 60 at a time always take one
+    Q, K, V, la, kg, dO = inputs(940, 3, 60, 60, 321, dqk, dv, "mamba2")
+    whole = run(A, Q, K, V, la, kg, dO, 0.1)
+    for b in range(3):
+        part = run(A, *(t[b:b + 1].contiguous() for t in (Q, K, V, la, kg, dO)), 0.1)
+        for x, y in zip(whole, part):
+            assert np.array_equal(x[b:b + 1], y)
+
+
 @pytest.mark.parametrize("dqk,dv,H,H_qk", [(128, 128, 2, 2), (64, 64, 3, 3), (128, 64, 4, 1)])
 @pytest.mark.parametrize("kind", ["gated_retention", "mamba2"])
 @pytest.mark.parametrize("L", [1061, 2560])
