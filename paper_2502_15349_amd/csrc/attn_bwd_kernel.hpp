@@ -13,7 +13,7 @@
 //     sign(sum_j S'); the gradient of the raw score is dS' * decay
 //   dQ  = scale * dS' K                   dK = scale * dS'^T Q
 //
-// A launch per side, no atomics, every output written once:
+// Two sides, in one launch or one each, no atomics, every output written once:
 //   * key side (KV_SIDE): a workgroup owns 128 keys of one k/v head and walks the query tiles of
 //     the q heads that share it: dK and dV;
 //   * query side: a workgroup owns 128 query rows of one q head and walks the key tiles: dQ.
@@ -28,8 +28,8 @@
 //
 // What bounds it is how well a SIMD's vector and matrix work overlap, and that takes two wavefronts per SIMD of at most
 // 256 registers.  Where accumulators, resident operands and score tiles of 32 own rows fit that (64/64; 128/128, query
-// side), a wavefront does all of the above and two workgroups share a CU: attn_bwd_kernel.  Where they do not, the 32
-// rows go to a pair of wavefronts: attn_bwd_pair_kernel (its key side at 128/256 still spills up to 9 registers), but for
+// side), a wavefront does all of the above and two workgroups share a CU: bwd_single_walk.  Where they do not, the 32
+// rows go to a pair of wavefronts: bwd_pair_walk (its key side at 128/256 still spills up to 9 registers), but for
 // short walks, which the first form takes with one workgroup per CU and up to 472 registers.  The lines between the two
 // stand in bwd_launch.hpp.
 #pragma once
@@ -70,7 +70,7 @@ struct BwdParams {
   // handles without decay may have more heads than that)
   int has_decay;
   // (batch, k/v head) groups that one XCD walks together, per kernel ([0]: query side, [1]: key side); see the
-  // mapping at the top of attn_bwd_kernel
+  // mapping at the top of bwd_single_walk
   int together[2];
 };
 
@@ -97,6 +97,7 @@ struct BwdCfg {
   static constexpr int DQK = DQK_, DV = DV_, NORM = NORM_, OUT = OUT_;
   static constexpr bool CAUSAL = CAUSAL_, KV_SIDE = OUT_ == BWD_DKV;
   static constexpr int WAVES = 4, THREADS = 256, OWN = 128;  // own rows per workgroup
+  static constexpr bool PAIR = false;
   static constexpr int T1 = DQK / 16, T2 = DV / 16;
   static constexpr int DB = DQK / 32;  // 32-row blocks of the transposed result dQ^T / dK^T
   static constexpr bool HAS2 = KV_SIDE;               // key side: a second result, dV^T
@@ -143,9 +144,7 @@ __device__ __forceinline__ bf16x8 pack8(const float (&x)[16], int t) {
 }
 
 template <class C>
-__global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(const BwdParams p, const DecayTable dt) {
-  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
+__device__ __forceinline__ void bwd_single_walk(const BwdParams& p, const DecayTable& dt, int block, uint32_t lds0) {
   const uint32_t rows0 = lds0 + 2 * C::STAGE_BYTES;
   const uint32_t bias0 = rows0 + 2 * C::ROW_BYTES;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -164,7 +163,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC2 ? 2 : 1) void attn_bwd_kernel(c
   const int n_groups = p.B * p.H_kv;
   const int per_group = C::KV_SIDE ? n_own_tiles : n_own_tiles * p.g;
   const int tg = p.together[C::KV_SIDE ? 1 : 0];
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int xcd = block & 7, slot = block >> 3;
   const int set = slot / (tg * per_group), within = slot % (tg * per_group);
   const int item = within / tg, group = (set * tg + within % tg) * 8 + xcd;
   if (group >= n_groups) return;
@@ -596,6 +595,7 @@ struct BwdPairCfg {
   static constexpr int DQK = DQK_, DV = DV_, NORM = NORM_, OUT = OUT_;
   static constexpr bool CAUSAL = CAUSAL_, KV_SIDE = OUT_ == BWD_DKV;
   static constexpr int WAVES = 8, THREADS = 512, OWN = 128, TILE = 32;
+  static constexpr bool PAIR = true, OCC2 = false;
   static constexpr int T1 = DQK / 16, T2 = DV / 16, DB = DQK / 32, DB2 = KV_SIDE ? DV / 32 : 0;
   static constexpr bool ABS = NORM == NORM_ABSSUM || NORM == NORM_ABS_OF_SUM;
   static constexpr bool ROWS = NORM == NORM_SOFTMAX || ABS;
@@ -642,9 +642,7 @@ __device__ __forceinline__ u32x4 lds_read16u(uint32_t addr) {
 }
 
 template <class C>
-__global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdParams p, const DecayTable dt) {
-  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
+__device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTable& dt, int block, uint32_t lds0) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w4 = wave & 3;
   const int ln = lane & 31, half = lane >> 5;
   const int off = p.L_k - p.L_q;
@@ -654,7 +652,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
   const int n_groups = p.B * p.H_kv;
   const int per_group = C::KV_SIDE ? n_own_tiles : n_own_tiles * p.g;
   const int tg = p.together[C::KV_SIDE ? 1 : 0];
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int xcd = block & 7, slot = block >> 3;
   const int set = slot / (tg * per_group), within = slot % (tg * per_group);
   const int item = within / tg, group = (set * tg + within % tg) * 8 + xcd;
   if (group >= n_groups) return;
@@ -1175,6 +1173,45 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_bwd_pair_kernel(const BwdP
   };
   if (wave < 4) walk(std::integral_constant<int, 0>{});
   else walk(std::integral_constant<int, 1>{});
+}
+
+// ---- the kernels ----------------------------------------------------------------------------------------------------
+template <class C>
+__device__ __forceinline__ void bwd_walk(const BwdParams& p, const DecayTable& dt, int block, uint32_t lds0) {
+  if constexpr (C::PAIR) bwd_pair_walk<C>(p, dt, block, lds0);
+  else bwd_single_walk<C>(p, dt, block, lds0);
+}
+// wavefronts per SIMD that the registers are shared among
+template <class C>
+constexpr int bwd_waves_per_simd() { return C::PAIR || C::OCC2 ? 2 : 1; }
+
+// One side.
+template <class C>
+__global__ __launch_bounds__(C::THREADS, bwd_waves_per_simd<C>()) void attn_bwd_kernel(const BwdParams p, const DecayTable dt) {
+  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
+  bwd_walk<C>(p, dt, blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem));
+}
+
+// Both sides, the key side's workgroups (K) first: they need nothing of each other, and the second one's workgroups go where the
+// first one's leave the device idle.
+template <class K, class Q>
+struct BwdBoth {
+  static constexpr int THREADS = K::THREADS > Q::THREADS ? K::THREADS : Q::THREADS;
+  static constexpr int LDS_BYTES = K::LDS_BYTES > Q::LDS_BYTES ? K::LDS_BYTES : Q::LDS_BYTES;
+  static constexpr int WAVES_PER_SIMD = THREADS == 512 || bwd_waves_per_simd<K>() + bwd_waves_per_simd<Q>() == 4 ? 2 : 1;
+};
+template <class K, class Q>
+__global__ __launch_bounds__((BwdBoth<K, Q>::THREADS), (BwdBoth<K, Q>::WAVES_PER_SIMD))
+void attn_bwd_both_kernel(const BwdParams p, const DecayTable dt, int key_blocks) {
+  __shared__ __attribute__((aligned(1024))) char smem[BwdBoth<K, Q>::LDS_BYTES];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
+  // (wavefronts beyond those of the walk end here: a barrier counts those that are left)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), block = (int)blockIdx.x;
+  if (block < key_blocks) {
+    if (wave < K::WAVES) bwd_walk<K>(p, dt, block, lds0);
+  } else {
+    if (wave < Q::WAVES) bwd_walk<Q>(p, dt, block - key_blocks, lds0);
+  }
 }
 
 }  // namespace ae

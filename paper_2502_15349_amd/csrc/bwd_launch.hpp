@@ -1,13 +1,15 @@
 // Launch templates of the backward kernels, shared by the per-head-dim instantiation files
 // (attn_bwd_<D_qk>_<D_v>.hip), each of which defines one launch_backward_<D_qk>_<D_v>().
 #pragma once
+#include <algorithm>
+
 #include "bwd.hpp"
 
 namespace ae {
 namespace {
 
 // One wavefront per 32 own rows where two workgroups of it fit a CU (64/64, and the query side of 128/128 without a bias
-// tensor), a pair of wavefronts elsewhere (the measurements stand at attn_bwd_pair_kernel).  64/64 with a bias tensor has
+// tensor), a pair of wavefronts elsewhere (the measurements stand at bwd_pair_walk).  64/64 with a bias tensor has
 // both: the pair pays on long walks while an XCD holds no more than one workgroup per CU.  Whole backward pass, one wavefront /
 // pair, us: 1 x 6 heads x 1023 x 1060 (8 and 9 workgroups per XCD) 73 / 68, 2 x 12 x 1023 x 1060 (24 and 27) 83 / 80;
 // 1 x 6 x 4096 x 4133 (32 and 33) 342 / 398, 8 x 16 x 512 x 549 (64 and 80) 96 / 113, 8 x 16 x 2048 causal (256) 744 / 919,
@@ -24,57 +26,99 @@ constexpr int64_t kLongBiasWalk = 384;
 // 100 28.2 / 29.3 (192/128 with one 21.9 / 22.3, 32.8 / 32.3: always pairs).
 constexpr int64_t short_window(int dv) { return dv == 256 ? 96 : 256; }
 constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
+// Both sides go in one launch (the key side's workgroups first): two launches / one, us, causal unless said: 64/64 1 x 16 heads x
+// 1024 54 / 34, 1 x 16 x 4096 186 / 140, 4 x 32/8 x 2048 335 / 289, 8 x 16 x 2048 unmasked 506 / 510, with a bias tensor 2 x 12 x 1023 x 1201
+// 85 / 68; 192/128 1 x 16 x 500 53 / 33, 1 x 6 x 4096 259 / 172, 1 x 128 x 4096 2597 / 2607; 128/256 2 x 16 x 1024 100 / 74, 4 x 16 x
+// 2048 438 / 433.  Two exceptions, where the two kernels do not fit the same mould:
+//   * 128/128 without a bias tensor: beside the key side's workgroups those of the query side get a CU each, which they otherwise
+//     share by two.  It pays while the key side leaves compute units idle: few workgroups (of 32 compute units per XCD), or
+//     causal ones of unequal length.  Causal (workgroups of the key side per XCD): 1 x 16 x 1024 (16) 75 / 44, 1 x 32/8 x 4096 (32) 676 / 550,
+//     2 x 12 x 2048 (48) 139 / 127, but 8 x 24/6 x 1000 (48) 297 / 332, 8 x 12 x 700 (72) 104 / 109, 4 x 32/8 x 2048 (64) 552 / 597; unmasked
+//     1 x 32/8 x 2048 (16) 332 / 256, 2 x 32/8 x 1500 (24) 298 / 290, 1 x 16 x 2048 (32, 64 of both sides) 142 / 141, but 2 x 32/8 x 2048 (32)
+//     461 / 506, 2 x 12 x 2048 (48) 221 / 252.
+//   * 128/256, abs-sum family: as one kernel it spills 26 registers instead of 9.  2 x 16 x 1024 (64 workgroups of both sides per XCD)
+//     117 / 91, 1 x 24/6 x 2048 (80) 480 / 422, 2 x 16 x 2048 (128) 254 / 263, 4 x 16 x 2048 (256) 511 / 533.
+// The workgroups of a side: whole sets of `together` groups per XCD (the kernels' mapping): sets x together x 8 XCDs x
+// workgroups per group.
+inline int64_t side_rounds(const BwdParams& p) { return ((int64_t)p.B * p.H_kv + 7) / 8; }
+inline int64_t side_per_group(const BwdParams& p, bool key_side) {
+  return (int64_t)(((key_side ? p.L_k : p.L_q) + 127) / 128) * (key_side ? 1 : p.g);  // (all kernels own 128 rows per workgroup)
+}
+inline int64_t side_blocks(const BwdParams& p, bool key_side) {
+  const int64_t tg = p.together[key_side ? 1 : 0];
+  return tg < 1 ? -1 : (side_rounds(p) + tg - 1) / tg * tg * 8 * side_per_group(p, key_side);
+}
 
-template <int DQK, int DV, int NORM, bool CAUSAL, int OUT, bool BIAS>
-hipError_t launch_one(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
-  constexpr bool kKvSide = OUT == BWD_DKV;
-  constexpr int kOwn = 128;  // (both kernels own 128 rows per workgroup)
-  // whole sets of `together` groups per XCD (the kernel's mapping): sets x together x 8 XCDs x workgroups per group
-  const int L = kKvSide ? p.L_k : p.L_q;
-  const int64_t per_group = (int64_t)((L + kOwn - 1) / kOwn) * (kKvSide ? 1 : p.g);
-  const int64_t rounds = ((int64_t)p.B * p.H_kv + 7) / 8, tg = p.together[kKvSide ? 1 : 0];
-  const int64_t grid = ((rounds + tg - 1) / tg) * tg * 8 * per_group;
-  if (tg < 1 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  constexpr bool kTwoPerCu = DQK == 64 || (DQK == 128 && DV == 128 && !kKvSide && !BIAS);
-  constexpr bool kShort = !kTwoPerCu && CAUSAL && (!BIAS || DQK == 128);
-  const int64_t walk = (kKvSide ? (int64_t)p.L_q * p.g : p.L_k), window = p.window < (kKvSide ? p.L_q : p.L_k) ? p.window : 0;
-  bool pair = !kTwoPerCu;
-  if constexpr (kTwoPerCu && BIAS) pair = rounds * per_group <= units_per_xcd(CAUSAL) && walk / (CAUSAL ? 2 : 1) >= kLongBiasWalk;
-  if constexpr (kShort) pair = window ? window * (kKvSide ? p.g : 1) > short_window(DV) : walk > short_walk(DV);
-  if constexpr (kTwoPerCu || kShort) {
-    typedef BwdCfg<DQK, DV, NORM, CAUSAL, OUT, BIAS> C;
-    static_assert(C::OWN == kOwn, "");
-    if (!pair) hipLaunchKernelGGL(attn_bwd_kernel<C>, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p, dt);
-  }
-  if constexpr (!kTwoPerCu || BIAS) {
-    typedef BwdPairCfg<DQK, DV, NORM, CAUSAL, OUT, BIAS> C;
-    static_assert(C::OWN == kOwn, "");
-    if (pair) hipLaunchKernelGGL(attn_bwd_pair_kernel<C>, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p, dt);
-  }
+template <class C>
+hipError_t launch_side(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
+  const int64_t grid = side_blocks(p, C::KV_SIDE);
+  if (grid < 1 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(attn_bwd_kernel<C>, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p, dt);
+  return hipGetLastError();
+}
+template <class K, class Q>
+hipError_t launch_both(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
+  static_assert(K::KV_SIDE && !Q::KV_SIDE && K::OWN == 128 && Q::OWN == 128, "");
+  const int64_t key = side_blocks(p, true), query = side_blocks(p, false);
+  if (key < 1 || query < 1 || key + query > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((attn_bwd_both_kernel<K, Q>), dim3((unsigned)(key + query)), dim3(BwdBoth<K, Q>::THREADS), 0, s, p, dt, (int)key);
   return hipGetLastError();
 }
 
+template <class K, class Q>
+hipError_t launch_sides(const BwdParams& p, const DecayTable& dt, hipStream_t s, bool both) {
+  if (both) return launch_both<K, Q>(p, dt, s);
+  const hipError_t e = launch_side<K>(p, dt, s);
+  return e != hipSuccess ? e : launch_side<Q>(p, dt, s);
+}
+
+template <int DQK, int DV, int NORM, bool CAUSAL, bool BIAS>
+hipError_t launch_kernels(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
+  typedef BwdCfg<DQK, DV, NORM, CAUSAL, BWD_DKV, BIAS> K1;
+  typedef BwdCfg<DQK, DV, NORM, CAUSAL, BWD_DQ, BIAS> Q1;
+  typedef BwdPairCfg<DQK, DV, NORM, CAUSAL, BWD_DKV, BIAS> K2;
+  typedef BwdPairCfg<DQK, DV, NORM, CAUSAL, BWD_DQ, BIAS> Q2;
+  const int64_t key_wgs = side_rounds(p) * side_per_group(p, true), workgroups = key_wgs + side_rounds(p) * side_per_group(p, false);  // per XCD
+  if constexpr (DQK == 64) {
+    if constexpr (BIAS) {
+      const int64_t walk = std::min((int64_t)p.L_q * p.g, (int64_t)p.L_k);
+      if (workgroups <= units_per_xcd(CAUSAL) && walk / (CAUSAL ? 2 : 1) >= kLongBiasWalk) return launch_both<K2, Q2>(p, dt, s);
+    }
+    return launch_both<K1, Q1>(p, dt, s);
+  } else {
+    auto is_short = [&](int64_t rows, int64_t heads) {
+      const int64_t window = p.window < rows ? p.window : 0;
+      return window ? window * heads <= short_window(DV) : rows * heads <= short_walk(DV);
+    };
+    if constexpr (DQK == 128 && DV == 128 && !BIAS) {
+      const bool short_key = CAUSAL && is_short(p.L_q, p.g);
+      const bool both = CAUSAL ? key_wgs <= (p.g == 1 ? 48 : 32) : key_wgs <= 24 || workgroups <= 64;
+      if constexpr (CAUSAL)
+        if (short_key) return launch_sides<K1, Q1>(p, dt, s, both);
+      return launch_sides<K2, Q1>(p, dt, s, both);
+    } else {
+      if constexpr (CAUSAL && (!BIAS || DQK == 128))
+        if (is_short(p.L_q, p.g) && is_short(p.L_k, 1)) return launch_both<K1, Q1>(p, dt, s);
+      if constexpr (K2::ABS && DV == 256) return launch_sides<K2, Q2>(p, dt, s, workgroups <= 96);
+      else return launch_both<K2, Q2>(p, dt, s);
+    }
+  }
+}
+
 template <int DQK, int DV, int NORM, bool CAUSAL>
-hipError_t launch_pair(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
+hipError_t launch_bias(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
   // the bias tensor comes with softmax, sigmoid and no normalization, and not with head dims 128/256
   constexpr bool kBiasBuilt = (NORM == NORM_SOFTMAX || NORM == NORM_SIGMOID || NORM == NORM_NONE) && !(DQK == 128 && DV == 256);
   if (p.bias != nullptr) {
-    if constexpr (kBiasBuilt) {
-      const hipError_t e = launch_one<DQK, DV, NORM, CAUSAL, BWD_DKV, true>(p, dt, s);
-      if (e != hipSuccess) return e;
-      return launch_one<DQK, DV, NORM, CAUSAL, BWD_DQ, true>(p, dt, s);
-    } else {
-      return hipErrorInvalidValue;
-    }
+    if constexpr (kBiasBuilt) return launch_kernels<DQK, DV, NORM, CAUSAL, true>(p, dt, s);
+    else return hipErrorInvalidValue;
   }
-  const hipError_t e = launch_one<DQK, DV, NORM, CAUSAL, BWD_DKV, false>(p, dt, s);
-  if (e != hipSuccess) return e;
-  return launch_one<DQK, DV, NORM, CAUSAL, BWD_DQ, false>(p, dt, s);
+  return launch_kernels<DQK, DV, NORM, CAUSAL, false>(p, dt, s);
 }
 
 template <int DQK, int DV, int NORM>
 hipError_t launch_norm(const BwdParams& p, const DecayTable& dt, int causal, hipStream_t s) {
-  return causal ? launch_pair<DQK, DV, NORM, true>(p, dt, s) : launch_pair<DQK, DV, NORM, false>(p, dt, s);
+  return causal ? launch_bias<DQK, DV, NORM, true>(p, dt, s) : launch_bias<DQK, DV, NORM, false>(p, dt, s);
 }
 
 template <int DQK, int DV>

@@ -162,6 +162,28 @@ def test_backward_sliding_window(A, window, Lq, Lk):
                          norm="sigmoid", score_mod="bias", bias=-1.0))
 
 
+@pytest.mark.parametrize("dims,kw", [((128, 128), dict(mask="causal")), ((128, 128), dict(mask="sliding_window", window=64)), ((128, 128), dict()),
+                                     ((64, 64), dict(mask="causal")), ((192, 128), dict(mask="causal")),
+                                     ((128, 256), dict(score_mod="head_decay", norm="abssum", mask="causal", decay=True))],
+                         ids=["d128_causal", "d128_window", "d128", "d64", "d192", "d128_256_abssum"])
+def test_backward_batch_entries_do_not_depend_on_the_launches(A, dims, kw):
+    # seven batch entries at once, where some head dims take a launch for each side, and one at a time, where both sides
+    # share one: the same values
+    w = Workload("launches", 47, 7, 8, 8, 1000, 1030, dims[0], dims[1], **kw)
+    dev = torch.device("cuda:0")
+    Q, K, V = (t.to(dev) for t in make_inputs(w))
+    dO = make_grad(w).to(dev)
+    stats = torch.empty((w.B, w.H_q, w.L_q), dtype=torch.float32, device=dev)
+    O = A.run_workload(w, Q, K, V, stats=stats)
+    args = dict(scale=w.scale_value, score_mod=w.score_mod, bias=w.bias, gamma=w.gamma(), norm=w.norm, mask=w.mask, window=w.window)
+    whole = A.attention_backward(Q, K, V, O, dO, stats, **args)
+    for b in range(w.B):
+        part = A.attention_backward(*(t[b:b + 1].contiguous() for t in (Q, K, V, O, dO, stats)), **args)
+        torch.cuda.synchronize()
+        for x, y in zip(whole, part):
+            assert torch.equal(x[b:b + 1], y)
+
+
 def test_backward_more_heads_than_the_decay_table(A):
     # handles without a per-head decay may have more query heads than the decay table holds (256): the kernels of
     # the linear normalizations must not read the table then
