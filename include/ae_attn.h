@@ -136,7 +136,7 @@ typedef struct {
  * no device.  Supported head dims (D_qk/D_v): 64/64, 128/128, 128/256, 192/128;
  * and, for the retention variants only (HEAD_DECAY with ABSSUM, ABS_OF_SUM or
  * NONE, CAUSAL; Table 2, "Retention Parallel"): 256/128 and 256/512, the latter
- * evaluated as four launches over 128 value columns each (no split keys).
+ * without split keys.
  * Supported (score_mod, norm) pairs: NONE or BIAS with every norm;
  * HEAD_DECAY with ABSSUM, ABS_OF_SUM or NONE (CAUSAL mask only); RELU with NONE.
  * AE_MASK_SLIDING_WINDOW: score_mod NONE or BIAS with SOFTMAX, SIGMOID or NONE.

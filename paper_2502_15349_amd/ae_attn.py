@@ -407,7 +407,9 @@ def attention_backward(Q, K, V, O, dO, stats, *, scale, score_mod="none", bias=0
             if bias_tensor is not None:
                 ld = (L_k + 3) // 4 * 4
                 if want_dbias:
-                    dB = torch.zeros((B, H_q, L_q, ld), dtype=torch.bfloat16, device=Q.device)
+                    # (unmasked, every entry is written: clearing it first cost 9 of 72 us at 2 x 12 x 1023 x 1201)
+                    make = torch.empty if mask == "none" else torch.zeros
+                    dB = make((B, H_q, L_q, ld), dtype=torch.bfloat16, device=Q.device)
                 ae_attn_backward_bias(h, Q.data_ptr(), K.data_ptr(), V.data_ptr(), bias_tensor.data_ptr(), *tail[:6],
                                       0 if dB is None else dB.data_ptr(), ld, *tail[6:])
             else:

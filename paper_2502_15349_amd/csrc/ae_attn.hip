@@ -38,7 +38,7 @@ ae_status_t fail(ae_status_t code, const char* fmt, ...) {
 
 const ae::KernelEntry* find_kernel(int dqk, int dv, int norm, int mod, int mask, int fold) {
   typedef const ae::KernelEntry* (*table_fn)(int*);
-  static const table_fn tables[] = {ae::table_64_64, ae::table_128_128, ae::table_128_256, ae::table_192_128, ae::table_256_128};
+  static const table_fn tables[] = {ae::table_64_64, ae::table_128_128, ae::table_128_256, ae::table_192_128, ae::table_256_128, ae::table_256_512};
   for (table_fn tf : tables) {
     int n = 0;
     const ae::KernelEntry* t = tf(&n);
@@ -181,10 +181,6 @@ struct ae_attn {
   ae::DecayTable decay;
   int grid;
   size_t ws_bytes;  // workspace the split-key forward needs (0: keys are not split)
-  // D_v = 512 (Table 2, "Retention Parallel" 256 / 512): the output accumulators of 512 columns do not fit the
-  // register file beside the 256-wide query fragments, so the forward pass is v_slices launches of the 256 / 128
-  // kernel, each over 128 columns of V and O (the scores and the row normalizer are the same in every launch)
-  int v_slices;
   // One query row per head, softmax, every key visible (a decoding step): the keys, split or not, are walked by the
   // streaming kernel of attn_decode.hip instead of the 256-row attention kernel (unsplit 1.9 times as fast on the average of 238
   // shapes of 17 to 16k keys and 1 to 4096 q heads; of these 17 x 16 heads x 16384, 64/64, and 17 x 8/1 x 16384, 128/128, were slower,
@@ -251,10 +247,9 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
   // Larger scales keep the scale in fp32 on the scores.
   const bool fold = (d->norm == AE_NORM_SOFTMAX || d->norm == AE_NORM_SIGMOID) && mod == ae::MOD_PLAIN &&
                     std::fabs(d->scale) * std::sqrt((float)d->D_qk) <= 2.f;
-  const int v_slices = d->D_v == 512 ? 4 : 1;
-  if (v_slices > 1 && d->kv_splits > 1) return fail(AE_ERR_UNSUPPORTED, "ae_attn_create: D_v = 512 comes without split keys");
-  const ae::KernelEntry* k = find_kernel(d->D_qk, d->D_v / v_slices, (int)d->norm, mod, (int)d->mask, fold ? 1 : 0);
-  if (!k && fold) k = find_kernel(d->D_qk, d->D_v / v_slices, (int)d->norm, mod, (int)d->mask, 0);
+  if (d->D_v == 512 && d->kv_splits > 1) return fail(AE_ERR_UNSUPPORTED, "ae_attn_create: D_v = 512 comes without split keys");
+  const ae::KernelEntry* k = find_kernel(d->D_qk, d->D_v, (int)d->norm, mod, (int)d->mask, fold ? 1 : 0);
+  if (!k && fold) k = find_kernel(d->D_qk, d->D_v, (int)d->norm, mod, (int)d->mask, 0);
   if (!k)
     return fail(AE_ERR_UNSUPPORTED, "ae_attn_create: no kernel for score_mod %d with norm %d and mask %d",
                 (int)d->score_mod, (int)d->norm, (int)d->mask);
@@ -265,7 +260,6 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
   h->desc = *d;
   h->desc.gamma = nullptr;  // the caller's array is not kept
   h->kernel = k;
-  h->v_slices = v_slices;
 
   ae::Params& p = h->params;
   p.B = d->B; p.H_q = d->H_q; p.H_kv = d->H_kv; p.L_q = d->L_q; p.L_k = d->L_k;
@@ -364,7 +358,7 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
   h->ws_bytes = 0;
   int kv_splits = d->kv_splits;
   h->decode = d->L_q == 1 && d->norm == AE_NORM_SOFTMAX && mod == ae::MOD_PLAIN && d->mask != AE_MASK_SLIDING_WINDOW &&
-              v_slices == 1 && ae::decode_supported(d->D_qk, d->D_v);
+              ae::decode_supported(d->D_qk, d->D_v);
   if (kv_splits == AE_KV_SPLITS_AUTO && h->decode) {
     // Measured on the decoding row of Table 2 (16 heads, batch 1 and 8, 2k-8k keys): fastest with 128-256
     // workgroups (8 ranges at batch 1, 2 at batch 8) -- every workgroup pays the latency of its first loads and of
@@ -379,7 +373,7 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
     // ranges cost a start and an end of a workgroup apiece.  Only where the keys may be split
     // and the query tiles alone leave most of the device idle.
     kv_splits = 0;
-    if (d->norm == AE_NORM_SOFTMAX && d->mask != AE_MASK_SLIDING_WINDOW && mod != ae::MOD_BIAS_T && v_slices == 1 && grid < 160) {
+    if (d->norm == AE_NORM_SOFTMAX && d->mask != AE_MASK_SLIDING_WINDOW && mod != ae::MOD_BIAS_T && grid < 160) {
       const int key_tiles = (d->L_k + h->kernel->block_n - 1) / h->kernel->block_n;
       const int64_t want = (192 + grid / 2) / grid;  // round(192 / workgroups)
       kv_splits = (int)std::min<int64_t>(std::min<int64_t>(want, key_tiles / 8), 256);
@@ -476,13 +470,7 @@ static ae_status_t forward_impl(const ae_attn_t* h, const void* Q, const void* K
     q.bias = h->desc.score_mod == AE_MOD_BIAS ? h->desc.bias : 0.f;
     e = ae::launch_decode(q, h->desc.D_qk, h->desc.D_v, static_cast<hipStream_t>(stream));
   }
-  for (int sl = 0; sl < h->v_slices && e == hipSuccess && !decode; ++sl) {
-    if (sl > 0) {  // the next 128 columns of V and O
-      p.V += h->kernel->dv;
-      p.O = static_cast<char*>(p.O) + (size_t)h->kernel->dv * (p.out_bf16 ? 2 : 4);
-    }
-    e = h->kernel->launch(p, h->decay, h->grid, static_cast<hipStream_t>(stream));
-  }
+  if (!decode) e = h->kernel->launch(p, h->decay, h->grid, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(AE_ERR_HIP, "ae_attn_forward: launch failed: %s", hipGetErrorString(e));
   if (p.n_splits > 1) {
     MergeParams m;

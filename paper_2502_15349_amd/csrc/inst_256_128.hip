@@ -1,5 +1,4 @@
-// Kernel instantiations for D_qk = 256, D_v = 128: the retention variants (Table 2, "Retention Parallel": 256 / 512,
-// whose D_v = 512 runs as four launches over 128 value columns each, see ae_attn_create).
+// Kernel instantiations for D_qk = 256, D_v = 128: the retention variants.
 #include "dispatch.hpp"
 
 namespace ae {

@@ -36,7 +36,7 @@ import time
 SQ_COUNTERS = ["SQ_VALU_MFMA_BUSY_CYCLES", "SQ_BUSY_CU_CYCLES", "SQ_INSTS_VALU_MFMA_MOPS_BF16", "GRBM_GUI_ACTIVE",
                "SQ_LDS_BANK_CONFLICT", "SQ_LDS_IDX_ACTIVE", "SQ_INSTS_LDS", "SQ_INSTS_VALU"]
 # kernels of this library (everything else in a trace -- torch's fills and copies -- is listed but not analysed)
-OURS = ("attn_fwd_kernel", "attn_bwd_kernel", "attn_bwd_both_kernel", "attn_bwd_delta_kernel", "attn_decode_kernel", "attn_merge_kernel",
+OURS = ("attn_fwd_kernel", "attn_fwd_wide_kernel", "attn_bwd_kernel", "attn_bwd_both_kernel", "attn_bwd_delta_kernel", "attn_decode_kernel", "attn_merge_kernel",
         "rec_state_kernel", "rec_step_kernel", "rec_scan_kernel", "rec_fused_kernel", "gated_", "calib_mfma_kernel")
 N_XCD, N_SIMD = 8, 1024
 GIB = 1 << 30

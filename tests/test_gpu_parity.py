@@ -96,8 +96,7 @@ def test_small_ragged_all_variants(A, dims, variant):
 @pytest.mark.parametrize("variant", ["retnet_abssum", "retnet_abs_of_sum", "decay_nonorm"])
 @pytest.mark.parametrize("Lq,Lk", [(300, 333), (1, 1), (513, 513), (700, 40)])
 def test_retention_head_dims_256(A, dv, variant, Lq, Lk):
-    """Table 2's "Retention Parallel" head dims, D_qk = 256 with D_v = 512 (four launches over 128 value columns
-    each) and D_v = 128 (one): ragged shapes, more queries than keys, grouped heads."""
+    """Table 2's "Retention Parallel" head dims, D_qk = 256 with D_v = 512 and D_v = 128: ragged shapes, more queries than keys, grouped heads."""
     kw = dict(VARIANTS[variant])
     w = Workload(variant, 21, 2, 4, 2, Lq, Lk, 256, dv, **kw)
     Q, K, V = make_inputs(w)
@@ -107,6 +106,38 @@ def test_retention_head_dims_256(A, dv, variant, Lq, Lk):
         rs = np.maximum(np.abs(ref).max(axis=-1, keepdims=True), 1.0)
         got, ref = got / rs, ref / rs
     check(got, ref, f"{variant} 256/{dv}")
+
+
+@pytest.mark.parametrize("Lq,Lk", [(31, 31), (32, 33), (64, 64), (65, 96), (127, 129), (128, 160), (129, 31), (257, 385), (190, 1100)])
+@pytest.mark.parametrize("kw", [dict(norm="abssum"), dict(norm="abssum", scale=-0.2), dict(norm="none", scale=0.01)], ids=["abssum", "negative_scale", "none"])
+def test_retention_512_value_columns(A, Lq, Lk, kw):
+    """256 / 512 at the edges of its tiles (128 query rows in two groups, 32 keys, three tiles in flight), grouped heads, a head
+    that forgets within a tile beside slow ones, bf16 output, and the row statistic."""
+    w = Workload("wide", 24, 1, 4, 2, Lq, Lk, 256, 512, score_mod="head_decay", mask="causal", decay=True, **kw)
+    Q, K, V = make_inputs(w)
+    gamma = [0.03] + [1.0 - 2.0 ** (-4 - h) for h in range(3)]
+    dev = torch.device("cuda:0")
+    args = dict(scale=w.scale_value, score_mod="head_decay", gamma=gamma, norm=w.norm, mask="causal")
+    stats = torch.empty((1, 4, Lq), dtype=torch.float32, device=dev)
+    Qd, Kd, Vd = Q.to(dev), K.to(dev), V.to(dev)
+    O = A.attention_forward(Qd, Kd, Vd, stats=stats if w.norm == "abssum" else None, **args)
+    rounded = A.attention_forward(Qd, Kd, Vd, out_dtype=torch.bfloat16, **args)
+    torch.cuda.synchronize()
+    assert torch.equal(rounded, O.to(torch.bfloat16))
+    ref = attention(Q, K, V, scale=w.scale_value, score_mod="head_decay", gamma=gamma, norm=w.norm, mask="causal")
+    # the bar of the other retention tests: relative to max(1, the row's largest value), because a row is a sum of weights that carry
+    # 2^-9 of themselves each (one or two keys of weight and values of up to 4 give 4 x 2^-9 = 0.8e-2 and more)
+    rs = np.maximum(np.abs(ref).max(axis=-1, keepdims=True), 1.0)
+    check(O.cpu().double().numpy() / rs, ref / rs, f"256/512 {kw} Lq={Lq} Lk={Lk}")
+    if w.norm == "abssum":
+        d = torch.arange(Lq).view(-1, 1) + (Lk - Lq) - torch.arange(Lk).view(1, -1)
+        decay = torch.tensor([float(np.float32(g)) for g in gamma], dtype=torch.float64).view(-1, 1, 1) ** d.clamp(min=0)
+        S = w.scale_value * torch.einsum("hqd,hkd->hqk", Q[0].double(), K[0].double().repeat_interleave(2, dim=0)) * decay * (d >= 0)
+        r = S.abs().sum(dim=-1)
+        # products of bf16 numbers summed over 256 and over the keys in 32 bits, the decay's exponent too: 2^-24 x (256 + Lk) at worst,
+        # and 2^-24 x the exponent (some -5 per key of distance, weighted by what is left at that distance: at most 1 / e of it)
+        bound = 2.0 ** -23 * (256 + Lk + 64) * (r + 1.0)
+        assert ((stats[0].cpu().double() - r).abs() <= bound).all()
 
 
 @pytest.mark.parametrize("Lq,Lk", [(1, 1), (1, 77), (77, 1), (64, 64), (257, 255), (40, 700), (700, 40), (513, 513)])
