@@ -334,12 +334,20 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
   // whose workgroups fill the XCD's 32 CUs on their own runs best with 1-2 groups
   // walked together, smaller groups with 8 (more K/V streams spread the reads
   // over more L2 channels).
-  const int64_t per_group = (int64_t)p.n_qtiles * p.g;
-  const int64_t rounds = (p.n_groups + 7) / 8;  // groups per XCD
+  p.cut = ae::group_cut(p.n_groups);
+  if (p.cut > 0) {
+    // Not where an XCD has no more than 8 workgroups anyway (1 x 6 heads x 300 16.5 us, cut 16.8); nor, with workgroups of one length,
+    // where its 32 compute units take as many rounds, two or more, either way (1 x 12 x 6000, 128/256, unmasked 385 us, cut 392).
+    const int64_t whole = ((int64_t)p.n_groups + 7) / 8 * p.n_qtiles * p.g, part = (((int64_t)p.n_qtiles * p.g + (1 << p.cut) - 1) >> p.cut);
+    const int64_t whole_rounds = (whole + 31) / 32, cut_rounds = (((int64_t)p.n_groups << p.cut) / 8 * part + 31) / 32;
+    if (whole <= 8 || (d->mask == AE_MASK_NONE && whole_rounds > 1 && cut_rounds >= whole_rounds)) p.cut = 0;
+  }
+  const int64_t per_group = ((int64_t)p.n_qtiles * p.g + (1 << p.cut) - 1) >> p.cut;  // (or part of a group)
+  const int64_t rounds = (((int64_t)p.n_groups << p.cut) + 7) / 8;                      // groups, or parts, per XCD
 #ifdef AE_TUNE_INTERLEAVE  // build-time knob of the mapping sweeps, like the AE_SHAPE_* entries of the tile table
   int interleave = AE_TUNE_INTERLEAVE;
 #else
-  int interleave = per_group >= 32 ? 2 : 8;
+  int interleave = (per_group >= 32 ? 2 : 8) << p.cut;
 #endif
   if (interleave < 1) interleave = 1;
   if (interleave > rounds) interleave = (int)rounds;
@@ -654,8 +662,12 @@ static ae_status_t backward_impl(const ae_attn_t* h, const void* Q, const void* 
   // put a workgroup on every compute unit of the XCD, though, and with a causal mask four at least, so that the
   // last set to run -- heaviest workgroups first within a set -- is a small part of the grid.
   {
-    const int64_t tiles_q = (d.L_q + 127) / 128 * (int64_t)p.g, tiles_kv = (d.L_k + 127) / 128;
-    const int64_t rounds = ((int64_t)d.B * d.H_kv + 7) / 8;
+    p.cut = ae::group_cut((int64_t)d.B * d.H_kv);
+    // (a bias tensor, unmasked, more than a round of workgroups: 1 x 12 heads x 3000 244 us, cut 253; of one round 1 x 12 x 2000 93 / 87)
+    if (p.bias && d.mask == AE_MASK_NONE && ((int64_t)d.B * d.H_kv + 7) / 8 * ((d.L_q + 127) / 128 * p.g + (d.L_k + 127) / 128) > 64) p.cut = 0;
+    auto part = [&](int64_t n) { return (n + (1 << p.cut) - 1) >> p.cut; };
+    const int64_t tiles_q = part((d.L_q + 127) / 128 * (int64_t)p.g), tiles_kv = part((d.L_k + 127) / 128);
+    const int64_t rounds = (((int64_t)d.B * d.H_kv << p.cut) + 7) / 8;
 #ifdef AE_TUNE_BWD_TOGETHER_Q  // build-time knobs of the mapping sweeps
     int64_t tq = AE_TUNE_BWD_TOGETHER_Q, tk = AE_TUNE_BWD_TOGETHER_KV;
 #else

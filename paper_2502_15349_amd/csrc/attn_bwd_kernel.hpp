@@ -69,9 +69,10 @@ struct BwdParams {
   // the handle has a per-head decay: only then is the decay table read (it holds AE_MAX_DECAY_HEADS entries, and
   // handles without decay may have more heads than that)
   int has_decay;
-  // (batch, k/v head) groups that one XCD walks together, per kernel ([0]: query side, [1]: key side); see the
+  // (batch, k/v head) groups, or parts of groups, that one XCD walks together, per kernel ([0]: query side, [1]: key side); see the
   // mapping at the top of bwd_single_walk
   int together[2];
+  int cut;  // a group's workgroups go to 2^cut XCDs in turn (see group_cut)
 };
 
 // Chunk swizzle of the backward tiles.  A tile row is read both ways -- 128-bit row
@@ -160,13 +161,8 @@ __device__ __forceinline__ void bwd_single_walk(const BwdParams& p, const DecayT
   // there at the same time, `together` groups side by side: they stream the same rows of the other side a few
   // tiles apart, so a tile that one of them pulled into L2 serves the others.  Within a set of groups the
   // workgroups with most work come first (causal).  The grid is padded to whole sets; the surplus exits here.
-  const int n_groups = p.B * p.H_kv;
-  const int per_group = C::KV_SIDE ? n_own_tiles : n_own_tiles * p.g;
-  const int tg = p.together[C::KV_SIDE ? 1 : 0];
-  const int xcd = block & 7, slot = block >> 3;
-  const int set = slot / (tg * per_group), within = slot % (tg * per_group);
-  const int item = within / tg, group = (set * tg + within % tg) * 8 + xcd;
-  if (group >= n_groups) return;
+  int group, item;
+  if (!place_in_group(block, p.B * p.H_kv, C::KV_SIDE ? n_own_tiles : n_own_tiles * p.g, p.together[C::KV_SIDE ? 1 : 0], p.cut, group, item)) return;
   const int b = group / p.H_kv, hk = group % p.H_kv;
   int ot = C::KV_SIDE ? item : n_own_tiles - 1 - item / p.g;
   const int ho = C::KV_SIDE ? hk : hk * p.g + item % p.g;  // ho: k/v head (key side) or q head (query side)
@@ -649,13 +645,8 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
   const int L_own = C::KV_SIDE ? p.L_k : p.L_q, L_oth = C::KV_SIDE ? p.L_q : p.L_k;
 
   const int n_own_tiles = (L_own + C::OWN - 1) / C::OWN;
-  const int n_groups = p.B * p.H_kv;
-  const int per_group = C::KV_SIDE ? n_own_tiles : n_own_tiles * p.g;
-  const int tg = p.together[C::KV_SIDE ? 1 : 0];
-  const int xcd = block & 7, slot = block >> 3;
-  const int set = slot / (tg * per_group), within = slot % (tg * per_group);
-  const int item = within / tg, group = (set * tg + within % tg) * 8 + xcd;
-  if (group >= n_groups) return;
+  int group, item;
+  if (!place_in_group(block, p.B * p.H_kv, C::KV_SIDE ? n_own_tiles : n_own_tiles * p.g, p.together[C::KV_SIDE ? 1 : 0], p.cut, group, item)) return;
   const int b = group / p.H_kv, hk = group % p.H_kv;
   const int ot = C::KV_SIDE ? item : n_own_tiles - 1 - item / p.g;
   const int ho = C::KV_SIDE ? hk : hk * p.g + item % p.g;  // ho: k/v head (key side) or q head (query side)

@@ -72,7 +72,8 @@ struct Params {
   int g;           // H_q / H_kv
   int n_qtiles;    // ceil(L_q / BLOCK_M)
   int n_groups;    // B * H_kv
-  int interleave;  // (batch, kv head) groups walked together on one XCD
+  int interleave;  // (batch, kv head) groups, or parts of groups, walked together on one XCD
+  int cut;         // a group's workgroups go to 2^cut XCDs in turn (see group_cut)
   int64_t qs[3], ks[3], vs[3], os[3];  // element strides {batch, head, row}
   float c;         // |scale| * log2(e)  (softmax, sigmoid)  or |scale| (others)
   float b2;        // bias * log2(e)     (softmax, sigmoid)  or bias (others)
@@ -97,6 +98,19 @@ struct Params {
 struct DecayTable {
   float log2_gamma[kMaxDecayHeads];
 };
+
+// The workgroups of a (batch, kv head) group go to one XCD, for the sake of its L2; where the number of groups is not a multiple
+// of the 8 XCDs that leaves some of them a group short (6 groups: two idle; 12: four with half the work).  Then the groups are cut into
+// 2, 4 or 8 parts, the fewest that come out even: log2 of that number.  From 15 % of imbalance on: what it costs is K and V read
+// by several XCDs.  Whole groups / parts (us), causal: 1 x 12 heads x 4096 128/128 82 / 75, backward 279 / 224; 1 x 12 x 8192 192/128 271 / 228; 1 x 6
+// x 8192 152 / 138, backward 523 / 417; 1 x 24/6 x 4096 120 / 98; 2 x 24/6 x 2000 192/128 backward 328 / 292; 1 x 1 x 8192 backward 491 / 238.  At 12 %
+// (5 x 10 heads) 98 / 108 backward.
+inline int group_cut(int64_t n_groups) {
+  int cut = 0;
+  if ((n_groups + 7) / 8 * 8 * 20 >= n_groups * 23)
+    while ((n_groups << cut) % 8 != 0) ++cut;
+  return cut;
+}
 
 // MASK_: 0 none, 1 causal, 2 causal with a sliding window (Params::window keys per query)
 // FOLD_ (softmax and sigmoid without a bias tensor): the exponent comes out of the scoring MFMA ready to use.
@@ -885,6 +899,19 @@ struct KeyLoop {
   }
 };
 
+// Workgroup w -> group and its place in the group's work.  w % 8 is its XCD; `together` groups, or parts of a group, are walked side
+// by side there; a part takes one place of every 2^cut, another one each time (causal places get lighter).  False: a surplus
+// workgroup of the padded grid.
+__device__ __forceinline__ bool place_in_group(int w, int n_groups, int per_group, int together, int cut, int& group, int& place) {
+  const int per_part = (per_group + (1 << cut) - 1) >> cut, slot = w >> 3;
+  const int blk = slot / (together * per_part), r_in = slot % (together * per_part);
+  const int part = (blk * together + r_in % together) * 8 + (w & 7);
+  group = part >> cut;
+  const int turn = r_in / together;
+  place = (turn << cut) + ((part + (part >> 3) + turn) & ((1 << cut) - 1));
+  return group < n_groups && place < per_group;
+}
+
 template <class C>
 __global__ __launch_bounds__(C::THREADS) void attn_fwd_kernel(const Params p, const DecayTable dt) {
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
@@ -902,13 +929,8 @@ __global__ __launch_bounds__(C::THREADS) void attn_fwd_kernel(const Params p, co
     split = w / p.base_grid;
     w -= split * p.base_grid;
   }
-  const int per_group = p.n_qtiles * p.g;
-  const int I = p.interleave;
-  const int slot = w >> 3;
-  const int blk = slot / (I * per_group), r_in = slot % (I * per_group);
-  const int group = (blk * I + (r_in % I)) * 8 + (w & 7);
-  if (group >= p.n_groups) return;
-  const int t_in = r_in / I;
+  int group, t_in;
+  if (!place_in_group(w, p.n_groups, p.n_qtiles * p.g, p.interleave, p.cut, group, t_in)) return;
   const int b = group / p.H_kv, hkv = group % p.H_kv;
   const int hq = hkv * p.g + (t_in % p.g);
   const int qt_lin = t_in / p.g;

@@ -38,11 +38,12 @@ constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
 //     461 / 506, 2 x 12 x 2048 (48) 221 / 252.
 //   * 128/256, abs-sum family: as one kernel it spills 26 registers instead of 9.  2 x 16 x 1024 (64 workgroups of both sides per XCD)
 //     117 / 91, 1 x 24/6 x 2048 (80) 480 / 422, 2 x 16 x 2048 (128) 254 / 263, 4 x 16 x 2048 (256) 511 / 533.
-// The workgroups of a side: whole sets of `together` groups per XCD (the kernels' mapping): sets x together x 8 XCDs x
-// workgroups per group.
-inline int64_t side_rounds(const BwdParams& p) { return ((int64_t)p.B * p.H_kv + 7) / 8; }
+// The workgroups of a side: whole sets of `together` groups (or parts of groups) per XCD (the kernels' mapping): sets x together x
+// 8 XCDs x workgroups per group or part.
+inline int64_t side_rounds(const BwdParams& p) { return (((int64_t)p.B * p.H_kv << p.cut) + 7) / 8; }
 inline int64_t side_per_group(const BwdParams& p, bool key_side) {
-  return (int64_t)(((key_side ? p.L_k : p.L_q) + 127) / 128) * (key_side ? 1 : p.g);  // (all kernels own 128 rows per workgroup)
+  const int64_t n = (int64_t)(((key_side ? p.L_k : p.L_q) + 127) / 128) * (key_side ? 1 : p.g);  // (all kernels own 128 rows per workgroup)
+  return (n + (1 << p.cut) - 1) >> p.cut;
 }
 inline int64_t side_blocks(const BwdParams& p, bool key_side) {
   const int64_t tg = p.together[key_side ? 1 : 0];

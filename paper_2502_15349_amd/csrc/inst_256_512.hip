@@ -44,11 +44,9 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_fwd_wide_kernel(const Para
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
   // workgroup -> (batch, kv head, q head, q tile): as in attn_fwd_kernel
-  const int w = blockIdx.x, per_group = p.n_qtiles * p.g, I = p.interleave, slot = w >> 3;
-  const int blk = slot / (I * per_group), r_in = slot % (I * per_group);
-  const int group = (blk * I + (r_in % I)) * 8 + (w & 7);
-  if (group >= p.n_groups) return;
-  const int t_in = r_in / I, b = group / p.H_kv, hkv = group % p.H_kv;
+  int group, t_in;
+  if (!place_in_group(blockIdx.x, p.n_groups, p.n_qtiles * p.g, p.interleave, p.cut, group, t_in)) return;
+  const int b = group / p.H_kv, hkv = group % p.H_kv;
   const int hq = hkv * p.g + (t_in % p.g), qtile = p.n_qtiles - 1 - t_in / p.g;
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

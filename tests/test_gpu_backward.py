@@ -184,6 +184,27 @@ def test_backward_batch_entries_do_not_depend_on_the_launches(A, dims, kw):
             assert torch.equal(x[b:b + 1], y)
 
 
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("mask", ["none", "causal"])
+@pytest.mark.parametrize("n", [1, 2, 3, 6])
+def test_heads_do_not_depend_on_their_number(A, dims, mask, n):
+    # eight k/v heads, one per XCD, against the first n of them, whose workgroups are shared out over 8, 4, 8 and 4 XCDs: every
+    # workgroup is there once and the values are the same, forwards and backwards
+    w = Workload("heads", 48, 1, 16, 8, 1500, 1530, dims[0], dims[1], mask=mask)
+    dev = torch.device("cuda:0")
+    Q, K, V = (t.to(dev) for t in make_inputs(w))
+    dO = make_grad(w).to(dev)
+
+    def both(nq, nkv):
+        q, k, v, g = Q[:, :nq].contiguous(), K[:, :nkv].contiguous(), V[:, :nkv].contiguous(), dO[:, :nq].contiguous()
+        stats = torch.empty((1, nq, w.L_q), dtype=torch.float32, device=dev)
+        O = A.attention_forward(q, k, v, stats=stats, scale=w.scale_value, mask=mask)
+        return (O, stats) + tuple(A.attention_backward(q, k, v, O, g, stats, scale=w.scale_value, mask=mask))
+
+    for x, y in zip(both(2 * n, n), both(16, 8)):
+        assert torch.equal(x, y[:, :x.shape[1]])
+
+
 def test_backward_more_heads_than_the_decay_table(A):
     # handles without a per-head decay may have more query heads than the decay table holds (256): the kernels of
     # the linear normalizations must not read the table then
