@@ -29,13 +29,15 @@ constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
 // Both sides go in one launch (the key side's workgroups first): two launches / one, us, causal unless said: 64/64 1 x 16 heads x
 // 1024 54 / 34, 1 x 16 x 4096 186 / 140, 4 x 32/8 x 2048 335 / 289, 8 x 16 x 2048 unmasked 506 / 510, with a bias tensor 2 x 12 x 1023 x 1201
 // 85 / 68; 192/128 1 x 16 x 500 53 / 33, 1 x 6 x 4096 259 / 172, 1 x 128 x 4096 2597 / 2607; 128/256 2 x 16 x 1024 100 / 74, 4 x 16 x
-// 2048 438 / 433.  Two exceptions, where the two kernels do not fit the same mould:
+// 2048 438 / 433.  Three exceptions:
 //   * 128/128 without a bias tensor: beside the key side's workgroups those of the query side get a CU each, which they otherwise
 //     share by two.  It pays while the key side leaves compute units idle: few workgroups (of 32 compute units per XCD), or
 //     causal ones of unequal length.  Causal (workgroups of the key side per XCD): 1 x 16 x 1024 (16) 75 / 44, 1 x 32/8 x 4096 (32) 676 / 550,
 //     2 x 12 x 2048 (48) 139 / 127, but 8 x 24/6 x 1000 (48) 297 / 332, 8 x 12 x 700 (72) 104 / 109, 4 x 32/8 x 2048 (64) 552 / 597; unmasked
 //     1 x 32/8 x 2048 (16) 332 / 256, 2 x 32/8 x 1500 (24) 298 / 290, 1 x 16 x 2048 (32, 64 of both sides) 142 / 141, but 2 x 32/8 x 2048 (32)
 //     461 / 506, 2 x 12 x 2048 (48) 221 / 252.
+//   * 192/128, causal, very many workgroups: the end of one side among the start of the other costs more in the L2 than it fills (1 x
+//     128 heads x 8192, 2048 workgroups of both sides per XCD, 10.00 / 10.07 ms; 4096 2.60 / 2.60, 8 x 16 x 1024 unmasked 0.397 / 0.383).
 //   * 128/256, abs-sum family: as one kernel it spills 26 registers instead of 9.  2 x 16 x 1024 (64 workgroups of both sides per XCD)
 //     117 / 91, 1 x 24/6 x 2048 (80) 480 / 422, 2 x 16 x 2048 (128) 254 / 263, 4 x 16 x 2048 (256) 511 / 533.
 // The workgroups of a side: whole sets of `together` groups (or parts of groups) per XCD (the kernels' mapping): sets x together x
@@ -101,6 +103,7 @@ hipError_t launch_kernels(const BwdParams& p, const DecayTable& dt, hipStream_t 
       if constexpr (CAUSAL && (!BIAS || DQK == 128))
         if (is_short(p.L_q, p.g) && is_short(p.L_k, 1)) return launch_both<K1, Q1>(p, dt, s);
       if constexpr (K2::ABS && DV == 256) return launch_sides<K2, Q2>(p, dt, s, workgroups <= 96);
+      else if constexpr (DQK == 192 && CAUSAL) return launch_sides<K2, Q2>(p, dt, s, workgroups <= 1024);
       else return launch_both<K2, Q2>(p, dt, s);
     }
   }
@@ -117,22 +120,21 @@ hipError_t launch_bias(const BwdParams& p, const DecayTable& dt, hipStream_t s) 
   return launch_kernels<DQK, DV, NORM, CAUSAL, false>(p, dt, s);
 }
 
-template <int DQK, int DV, int NORM>
-hipError_t launch_norm(const BwdParams& p, const DecayTable& dt, int causal, hipStream_t s) {
-  return causal ? launch_bias<DQK, DV, NORM, true>(p, dt, s) : launch_bias<DQK, DV, NORM, false>(p, dt, s);
-}
-
-template <int DQK, int DV>
-hipError_t launch_dims(const BwdParams& p, const DecayTable& dt, int norm, int causal, hipStream_t s) {
+template <int DQK, int DV, bool CAUSAL>
+hipError_t launch_mask(const BwdParams& p, const DecayTable& dt, int norm, hipStream_t s) {
   switch (norm) {
-    case NORM_SOFTMAX: return launch_norm<DQK, DV, NORM_SOFTMAX>(p, dt, causal, s);
-    case NORM_SIGMOID: return launch_norm<DQK, DV, NORM_SIGMOID>(p, dt, causal, s);
-    case NORM_ABSSUM: return launch_norm<DQK, DV, NORM_ABSSUM>(p, dt, causal, s);
-    case NORM_ABS_OF_SUM: return launch_norm<DQK, DV, NORM_ABS_OF_SUM>(p, dt, causal, s);
-    case NORM_NONE: return launch_norm<DQK, DV, NORM_NONE>(p, dt, causal, s);
-    case BWD_NORM_NONE_RELU: return launch_norm<DQK, DV, BWD_NORM_NONE_RELU>(p, dt, causal, s);
+    case NORM_SOFTMAX: return launch_bias<DQK, DV, NORM_SOFTMAX, CAUSAL>(p, dt, s);
+    case NORM_SIGMOID: return launch_bias<DQK, DV, NORM_SIGMOID, CAUSAL>(p, dt, s);
+    case NORM_ABSSUM: return launch_bias<DQK, DV, NORM_ABSSUM, CAUSAL>(p, dt, s);
+    case NORM_ABS_OF_SUM: return launch_bias<DQK, DV, NORM_ABS_OF_SUM, CAUSAL>(p, dt, s);
+    case NORM_NONE: return launch_bias<DQK, DV, NORM_NONE, CAUSAL>(p, dt, s);
+    case BWD_NORM_NONE_RELU: return launch_bias<DQK, DV, BWD_NORM_NONE_RELU, CAUSAL>(p, dt, s);
   }
   return hipErrorInvalidValue;
+}
+template <int DQK, int DV>
+hipError_t launch_dims(const BwdParams& p, const DecayTable& dt, int norm, int causal, hipStream_t s) {
+  return causal ? launch_mask<DQK, DV, true>(p, dt, norm, s) : launch_mask<DQK, DV, false>(p, dt, norm, s);
 }
 
 }  // namespace
