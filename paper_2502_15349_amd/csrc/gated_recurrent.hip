@@ -212,12 +212,12 @@ __device__ __forceinline__ f32x16 block_scores(const uint32_t (&rq)[C::T], uint3
   for (int t = 0; t < C::T; ++t) s = mfma(read_k_frag(kt + rq[t]), read_k_frag(qt + rq[t]), s);
   return s;
 }
-// weights of the block: s_i e^{b_i - b_j} g_j (q_i . k_j) for key j <= query i (positions inside the chunk), else 0; inside a
+// weights of the block: scale e^{b_i - b_j} g_j (q_i . k_j) for key j <= query i (positions inside the chunk), else 0; inside a
 // diagonal block keys behind the lane's query (last_key) get weight 0
 template <class C>
-__device__ __forceinline__ void block_weights(const f32x16& sc, uint32_t gate, int lane, int kb, int qb, int last_key, uint32_t dst) {
+__device__ __forceinline__ void block_weights(const f32x16& sc, float scale, uint32_t gate, int lane, int kb, int qb, int last_key, uint32_t dst) {
   const int ln = lane & 31, half = lane >> 5;
-  const float bi = lds_read4(gate + (C::kB + 32 * qb + ln) * 4), si = lds_read4(gate + (C::kS + 32 * qb + ln) * 4);
+  const float bi = lds_read4(gate + (C::kB + 32 * qb + ln) * 4);
   float ref[4];
   f32x4 uj[4];
 #pragma unroll
@@ -229,7 +229,7 @@ __device__ __forceinline__ void block_weights(const f32x16& sc, uint32_t gate, i
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     // (groups past the lane's query have bi > ref: whatever the factor becomes there, the mask below discards it)
-    const float qfac = si * __expf(bi - ref[a]);
+    const float qfac = scale * __expf(bi - ref[a]);
     float x[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -293,7 +293,9 @@ struct TileCopy {
 // STATE_ONLY: no outputs, only the state update is walked (see GatedParams::state_only): no queries, no weights, one barrier
 // per chunk.
 // block: the workgroup's number among those of this walk; const_decay(h): the log-decay of head h where p.log_decay is null.
-template <class C, bool STATE_ONLY, class F>
+// OUT_GATE: output rows have a factor of their own (1 without GatedParams::gate_on_output).  Not a run-time test: that took 117 us
+// for 113 at 8 x 16 heads x 4096, 64/64, where there is none.
+template <class C, bool STATE_ONLY, bool OUT_GATE, class F>
 __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint32_t lds0, F&& const_decay) {
   using Y = GLayout<C, STATE_ONLY>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -368,10 +370,16 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
       for (int c = 0; c < n_chunks; ++c) {
         const uint32_t sb = stage_of(c);
         const int t0 = c * C::CH;
-        // ---- read-out of the state in front of the chunk: O^T = H^T Q^T, times s_i e^{b_i} ----
+        // ---- read-out of the state in front of the chunk: O^T = H^T Q^T, times scale e^{b_i} ----
         const float dec = lds_read4(gate + (C::kDec + (c & 1)) * 4);
-        const float f0 = lds_read4(gate + (C::kS + ln) * 4) * __expf(lds_read4(gate + (C::kB + ln) * 4));
-        const float f1 = lds_read4(gate + (C::kS + 32 + ln) * 4) * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
+        const float f0 = p.scale * __expf(lds_read4(gate + (C::kB + ln) * 4));
+        const float f1 = p.scale * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
+        // (factors of the finished rows, in 32 bits: on the weights they would take part in the rounding to bf16)
+        float g0 = 1.f, g1 = 1.f;
+        if constexpr (OUT_GATE) {
+          g0 = lds_read4(gate + (C::kS + ln) * 4);
+          g1 = lds_read4(gate + (C::kS + 32 + ln) * 4);
+        }
         f32x16 o0, o1;
         read_out<C>(H, dec, rq0, sb, o0, o1);
 #pragma unroll
@@ -384,6 +392,13 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
         bf16x8 vf[4];
         v_frags(c, vf);
         add_pairs(vf, lds0 + Y::kP + hw * C::P_BYTES + lane * 16, o0, o1);
+        if constexpr (OUT_GATE) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            o0[r] *= g0;
+            o1[r] *= g1;
+          }
+        }
         // ---- store ----
         const uint32_t out = Y::kOutInQ ? sb + wave * 4096 : lds0 + Y::kOut + wave * 4096;
         auto store_block = [&](auto ibc, const f32x16& o) {
@@ -447,10 +462,10 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
         // log-decay (0 past the end: the state is carried unchanged; at least -20: a token that lets less than e^-20
         // through lets nothing through at the precision of the path, and the bound keeps the factorised weights below in
         // range) and key gate (0 past the end); a constant decay is the same for every token: nothing to shift or to bound
-        float a = la[hh], k = g[hh], s = p.scale;
+        float a = la[hh], k = g[hh], s = 1.f;
         if (p.log_decay) a = rev && t == 0 && first == 0 ? 0.f : fmaxf(a, -20.f);
         if (p.gate_on_output) {  // the gate as a factor on the output rows instead of the keys
-          s *= k;
+          s = k;
           k = 1.f;
         }
         if (t >= L) a = k = 0.f;
@@ -489,7 +504,7 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
   auto scores = [&](int c) { return block_scores<C>(rq0, stage_of(c) + Y::kK + 32 * kb * C::RBQ, stage_of(c) + 32 * qb * C::RBQ); };
   auto weigh = [&](const f32x16& sc) {
 #pragma unroll
-    for (int hh = 0; hh < C::HPW; ++hh) block_weights<C>(sc, gates_of(hh), lane, kb, qb, last_key, lds0 + Y::kP + hh * C::P_BYTES + role * 2048);
+    for (int hh = 0; hh < C::HPW; ++hh) block_weights<C>(sc, p.scale, gates_of(hh), lane, kb, qb, last_key, lds0 + Y::kP + hh * C::P_BYTES + role * 2048);
   };
   auto help = [&](const auto& cp) {
     constexpr int N = std::decay_t<decltype(cp)>::N;
@@ -543,10 +558,10 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
   }
 }
 
-template <class C, bool STATE_ONLY>
+template <class C, bool STATE_ONLY, bool OUT_GATE = false>
 __global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt) {
   __shared__ __attribute__((aligned(1024))) char smem[GLayout<C, STATE_ONLY>::LDS_BYTES];
-  gated_walk<C, STATE_ONLY>(p, blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
+  gated_walk<C, STATE_ONLY, OUT_GATE>(p, blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
                             [&](int h) { return dt.log2_gamma[h] * 0.6931471805599453f; });  // ln gamma
 }
 
@@ -562,10 +577,9 @@ template <int DQK_, int DV_>
 struct GroupCfg : GCfg<DQK_, DV_> {
   using G = GCfg<DQK_, DV_>;
   static constexpr int HEADS = kGatedGroupHeads;  // at most, per workgroup: 32 registers of state each at head dim 64
-  static constexpr int kG = G::GATE_BYTES / 4, GATES = G::GATE_BYTES + 256;  // (behind the gates' values: the factor of the head's rows in the sum)
   static constexpr int UNIT_BYTES = 2 * G::Q_BYTES, SHARED_BYTES = 2 * G::V_BYTES;
   static constexpr int kShared = 3 * UNIT_BYTES, kP = kShared + 2 * SHARED_BYTES, kGates = kP + G::P_BYTES;
-  static constexpr int kDots = kGates + GATES, kOut = kDots + G::NB * 256, LDS_BYTES = kOut + G::NB * 4096;
+  static constexpr int kDots = kGates + G::GATE_BYTES, kOut = kDots + G::NB * 256, LDS_BYTES = kOut + G::NB * 4096;
   static_assert(LDS_BYTES <= 160 * 1024, "tiles do not fit LDS");
 };
 
@@ -615,9 +629,9 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
         if (n < nh) {
           const uint32_t sb = unit_stage(st);
           const float dec = lds_read4(gate + (C::kDec + odd) * 4);
-          const float f0 = lds_read4(gate + (C::kS + ln) * 4) * __expf(lds_read4(gate + (C::kB + ln) * 4));
-          const float f1 = lds_read4(gate + (C::kS + 32 + ln) * 4) * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
-          const float g0 = lds_read4(gate + (C::kG + ln) * 4), g1 = lds_read4(gate + (C::kG + 32 + ln) * 4);
+          const float f0 = p.scale * __expf(lds_read4(gate + (C::kB + ln) * 4));
+          const float f1 = p.scale * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
+          const float g0 = lds_read4(gate + (C::kS + ln) * 4), g1 = lds_read4(gate + (C::kS + 32 + ln) * 4);
           f32x16 o0, o1;
           read_out<C>(H[n], dec, rq0, sb, o0, o1);
 #pragma unroll
@@ -697,8 +711,7 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
       const int t = c * C::CH + lane;
       float a = rev && t == 0 ? 0.f : fmaxf(la, -20.f), k = rev ? 1.f : g;
       if (t >= L) a = k = 0.f;
-      put_factors<C, false>(gate, lane, odd, a, k, p.scale);
-      lds_store4(gate + (C::kG + lane) * 4, rev ? g : 1.f);
+      put_factors<C, false>(gate, lane, odd, a, k, rev ? g : 1.f);
     };
     auto finish = [&](int c, int n) {
       float d = 0.f;
@@ -762,7 +775,7 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
     chunk_barrier();
     for (int u = 0; u < units; ++u) {
       copy(u);
-      block_weights<C>(s, gate, lane, kb, qb, last_key, lds0 + C::kP + role * 2048);
+      block_weights<C>(s, p.scale, gate, lane, kb, qb, last_key, lds0 + C::kP + role * 2048);
       landed(u);
       chunk_barrier();
       st = next(st);
@@ -822,7 +835,8 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
 // waits for the last workgroup of the one before.  Side by side they fill the compute units that one of them leaves idle.
 // Three launches / one (us): 1 x 8 heads x 768, 128/128, 66.6 / 32.3, 2 x 32 x 768 120 / 57, 4 x 32 x 768 131 / 103,
 // 8 x 32 x 768 203 / 195, 4 x 8 x 500 64/64 58 / 28, Mamba2 8 x 80 x 768 256 / 224, 1 x 80 x 300 61 / 31.
-// A: head dims of the walks for the gradients of q and k (D_v, D_qk), E: of the one for that of v (D_qk, D_v).  The longest
+// A: head dims of the walks for the gradients of q and k (D_v, D_qk), E: of the one for that of v (D_qk, D_v); GATED: with key
+// gates, which are factors of the rows of the latter.  The longest
 // workgroups come first: GROUP: those that take several heads; otherwise all are alike and the gradient of v, which no
 // later kernel reads, goes first (the others are still in the caches then: 8 x 32 x 768 202 against 192).
 struct GatedBackwardWalks {
@@ -841,7 +855,7 @@ struct BackwardCfg {
   static constexpr int THIRD = GLayout<E, STATE_ONLY>::LDS_BYTES;
   static constexpr int LDS_BYTES = first_two() > THIRD ? first_two() : THIRD;
 };
-template <class A, class E, bool STATE_ONLY, bool GROUP>
+template <class A, class E, bool STATE_ONLY, bool GROUP, bool GATED>
 __global__ __launch_bounds__((BackwardCfg<A, E, STATE_ONLY, GROUP>::THREADS), (BackwardCfg<A, E, STATE_ONLY, GROUP>::WAVES_PER_SIMD))
 void gated_backward_kernel(const GatedBackwardWalks w) {
   typedef BackwardCfg<A, E, STATE_ONLY, GROUP> C;
@@ -852,15 +866,15 @@ void gated_backward_kernel(const GatedBackwardWalks w) {
   const auto no_const = [](int) { return 0.f; };
   constexpr int kE = GROUP ? 2 : 0;  // place of the walk for the gradient of v
   if constexpr (std::is_same<A, E>::value) {
-    gated_walk<E, STATE_ONLY>(w.walk[which], block, lds0, no_const);
+    gated_walk<E, STATE_ONLY, GATED>(w.walk[which], block, lds0, no_const);
   } else {
     // (wavefronts beyond those of the walk end here: a barrier counts those that are left)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (which == kE) {
-      if (wave < E::WAVES) gated_walk<E, STATE_ONLY>(w.walk[kE], block, lds0, no_const);
+      if (wave < E::WAVES) gated_walk<E, STATE_ONLY, GATED>(w.walk[kE], block, lds0, no_const);
     } else if (wave < A::WAVES) {
       if constexpr (GROUP) gated_group_walk<A>(w.group[which], block, lds0);
-      else gated_walk<A, STATE_ONLY>(w.walk[which], block, lds0, no_const);
+      else gated_walk<A, STATE_ONLY, false>(w.walk[which], block, lds0, no_const);
     }
   }
 }
@@ -878,12 +892,13 @@ __global__ __launch_bounds__(256) void gated_group_sum_kernel(const float* dq_pa
   *reinterpret_cast<f32x4*>((blockIdx.y ? dK : dQ) + e) = x;
 }
 
-template <int DQK, int DV, int HPW = 1>
+template <int DQK, int DV, int HPW = 1, bool OUT_GATE = false>
 hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
   typedef GCfg<DQK, DV, HPW> C;
+  if (p.gate_on_output && !OUT_GATE && !p.state_only) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(p.B * p.H / HPW * p.nseg));
   if (p.state_only) hipLaunchKernelGGL((gated_recurrent_kernel<C, true>), grid, dim3(C::THREADS), 0, s, p, dt);
-  else hipLaunchKernelGGL((gated_recurrent_kernel<C, false>), grid, dim3(C::THREADS), 0, s, p, dt);
+  else hipLaunchKernelGGL((gated_recurrent_kernel<C, false, OUT_GATE>), grid, dim3(C::THREADS), 0, s, p, dt);
   return hipGetLastError();
 }
 
@@ -1062,11 +1077,13 @@ static hipError_t launch_walks(const GatedBackwardWalks& w, int64_t blocks, hipS
   const dim3 grid((unsigned)blocks);
   if constexpr (!GROUP) {
     if (w.walk[0].state_only) {
-      hipLaunchKernelGGL((gated_backward_kernel<A, E, true, false>), grid, dim3(BackwardCfg<A, E, true, false>::THREADS), 0, s, w);
+      hipLaunchKernelGGL((gated_backward_kernel<A, E, true, false, false>), grid, dim3(BackwardCfg<A, E, true, false>::THREADS), 0, s, w);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP>), grid, dim3(BackwardCfg<A, E, false, GROUP>::THREADS), 0, s, w);
+  const dim3 threads(BackwardCfg<A, E, false, GROUP>::THREADS);
+  if (w.walk[GROUP ? 2 : 0].gate_on_output) hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, true>), grid, threads, 0, s, w);
+  else hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, false>), grid, threads, 0, s, w);
   return hipGetLastError();
 }
 
@@ -1105,7 +1122,7 @@ hipError_t launch_gated_backward(const GatedParams (&walk)[3], const GatedGroupP
     if (!w.walk[0].state_only && blocks > 3 * 160 && blocks <= 3 * 256 && w.walk[0].L >= 320) {
       static const DecayTable none = {};
       hipError_t e = hipSuccess;
-      for (int i = 0; i < 3 && e == hipSuccess; ++i) e = launch<64, 64>(w.walk[i], none, s);
+      for (int i = 0; i < 3 && e == hipSuccess; ++i) e = w.walk[i].gate_on_output ? launch<64, 64, 1, true>(w.walk[i], none, s) : launch<64, 64>(w.walk[i], none, s);
       return e;
     }
     return launch_walks<GCfg<64, 64>, GCfg<64, 64>>(w, blocks, s);

@@ -189,6 +189,16 @@ def test_several_heads_per_workgroup(A, dqk, H, H_qk, heads, kind, L):
     close(dla, ela, (2 * dqk * eps * (rows_q + rows_k) + 1e-7)[..., ::-1].cumsum(axis=-1)[..., ::-1] + 2 * eps * np.abs(ela), "dlog_decay")
 
 
+@pytest.mark.parametrize("dqk,dv,B,H,H_qk,L", [(64, 64, 1, 3, 3, 200), (128, 64, 2, 6, 2, 129), (128, 64, 2, 132, 22, 130), (64, 128, 1, 2, 2, 64),
+                                               (128, 128, 1, 2, 2, 1061)])
+def test_gate_multiplies_finished_rows_of_dv(A, dqk, dv, B, H, H_qk, L):
+    # the key gate of token j is a factor of row j of dV and of nothing that is summed into it: one product in 32 bits, so dV is
+    # that of a call without gates times the gates, bit for bit -- whole and cut walks, one head per workgroup and two
+    Q, K, V, la, kg, dO = inputs(950 + L % 7, B, H, H_qk, L, dqk, dv, "mamba2")
+    dV, bare = (run(A, Q, K, V, la, g, dO, 0.1)[2] for g in (kg, None))
+    assert np.array_equal(dV, (bare.astype(np.float32) * kg.numpy()[..., None]).astype(np.float64))
+
+
 @pytest.mark.parametrize("dqk,dv", [(64, 64), (128, 64), (64, 128), (128, 128)])
 def test_batch_entries_do_not_depend_on_the_launches(A, dqk, dv):
     # 180 (batch, head) pairs: one launch for the three walks or (64/64) one each; 60 at a time always take one
