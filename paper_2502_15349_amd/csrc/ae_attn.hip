@@ -342,18 +342,20 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
     const int64_t whole_rounds = (whole + 31) / 32, cut_rounds = (((int64_t)p.n_groups << p.cut) / 8 * part + 31) / 32;
     if (whole <= 8 || (d->mask == AE_MASK_NONE && whole_rounds > 1 && cut_rounds >= whole_rounds)) p.cut = 0;
   }
-  const int64_t per_group = ((int64_t)p.n_qtiles * p.g + (1 << p.cut) - 1) >> p.cut;  // (or part of a group)
-  const int64_t rounds = (((int64_t)p.n_groups << p.cut) + 7) / 8;                      // groups, or parts, per XCD
+  // workgroups, those included that pad the grid to whole sets, where the groups are cut into 2^cut parts
+  auto grid_of = [&](int cut, int* together) {
+    const int64_t per_group = ((int64_t)p.n_qtiles * p.g + (1 << cut) - 1) >> cut;  // (or part of a group)
+    const int64_t rounds = (((int64_t)p.n_groups << cut) + 7) / 8;                  // groups, or parts, per XCD
 #ifdef AE_TUNE_INTERLEAVE  // build-time knob of the mapping sweeps, like the AE_SHAPE_* entries of the tile table
-  int interleave = AE_TUNE_INTERLEAVE;
+    int64_t n = AE_TUNE_INTERLEAVE;
 #else
-  int interleave = (per_group >= 32 ? 2 : 8) << p.cut;
+    int64_t n = (per_group >= 32 ? 2 : 8) << cut;
 #endif
-  if (interleave < 1) interleave = 1;
-  if (interleave > rounds) interleave = (int)rounds;
-  p.interleave = interleave;
-  const int64_t blocks = (rounds + interleave - 1) / interleave;
-  const int64_t grid = blocks * interleave * 8 * per_group;
+    n = std::min<int64_t>(std::max<int64_t>(n, 1), rounds);
+    *together = (int)n;
+    return (rounds + n - 1) / n * n * 8 * per_group;
+  };
+  const int64_t grid = grid_of(p.cut, &p.interleave);
   if (grid > 0x7fffffffLL) {
     delete h;
     return fail(AE_ERR_UNSUPPORTED, "ae_attn_create: grid of %lld workgroups exceeds the launch limit", (long long)grid);
@@ -379,11 +381,15 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
     // Measured on decoding shapes (one query row, 16 heads, 2k-8k keys, batch 1 and 8): the
     // fastest launches hold some 128-256 workgroups with at least 8 key tiles each; more
     // ranges cost a start and an end of a workgroup apiece.  Only where the keys may be split
-    // and the query tiles alone leave most of the device idle.
+    // and the query tiles alone leave most of the device idle.  The workgroups are counted with whole groups, however the groups are
+    // dealt to the XCDs: by the fewer ones of a grid of parts, 1 head x 4096 rows was cut into 12 ranges instead of 2 and 12 heads x 2086
+    // into 2 instead of none, and the partial results no longer fitted the static scratch.
     kv_splits = 0;
-    if (d->norm == AE_NORM_SOFTMAX && d->mask != AE_MASK_SLIDING_WINDOW && mod != ae::MOD_BIAS_T && grid < 160) {
+    int unused = 0;
+    const int64_t count = grid_of(0, &unused);
+    if (d->norm == AE_NORM_SOFTMAX && d->mask != AE_MASK_SLIDING_WINDOW && mod != ae::MOD_BIAS_T && count < 160) {
       const int key_tiles = (d->L_k + h->kernel->block_n - 1) / h->kernel->block_n;
-      const int64_t want = (192 + grid / 2) / grid;  // round(192 / workgroups)
+      const int64_t want = (192 + count / 2) / count;  // round(192 / workgroups)
       kv_splits = (int)std::min<int64_t>(std::min<int64_t>(want, key_tiles / 8), 256);
     }
   }

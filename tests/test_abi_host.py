@@ -186,6 +186,17 @@ def test_split_keys_descriptor_and_workspace():
         A.ae_attn_destroy(h)
 
 
+@pytest.mark.parametrize("H,L_q,L_k,D,splits", [(1, 3548, 16786, 128, 2), (1, 4096, 16384, 64, 2), (12, 2086, 2368, 128, 0), (10, 2783, 3717, 128, 0),
+                                              (5, 4202, 4522, 64, 0), (2, 300, 8192, 64, 12), (8, 300, 8192, 64, 12)])
+def test_automatic_split_does_not_depend_on_the_placement(H, L_q, L_k, D, splits):
+    from paper_2502_15349_amd import ae_attn as A
+    # one to twelve heads, whose workgroups are shared out over the XCDs in whole groups or in parts: the number of key ranges, and so
+    # the workspace, follows from the query tiles of 256 rows, padded to whole rounds of the eight XCDs
+    h = A.ae_attn_create(B=1, H_q=H, H_kv=H, L_q=L_q, L_k=L_k, D_qk=D, D_v=D, scale=0.1, mask="causal", kv_splits=-1)
+    assert A.ae_attn_workspace_bytes(h) == splits * H * L_q * (D + 1) * 4
+    A.ae_attn_destroy(h)
+
+
 def test_backward_rejects_bad_arguments_without_launching():
     from paper_2502_15349_amd import ae_attn as A
     d = _ok_desc()
