@@ -63,8 +63,18 @@ template <class K, class Q>
 hipError_t launch_both(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
   static_assert(K::KV_SIDE && !Q::KV_SIDE && K::OWN == 128 && Q::OWN == 128, "");
   const int64_t key = side_blocks(p, true), query = side_blocks(p, false);
-  if (key < 1 || query < 1 || key + query > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((attn_bwd_both_kernel<K, Q>), dim3((unsigned)(key + query)), dim3(BwdBoth<K, Q>::THREADS), 0, s, p, dt, (int)key);
+  if (key < 1 || query < 1 || key > 0x7fffffffLL || query > 0x7fffffffLL) return hipErrorInvalidValue;
+  auto launch = [&](int64_t blocks, int64_t key_blocks) {
+    hipLaunchKernelGGL((attn_bwd_both_kernel<K, Q>), dim3((unsigned)blocks), dim3(BwdBoth<K, Q>::THREADS), 0, s, p, dt, (int)key_blocks);
+  };
+  if ((key + query) * BwdBoth<K, Q>::THREADS <= 0xffffffffLL) {
+    launch(key + query, key);
+  } else {  // (a launch holds fewer than 2^32 threads)
+    launch(key, key);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    launch(query, 0);
+  }
   return hipGetLastError();
 }
 

@@ -559,9 +559,9 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
 }
 
 template <class C, bool STATE_ONLY, bool OUT_GATE = false>
-__global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt) {
+__global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[GLayout<C, STATE_ONLY>::LDS_BYTES];
-  gated_walk<C, STATE_ONLY, OUT_GATE>(p, blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
+  gated_walk<C, STATE_ONLY, OUT_GATE>(p, first_block + (int)blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
                             [&](int h) { return dt.log2_gamma[h] * 0.6931471805599453f; });  // ln gamma
 }
 
@@ -842,7 +842,8 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
 struct GatedBackwardWalks {
   GatedParams walk[3];
   GatedGroupParams group[2];
-  int first[2];  // number of the first workgroup of walks 1 and 2
+  int first[2];     // number of the first workgroup of walks 1 and 2
+  int first_block;  // ... and of the launch
 };
 template <class A, class E, bool STATE_ONLY, bool GROUP>
 struct BackwardCfg {
@@ -861,7 +862,7 @@ void gated_backward_kernel(const GatedBackwardWalks w) {
   typedef BackwardCfg<A, E, STATE_ONLY, GROUP> C;
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
   const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
-  const int n = (int)blockIdx.x, which = (n >= w.first[0] ? 1 : 0) + (n >= w.first[1] ? 1 : 0);
+  const int n = w.first_block + (int)blockIdx.x, which = (n >= w.first[0] ? 1 : 0) + (n >= w.first[1] ? 1 : 0);
   const int block = n - (which == 0 ? 0 : w.first[which - 1]);
   const auto no_const = [](int) { return 0.f; };
   constexpr int kE = GROUP ? 2 : 0;  // place of the walk for the gradient of v
@@ -892,14 +893,26 @@ __global__ __launch_bounds__(256) void gated_group_sum_kernel(const float* dq_pa
   *reinterpret_cast<f32x4*>((blockIdx.y ? dK : dQ) + e) = x;
 }
 
+// A launch holds fewer than 2^32 threads: more workgroups than that go in several, launch(first workgroup, their number) each.
+template <class F>
+hipError_t launch_in_parts(int64_t blocks, int threads, F&& launch) {
+  const int64_t most = 0xffffffffLL / threads;
+  hipError_t e = hipSuccess;
+  for (int64_t first = 0; first < blocks && e == hipSuccess; first += most) {
+    launch((int)first, dim3((unsigned)(blocks - first < most ? blocks - first : most)));
+    e = hipGetLastError();
+  }
+  return e;
+}
+
 template <int DQK, int DV, int HPW = 1, bool OUT_GATE = false>
 hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
   typedef GCfg<DQK, DV, HPW> C;
   if (p.gate_on_output && !OUT_GATE && !p.state_only) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(p.B * p.H / HPW * p.nseg));
-  if (p.state_only) hipLaunchKernelGGL((gated_recurrent_kernel<C, true>), grid, dim3(C::THREADS), 0, s, p, dt);
-  else hipLaunchKernelGGL((gated_recurrent_kernel<C, false, OUT_GATE>), grid, dim3(C::THREADS), 0, s, p, dt);
-  return hipGetLastError();
+  return launch_in_parts((int64_t)p.B * p.H / HPW * p.nseg, C::THREADS, [&](int first, dim3 grid) {
+    if (p.state_only) hipLaunchKernelGGL((gated_recurrent_kernel<C, true>), grid, dim3(C::THREADS), 0, s, p, dt, first);
+    else hipLaunchKernelGGL((gated_recurrent_kernel<C, false, OUT_GATE>), grid, dim3(C::THREADS), 0, s, p, dt, first);
+  });
 }
 
 // ---- segments: from the final states of the segments (each from a zero start) to the states in front of them ----
@@ -1073,18 +1086,21 @@ hipError_t launch_gated_recurrent(const GatedParams& p_in, const DecayTable& dt,
 }
 
 template <class A, class E, bool GROUP = false>
-static hipError_t launch_walks(const GatedBackwardWalks& w, int64_t blocks, hipStream_t s) {
-  const dim3 grid((unsigned)blocks);
-  if constexpr (!GROUP) {
-    if (w.walk[0].state_only) {
-      hipLaunchKernelGGL((gated_backward_kernel<A, E, true, false, false>), grid, dim3(BackwardCfg<A, E, true, false>::THREADS), 0, s, w);
-      return hipGetLastError();
+static hipError_t launch_walks(GatedBackwardWalks& w, int64_t blocks, hipStream_t s) {
+  constexpr int kThreads = BackwardCfg<A, E, false, GROUP>::THREADS;
+  static_assert(GROUP || BackwardCfg<A, E, true, false>::THREADS == kThreads, "");
+  const bool gated = w.walk[GROUP ? 2 : 0].gate_on_output != 0;
+  return launch_in_parts(blocks, kThreads, [&](int first, dim3 grid) {
+    w.first_block = first;
+    if constexpr (!GROUP) {
+      if (w.walk[0].state_only) {
+        hipLaunchKernelGGL((gated_backward_kernel<A, E, true, false, false>), grid, dim3(kThreads), 0, s, w);
+        return;
+      }
     }
-  }
-  const dim3 threads(BackwardCfg<A, E, false, GROUP>::THREADS);
-  if (w.walk[GROUP ? 2 : 0].gate_on_output) hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, true>), grid, threads, 0, s, w);
-  else hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, false>), grid, threads, 0, s, w);
-  return hipGetLastError();
+    if (gated) hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, true>), grid, dim3(kThreads), 0, s, w);
+    else hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, false>), grid, dim3(kThreads), 0, s, w);
+  });
 }
 
 hipError_t launch_gated_backward(const GatedParams (&walk)[3], const GatedGroupParams* group, int dqk, int dv, hipStream_t s) {

@@ -492,3 +492,20 @@ def test_backward_hidden_entries_stay_zero(A, dims, form):
     free = zero[:, ::2, 60, :]
     assert free.any() and torch.equal(got[1][free], clean[1][free])
     assert not torch.isfinite(got[1][~free]).all()
+
+
+def test_more_workgroups_than_one_launch_holds(A):
+    # 8.4 million heads of one token: either side of the backward pass has 2^31 threads, both together more than a launch holds.  With
+    # s = scale q . k and d = scale v . dO (64 terms each, summed in 32 bits: 2^-18 of the sum of their absolute values), rounded to
+    # bf16 (2^-9): dQ = d k, dK = d q, dV = s dO
+    B, H, D = 131073, 64, 64
+    g = torch.Generator("cuda").manual_seed(90)
+    Q, K, V, dO = (torch.randn(B, H, 1, D, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    dQ, dK, dV = A.attention_backward(Q, K, V, None, dO, None, scale=0.1, norm="none")
+    n = 10000
+    for b0 in range(0, B, n):
+        q, k, v, do = (t[b0:b0 + n].double() for t in (Q, K, V, dO))
+        s, d = 0.1 * (q * k).sum(-1, keepdim=True), 0.1 * (v * do).sum(-1, keepdim=True)
+        es, ed = 0.1 * (q * k).abs().sum(-1, keepdim=True), 0.1 * (v * do).abs().sum(-1, keepdim=True)
+        for name, got, w, e, x in (("dQ", dQ, d, ed, k), ("dK", dK, d, ed, q), ("dV", dV, s, es, do)):
+            assert ((got[b0:b0 + n].double() - w * x).abs() <= (2.0 ** -8 * w.abs() + 2.0 ** -17 * e) * x.abs() + 1e-7).all(), (name, b0)

@@ -182,3 +182,19 @@ def test_sampled_heads_at_benchmark_size(A):
     for b, h in ((0, 0), (3, 17), (7, 31)):
         ref = gated_recurrent_head(Q[b, h].float().numpy(), K[b, h].float().numpy(), V[b, h].float().numpy(), la[b, h].numpy(), scale=scale)
         check(got[b, h].double().numpy(), ref, f"benchmark size head ({b},{h})")
+
+
+def test_more_workgroups_than_one_launch_holds(A):
+    # 8.4 million (batch, head) pairs of one token, 512 threads each: more than 2^32 threads.  o = scale g (q . k) v, whose weight is
+    # rounded to bf16 (2^-9 of itself) behind a sum in 32 bits (128 terms: 2^-17 of the sum of their absolute values)
+    B, H, D = 131250, 64, 128
+    g = torch.Generator("cuda").manual_seed(88)
+    Q, K, V = (torch.randn(B, H, 1, D, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    la = torch.zeros(B, H, 1, device="cuda")
+    kg = torch.rand(B, H, 1, generator=g, device="cuda")
+    O = A.gated_recurrent(Q, K, V, la, kg, scale=0.1)
+    for b0 in range(0, B, 8750):
+        q, k, v, w = (t[b0:b0 + 8750].double() for t in (Q, K, V, kg.unsqueeze(-1)))
+        ref = 0.1 * w * (q * k).sum(-1, keepdim=True) * v
+        bound = 2.0 ** -8 * ref.abs() + 2.0 ** -17 * 0.1 * w * (q * k).abs().sum(-1, keepdim=True) * v.abs() + 1e-7
+        assert ((O[b0:b0 + 8750].double() - ref).abs() <= bound).all(), b0

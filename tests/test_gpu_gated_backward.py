@@ -252,3 +252,35 @@ def test_sampled_heads_at_benchmark_size(A):
         qn, kn = Q[b, h].float().numpy().astype(np.float64), K[b, h].float().numpy().astype(np.float64)
         b_dla = token_bounds_proxy(np.sum(qn * ref["dq"], axis=-1), np.sum(kn * ref["dk"], axis=-1))
         check_tokens(dla[b, h], b_dla, ref["dlog_decay"], f"benchmark size ({b},{h}) dlog_decay")
+
+
+@pytest.mark.parametrize("B,H_qk", [(59375, 64), (89063, 32)])
+def test_more_workgroups_than_one_launch_holds(A, B, H_qk):
+    # 3.8 and 5.7 million (batch, head) pairs of one token, 64 heads each (alone, or in groups of two): the three walks have more than
+    # 2^32 threads.  With s = q . k, d = v . dO (64 terms each, summed in 32 bits: 2^-18 of the sum of their absolute values) and weights
+    # in bf16 (2^-9 of themselves): dq = scale g d k, dk = scale g d q, dv = scale g s dO, dg = scale s d, and no gradient of the decay
+    # but the difference of two such products.
+    H, D = 64, 64
+    g = torch.Generator("cuda").manual_seed(89)
+    Q, K = (torch.randn(B, H_qk, 1, D, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    V, dO = (torch.randn(B, H, 1, D, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    kg = torch.rand(B, H, 1, generator=g, device="cuda")
+    dQ, dK, dV, dla, dkg = A.gated_recurrent_backward(Q, K, V, torch.zeros(B, H, 1, device="cuda"), kg, dO, scale=0.1)
+    n, grp = 5000, H // H_qk
+    for b0 in range(0, B, n):
+        q, k, v, do, w = (t[b0:b0 + n].double() for t in (Q, K, V, dO, kg.unsqueeze(-1)))
+        qx, kx = (t.repeat_interleave(grp, dim=1) for t in (q, k))
+        s, d = 0.1 * (qx * kx).sum(-1, keepdim=True), (v * do).sum(-1, keepdim=True)
+        es, ed = 0.1 * (qx * kx).abs().sum(-1, keepdim=True), (v * do).abs().sum(-1, keepdim=True)
+
+        def close(got, ref, size, terms, what):
+            assert ((got[b0:b0 + n].double() - ref).abs() <= 2.0 ** -8 * size + 2.0 ** -17 * terms + 1e-6).all(), (what, b0)
+
+        def group(x):
+            return x.reshape(x.shape[0], H_qk, grp, 1, -1).sum(dim=2)
+
+        close(dV, w * s * do, (w * s * do).abs(), w * es * do.abs(), "dV")
+        close(dQ, group(0.1 * w * d * kx), group((0.1 * w * d * kx).abs()), group(0.1 * w * ed * kx.abs()), "dQ")
+        close(dK, group(0.1 * w * d * qx), group((0.1 * w * d * qx).abs()), group(0.1 * w * ed * qx.abs()), "dK")
+        close(dkg, (s * d)[..., 0], (es * d.abs())[..., 0], (es * ed)[..., 0], "dkey_gate")
+        close(dla, torch.zeros_like((s * d)[..., 0]), 2 * (w * es * d.abs())[..., 0], 2 * (w * es * ed)[..., 0], "dlog_decay")
