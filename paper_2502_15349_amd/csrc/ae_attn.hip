@@ -456,6 +456,9 @@ static ae_status_t forward_impl(const ae_attn_t* h, const void* Q, const void* K
   }
   hipError_t e = hipSuccess;
   const bool decode = h->decode && !carried && !bias;
+  const int64_t merge_grid = ((int64_t)p.B * p.H_q * p.L_q + 3) / 4;
+  if ((!decode && !ae::launch_fits(h->grid, h->kernel->threads)) || (p.n_splits > 1 && !ae::launch_fits(merge_grid, 256)))
+    return fail(AE_ERR_UNSUPPORTED, "ae_attn_forward: more threads than one launch holds; call it for parts of the batch");
   if (decode) {
     ae::DecodeParams q;
     q.Q = p.Q;
@@ -500,8 +503,7 @@ static ae_status_t forward_impl(const ae_attn_t* h, const void* Q, const void* K
     m.out_bf16 = p.out_bf16;
     m.bias = decode && h->desc.score_mod == AE_MOD_BIAS ? h->desc.bias : 0.f;
     for (int a = 0; a < 3; ++a) m.os[a] = p.os[a];
-    const int64_t rows = (int64_t)p.B * p.H_q * p.L_q;
-    const dim3 grid((unsigned)((rows + 3) / 4));
+    const dim3 grid((unsigned)merge_grid);
     switch (m.D_v / 64) {  // (head dims with split keys: D_v is 64, 128 or 256)
       case 1: hipLaunchKernelGGL(attn_merge_kernel<1>, grid, dim3(256), 0, static_cast<hipStream_t>(stream), m); break;
       case 2: hipLaunchKernelGGL(attn_merge_kernel<2>, grid, dim3(256), 0, static_cast<hipStream_t>(stream), m); break;

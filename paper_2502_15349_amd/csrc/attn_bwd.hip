@@ -61,7 +61,7 @@ template <int DV>
 hipError_t launch_delta(const BwdParams& p, int norm, hipStream_t stream) {
   constexpr int RPW = 64 / (DV / 8) * kDeltaPasses;
   const int64_t rows = (int64_t)p.B * p.H_q * p.L_q, grid = (rows + 4 * RPW - 1) / (4 * RPW);
-  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (!launch_fits(grid, 256)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(attn_bwd_delta_kernel<DV>, dim3((unsigned)grid), dim3(256), 0, stream, p, norm);
   return hipGetLastError();
 }

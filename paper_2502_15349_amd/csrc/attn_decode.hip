@@ -222,7 +222,7 @@ constexpr int64_t kUnits = 256;  // compute units
 template <int DQK, int DV, int G>
 hipError_t launch_heads(const DecodeParams& p, hipStream_t s) {
   const int64_t grid = p.rows / p.g * ((p.g + G - 1) / G) * p.n_splits;
-  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (!launch_fits(grid, 256)) return hipErrorInvalidValue;  // (more wavefronts only for few workgroups, see below)
   DecodeParams q = p;
   q.units = (int)(p.rows / p.g * p.n_splits);
   // Eight wavefronts instead of four keep more loads in flight and halve a workgroup's walk; taken where no compute unit has a

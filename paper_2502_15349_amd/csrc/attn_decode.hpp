@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch.hpp"
+
 namespace ae {
 struct DecodeParams {
   const __bf16* Q;       // one row per (batch, q head): element strides qs[] = {batch, head}

@@ -43,6 +43,8 @@
 
 #include <type_traits>
 
+#include "launch.hpp"
+
 namespace ae {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;

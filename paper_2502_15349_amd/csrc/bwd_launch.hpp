@@ -55,7 +55,7 @@ inline int64_t side_blocks(const BwdParams& p, bool key_side) {
 template <class C>
 hipError_t launch_side(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
   const int64_t grid = side_blocks(p, C::KV_SIDE);
-  if (grid < 1 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (!launch_fits(grid, C::THREADS)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(attn_bwd_kernel<C>, dim3((unsigned)grid), dim3(C::THREADS), 0, s, p, dt);
   return hipGetLastError();
 }
@@ -63,13 +63,13 @@ template <class K, class Q>
 hipError_t launch_both(const BwdParams& p, const DecayTable& dt, hipStream_t s) {
   static_assert(K::KV_SIDE && !Q::KV_SIDE && K::OWN == 128 && Q::OWN == 128, "");
   const int64_t key = side_blocks(p, true), query = side_blocks(p, false);
-  if (key < 1 || query < 1 || key > 0x7fffffffLL || query > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (!launch_fits(key, BwdBoth<K, Q>::THREADS) || !launch_fits(query, BwdBoth<K, Q>::THREADS)) return hipErrorInvalidValue;
   auto launch = [&](int64_t blocks, int64_t key_blocks) {
     hipLaunchKernelGGL((attn_bwd_both_kernel<K, Q>), dim3((unsigned)blocks), dim3(BwdBoth<K, Q>::THREADS), 0, s, p, dt, (int)key_blocks);
   };
-  if ((key + query) * BwdBoth<K, Q>::THREADS <= 0xffffffffLL) {
+  if (launch_fits(key + query, BwdBoth<K, Q>::THREADS)) {
     launch(key + query, key);
-  } else {  // (a launch holds fewer than 2^32 threads)
+  } else {
     launch(key, key);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -893,7 +893,7 @@ __global__ __launch_bounds__(256) void gated_group_sum_kernel(const float* dq_pa
   *reinterpret_cast<f32x4*>((blockIdx.y ? dK : dQ) + e) = x;
 }
 
-// A launch holds fewer than 2^32 threads: more workgroups than that go in several, launch(first workgroup, their number) each.
+// More workgroups than a launch holds (see launch_fits) go in several: launch(first workgroup, their number) each.
 template <class F>
 hipError_t launch_in_parts(int64_t blocks, int threads, F&& launch) {
   const int64_t most = 0xffffffffLL / threads;
@@ -1040,12 +1040,13 @@ bool gated_group_supported(int dqk, int dv) { return (dqk == 64 || dqk == 128) &
 hipError_t launch_gated_group_sum(const float* dq_parts, const float* dk_parts, float* dQ, float* dK, int parts, int64_t head_elems,
                                   int64_t elems, hipStream_t s) {
   const int64_t grid = (elems / 4 + 255) / 256;
-  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (!launch_fits(grid, 256)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(gated_group_sum_kernel, dim3((unsigned)grid, 2), dim3(256), 0, s, dq_parts, dk_parts, dQ, dK, parts, head_elems, elems);
   return hipGetLastError();
 }
 
 hipError_t launch_gated_suffix_sum(const float* dB, const float* minus, float* dlog_decay, int BH, int L, hipStream_t s) {
+  if (!launch_fits(BH, 64)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(gated_bwd_suffix_sum_kernel, dim3((unsigned)BH), dim3(64), 0, s, dB, minus, dlog_decay, L);
   return hipGetLastError();
 }
@@ -1053,7 +1054,7 @@ hipError_t launch_gated_suffix_sum(const float* dB, const float* minus, float* d
 hipError_t launch_gated_backward_epilogue(const GatedBwdEpilogueParams& p, int dqk, hipStream_t s) {
   const int tpb = 4 * (64 / (dqk / 4));
   const int64_t grid = (int64_t)p.B * p.H_qk * (((int64_t)p.L + tpb - 1) / tpb);
-  if (grid > 0x7fffffffLL || (dqk != 64 && dqk != 128)) return hipErrorInvalidValue;
+  if (!launch_fits(grid, 256) || (dqk != 64 && dqk != 128)) return hipErrorInvalidValue;
   if (dqk == 64) hipLaunchKernelGGL(gated_bwd_rows_kernel<64>, dim3((unsigned)grid), dim3(256), 0, s, p);
   else hipLaunchKernelGGL(gated_bwd_rows_kernel<128>, dim3((unsigned)grid), dim3(256), 0, s, p);
   const hipError_t e = hipGetLastError();

@@ -310,6 +310,22 @@ def test_bias_tensor_descriptor_and_entry_point_checks():
     A.ae_attn_destroy(h)
 
 
+def test_more_threads_than_a_launch_holds_are_refused():
+    # the runtime would launch the remainder modulo 2^32 threads and leave the other rows unwritten: 8.4 million workgroups of 512
+    # threads, and 67 million rows to merge at 64 threads each
+    from paper_2502_15349_amd import ae_attn as A
+    h = A.ae_attn_create(B=1 << 17, H_q=65, H_kv=65, L_q=2, L_k=2, D_qk=64, D_v=64, scale=0.1)
+    with pytest.raises(A.AeAttnError) as ei:
+        A.ae_attn_forward(h, 256, 512, 768, 1024)
+    assert ei.value.status == A.AE_ERR_UNSUPPORTED and "launch" in str(ei.value)
+    A.ae_attn_destroy(h)
+    h = A.ae_attn_create(B=1, H_q=4, H_kv=4, L_q=(1 << 24) + 1, L_k=256, D_qk=64, D_v=64, scale=0.1, kv_splits=2)
+    with pytest.raises(A.AeAttnError) as ei:
+        A.ae_attn_forward_split(h, 256, 512, 768, 1024, 0, 1280, A.ae_attn_workspace_bytes(h))
+    assert ei.value.status == A.AE_ERR_UNSUPPORTED and "launch" in str(ei.value)
+    A.ae_attn_destroy(h)
+
+
 def test_slabs_beyond_32_bit_offsets_are_refused():
     from paper_2502_15349_amd import ae_attn as A
     d = _ok_desc()
