@@ -61,6 +61,9 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_fwd_wide_kernel(const Para
   // keys the workgroup walks, and those of them that some row of this row group sees
   const int kmax = max(0, min(p.L_k, i_wg + C::BLOCK_M + off)), kmax_rg = i_rg < p.L_q ? max(0, min(p.L_k, i_rg + 64 + off)) : 0;
   const int n_tiles = (kmax + C::BLOCK_N - 1) / C::BLOCK_N, n_rg = (kmax_rg + C::BLOCK_N - 1) / C::BLOCK_N;
+  // ... and that some row of its first 32 sees: as many tiles or one less.  Weight 0 times an infinite value is NaN, so rows meet no
+  // value rows behind the tile that their block of 32 ends in, as in attn_fwd_kernel.
+  const int kmax_32 = i_rg < p.L_q ? max(0, min(p.L_k, i_rg + 32 + off)) : 0, n_32 = (kmax_32 + C::BLOCK_N - 1) / C::BLOCK_N;
 
   // ---- copies: a wavefront moves blocks wave and wave + 8 of a K tile (two rows each) and rows wave + 8 i of a V tile ----
   // (16-byte chunk k of row r stands at k ^ (r % 16) in a K tile, at k ^ 4 (r % 4) in a V tile)
@@ -144,7 +147,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_fwd_wide_kernel(const Para
   // Scores of the tile in K stage su; behind its last key fragments the first ones that values() needs are requested.
   // (the copies go out one instruction at a time between the products: queued together they hold up every wavefront at the
   // compute unit's memory pipe; k_copy, v_copy: issues instruction number ic of the step's)
-  auto scores = [&](auto aheadc, uint32_t su, uint32_t sv, int t, auto&& k_copy) {
+  auto scores = [&](auto aheadc, uint32_t su, uint32_t sv, auto&& k_copy) {
     constexpr bool AHEAD = decltype(aheadc)::value;
     constexpr int RING = 8;
     const uint32_t so = su * C::K_BYTES;
@@ -207,13 +210,22 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_fwd_wide_kernel(const Para
       sched_fence();
     });
   };
+  // the same for the second 32 rows of the row group alone, for its last tile (behind which no weights are wanted)
+  auto values_of_second = [&](int t, uint32_t sv) {
+    static_for<0, 8>([&](auto nc) {
+      constexpr int n = decltype(nc)::value;
+      if constexpr (n % 4 == 0) pf[1] = read_k_frag((pr ^ (8u * n)) + (t & 1) * C::P_BYTES + 2048);
+      o[1][n % 4] = mfma(v_frag(n, sv * C::V_BYTES), pf[1], o[1][n % 4]);
+      sched_fence();
+    });
+  };
   auto next = [](uint32_t s) { return s == C::STAGES - 1 ? 0u : s + 1; };
 
   if (n_tiles > 0) {
     // tile 0 of K has landed (the copies behind it: V 0, K 1, V 1, K 2)
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * kCopies) : "memory");
     if (n_rg > 0) {
-      scores(std::false_type{}, 0, 0, 0, [](auto) {});
+      scores(std::false_type{}, 0, 0, [](auto) {});
       weights(std::integral_constant<int, 0>{}, 0);
       weights(std::integral_constant<int, 1>{}, 0);
     }
@@ -221,8 +233,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_fwd_wide_kernel(const Para
     // Step t of the walk: V of tile t, K of tile t + 1 and the weights of tile t are there for all, and every wavefront is done with
     // K of tile t and V of tile t - 1, whose stages take K of tile t + 3 and V of tile t + 2.
     uint32_t st = 0;  // t % 3
-#pragma clang loop unroll(disable)
-    for (int t = 0; t < n_tiles; ++t) {
+    auto step = [&](auto&& work) {
       const uint32_t st1 = next(st), st2 = next(st1);
       // (hidden from the optimiser: what is derived from these is formed where it is used, not kept through the loop: registers)
       pin(ka);
@@ -230,16 +241,24 @@ __global__ __launch_bounds__(C::THREADS, 2) void attn_fwd_wide_kernel(const Para
       pin(pr);
       pin(pw);
       pin(ln);
-      if (t < n_rg) {
-        scores(std::true_type{}, st1, st, t, [&](auto ic) { copy_k(ic, st); });
-        values(t, st, [&](auto ic) { copy_v(ic, st2); });
-      } else {
-        whole_k(st);
-        whole_v(st2);
-      }
+      work(st1, st2);
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kCopies) : "memory");
       st = st1;
-    }
+    };
+    int t = 0;
+#pragma clang loop unroll(disable)
+    for (; t < n_32; ++t)
+      step([&](uint32_t st1, uint32_t st2) {
+        scores(std::true_type{}, st1, st, [&](auto ic) { copy_k(ic, st); });
+        values(t, st, [&](auto ic) { copy_v(ic, st2); });
+      });
+#pragma clang loop unroll(disable)
+    for (; t < n_tiles; ++t)
+      step([&](uint32_t, uint32_t st2) {
+        whole_k(st);
+        whole_v(st2);
+        if (t < n_rg) values_of_second(t, st);
+      });
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");  // the LDS of the tiles is free
   }
 

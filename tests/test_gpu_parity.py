@@ -140,6 +140,29 @@ def test_retention_512_value_columns(A, Lq, Lk, kw):
         assert ((stats[0].cpu().double() - r).abs() <= bound).all()
 
 
+@pytest.mark.parametrize("dv", [128, 512])
+@pytest.mark.parametrize("norm", ["abssum", "none"])
+@pytest.mark.parametrize("Lq,Lk", [(300, 300), (200, 230), (290, 270)])
+def test_retention_infinite_value_reaches_back_32_rows(A, dv, norm, Lq, Lk):
+    """A value row that a query row does not see has weight 0 there, and 0 times infinity is NaN: rows meet it only in the tile of 32 keys
+    that their block of 32 rows ends in.  All rows in front of that are what they are without it, bit for bit."""
+    w = Workload("reach", 25, 1, 2, 2, Lq, Lk, 256, dv, score_mod="head_decay", norm=norm, mask="causal", decay=True, scale=0.01)
+    Q, K, V = (t.cuda() for t in make_inputs(w))
+    args = dict(scale=w.scale_value, score_mod="head_decay", gamma=w.gamma(), norm=norm, mask="causal")
+    ref = A.attention_forward(Q, K, V, **args)
+    block_end = torch.arange(Lq) // 32 * 32 + 32 + Lk - Lq        # first key that no row of the block sees
+    tiles = (block_end.clamp(0, Lk) + 31) // 32
+    for j in (40, 100, 130, 161, 225, Lk - 1):
+        x = V.clone()
+        x[:, :, j] = float("inf")
+        O = A.attention_forward(Q, K, x, **args)
+        torch.cuda.synchronize()
+        free = j >= 32 * tiles
+        assert torch.equal(O[:, :, free], ref[:, :, free]), j
+        sees = torch.arange(Lq) + Lk - Lq >= j
+        assert not torch.isfinite(O[:, :, sees]).any()
+
+
 @pytest.mark.parametrize("Lq,Lk", [(1, 1), (1, 77), (77, 1), (64, 64), (257, 255), (40, 700), (700, 40), (513, 513)])
 @pytest.mark.parametrize("mask", ["none", "causal"])
 def test_shapes_softmax(A, Lq, Lk, mask):
