@@ -65,8 +65,12 @@ struct GCfg {
   // the gates' values of a head's chunk, in floats: b, u, s (see put_gates), two sets of w, the groups' references, two decays
   static constexpr int kB = 0, kU = 64, kS = 128, kW = 192, kRef = 320, kDec = 336, GATE_BYTES = 352 * 4;
   static constexpr int P_BYTES = 3 * 2048;  // per head: the chunk's weights, three blocks of 32 x 32 in bf16
-  // 64/64, one head: two workgroups per compute unit (three wavefronts per SIMD)
-  static constexpr int WAVES_PER_SIMD = DQK == 64 && DV == 64 && HPW == 1 ? 3 : 2;
+  // 64/64, one head: two workgroups of six wavefronts per compute unit.  Both begin on the same SIMD, which gives two of the SIMDs
+  // four wavefronts: 128 registers each.  With 144, for three, only one workgroup was resident, and 257 pairs took two rounds:
+  // 9 x 32 heads x 1024 60 us, 42 now; 8 x 48 x 1024 62 / 47, its backward pass 229 / 184; 5 x 32 x 768 backward 74 / 55.
+  // BOUND_THREADS: what the launch bound says, so that the compiler counts four wavefronts too.
+  static constexpr bool SHARES_CU = DQK == 64 && DV == 64 && HPW == 1;
+  static constexpr int WAVES_PER_SIMD = SHARES_CU ? 4 : 2, BOUND_THREADS = SHARES_CU ? 512 : THREADS;
 };
 
 // LDS layout: a stage holds the tiles Q (full walks only), K, V of every head
@@ -80,7 +84,7 @@ struct GLayout {
   static constexpr bool kOutInQ = C::Q_BYTES >= C::SW * 4096;
   static constexpr int kOut = kGates + C::HPW * C::GATE_BYTES;
   static constexpr int LDS_BYTES = kOut + (STATE_ONLY || kOutInQ ? 0 : C::SW * 4096);
-  static_assert(LDS_BYTES <= 160 * 1024 / (C::WAVES_PER_SIMD == 3 ? 2 : 1), "tiles do not fit LDS");
+  static_assert(LDS_BYTES <= 160 * 1024 / (C::SHARES_CU ? 2 : 1), "tiles do not fit LDS");
 };
 
 // x of the lane that the control word selects, 0 where it selects none or the masks switch the lane off
@@ -104,17 +108,19 @@ __device__ __forceinline__ uint32_t tr_lane(int lane, int k, int j, int piece) {
 }
 // pieces 1 and 2 of every 16 columns exchanged: the order that makes a lane's eight packed state registers consecutive rows d
 __device__ __forceinline__ int swapped_piece(int lane) { return 2 * (lane & 1) + ((lane >> 1) & 1); }
-// row fragment of Q or K for d-step t (d = 16 t + 8 half + {0..7}), row lane % 32 of a 32-row block
+// row fragment of Q or K for d-step 0 (d = 16 t + 8 half + {0..7} in step t), row lane % 32 of a 32-row block; in step t the
+// address (tiles stand at multiples of 256 bytes) is that of step 0 with the bits of 32 t turned over
 template <class C>
-__device__ __forceinline__ uint32_t row_lane(int lane, int t) {
-  return (uint32_t)((lane & 31) * C::RBQ + (((2 * t + (lane >> 5)) ^ bswz<C::CPRQ>(lane & 31)) << 4));
+__device__ __forceinline__ uint32_t row_lane(int lane) {
+  return (uint32_t)((lane & 31) * C::RBQ + (((lane >> 5) ^ bswz<C::CPRQ>(lane & 31)) << 4));
 }
 
 // ---- a state wavefront's share of a chunk ----
 // O^T = H^T Q^T for both blocks of 32 queries (H rounded to bf16); in the same pass over the accumulators H takes the chunk's
-// whole decay.  q: the lane's fragment addresses rq plus the queries' tile.
+// whole decay.  q: the lane's address of the first fragment of the queries.
 template <class C>
-__device__ __forceinline__ void read_out(f32x16 (&H)[C::DBQ], float dec, const uint32_t (&rq)[C::T], uint32_t q, f32x16& o0, f32x16& o1) {
+__device__ __forceinline__ void read_out(f32x16 (&H)[C::DBQ], float dec, uint32_t q, f32x16& o0, f32x16& o1) {
+  pin(q);
   o0 = zero16();
   o1 = zero16();
 #pragma unroll
@@ -128,7 +134,7 @@ __device__ __forceinline__ void read_out(f32x16 (&H)[C::DBQ], float dec, const u
     }
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
-      const uint32_t a = q + rq[2 * db + tt];
+      const uint32_t a = q ^ (32 * (2 * db + tt));
       o0 = mfma(hp[tt], read_k_frag(a), o0);
       o1 = mfma(hp[tt], read_k_frag(a + 32 * C::RBQ), o1);
     }
@@ -150,6 +156,14 @@ __device__ __forceinline__ void update_state(f32x16 (&H)[C::DBQ], const bf16x8 (
   f32x4 wv[8];
 #pragma unroll
   for (int s = 0; s < 8; ++s) wv[s] = lds_read16(w + 32 * s);
+  uint32_t ka[C::DBQ][2];
+#pragma unroll
+  for (int db = 0; db < C::DBQ; ++db)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      ka[db][j] = k + kt[db][j];
+      pin(ka[db][j]);
+    }
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     bf16x8 vw;
@@ -160,18 +174,20 @@ __device__ __forceinline__ void update_state(f32x16 (&H)[C::DBQ], const bf16x8 (
     }
 #pragma unroll
     for (int db = 0; db < C::DBQ; ++db)
-      H[db] = mfma(read_tr_frag(k + kt[db][0] + 16 * s * C::RBQ, k + kt[db][1] + 16 * s * C::RBQ), vw, H[db]);
+      H[db] = mfma(read_tr_frag(ka[db][0] + 16 * s * C::RBQ, ka[db][1] + 16 * s * C::RBQ), vw, H[db]);
   }
 }
 // One block of 32 queries x 32 columns, turned around in the wavefront's 4 KB of LDS (16-byte chunk k of row r at k ^ (r % 8)):
 // afterwards v[k] holds columns 4 (lane % 8) .. + 3 of row 8 k + lane / 8.
 __device__ __forceinline__ void turn_around(uint32_t out, int lane, const f32x16& o, f32x4 (&v)[4]) {
   const int ln = lane & 31, half = lane >> 5, row = lane >> 3;
+  uint32_t w = out + ln * 128 + ((half ^ (ln & 7)) << 4), r = out + row * 128 + (((lane & 7) ^ row) << 4);
+  pin(w);
+  pin(r);
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-    lds_write16(out + ln * 128 + (((2 * a + half) ^ (ln & 7)) << 4), (f32x4){o[4 * a], o[4 * a + 1], o[4 * a + 2], o[4 * a + 3]});
+  for (int a = 0; a < 4; ++a) lds_write16(w ^ (32 * a), (f32x4){o[4 * a], o[4 * a + 1], o[4 * a + 2], o[4 * a + 3]});
 #pragma unroll
-  for (int k = 0; k < 4; ++k) v[k] = lds_read16(out + (8 * k + row) * 128 + (((lane & 7) ^ row) << 4));
+  for (int k = 0; k < 4; ++k) v[k] = lds_read16(r + 1024 * k);
 }
 
 // ---- the helpers' shares ----
@@ -204,12 +220,14 @@ __device__ __forceinline__ float put_factors(uint32_t gate, int lane, int odd, f
   }
   return b_last;
 }
-// scores of a 32 x 32 block: K rows at kt, Q rows at qt
+// scores of a 32 x 32 block; k, q: the lane's addresses of their first row fragments
 template <class C>
-__device__ __forceinline__ f32x16 block_scores(const uint32_t (&rq)[C::T], uint32_t kt, uint32_t qt) {
+__device__ __forceinline__ f32x16 block_scores(uint32_t k, uint32_t q) {
+  pin(k);
+  pin(q);
   f32x16 s = zero16();
 #pragma unroll
-  for (int t = 0; t < C::T; ++t) s = mfma(read_k_frag(kt + rq[t]), read_k_frag(qt + rq[t]), s);
+  for (int t = 0; t < C::T; ++t) s = mfma(read_k_frag(k ^ (32 * t)), read_k_frag(q ^ (32 * t)), s);
   return s;
 }
 // weights of the block: scale e^{b_i - b_j} g_j (q_i . k_j) for key j <= query i (positions inside the chunk), else 0; inside a
@@ -332,9 +350,8 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
       }
       pin(H[db]);
     }
-    uint32_t rq0[C::T], kt0[C::DBQ][2], vt0[2];
-#pragma unroll
-    for (int t = 0; t < C::T; ++t) rq0[t] = row_lane<C>(lane, t);
+    uint32_t kt0[C::DBQ][2], vt0[2];
+    const uint32_t rq0 = row_lane<C>(lane);
 #pragma unroll
     for (int k = 0; k < C::DBQ; ++k)
 #pragma unroll
@@ -345,9 +362,11 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
       update_state<C>(H, vf, gate + (C::kW + (c & 1) * 64 + 4 * half) * 4, stage_of(c) + Y::kK, kt0);
     };
     auto v_frags = [&](int c, bf16x8 (&vf)[4]) {
-      const uint32_t sb = stage_of(c);
+      uint32_t a0 = stage_of(c) + vt0[0], a1 = stage_of(c) + vt0[1];
+      pin(a0);
+      pin(a1);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) vf[s] = read_tr_frag(sb + vt0[0] + 16 * s * C::RBV, sb + vt0[1] + 16 * s * C::RBV);
+      for (int s = 0; s < 4; ++s) vf[s] = read_tr_frag(a0 + 16 * s * C::RBV, a1 + 16 * s * C::RBV);
     };
 
     if constexpr (STATE_ONLY) {
@@ -366,7 +385,10 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
     } else {
       chunk_barrier();
       chunk_barrier();
+      // eight rows at a time: their lowest address is the same for all lanes, the rest of it the lane's own
       const int64_t o_head = (int64_t)bh * Lt + row_lo;
+      const int o_log = p.out_bf16 ? 1 : 2;
+      const uint32_t o_lane = (uint32_t)((rev ? 7 - (lane >> 3) : lane >> 3) * C::DV + 4 * (lane & 7)) << o_log;
       for (int c = 0; c < n_chunks; ++c) {
         const uint32_t sb = stage_of(c);
         const int t0 = c * C::CH;
@@ -381,7 +403,7 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
           g1 = lds_read4(gate + (C::kS + 32 + ln) * 4);
         }
         f32x16 o0, o1;
-        read_out<C>(H, dec, rq0, sb, o0, o1);
+        read_out<C>(H, dec, sb + rq0, o0, o1);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           o0[r] *= f0;
@@ -407,16 +429,16 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
           turn_around(out, lane, o, v);
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            const int i = t0 + 32 * IB + 8 * k + (lane >> 3);
-            if (i < L) {
-              const int64_t e0 = (o_head + (rev ? L - 1 - i : i)) * C::DV + 32 * vblk + 4 * (lane & 7);
+            const int i0 = t0 + 32 * IB + 8 * k;
+            if (lane >> 3 < L - i0) {
+              char* dst = static_cast<char*>(p.O) + (((o_head + (rev ? L - 8 - i0 : i0)) * C::DV + 32 * vblk) << o_log) + o_lane;
               if (p.out_bf16) {
                 bf16x4 hv;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) hv[e] = (__bf16)v[k][e];
-                *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.O) + e0) = hv;
+                *reinterpret_cast<bf16x4*>(dst) = hv;
               } else {
-                *reinterpret_cast<f32x4*>(static_cast<float*>(p.O) + e0) = v[k];
+                *reinterpret_cast<f32x4*>(dst) = v[k];
               }
             }
           }
@@ -498,10 +520,8 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
   // scores of this helper's block in front of the weights: role 0: keys 0-31 x queries 0-31, 1: 32-63 x 32-63, 2: 0-31 x 32-63
   const int kb = role == 1 ? 1 : 0, qb = role == 0 ? 0 : 1;
   const int last_key = role == 2 ? C::CH : ln;  // inside a diagonal block keys behind the lane's query get weight 0
-  uint32_t rq0[C::T];
-#pragma unroll
-  for (int t = 0; t < C::T; ++t) rq0[t] = row_lane<C>(lane, t);
-  auto scores = [&](int c) { return block_scores<C>(rq0, stage_of(c) + Y::kK + 32 * kb * C::RBQ, stage_of(c) + 32 * qb * C::RBQ); };
+  const uint32_t rq0 = row_lane<C>(lane);
+  auto scores = [&](int c) { return block_scores<C>(stage_of(c) + Y::kK + 32 * kb * C::RBQ + rq0, stage_of(c) + 32 * qb * C::RBQ + rq0); };
   auto weigh = [&](const f32x16& sc) {
 #pragma unroll
     for (int hh = 0; hh < C::HPW; ++hh) block_weights<C>(sc, p.scale, gates_of(hh), lane, kb, qb, last_key, lds0 + Y::kP + hh * C::P_BYTES + role * 2048);
@@ -558,11 +578,11 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
   }
 }
 
-template <class C, bool STATE_ONLY, bool OUT_GATE = false>
-__global__ __launch_bounds__(C::THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt, int first_block) {
+template <class C, bool STATE_ONLY>
+__global__ __launch_bounds__(C::BOUND_THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[GLayout<C, STATE_ONLY>::LDS_BYTES];
-  gated_walk<C, STATE_ONLY, OUT_GATE>(p, first_block + (int)blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
-                            [&](int h) { return dt.log2_gamma[h] * 0.6931471805599453f; });  // ln gamma
+  gated_walk<C, STATE_ONLY, false>(p, first_block + (int)blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
+                                   [&](int h) { return dt.log2_gamma[h] * 0.6931471805599453f; });  // ln gamma
 }
 
 // ---- backward pass where value heads share a q/k head: the gradients of q and k, summed over heads ----
@@ -604,9 +624,8 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
     for (int n = 0; n < C::HEADS; ++n)
 #pragma unroll
       for (int db = 0; db < C::DBQ; ++db) H[n][db] = zero16();
-    uint32_t rq0[C::T], kt0[C::DBQ][2], vt0[2], rr0[4];
-#pragma unroll
-    for (int t = 0; t < C::T; ++t) rq0[t] = row_lane<C>(lane, t);
+    uint32_t kt0[C::DBQ][2], vt0[2], rr0[4];
+    const uint32_t rq0 = row_lane<C>(lane);
 #pragma unroll
     for (int k = 0; k < C::DBQ; ++k)
 #pragma unroll
@@ -633,7 +652,7 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
           const float f1 = p.scale * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
           const float g0 = lds_read4(gate + (C::kS + ln) * 4), g1 = lds_read4(gate + (C::kS + 32 + ln) * 4);
           f32x16 o0, o1;
-          read_out<C>(H[n], dec, rq0, sb, o0, o1);
+          read_out<C>(H[n], dec, sb + rq0, o0, o1);
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             o0[r] *= f0;
@@ -763,10 +782,8 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
   // ================= copies (helper 0: queries, 1: keys of a unit, 2: values and rows of a chunk) and weights =================
   const int kb = role == 1 ? 1 : 0, qb = role == 0 ? 0 : 1;
   const int last_key = role == 2 ? C::CH : ln;
-  uint32_t rq0[C::T];
-#pragma unroll
-  for (int t = 0; t < C::T; ++t) rq0[t] = row_lane<C>(lane, t);
-  auto scores = [&](int st) { return block_scores<C>(rq0, unit_stage(st) + C::Q_BYTES + 32 * kb * C::RBQ, unit_stage(st) + 32 * qb * C::RBQ); };
+  const uint32_t rq0 = row_lane<C>(lane);
+  auto scores = [&](int st) { return block_scores<C>(unit_stage(st) + C::Q_BYTES + 32 * kb * C::RBQ + rq0, unit_stage(st) + 32 * qb * C::RBQ + rq0); };
   auto help = [&](auto&& start, auto&& copy, auto&& landed) {
     start();
     chunk_barrier();
@@ -848,7 +865,8 @@ struct GatedBackwardWalks {
 template <class A, class E, bool STATE_ONLY, bool GROUP>
 struct BackwardCfg {
   static constexpr int THREADS = A::THREADS > E::THREADS ? A::THREADS : E::THREADS;
-  static constexpr int WAVES_PER_SIMD = A::WAVES_PER_SIMD < E::WAVES_PER_SIMD || GROUP ? 2 : E::WAVES_PER_SIMD;
+  static constexpr bool SHARES_CU = A::SHARES_CU && E::SHARES_CU && !GROUP;
+  static constexpr int WAVES_PER_SIMD = SHARES_CU ? 4 : 2, BOUND_THREADS = SHARES_CU ? 512 : THREADS;
   static constexpr int first_two() {
     if constexpr (GROUP) return A::LDS_BYTES;
     else return GLayout<A, STATE_ONLY>::LDS_BYTES;
@@ -857,7 +875,7 @@ struct BackwardCfg {
   static constexpr int LDS_BYTES = first_two() > THIRD ? first_two() : THIRD;
 };
 template <class A, class E, bool STATE_ONLY, bool GROUP, bool GATED>
-__global__ __launch_bounds__((BackwardCfg<A, E, STATE_ONLY, GROUP>::THREADS), (BackwardCfg<A, E, STATE_ONLY, GROUP>::WAVES_PER_SIMD))
+__global__ __launch_bounds__((BackwardCfg<A, E, STATE_ONLY, GROUP>::BOUND_THREADS), (BackwardCfg<A, E, STATE_ONLY, GROUP>::WAVES_PER_SIMD))
 void gated_backward_kernel(const GatedBackwardWalks w) {
   typedef BackwardCfg<A, E, STATE_ONLY, GROUP> C;
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
@@ -905,13 +923,25 @@ hipError_t launch_in_parts(int64_t blocks, int threads, F&& launch) {
   return e;
 }
 
-template <int DQK, int DV, int HPW = 1, bool OUT_GATE = false>
+// LDS that a launch asks for on top, so that workgroups which could share a compute unit (GCfg::SHARES_CU) have one each.  Sharing
+// evens out the last round and covers the start and the end of a walk; where the rounds of one each are full (at least `fill` of their places taken) and the calls stream through memory, one each reads it better (us, shared / one
+// each): 9 x 32 heads x 2048 102 / 120, 12 x 32 x 2048 111 / 119, 18 x 32 x 2048 184 / 188, 64 x 32 x 512 135 / 142, 16 x 32 x 1024 70 / 71; but
+// 15 x 32 x 2048 133 / 128, 28 x 32 x 2048 264 / 247, 32 x 32 x 2048 278 / 260, 16 x 64 x 1024 141 / 137.  Backward: 12 x 32 x 2048 406 / 439,
+// 8 x 32 x 1024 124 / 134, 20 x 32 x 2048 687 / 703; 8 x 32 x 4096 549 / 544, 8192 1100 / 1078.
+static int lds_for_one_each(int64_t workgroups, int64_t tokens, int64_t from_tokens, double fill) {
+  const int64_t rounds = (workgroups + 255) / 256;
+  return tokens >= from_tokens && workgroups * tokens >= 900000 && workgroups >= fill * 256 * rounds ? 1024 : 0;
+}
+
+template <int DQK, int DV, int HPW = 1>
 hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
   typedef GCfg<DQK, DV, HPW> C;
-  if (p.gate_on_output && !OUT_GATE && !p.state_only) return hipErrorInvalidValue;
-  return launch_in_parts((int64_t)p.B * p.H / HPW * p.nseg, C::THREADS, [&](int first, dim3 grid) {
+  if (p.gate_on_output && !p.state_only) return hipErrorInvalidValue;
+  const int64_t blocks = (int64_t)p.B * p.H / HPW * p.nseg;
+  const int lds = C::SHARES_CU && p.nseg == 1 ? lds_for_one_each(blocks, p.L, 1024, 0.85) : 0;
+  return launch_in_parts(blocks, C::THREADS, [&](int first, dim3 grid) {
     if (p.state_only) hipLaunchKernelGGL((gated_recurrent_kernel<C, true>), grid, dim3(C::THREADS), 0, s, p, dt, first);
-    else hipLaunchKernelGGL((gated_recurrent_kernel<C, false, OUT_GATE>), grid, dim3(C::THREADS), 0, s, p, dt, first);
+    else hipLaunchKernelGGL((gated_recurrent_kernel<C, false>), grid, dim3(C::THREADS), lds, s, p, dt, first);
   });
 }
 
@@ -1091,6 +1121,7 @@ static hipError_t launch_walks(GatedBackwardWalks& w, int64_t blocks, hipStream_
   constexpr int kThreads = BackwardCfg<A, E, false, GROUP>::THREADS;
   static_assert(GROUP || BackwardCfg<A, E, true, false>::THREADS == kThreads, "");
   const bool gated = w.walk[GROUP ? 2 : 0].gate_on_output != 0;
+  const int lds = BackwardCfg<A, E, false, GROUP>::SHARES_CU && w.walk[0].nseg == 1 ? lds_for_one_each(blocks, w.walk[0].L, 4096, 0.95) : 0;
   return launch_in_parts(blocks, kThreads, [&](int first, dim3 grid) {
     w.first_block = first;
     if constexpr (!GROUP) {
@@ -1099,8 +1130,8 @@ static hipError_t launch_walks(GatedBackwardWalks& w, int64_t blocks, hipStream_
         return;
       }
     }
-    if (gated) hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, true>), grid, dim3(kThreads), 0, s, w);
-    else hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, false>), grid, dim3(kThreads), 0, s, w);
+    if (gated) hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, true>), grid, dim3(kThreads), lds, s, w);
+    else hipLaunchKernelGGL((gated_backward_kernel<A, E, false, GROUP, false>), grid, dim3(kThreads), lds, s, w);
   });
 }
 
@@ -1132,18 +1163,7 @@ hipError_t launch_gated_backward(const GatedParams (&walk)[3], const GatedGroupP
     return pairs ? launch_walks<GroupCfg<64, 128>, GCfg<128, 64, 2>, true>(w, blocks, s) : launch_walks<GroupCfg<64, 128>, GCfg<128, 64>, true>(w, blocks, s);
   }
   if (pairs) return hipErrorInvalidValue;
-  if (dqk == 64 && dv == 64) {
-    // Two workgroups share a compute unit here, each the slower for it: where a walk by itself gives every compute unit one and
-    // its chunks outweigh two more launches, one behind the other (us, one launch / three: 8 x 32 heads x 768 109.6 / 105.4, 6 x 32 x
-    // 2000 258 / 247; but 8 x 32 x 200 43.2 / 44.3, 5 x 32 x 768 75 / 95, 9 x 32 x 768 136 / 173).
-    if (!w.walk[0].state_only && blocks > 3 * 160 && blocks <= 3 * 256 && w.walk[0].L >= 320) {
-      static const DecayTable none = {};
-      hipError_t e = hipSuccess;
-      for (int i = 0; i < 3 && e == hipSuccess; ++i) e = w.walk[i].gate_on_output ? launch<64, 64, 1, true>(w.walk[i], none, s) : launch<64, 64>(w.walk[i], none, s);
-      return e;
-    }
-    return launch_walks<GCfg<64, 64>, GCfg<64, 64>>(w, blocks, s);
-  }
+  if (dqk == 64 && dv == 64) return launch_walks<GCfg<64, 64>, GCfg<64, 64>>(w, blocks, s);
   if (dqk == 128 && dv == 128) return launch_walks<GCfg<128, 128>, GCfg<128, 128>>(w, blocks, s);
   if (dqk == 64 && dv == 128) return launch_walks<GCfg<128, 64>, GCfg<64, 128>>(w, blocks, s);
   if (dqk == 128 && dv == 64) return launch_walks<GCfg<64, 128>, GCfg<128, 64>>(w, blocks, s);

@@ -184,6 +184,19 @@ def test_sampled_heads_at_benchmark_size(A):
         check(got[b, h].double().numpy(), ref, f"benchmark size head ({b},{h})")
 
 
+@pytest.mark.parametrize("B,L", [(9, 1), (9, 130), (16, 1000), (30, 1024)])
+def test_workgroups_that_share_a_compute_unit(A, B, L):
+    # 64/64, 288 and 512 (batch, head) pairs: two workgroups on a compute unit; 960 x 1024 tokens: one again.  The same values as 32
+    # pairs at a time, which have one each
+    g = torch.Generator("cuda").manual_seed(90)
+    Q, K, V = (torch.randn(B, 32, L, 64, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    la, kg = (torch.rand(B, 32, L, generator=g, device="cuda") * f for f in (-0.2, 1.0))
+    whole, h = A.gated_recurrent(Q, K, V, la, kg, scale=0.125, want_state=True)
+    for b in range(B):
+        part, h_part = A.gated_recurrent(*(t[b:b + 1].contiguous() for t in (Q, K, V, la, kg)), scale=0.125, want_state=True)
+        assert torch.equal(whole[b:b + 1], part) and torch.equal(h[b:b + 1], h_part), b
+
+
 def test_more_workgroups_than_one_launch_holds(A):
     # 8.4 million (batch, head) pairs of one token, 512 threads each: more than 2^32 threads.  o = scale g (q . k) v, whose weight is
     # rounded to bf16 (2^-9 of itself) behind a sum in 32 bits (128 terms: 2^-17 of the sum of their absolute values)

@@ -201,7 +201,7 @@ def test_gate_multiplies_finished_rows_of_dv(A, dqk, dv, B, H, H_qk, L):
 
 @pytest.mark.parametrize("dqk,dv", [(64, 64), (128, 64), (64, 128), (128, 128)])
 def test_batch_entries_do_not_depend_on_the_launches(A, dqk, dv):
-    # 180 (batch, head) pairs: one launch for the three walks or (64/64) one each; 60 at a time always take one
+    # 180 (batch, head) pairs: more workgroups than compute units, of which (64/64) two share one; 60 at a time have one each
     Q, K, V, la, kg, dO = inputs(940, 3, 60, 60, 321, dqk, dv, "mamba2")
     whole = run(A, Q, K, V, la, kg, dO, 0.1)
     for b in range(3):
@@ -252,6 +252,19 @@ def test_sampled_heads_at_benchmark_size(A):
         qn, kn = Q[b, h].float().numpy().astype(np.float64), K[b, h].float().numpy().astype(np.float64)
         b_dla = token_bounds_proxy(np.sum(qn * ref["dq"], axis=-1), np.sum(kn * ref["dk"], axis=-1))
         check_tokens(dla[b, h], b_dla, ref["dlog_decay"], f"benchmark size ({b},{h}) dlog_decay")
+
+
+def test_one_workgroup_per_compute_unit_again_at_many_tokens(A):
+    # 64/64: the three walks of 256 pairs x 4096 fill three rounds of one workgroup per compute unit each; those of 128 pairs share
+    B, H, L = 8, 32, 4096
+    g = torch.Generator("cuda").manual_seed(91)
+    Q, K, V, dO = (torch.randn(B, H, L, 64, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    la = torch.nn.functional.logsigmoid(torch.randn(B, H, L, generator=g, device="cuda")) / 16
+    whole = A.gated_recurrent_backward(Q, K, V, la, None, dO, scale=0.125)
+    for b in (0, 4):
+        part = A.gated_recurrent_backward(*(t[b:b + 4].contiguous() for t in (Q, K, V, la)), None, dO[b:b + 4].contiguous(), scale=0.125)
+        for x, y in zip(whole[:4], part[:4]):
+            assert torch.equal(x[b:b + 4], y)
 
 
 @pytest.mark.parametrize("B,H_qk", [(59375, 64), (89063, 32)])
