@@ -29,15 +29,23 @@ constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
 // Both sides go in one launch (the key side's workgroups first): two launches / one, us, causal unless said: 64/64 1 x 16 heads x
 // 1024 54 / 34, 1 x 16 x 4096 186 / 140, 4 x 32/8 x 2048 335 / 289, 8 x 16 x 2048 unmasked 506 / 510, with a bias tensor 2 x 12 x 1023 x 1201
 // 85 / 68; 192/128 1 x 16 x 500 53 / 33, 1 x 6 x 4096 259 / 172, 1 x 128 x 4096 2597 / 2607; 128/256 2 x 16 x 1024 100 / 74, 4 x 16 x
-// 2048 438 / 433.  Three exceptions:
+// 2048 438 / 433.  Four exceptions:
+//   * 64/64 without a bias tensor: alone, the query side has 134 registers, three workgroups per CU; beside the key side it has that
+//     one's 202, two.  What the shared launch saves is at its ends: calls of much work (the keys that the query workgroups of an XCD
+//     walk, see walked_keys), whose key side fills the device, go one behind the other.  Causal (thousands of walked keys): 1 x 16 x 8192 (524)
+//     510 / 490, 1 x 64 x 4096 (524) 535 / 532, 8 x 12 x 4096 (786) 806 / 810, 1 x 32 x 8192 (1049) 970 / 989, 1 x 64 x 8192 (2097) 1963 / 2000; with
+//     64 workgroups of the key side per XCD 1 x 128/16 x 4096 (1049) 1207 / 1047, with 128 4 x 32/8 x 4096 1024 / 1027.  Unmasked 8 x 16 x 1024
+//     (131) 151 / 146, 1 x 16 x 4096 (262) 249 / 245, 1 x 32 x 4096 (524) 480 / 483, 8 x 64 x 1024 (524) 584 / 593, 8 x 16 x 4096 (2097) 1882 / 1930.
 //   * 128/128 without a bias tensor: beside the key side's workgroups those of the query side get a CU each, which they otherwise
 //     share by two.  It pays while the key side leaves compute units idle: few workgroups (of 32 compute units per XCD), or
 //     causal ones of unequal length.  Causal (workgroups of the key side per XCD): 1 x 16 x 1024 (16) 75 / 44, 1 x 32/8 x 4096 (32) 676 / 550,
 //     2 x 12 x 2048 (48) 139 / 127, but 8 x 24/6 x 1000 (48) 297 / 332, 8 x 12 x 700 (72) 104 / 109, 4 x 32/8 x 2048 (64) 552 / 597; unmasked
 //     1 x 32/8 x 2048 (16) 332 / 256, 2 x 32/8 x 1500 (24) 298 / 290, 1 x 16 x 2048 (32, 64 of both sides) 142 / 141, but 2 x 32/8 x 2048 (32)
 //     461 / 506, 2 x 12 x 2048 (48) 221 / 252.
-//   * 192/128, causal, very many workgroups: the end of one side among the start of the other costs more in the L2 than it fills (1 x
-//     128 heads x 8192, 2048 workgroups of both sides per XCD, 10.00 / 10.07 ms; 4096 2.60 / 2.60, 8 x 16 x 1024 unmasked 0.397 / 0.383).
+//   * 192/128, causal, much work: the two sides among each other cost more in the L2 than the ends save (thousands of walked keys; on a
+//     second card the long calls were alike either way): 1 x 128 heads x 2048 (262) 812 / 798, 8 x 128 x 1024 (524) 2077 / 2064, 1 x 64 x 4096 (524)
+//     1367 / 1366, 1 x 128 x 3500 (784) 2108 / 2122, 1 x 24 x 8192 (786) 1855 / 1883, 1 x 128 x 4096 (1049) 2731 / 2755, 1 x 128/16 x 4096 (1049) 2657 /
+//     2693, 1 x 64 x 6000 (1128) 2781 / 2828, 1 x 128 x 8192 (4194) 10216 / 10286.  Unmasked: 8 x 16 x 1024 397 / 383, 1 x 64 x 4096 2413 / 2432.
 //   * 128/256, abs-sum family: as one kernel it spills 26 registers instead of 9.  2 x 16 x 1024 (64 workgroups of both sides per XCD)
 //     117 / 91, 1 x 24/6 x 2048 (80) 480 / 422, 2 x 16 x 2048 (128) 254 / 263, 4 x 16 x 2048 (256) 511 / 533.
 // The workgroups of a side: whole sets of `together` groups (or parts of groups) per XCD (the kernels' mapping): sets x together x
@@ -50,6 +58,13 @@ inline int64_t side_per_group(const BwdParams& p, bool key_side) {
 inline int64_t side_blocks(const BwdParams& p, bool key_side) {
   const int64_t tg = p.together[key_side ? 1 : 0];
   return tg < 1 ? -1 : (side_rounds(p) + tg - 1) / tg * tg * 8 * side_per_group(p, key_side);
+}
+
+// The keys that the query side's workgroups of an XCD walk together.
+template <bool CAUSAL>
+int64_t walked_keys(const BwdParams& p) {
+  const int64_t keys = CAUSAL ? p.L_k / 2 : p.L_k;
+  return side_rounds(p) * side_per_group(p, false) * std::min<int64_t>(keys, p.window);
 }
 
 template <class C>
@@ -97,7 +112,8 @@ hipError_t launch_kernels(const BwdParams& p, const DecayTable& dt, hipStream_t 
       const int64_t walk = std::min((int64_t)p.L_q * p.g, (int64_t)p.L_k);
       if (workgroups <= units_per_xcd(CAUSAL) && walk / (CAUSAL ? 2 : 1) >= kLongBiasWalk) return launch_both<K2, Q2>(p, dt, s);
     }
-    return launch_both<K1, Q1>(p, dt, s);
+    if constexpr (BIAS) return launch_both<K1, Q1>(p, dt, s);
+    else return launch_sides<K1, Q1>(p, dt, s, walked_keys<CAUSAL>(p) < (CAUSAL ? 750000 : 500000) || key_wgs < (CAUSAL ? 128 : 64));
   } else {
     auto is_short = [&](int64_t rows, int64_t heads) {
       const int64_t window = p.window < rows ? p.window : 0;
@@ -113,7 +129,7 @@ hipError_t launch_kernels(const BwdParams& p, const DecayTable& dt, hipStream_t 
       if constexpr (CAUSAL && (!BIAS || DQK == 128))
         if (is_short(p.L_q, p.g) && is_short(p.L_k, 1)) return launch_both<K1, Q1>(p, dt, s);
       if constexpr (K2::ABS && DV == 256) return launch_sides<K2, Q2>(p, dt, s, workgroups <= 96);
-      else if constexpr (DQK == 192 && CAUSAL) return launch_sides<K2, Q2>(p, dt, s, workgroups <= 1024);
+      else if constexpr (DQK == 192 && CAUSAL) return launch_sides<K2, Q2>(p, dt, s, walked_keys<true>(p) < 700000 || key_wgs < 64);
       else return launch_both<K2, Q2>(p, dt, s);
     }
   }

@@ -184,6 +184,22 @@ def test_backward_batch_entries_do_not_depend_on_the_launches(A, dims, kw):
             assert torch.equal(x[b:b + 1], y)
 
 
+@pytest.mark.parametrize("dims,mask,B,H,L", [((64, 64), "none", 8, 16, 2048), ((64, 64), "causal", 8, 16, 3500), ((192, 128), "causal", 2, 64, 4095)],
+                         ids=["d64", "d64_causal", "d192_causal"])
+def test_backward_calls_of_much_work_take_a_launch_for_each_side(A, dims, mask, B, H, L):
+    # all batch entries at once stand beyond the line, one at a time in front of it: the same values
+    g = torch.Generator("cuda").manual_seed(49)
+    Q, K, V, dO = (torch.randn(B, H, L, D, generator=g, device="cuda", dtype=torch.bfloat16) for D in (dims[0], dims[0], dims[1], dims[1]))
+    stats = torch.empty((B, H, L), dtype=torch.float32, device="cuda")
+    args = dict(scale=dims[0] ** -0.5, mask=mask)
+    O = A.attention_forward(Q, K, V, stats=stats, **args)
+    whole = A.attention_backward(Q, K, V, O, dO, stats, **args)
+    for b in range(B):
+        part = A.attention_backward(*(t[b:b + 1].contiguous() for t in (Q, K, V, O, dO, stats)), **args)
+        for x, y in zip(whole, part):
+            assert torch.equal(x[b:b + 1], y)
+
+
 @pytest.mark.parametrize("dims", [(64, 64), (128, 128), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
 @pytest.mark.parametrize("mask", ["none", "causal"])
 @pytest.mark.parametrize("n", [1, 2, 3, 6])
