@@ -1321,10 +1321,11 @@ __global__ __launch_bounds__(C::THREADS) void attn_fwd_kernel(const Params p, co
     kcp = kbase + (jtm + 2) * ktile_step;  // the first tile the short form copies
     vcp = vbase + (jtm + 2) * vtile_step;
     int pos = 0;
-    // 192/128: the loop's place in memory must not depend on the length of the code in front of it.  Of twelve places tried, 1 x 128
+    // The loop's place in memory must not depend on the length of the code in front of it.  192/128: of twelve places tried, 1 x 128
     // heads x 8192, causal, took 2112 to 2126 us; longer address arithmetic of the prologue had moved it to one of the slow ones (2254 us
-    // became 2271, on another box 2144 became 2162; with this 2145).  The other head dims and the unmasked form showed no difference.
-    if constexpr (C::DQK == 192) asm volatile(".p2align 7");
+    // became 2271, on another card 2144 became 2162; with this 2145).  128/128, sigmoid: 1 x 16 x 2048 causal 50.1 had become 50.7, so 50.2;
+    // 1 x 16 x 1000 unmasked 29.0, 29.4, 29.0.  The other kernels showed no difference.
+    if constexpr (C::DQK == 192 || (C::DQK == 128 && C::DV == 128 && C::NORM == NORM_SIGMOID)) asm volatile(".p2align 7");
     for (; pos < n_fast; ++pos) iteration(std::true_type{}, pos);
     for (; pos < n_walk; ++pos) iteration(std::false_type{}, pos);
     if (!trailing) phase_barrier();  // both halves are at the same point again
