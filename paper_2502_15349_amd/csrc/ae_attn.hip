@@ -1068,9 +1068,9 @@ ae_status_t ae_recurrent_destroy(ae_recurrent_t* h) {
 // head per workgroup and the sums in a kernel of their own (where that walk is not built or cut into segments).  Few heads fill
 // the device, many leave fewer parts to sum; the time is estimated in units of a walk over one head (16 us at 768 tokens):
 // heads + 1 for a workgroup of the first two walks, 1.6 to 2.4 for one of the third (which takes one head or two), handed to 256
-// compute units in this order, and the sum kernel's bytes.  Measured (us for 1 / 2 / 3 heads, 768 tokens): Mamba2 128/64 1 x 80 heads 52 / 63
-// / 79, 2 x 80 93 / 68 / 81, 4 x 80 208 / 127 / 120, 8 x 64 307 / 205 / 172, 8 x 80 391 / 270 / 224, 8 x 32/8 x 600 129 / 96 / 109;
-// 64/64 4 x 32/8 69 / 59 / 75, 8 x 24 94 / 81 / 74, 8 x 64 223 / 161 / 166.
+// compute units in this order, and the sum kernel's bytes.  Measured (us for 1 / 2 / 3 heads, 768 tokens): Mamba2 128/64 1 x 80 heads 49 / 59
+// / 72, 2 x 80 88 / 63 / 75, 4 x 80 199 / 118 / 112, 8 x 64 297 / 197 / 163, 8 x 80 377 / 259 / 216, 8 x 32/8 x 600 126 / 92 / 102;
+// 64/64 4 x 32/8 66 / 54 / 67, 8 x 24/8 93 / 82 / 71, 8 x 64/1 200 / 137 / 131.
 static double gated_walks_time(int64_t first_two, double cost, int64_t third, double cost3) {
   // all compute units are busy until `lo`, `n_hi` of them until `hi`; the third walk's workgroups go where one is free first
   double lo = (double)(first_two / 256) * cost, hi = lo + cost;
@@ -1106,8 +1106,16 @@ static int gated_group_heads(const ae_gated_desc_t* d, int bwd_nseg, int* third)
 }
 // Value heads of a q/k head that a workgroup of the forward walk takes, and the segments of its walk if it may be cut.  Two heads
 // share the tiles and the scores; a chunk then takes 1.23 (64/64) or 1.12 times as long as with one, and half the workgroups do.
-// Measured (us, one head / two): Mamba2 64/64, uncut, 8 x 64 heads x 768 48 / 33, 8 x 80 x 3000 246 / 221, but 8 x 32/8 x 2048 (256
-// workgroups of one head) 60 / 75; cut, 1 x 80 x 8192 111 / 79, 1 x 24 x 8192 42 / 37; 128/64 uncut 1 x 24 x 4096 147 / 160.
+// Those of one head at 64/64 share compute units (see gated_one_each): a full round of 512 takes 1.5 times as long as one of 256, one
+// of which no more than 128, or 256, are left, 0.8 or 1.25 times.  Measured (us, one head / two): 64/64, uncut, 8 x 32/8 x 2048 (256
+// workgroups of one head) 60 / 72, 6 x 64/8 x 1024 46 / 40, 8 x 64/8 x 768 42 / 34, 9 x 64/8 x 3000 215 / 223, 8 x 80/1 x 768 49 / 56, x 3000 198 / 214,
+// 12 x 64/8 x 1024 83 / 79, x 3000 250 / 227, 14 x 64/8 x 1024 122 / 82, 24 x 64/8 x 200 46 / 41; cut, 1 x 80 x 8192 111 / 79, 1 x 24 x 8192 42 / 37;
+// 128/64 uncut 8 x 32/8 x 2048 71 / 87, 8 x 80/1 x 1024 106 / 86.
+static double gated_rounds(int64_t workgroups, int L, bool may_share) {
+  if (!may_share || workgroups <= 256 || ae::gated_one_each(workgroups, L)) return (double)((workgroups + 255) / 256);
+  const int64_t left = workgroups % 512;
+  return 1.5 * (double)(workgroups / 512) + (left == 0 ? 0.0 : left <= 128 ? 0.8 : left <= 256 ? 1.25 : 1.45);
+}
 static void gated_forward_plan(const ae_gated_desc_t* d, bool may_cut, int* heads, int* nseg, int* seg_len) {
   const bool pairs = d->D_v == 64 && (d->H / d->H_qk) % 2 == 0;
   double least = 0;
@@ -1116,7 +1124,7 @@ static void gated_forward_plan(const ae_gated_desc_t* d, bool may_cut, int* head
     int ns = 1, len = 0;
     if (may_cut) gated_segments(workgroups, d->L, &ns, &len);
     // (cut: the state's walk takes a third of the time, and two more launches cost about 300 tokens)
-    const double tokens = ns > 1 ? 1.4 * len + 300 : (double)((workgroups + 255) / 256) * d->L;
+    const double tokens = ns > 1 ? 1.4 * len + 300 : gated_rounds(workgroups, d->L, n == 1 && d->D_qk == 64) * d->L;
     const double t = tokens * (n == 1 ? 1.0 : d->D_qk == 64 ? 1.23 : 1.12);
     if (n == 1 || t < 0.9 * least) {  // (3 x 80 x 4096, 64/64: 0.95 by this estimate, 115 / 126 us)
       least = t;

@@ -29,7 +29,7 @@
 // What bounds it is how well a SIMD's vector and matrix work overlap, and that takes two wavefronts per SIMD of at most
 // 256 registers.  Where accumulators, resident operands and score tiles of 32 own rows fit that (64/64; 128/128, query
 // side), a wavefront does all of the above and two workgroups share a CU: bwd_single_walk.  Where they do not, the 32
-// rows go to a pair of wavefronts: bwd_pair_walk (its key side at 128/256 still spills: 5 to 9 registers), but for
+// rows go to a pair of wavefronts: bwd_pair_walk (its key side at 128/256 still spills: 4 to 8 registers), but for
 // short walks, which the first form takes with one workgroup per CU and up to 472 registers.  The lines between the two
 // stand in bwd_launch.hpp.
 #pragma once

@@ -46,7 +46,7 @@ constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
 //     second card the long calls were alike either way): 1 x 128 heads x 2048 (262) 812 / 798, 8 x 128 x 1024 (524) 2077 / 2064, 1 x 64 x 4096 (524)
 //     1367 / 1366, 1 x 128 x 3500 (784) 2108 / 2122, 1 x 24 x 8192 (786) 1855 / 1883, 1 x 128 x 4096 (1049) 2731 / 2755, 1 x 128/16 x 4096 (1049) 2657 /
 //     2693, 1 x 64 x 6000 (1128) 2781 / 2828, 1 x 128 x 8192 (4194) 10216 / 10286.  Unmasked: 8 x 16 x 1024 397 / 383, 1 x 64 x 4096 2413 / 2432.
-//   * 128/256, abs-sum family: as one kernel it spills 26 registers instead of 9.  2 x 16 x 1024 (64 workgroups of both sides per XCD)
+//   * 128/256, abs-sum family: as one kernel it spills 20 to 22 registers instead of 4.  2 x 16 x 1024 (64 workgroups of both sides per XCD)
 //     117 / 91, 1 x 24/6 x 2048 (80) 480 / 422, 2 x 16 x 2048 (128) 254 / 263, 4 x 16 x 2048 (256) 511 / 533.
 // The workgroups of a side: whole sets of `together` groups (or parts of groups) per XCD (the kernels' mapping): sets x together x
 // 8 XCDs x workgroups per group or part.

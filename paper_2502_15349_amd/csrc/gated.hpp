@@ -90,6 +90,16 @@ hipError_t launch_gated_group_sum(const float* dq_parts, const float* dk_parts, 
 // dlog_decay[h, t] = sum_{i >= t} dB[h, i] - minus[h, i] (minus: null, or dlog_decay itself); launch_gated_backward_epilogue ends with it
 hipError_t launch_gated_suffix_sum(const float* dB, const float* minus, float* dlog_decay, int BH, int L, hipStream_t stream);
 bool gated_supported(int dqk, int dv);
+// 64/64, one head per workgroup: two workgroups can share a compute unit, and a launch can see to it that they don't.  Sharing evens out
+// the last round and covers the start and the end of a walk; where the rounds of one each are full (at least `fill` of their places
+// taken) and the calls stream through memory, one each reads it better (us, shared / one each): 9 x 32 heads x 2048 102 / 120, 12 x
+// 32 x 2048 111 / 119, 18 x 32 x 2048 184 / 188, 64 x 32 x 512 135 / 142, 16 x 32 x 1024 70 / 71; but 15 x 32 x 2048 133 / 128, 28 x 32 x 2048 264 /
+// 247, 32 x 32 x 2048 278 / 260, 16 x 64 x 1024 141 / 137.  Backward (three walks' workgroups): 12 x 32 x 2048 406 / 439, 8 x 32 x 1024 124 / 134,
+// 20 x 32 x 2048 687 / 703; 8 x 32 x 4096 549 / 544, 8192 1100 / 1078.
+inline bool gated_one_each(int64_t workgroups, int64_t tokens, int64_t from = 1024, double fill = 0.85) {
+  return tokens >= from && workgroups * tokens >= 900000 && workgroups >= fill * 256 * ((workgroups + 255) / 256);
+}
+inline bool gated_backward_one_each(int64_t workgroups, int64_t tokens) { return gated_one_each(workgroups, tokens, 4096, 0.95); }
 // dt: log2 of the per-head decay, read only where p.log_decay is null
 hipError_t launch_gated_recurrent(const GatedParams& p, const DecayTable& dt, int dqk, int dv, hipStream_t stream);
 // The three walks of the backward pass (dims D_v / D_qk, D_v / D_qk, D_qk / D_v, all cut alike) in one launch; group: the first two

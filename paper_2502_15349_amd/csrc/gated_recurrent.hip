@@ -591,7 +591,8 @@ __global__ __launch_bounds__(C::BOUND_THREADS, C::WAVES_PER_SIMD) void gated_rec
 // the values (K, or Q in the walk that goes backwards) and the rows of the dot products (Q, or K) once per
 // chunk.  The outputs are summed over the heads in registers, and each head's row products
 // (q . dq, k . dk / g) are formed on the way.  Stored per head, as gated_bwd_rows_kernel takes them, the two walks wrote and that
-// kernel read 2 x 251 MB at 8 x 80 heads x 768 tokens: 379 us for the whole backward pass, 257 this way (three heads each).
+// kernel read 2 x 251 MB at 8 x 80 heads x 768 tokens: 379 us for the whole backward pass with a launch per walk, 257 this way; with the
+// walks in one launch see gated_group_heads.
 // DQK_, DV_: head dims of the walk, i.e. of dO and V, and of Q and K.
 template <int DQK_, int DV_>
 struct GroupCfg : GCfg<DQK_, DV_> {
@@ -923,22 +924,15 @@ hipError_t launch_in_parts(int64_t blocks, int threads, F&& launch) {
   return e;
 }
 
-// LDS that a launch asks for on top, so that workgroups which could share a compute unit (GCfg::SHARES_CU) have one each.  Sharing
-// evens out the last round and covers the start and the end of a walk; where the rounds of one each are full (at least `fill` of their places taken) and the calls stream through memory, one each reads it better (us, shared / one
-// each): 9 x 32 heads x 2048 102 / 120, 12 x 32 x 2048 111 / 119, 18 x 32 x 2048 184 / 188, 64 x 32 x 512 135 / 142, 16 x 32 x 1024 70 / 71; but
-// 15 x 32 x 2048 133 / 128, 28 x 32 x 2048 264 / 247, 32 x 32 x 2048 278 / 260, 16 x 64 x 1024 141 / 137.  Backward: 12 x 32 x 2048 406 / 439,
-// 8 x 32 x 1024 124 / 134, 20 x 32 x 2048 687 / 703; 8 x 32 x 4096 549 / 544, 8192 1100 / 1078.
-static int lds_for_one_each(int64_t workgroups, int64_t tokens, int64_t from_tokens, double fill) {
-  const int64_t rounds = (workgroups + 255) / 256;
-  return tokens >= from_tokens && workgroups * tokens >= 900000 && workgroups >= fill * 256 * rounds ? 1024 : 0;
-}
+// LDS that a launch asks for on top, so that workgroups which could share a compute unit have one each (see gated_one_each).
+static int lds_for_one_each(bool one_each) { return one_each ? 1024 : 0; }
 
 template <int DQK, int DV, int HPW = 1>
 hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
   typedef GCfg<DQK, DV, HPW> C;
   if (p.gate_on_output && !p.state_only) return hipErrorInvalidValue;
   const int64_t blocks = (int64_t)p.B * p.H / HPW * p.nseg;
-  const int lds = C::SHARES_CU && p.nseg == 1 ? lds_for_one_each(blocks, p.L, 1024, 0.85) : 0;
+  const int lds = lds_for_one_each(C::SHARES_CU && p.nseg == 1 && gated_one_each(blocks, p.L));
   return launch_in_parts(blocks, C::THREADS, [&](int first, dim3 grid) {
     if (p.state_only) hipLaunchKernelGGL((gated_recurrent_kernel<C, true>), grid, dim3(C::THREADS), 0, s, p, dt, first);
     else hipLaunchKernelGGL((gated_recurrent_kernel<C, false>), grid, dim3(C::THREADS), lds, s, p, dt, first);
@@ -1121,7 +1115,7 @@ static hipError_t launch_walks(GatedBackwardWalks& w, int64_t blocks, hipStream_
   constexpr int kThreads = BackwardCfg<A, E, false, GROUP>::THREADS;
   static_assert(GROUP || BackwardCfg<A, E, true, false>::THREADS == kThreads, "");
   const bool gated = w.walk[GROUP ? 2 : 0].gate_on_output != 0;
-  const int lds = BackwardCfg<A, E, false, GROUP>::SHARES_CU && w.walk[0].nseg == 1 ? lds_for_one_each(blocks, w.walk[0].L, 4096, 0.95) : 0;
+  const int lds = lds_for_one_each(BackwardCfg<A, E, false, GROUP>::SHARES_CU && w.walk[0].nseg == 1 && gated_backward_one_each(blocks, w.walk[0].L));
   return launch_in_parts(blocks, kThreads, [&](int first, dim3 grid) {
     w.first_block = first;
     if constexpr (!GROUP) {

@@ -168,7 +168,8 @@ def test_backward_sliding_window(A, window, Lq, Lk):
                          ids=["d128_causal", "d128_window", "d128", "d64", "d192", "d128_256_abssum"])
 def test_backward_batch_entries_do_not_depend_on_the_launches(A, dims, kw):
     # seven batch entries at once, where some head dims take a launch for each side, and one at a time, where both sides
-    # share one: the same values
+    # share one: the same values.  (64/64 and 192/128 share one either way at this size -- beyond their lines is the test below --
+    # and show that the workgroups' places in the grid leave the values alone)
     w = Workload("launches", 47, 7, 8, 8, 1000, 1030, dims[0], dims[1], **kw)
     dev = torch.device("cuda:0")
     Q, K, V = (t.to(dev) for t in make_inputs(w))
@@ -288,7 +289,7 @@ def test_backward_seeded_random_shapes(A):
 
 
 def test_backward_hip_graph_replays(A):
-    """ae_attn_backward allocates nothing: its three launches are captured into a HIP graph and replayed four
+    """ae_attn_backward allocates nothing: its launches are captured into a HIP graph and replayed four
     times with new dO values and eager work in between; every replay must equal the eager call bit for bit."""
     dev = torch.device("cuda:0")
     w = Workload("graph_bwd", 46, 1, 4, 2, 300, 420, 128, 128, mask="causal")
