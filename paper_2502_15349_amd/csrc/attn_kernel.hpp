@@ -185,7 +185,7 @@ struct Cfg {
   static_assert(LDS_BYTES <= 160 * 1024, "tiles do not fit LDS");
   // FOLD sigmoid at 64/64: the scoring accumulator's initial value (the bias, the same in all 16 registers) is built
   // where it is used instead of being held in registers: 138 -> 116 registers, which lets a second workgroup onto
-  // the compute unit (C3: 33.8 -> 36.5 % of peak on the same box)
+  // the compute unit (C3: 33.8 -> 36.5 % of peak on the same card)
   static constexpr bool kSplatInit = DQK_ == 64 && DV_ == 64;
 };
 

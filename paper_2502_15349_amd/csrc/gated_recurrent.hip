@@ -40,8 +40,10 @@
 // compute unit's memory pipe takes about 60 clocks for each of those (16 for a kilobyte of whole lines).
 // Q, K, V tiles arrive by LDS-DMA into a ring of three stages (chunk c is worked on, c + 1 is needed half a chunk later, c + 2
 // is in flight).  Measured against the form without helpers, where every state wavefront formed the gates and, for its own 32
-// columns, the weights (us, one box): 8 x 32 heads x 8192 tokens, 128/128, 592 -> 535 (5.0 TB/s: the memory's rate), 8 x 16 x 4096
+// columns, the weights (us, one card): 8 x 32 heads x 8192 tokens, 128/128, 592 -> 535 (5.0 TB/s: the memory's rate), 8 x 16 x 4096
 // 64/64 119 -> 92, 1 x 4 x 300 128/128 21.0 -> 14.8, Mamba2 1 x 80 x 8192 (three launches) 137 -> 113, 8 x 80 x 2048 259 -> 180.
+// The lanes' LDS addresses are formed chunk by chunk from one register for each kind of fragment and pinned there; left alone, the
+// compiler carried 35 of them through the loop (64/64 144 registers, now 123; 1 x 32 x 2000 128/128 80 -> 73, 2 x 24/8 x 2000 128/64 74.5 -> 68.5).
 // The same kernel serves the backward pass (other operands, a walk from the last token to the first,
 // see GatedParams::reverse) and walks cut into segments (GatedParams::nseg).
 #include <hip/hip_runtime.h>
