@@ -340,7 +340,14 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
     // where its 32 compute units take as many rounds, two or more, either way (1 x 12 x 6000, 128/256, unmasked 385 us, cut 392).
     const int64_t whole = ((int64_t)p.n_groups + 7) / 8 * p.n_qtiles * p.g, part = (((int64_t)p.n_qtiles * p.g + (1 << p.cut) - 1) >> p.cut);
     const int64_t whole_rounds = (whole + 31) / 32, cut_rounds = (((int64_t)p.n_groups << p.cut) / 8 * part + 31) / 32;
-    if (whole <= 8 || (d->mask == AE_MASK_NONE && whole_rounds > 1 && cut_rounds >= whole_rounds)) p.cut = 0;
+    // Nor where parts of unequal size pad the grid past the compute units: a workgroup goes to the next of an XCD's four engines whether
+    // one of its compute units is free or not, and the surplus ones stand at regular places (us, cut / whole: 1 x 33 heads x 1100, five
+    // workgroups for 8 parts, 128/128 unmasked 49 / 30, causal 37 / 28, 1 x 41 x 1100 40 / 28).  Nor from 25 groups on, where a handful of
+    // workgroups of unequal length per part fills the end of the grid no better (causal 1 x 25 x 4096 128/128 126 / 111, 192/128 150 / 133;
+    // 1 x 82/41 x 2273 134 / 126, 64/64 81 / 71; 1 x 33 x 4096 64/64 113 / 94; at most 5 % better: 1 x 54/27 x 2273 90 / 94).
+    const int64_t per_group = (int64_t)p.n_qtiles * p.g, places = part << p.cut;
+    const bool padded = ((int64_t)p.n_groups << p.cut) / 8 * part > 32 && places * 5 > per_group * 6;
+    if (whole <= 8 || padded || p.n_groups > 24 || (d->mask == AE_MASK_NONE && whole_rounds > 1 && cut_rounds >= whole_rounds)) p.cut = 0;
   }
   // workgroups, those included that pad the grid to whole sets, where the groups are cut into 2^cut parts
   auto grid_of = [&](int cut, int* together) {
@@ -670,12 +677,21 @@ static ae_status_t backward_impl(const ae_attn_t* h, const void* Q, const void* 
   // put a workgroup on every compute unit of the XCD, though, and with a causal mask four at least, so that the
   // last set to run -- heaviest workgroups first within a set -- is a small part of the grid.
   {
-    p.cut = ae::group_cut((int64_t)d.B * d.H_kv);
+    const int64_t n = (int64_t)d.B * d.H_kv;
+    p.cut = ae::group_cut(n);
+    // Causal and more than 8 groups: workgroups of unequal length, of which a part has few.  Cut only where measured to be the better (us,
+    // cut / whole): 9 to 12 groups from 2048 rows on but for 64/64 (1 x 9 heads x 4096 128/128 204 / 264, 192/128 235 / 296, 1 x 22/11 x 2273 128/256 211
+    // / 245; but x 1100 61 / 60, abs-sum 80 / 75; 64/64 x 4096 132 / 122), more than 32 from 2048 rows on (1 x 33 x 4096 128/128 692 / 900, 1 x
+    // 82/41 x 2273 192/128 650 / 796; but x 1100 128/128 117 / 102, abs-sum 191 / 160).  Whole in between: 1 x 40/20 x 2273 128/128 319 / 263, 1 x 25 x
+    // 1100 84 / 65, 1 x 27 x 1100 91 / 66, 1 x 18 x 4096 431 / 395.  Unmasked 1 x 9 x 1100 45 / 74, 1 x 36/18 x 2273 466 / 637, 1 x 25 x 4096 860 / 856.
+    if (d.mask != AE_MASK_NONE && n > 8 &&
+        !(d.mask == AE_MASK_CAUSAL && std::min(d.L_q, d.L_k) >= 2048 && (n > 32 || (n <= 12 && d.D_qk > 64))))
+      p.cut = 0;
     // (a bias tensor, unmasked, more than a round of workgroups: 1 x 12 heads x 3000 244 us, cut 253; of one round 1 x 12 x 2000 93 / 87)
-    if (p.bias && d.mask == AE_MASK_NONE && ((int64_t)d.B * d.H_kv + 7) / 8 * ((d.L_q + 127) / 128 * p.g + (d.L_k + 127) / 128) > 64) p.cut = 0;
-    auto part = [&](int64_t n) { return (n + (1 << p.cut) - 1) >> p.cut; };
+    if (p.bias && d.mask == AE_MASK_NONE && (n + 7) / 8 * ((d.L_q + 127) / 128 * p.g + (d.L_k + 127) / 128) > 64) p.cut = 0;
+    auto part = [&](int64_t tiles) { return (tiles + (1 << p.cut) - 1) >> p.cut; };
     const int64_t tiles_q = part((d.L_q + 127) / 128 * (int64_t)p.g), tiles_kv = part((d.L_k + 127) / 128);
-    const int64_t rounds = (((int64_t)d.B * d.H_kv << p.cut) + 7) / 8;
+    const int64_t rounds = ((n << p.cut) + 7) / 8;
 #ifdef AE_TUNE_BWD_TOGETHER_Q  // build-time knobs of the mapping sweeps
     int64_t tq = AE_TUNE_BWD_TOGETHER_Q, tk = AE_TUNE_BWD_TOGETHER_KV;
 #else

@@ -106,7 +106,7 @@ struct DecayTable {
 // 2, 4 or 8 parts, the fewest that come out even: log2 of that number.  From 15 % of imbalance on: what it costs is K and V read
 // by several XCDs.  Whole groups / parts (us), causal: 1 x 12 heads x 4096 128/128 82 / 75, backward 279 / 224; 1 x 12 x 8192 192/128 271 / 228; 1 x 6
 // x 8192 152 / 138, backward 523 / 417; 1 x 24/6 x 4096 120 / 98; 2 x 24/6 x 2000 192/128 backward 328 / 292; 1 x 1 x 8192 backward 491 / 238.  At 12 %
-// (5 x 10 heads) 98 / 108 backward.
+// (5 x 10 heads) 98 / 108 backward.  Where a cut does not pay after all, ae_attn_create and backward_impl set it back to 0.
 inline int group_cut(int64_t n_groups) {
   int cut = 0;
   if ((n_groups + 7) / 8 * 8 * 20 >= n_groups * 23)

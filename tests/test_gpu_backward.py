@@ -222,6 +222,27 @@ def test_heads_do_not_depend_on_their_number(A, dims, mask, n):
         assert torch.equal(x, y[:, :x.shape[1]])
 
 
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("mask", ["none", "causal"])
+@pytest.mark.parametrize("n,L", [(9, 1100), (9, 2100), (13, 2100), (25, 1100), (33, 1100), (33, 2100)])
+def test_heads_of_many_groups_do_not_depend_on_their_number(A, dims, mask, n, L):
+    # groups that are cut into parts and groups that stay whole, on both sides of the lines between them, against eight at a time
+    g = torch.Generator("cuda").manual_seed(50)
+    Q, K, V, dO = (torch.randn(1, n, L, D, generator=g, device="cuda", dtype=torch.bfloat16) for D in (dims[0], dims[0], dims[1], dims[1]))
+    args = dict(scale=dims[0] ** -0.5, mask=mask)
+
+    def both(h0, h1):
+        q, k, v, do = (t[:, h0:h1].contiguous() for t in (Q, K, V, dO))
+        stats = torch.empty((1, h1 - h0, L), dtype=torch.float32, device="cuda")
+        O = A.attention_forward(q, k, v, stats=stats, **args)
+        return (O, stats) + tuple(A.attention_backward(q, k, v, O, do, stats, **args))
+
+    whole = both(0, n)
+    for h0 in (0, n - 8):
+        for x, y in zip(whole, both(h0, h0 + 8)):
+            assert torch.equal(x[:, h0:h0 + 8], y)
+
+
 def test_backward_more_heads_than_the_decay_table(A):
     # handles without a per-head decay may have more query heads than the decay table holds (256): the kernels of
     # the linear normalizations must not read the table then
