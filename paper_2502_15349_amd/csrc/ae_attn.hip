@@ -340,9 +340,9 @@ ae_status_t ae_attn_create(const ae_attn_desc_t* d, ae_attn_t** out) {
     // where its 32 compute units take as many rounds, two or more, either way (1 x 12 x 6000, 128/256, unmasked 385 us, cut 392).
     const int64_t whole = ((int64_t)p.n_groups + 7) / 8 * p.n_qtiles * p.g, part = (((int64_t)p.n_qtiles * p.g + (1 << p.cut) - 1) >> p.cut);
     const int64_t whole_rounds = (whole + 31) / 32, cut_rounds = (((int64_t)p.n_groups << p.cut) / 8 * part + 31) / 32;
-    // Nor where parts of unequal size pad the grid past the compute units: a workgroup goes to the next of an XCD's four engines whether
-    // one of its compute units is free or not, and the surplus ones stand at regular places (us, cut / whole: 1 x 33 heads x 1100, five
-    // workgroups for 8 parts, 128/128 unmasked 49 / 30, causal 37 / 28, 1 x 41 x 1100 40 / 28).  Nor from 25 groups on, where a handful of
+    // Nor where the parts' surplus places make the grid longer than an XCD's compute units are many: the call then takes a second round,
+    // though no more than 21 of its 33 workgroups there have work (us, cut / whole: 1 x 33 heads x 1100, five workgroups for 8 parts,
+    // 128/128 unmasked 49 / 30, causal 37 / 28, 1 x 41 x 1100 40 / 28; 27 places 1 x 27 x 1100 27.6 / 27.1).  Nor from 25 groups on, where a handful of
     // workgroups of unequal length per part fills the end of the grid no better (causal 1 x 25 x 4096 128/128 126 / 111, 192/128 150 / 133;
     // 1 x 82/41 x 2273 134 / 126, 64/64 81 / 71; 1 x 33 x 4096 64/64 113 / 94; at most 5 % better: 1 x 54/27 x 2273 90 / 94).
     const int64_t per_group = (int64_t)p.n_qtiles * p.g, places = part << p.cut;

@@ -67,8 +67,8 @@ struct GCfg {
   // the gates' values of a head's chunk, in floats: b, u, s (see put_gates), two sets of w, the groups' references, two decays
   static constexpr int kB = 0, kU = 64, kS = 128, kW = 192, kRef = 320, kDec = 336, GATE_BYTES = 352 * 4;
   static constexpr int P_BYTES = 3 * 2048;  // per head: the chunk's weights, three blocks of 32 x 32 in bf16
-  // 64/64, one head: two workgroups of six wavefronts per compute unit.  Both begin on the same SIMD, which gives two of the SIMDs
-  // four wavefronts: 128 registers each.  With 144, for three, only one workgroup was resident, and 257 pairs took two rounds:
+  // 64/64, one head: two workgroups of six wavefronts per compute unit.  They were seen to share one only where a
+  // SIMD has room for four wavefronts (as if both began on the same SIMD): 128 registers each.  With 144, for three, only one workgroup was resident, and 257 pairs took two rounds:
   // 9 x 32 heads x 1024 60 us, 42 now; 8 x 48 x 1024 62 / 47, its backward pass 229 / 184; 5 x 32 x 768 backward 74 / 55.
   // BOUND_THREADS: what the launch bound says, so that the compiler counts four wavefronts too.
   static constexpr bool SHARES_CU = DQK == 64 && DV == 64 && HPW == 1;
