@@ -29,7 +29,7 @@
 // What bounds it is how well a SIMD's vector and matrix work overlap, and that takes two wavefronts per SIMD of at most
 // 256 registers.  Where accumulators, resident operands and score tiles of 32 own rows fit that (64/64; 128/128, query
 // side), a wavefront does all of the above and two workgroups share a CU: bwd_single_walk.  Where they do not, the 32
-// rows go to a pair of wavefronts: bwd_pair_walk (its key side at 128/256 still spills: 4 to 8 registers), but for
+// rows go to a pair of wavefronts: bwd_pair_walk (its key side at 128/256 spills up to 6 registers), but for
 // short walks, which the first form takes with one workgroup per CU and up to 472 registers.  The lines between the two
 // stand in bwd_launch.hpp.
 #pragma once
@@ -572,19 +572,24 @@ __device__ __forceinline__ void bwd_single_walk(const BwdParams& p, const DecayT
 }
 
 // ---- two wavefronts per 32 own rows -------------------------------------------------------------------------------
-// Role 0 (wavefronts 0..3) keeps X1, computes S and the weights P, writes per entry the factor that turns dP into dS' to
-// LDS (fp32: softmax P, sigmoid P (1 - P), ...) and, on the key side, accumulates dV.  Role 1 (wavefronts 4..7, on the
-// same SIMDs) keeps X2, computes dP, reads the factors and accumulates dK or dQ.  The products split evenly: D_qk + D_v
-// against D_v + D_qk on the key side.  Role 1 is a tile of 32 rows behind, so one barrier per tile hands over the
-// factors, the tiles that have landed and the stages that are free.  Within a tile role 0's order is S, weights, dV and
-// role 1's is dS', dK / dQ, dP of the next tile: one is in its vector work while the other issues matrix products.
+// Role 0 (wavefronts 0..3) keeps X1 and X2, computes S, dP, the weights P and their gradients dS', and hands P (key side)
+// and dS' on in LDS, in bfloat16 and in the order in which the other role's products take them.  Role 1 (wavefronts 4..7, on
+// the same SIMDs) keeps the accumulators and does nothing but products: dV and dK, or dQ.  The products split evenly on the
+// key side, D_qk + D_v of each.  Role 1 is a tile of 32 rows behind, so one barrier per tile hands over P and dS', the
+// tiles that have landed and the stages that are free.  Role 1 starts every tile with products while role 0 computes S, and
+// role 0's exponentials stand between its products of dP.
 //
-// Measured against one wavefront per 32 rows with 512 registers (us, whole backward pass, causal): 1 x 128 heads x 8192,
-// 192/128, 10340 -> 9640; 8 x 16 x 4096 192/128 2786 -> 2600, 128/256 3517 -> 2917, 128/128 (key side) 2106 -> 2013;
-// 1 x 32/8 x 1024 192/128 217 -> 182, 128/256 290 -> 207, 128/128 184 -> 164; 4 x 32/8 x 2048 128/128 579 -> 580.  Taking away the copies, the
-// LDS reads or the weights for timing gave 9-10 % each: no one of them bounds it, the hand-over per tile and the board's
-// power do.  Against two workgroups per CU where those fit (64/64 8 x 16 x 4096 1033, 128/128 query side
-// 4 x 32/8 x 2048 210) the pairs take 1212 and 316: the choice in bwd_launch.hpp.
+// Measured against a split in which role 0 computed S, the weights and dV and role 1 dP, dS' (from 32-bit factors that role 0
+// handed on) and dK / dQ, us, key side + query side: 1 x 128 heads x 8192 192/128 causal softmax 5240 + 4160 -> 4980 + 3860, 8 x 12 x
+// 4096 128/256 1265 + 850 -> 1200 + 795, abs-sum with decay 192/128 1215 + 990 -> 1120 + 857; key side of 128/128
+// 4 x 32/8 x 2048 300 -> 285.  There role 1 waited for eight LDS reads behind every barrier and then ran its vector work, both
+// in front of its products: 2430 clocks per tile of 1280 clocks of products, now 2020.  What bounds it now is power: the
+// same kernels on inputs of zeros take 4030 + 3015 us (the first split 4500 + 3575), the clock falls from 2.05 to 1.89 GHz as the
+// matrix units' share of the cycles goes from 0.48 to 0.54.  Left out for timing, of the 192/128 time: the copies 6-9 %,
+// the row fragments 3 %, the transposed ones 5 %, the row quantities 1-2 %, the hand-over 3 %, the exponentials 5 %, all of them 22 %.
+// Deeper rings, more products in front of the weights, raised wave priority: no difference.  The query side's copies all
+// go with role 1, which has less to do there (role 0 or both: 2 % more).  Against two workgroups per CU where those
+// fit (64/64; 128/128 query side, 4 x 32/8 x 2048 212) the pair takes longer (128/128 query side 250): the choice in bwd_launch.hpp.
 template <int DQK_, int DV_, int NORM_, bool CAUSAL_, int OUT_, bool BIAS_ = false>
 struct BwdPairCfg {
   static constexpr bool BIAS = BIAS_;
@@ -602,10 +607,15 @@ struct BwdPairCfg {
   static constexpr int STAGE_BYTES = Y1_BYTES + Y2_BYTES + BIAS_BYTES;
   static constexpr int ROW_BYTES = ROWQ ? 512 : 0;  // per stage: [64] statistic, [64] delta (32 of each are used)
   static constexpr int STAGES = 5 * (STAGE_BYTES + ROW_BYTES) + 2 * 4 * 4096 <= 160 * 1024 ? 5 : 4, LOOK = STAGES - 2;
-  static constexpr int ROWS0 = STAGES * STAGE_BYTES, E0 = ROWS0 + STAGES * ROW_BYTES, E_BYTES = 4 * 4096;
+  static constexpr int ROWS0 = STAGES * STAGE_BYTES, E0 = ROWS0 + STAGES * ROW_BYTES, E_PAIR = KV_SIDE ? 4096 : 2048, E_BYTES = 4 * E_PAIR;
   static constexpr int LDS_BYTES = E0 + 2 * E_BYTES;
-  // copies: groups of four 1 KB blocks, group q by the wavefronts of role q % 2
+  // copies: groups of four 1 KB blocks, group q by the wavefronts of role q % 2, or all by one role
   static constexpr int G1 = DQK / 64, G2 = DV / 64, GB = BIAS_ ? 2 : 0, GROUPS = G1 + G2 + GB;
+  static constexpr int COPIER = KV_SIDE ? (DV == 256 && !LIN ? 0 : 2) : 1;  // 0, 1: that role; 2: both in turn
+  // a lane's offsets of a short last tile are formed where they are used, in a branch, instead of being held in registers
+  static constexpr bool TAIL_BRANCH = KV_SIDE && DV == 256 && LIN;
+  // groups after which a lane's swizzle repeats (16 or 32 rows)
+  static constexpr int copy_period(int cpr) { return cpr == 24 ? 3 : cpr == 32 ? 2 : 1; }
   // swizzle periods of the fragment addresses (in fragments): beyond them an address repeats at a fixed distance
   static constexpr int PR1 = CPR1 % 16 == 0 ? 8 : 4, PR2 = CPR2 % 16 == 0 ? 8 : 4;
   static constexpr int PK1 = CPR1 % 16 == 0 ? 4 : 2, PK2 = CPR2 % 16 == 0 ? 4 : 2;
@@ -690,48 +700,36 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
   const int trow = 4 * half + (li >> 2), tcl = 2 * blk + ((li & 3) >> 1);
 
   auto walk = [&](auto rolec) {
-    constexpr int ROLE = decltype(rolec)::value;  // 0: scores and weights (and dV on the key side), 1: dP, dS and dK / dQ
-    constexpr int NC = (C::GROUPS - ROLE + 1) / 2;
-    constexpr int T = ROLE == 0 ? C::T1 : C::T2, CPRX = ROLE == 0 ? C::CPR1 : C::CPR2;
-    constexpr int DBX = ROLE == 0 ? C::DB2 : C::DB, CPRT = ROLE == 0 ? C::CPR2 : C::CPR1;  // accumulated blocks, and the tile they read
-    constexpr int PR = ROLE == 0 ? C::PR1 : C::PR2, PK = ROLE == 0 ? C::PK2 : C::PK1;
-    constexpr int RBX = CPRX * 16, RBT = CPRT * 16;
-    constexpr int OFFX = ROLE == 0 ? 0 : C::Y1_BYTES, OFFT = ROLE == 0 ? C::Y1_BYTES : 0;
-    // ---- own operand: B fragments, straight from global memory ----
-    const __bf16* x;
-    if constexpr (ROLE == 0) {
-      x = C::KV_SIDE ? p.K + b * p.ks[0] + hk * p.ks[1] + (int64_t)own_c * p.ks[2] : p.Q + b * p.qs[0] + ho * p.qs[1] + (int64_t)own_c * p.qs[2];
-    } else {
-      x = C::KV_SIDE ? p.V + b * p.vs[0] + hk * p.vs[1] + (int64_t)own_c * p.vs[2]
-                     : p.dO + (((int64_t)b * p.H_q + ho) * p.L_q + own_c) * C::DV;
-    }
-    bf16x8 xb[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) xb[t] = *reinterpret_cast<const bf16x8*>(x + (2 * t + half) * 8);
-    // query side: the row quantity of the lane's own row (role 0: converted behind the first copies)
-    constexpr bool OWN_ROW = !C::KV_SIDE && C::ROWS;
-    float rq_own = ROLE == 0 ? (OWN_ROW ? (C::ABS ? 0.f : -INFINITY) : C::LIN ? 1.f : -INFINITY) : 0.f;
-    if constexpr (OWN_ROW) {
-      if (own < p.L_q) rq_own = (ROLE == 0 ? p.lse : p.delta)[((int64_t)b * p.H_q + ho) * p.L_q + own];
-    }
-    auto convert_stat = [&](float v) {
-      return C::ABS ? fast_rcp(fmaxf(fabsf(v), 1.f)) : v == -INFINITY ? -INFINITY : p.b2 - v * 1.4426950408889634f;
-    };
+    constexpr int ROLE = decltype(rolec)::value;  // 0: scores, weights and their gradients, 1: the sums dV, dK / dQ
+    constexpr int NC = C::COPIER == 2 ? (C::GROUPS - ROLE + 1) / 2 : C::COPIER == ROLE ? C::GROUPS : 0;  // copies of a tile
+    constexpr int NCQ = C::COPIER == 2 ? 2 : 1, Q0 = C::COPIER == 2 ? ROLE : 0;  // copy k is group k NCQ + Q0
 
     // ---- copies ----
     const int64_t s1 = C::KV_SIDE ? p.qs[2] : p.ks[2], s2 = C::KV_SIDE ? (int64_t)C::DV : p.vs[2];
-    uint32_t co[NC], co_tail[NC];  // the lane's byte offset from the tile's first row; the same for a short last tile
     const int tail = (L_oth - 1) % C::TILE;  // the last tile's last row: rows past it repeat it
+    constexpr int PER1 = C::copy_period(C::CPR1), PER2 = C::copy_period(C::CPR2);
+    auto copy_offset = [&](auto cprc, int Q, int64_t stride, int last) {  // the lane's byte offset from the tile's first row, group Q
+      constexpr int CPR = decltype(cprc)::value;
+      const int pos = (4 * Q + w4) * 64 + lane, r = pos / CPR, c = (pos % CPR) ^ bswz<CPR>(r);
+      return (uint32_t)((min(r, last) * stride + c * 8) * 2);
+    };
+    constexpr std::integral_constant<int, C::CPR1> cpr1{};
+    constexpr std::integral_constant<int, C::CPR2> cpr2{};
+    uint32_t co[NC > 0 ? NC : 1], co_tail[NC > 0 ? NC : 1], co1[PER1], co2[PER2];  // co: of copy k; co1, co2: TAIL_BRANCH
     static_for<0, NC>([&](auto kc) {
-      constexpr int k = decltype(kc)::value, q = 2 * k + ROLE;
-      constexpr bool FIRST = q < C::G1;
-      constexpr int CPR = FIRST ? C::CPR1 : C::CPR2, Q = FIRST ? q : q - C::G1;
-      if constexpr (q < C::G1 + C::G2) {
-        const int pos = (4 * Q + w4) * 64 + lane, r = pos / CPR, c = (pos % CPR) ^ bswz<CPR>(r);
-        co[k] = (uint32_t)((r * (FIRST ? s1 : s2) + c * 8) * 2);
-        co_tail[k] = (uint32_t)((min(r, tail) * (FIRST ? s1 : s2) + c * 8) * 2);
+      constexpr int k = decltype(kc)::value, q = k * NCQ + Q0;
+      if constexpr (q < C::G1) {
+        co[k] = copy_offset(cpr1, q, s1, C::TILE);
+        co_tail[k] = copy_offset(cpr1, q, s1, tail);
+      } else if constexpr (q < C::G1 + C::G2) {
+        co[k] = copy_offset(cpr2, q - C::G1, s2, C::TILE);
+        co_tail[k] = copy_offset(cpr2, q - C::G1, s2, tail);
       }
     });
+#pragma unroll
+    for (int k = 0; k < PER1; ++k) co1[k] = copy_offset(cpr1, k, s1, C::TILE);
+#pragma unroll
+    for (int k = 0; k < PER2; ++k) co2[k] = copy_offset(cpr2, k, s2, C::TILE);
     // the copies' own position in the walk, with the addresses of its tile's first rows
     Pos ahead{t_first, h_first};
     const __bf16 *y1, *y2;
@@ -754,14 +752,25 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
     };
     // copy instruction k of this wavefront for the tile that the copies stand at
     auto issue = [&](auto stagec, auto kc) {
-      constexpr int ST = decltype(stagec)::value, k = decltype(kc)::value, q = 2 * k + ROLE;
+      constexpr int ST = decltype(stagec)::value, k = decltype(kc)::value, q = k * NCQ + Q0;
       const int r0 = ahead.t * C::TILE;
       const uint32_t base = lds0 + ST * C::STAGE_BYTES;
       if constexpr (q < C::G1 + C::G2) {
         constexpr bool FIRST = q < C::G1;
-        constexpr int Q = FIRST ? q : q - C::G1;
-        const uint32_t o = r0 + C::TILE > L_oth ? co_tail[k] : co[k];
-        dma16(FIRST ? y1 : y2, o, base + (FIRST ? 0 : C::Y1_BYTES) + (4 * Q + w4) * 1024);
+        constexpr int Q = FIRST ? q : q - C::G1, PER = FIRST ? PER1 : PER2, ROWS = PER * 256 / (FIRST ? C::CPR1 : C::CPR2);
+        uint32_t o;
+        const __bf16* y = FIRST ? y1 : y2;
+        if constexpr (!C::TAIL_BRANCH) {
+          o = r0 + C::TILE > L_oth ? co_tail[k] : co[k];
+        } else if (r0 + C::TILE > L_oth) {
+          asm volatile("" ::: "memory");  // (keeps this a branch, and what it computes out of the loop's registers)
+          if constexpr (FIRST) o = copy_offset(cpr1, Q, s1, tail);
+          else o = copy_offset(cpr2, Q, s2, tail);
+        } else {
+          o = FIRST ? co1[Q % PER1] : co2[Q % PER2];
+          y += Q / PER * ROWS * (FIRST ? s1 : s2);
+        }
+        dma16(y, o, base + (FIRST ? 0 : C::Y1_BYTES) + (4 * Q + w4) * 1024);
       } else {
         // The block of the bias tensor that this tile meets, rows = queries.  Query side: 128 rows x 64 bytes
         // (4 chunks), chunk slot c ^ ((row >> 2) & 3); key side: 32 rows x 256 bytes (16 chunks), slot
@@ -781,38 +790,28 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
     auto issue_rows = [&](auto stagec) {
       if constexpr (C::ROWQ) {
         constexpr int ST = decltype(stagec)::value;
-        if (w4 == 0) {
+        if (NC > 0 && w4 == 0) {
           const int i = min(ahead.t * C::TILE + lane, p.L_q - 1);
-          dma4((ROLE == 0 ? p.lse : p.delta) + ((int64_t)b * p.H_q + ahead.h) * p.L_q, (uint32_t)i * 4u,
-                    lds0 + C::ROWS0 + ST * C::ROW_BYTES + (ROLE == 0 ? 0 : 256));
+          const int64_t row0 = ((int64_t)b * p.H_q + ahead.h) * p.L_q;
+          const uint32_t rows = lds0 + C::ROWS0 + ST * C::ROW_BYTES;
+          if constexpr (ROLE == 0 || C::COPIER == 1) dma4(p.lse + row0, (uint32_t)i * 4u, rows);
+          if constexpr (ROLE == 1 || C::COPIER == 0) dma4(p.delta + row0, (uint32_t)i * 4u, rows + 256);
         }
       }
     };
+    auto all_copies = [&](auto copyc) {
+      static_for<0, NC>([&](auto kc) { issue(copyc, kc); });
+    };
+    // The copies of a tile go out one instruction at a time between the M products of this role: queued together they would
+    // hold up every wavefront at the compute unit's memory pipe (64 bytes per clock).
+    auto copies = [&](auto copyc, auto nc, auto mc) {
+      if constexpr (NC == 0) return;
+      constexpr int n = decltype(nc)::value, GAP = decltype(mc)::value / (NC + 1) > 0 ? decltype(mc)::value / (NC + 1) : 1;
+      if constexpr (n % GAP == 0 && n / GAP < NC) issue(copyc, std::integral_constant<int, n / GAP>{});
+    };
 
-    // ---- accumulators and fragment addresses (stage 0) ----
-    f32x16 acc[DBX > 0 ? DBX : 1];
-#pragma unroll
-    for (int d = 0; d < DBX; ++d) acc[d] = zero16();
-    constexpr int NR = T < PR ? T : PR, NK = DBX < PK ? DBX : PK;
-    uint32_t ar[NR], atl[NK > 0 ? NK : 1], ath[NK > 0 ? NK : 1];
-#pragma unroll
-    for (int t = 0; t < NR; ++t) ar[t] = lds0 + OFFX + ln * RBX + (((2 * t + half) ^ bswz<CPRX>(ln)) << 4);
-#pragma unroll
-    for (int k = 0; k < NK; ++k) {
-      const uint32_t tb = lds0 + OFFT + (li & 1) * 8 + trow * RBT;
-      atl[k] = tb + (((4 * k + tcl) ^ bswz<CPRT>(trow)) << 4);
-      ath[k] = tb + 8 * RBT + (((4 * k + tcl) ^ bswz<CPRT>(trow + 8)) << 4);
-    }
-    auto row_frag = [&](auto stagec, int t) {
-      return read_k_frag(ar[t % PR] + decltype(stagec)::value * C::STAGE_BYTES + (t / PR) * (PR * 32));
-    };
-    // fragment n of the accumulation: 16-row step n / DBX, block n % DBX
-    auto acc_frag = [&](auto stagec, int n) {
-      const int t = n / (DBX > 0 ? DBX : 1), k = n % (DBX > 0 ? DBX : 1);
-      const uint32_t o = decltype(stagec)::value * C::STAGE_BYTES + t * 16 * RBT + (k / PK) * (PK * 64);
-      return read_tr_frag(atl[k % PK] + o, ath[k % PK] + o);
-    };
-    uint32_t e_lane = lds0 + C::E0 + w4 * 4096 + lane * 16, e_flip = C::E_BYTES;  // (the two buffers in turn)
+    // the two buffers of the hand-over in turn, per pair and buffer: dS' (2 KB), weights (key side, 2 KB)
+    uint32_t e_lane = lds0 + C::E0 + w4 * C::E_PAIR + lane * 16, e_flip = C::E_BYTES;
 
     // anything of the tile visible to this wave's rows?  everything?
     auto visibility = [&](int o0, bool& any, bool& full) {
@@ -828,240 +827,16 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
         }
       }
     };
-
-    // Fragment ring: RF LDS reads in flight ahead of their MFMAs.
-    constexpr int RING = 4, RF = T < RING ? T : RING, NF = 2 * DBX, RA = NF < RING ? NF : RING;
-    bf16x8 fr[RF];  // role 0: the next tile's first row fragments, carried from one iteration to the next
-    f32x16 dp;      // role 1: dP of the next tile, carried likewise
-    auto prefetch = [&](auto stagec) {
-#pragma unroll
-      for (int n = 0; n < RF; ++n) fr[n] = row_frag(stagec, n);
-    };
-    float lg = 0.f;
     Pos here{t_first, h_first};  // the tile this role works on
-    if constexpr (ROLE == 0 && C::LIN) lg = p.has_decay ? dt.log2_gamma[h_first] : 0.f;
 
-    // The copies of tile i + LOOK go out one instruction at a time between the MFMAs of a product: queued together
-    // they would hold up every wavefront at the compute unit's memory pipe (64 bytes per clock).
-    auto copies = [&](auto copyc, auto tc) {
-      constexpr int t = decltype(tc)::value, GAP = T / (NC + 1) > 0 ? T / (NC + 1) : 1;
-      if constexpr (t % GAP == 0 && t / GAP < NC) issue(copyc, std::integral_constant<int, t / GAP>{});
+    // Iteration i of the walk: tiles i and i + 1 have landed (of this wave's copies only the youngest LOOK - 2 tiles'
+    // may be in flight), dS' and the weights of tile i - 1 are written (of role 0's LDS operations only the reads of
+    // prefetch() may be in flight), and every wave is done with tile i - 2, whose stage takes tile i + LOOK.  Role 0
+    // works on tile i, role 1 on tile i - 1.
+    constexpr int RING = 4;  // LDS reads in flight ahead of their MFMAs (8 or 10: no faster, the key side of 192/128 spills)
+    auto convert_stat = [&](float v) {
+      return C::ABS ? fast_rcp(fmaxf(fabsf(v), 1.f)) : v == -INFINITY ? -INFINITY : p.b2 - v * 1.4426950408889634f;
     };
-    auto all_copies = [&](auto copyc) {
-      static_for<0, NC>([&](auto kc) { issue(copyc, kc); });
-    };
-
-    auto scores = [&](auto stagec, int o0) {
-      constexpr int ST = decltype(stagec)::value;
-      constexpr std::integral_constant<int, (ST + C::LOOK) % C::STAGES> copyc{};
-      bool any, full;
-      visibility(o0, any, full);
-      if (!any) {
-        all_copies(copyc);
-        return;
-      }
-      // (with 128 accumulator registers the row quantities are read behind the scores: 16 registers less meanwhile)
-      constexpr bool LATE = C::DB2 >= 8;
-      f32x4 nl4[4];
-      auto read_rows = [&]() {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          nl4[q] = f32x4{rq_own, rq_own, rq_own, rq_own};
-          if constexpr (C::ROWQ) nl4[q] = lds_read16(lds0 + C::ROWS0 + ST * C::ROW_BYTES + (8 * q + 4 * half) * 4);
-        }
-      };
-      if constexpr (!LATE) read_rows();
-      sched_fence();
-      f32x16 s = zero16();
-      static_for<0, T>([&](auto tc) {
-        constexpr int t = decltype(tc)::value;
-        s = mfma(fr[t % RF], xb[t], s);
-        if constexpr (t + RF < T) fr[t % RF] = row_frag(stagec, t + RF);
-        sched_fence();
-        copies(copyc, tc);
-      });
-      if constexpr (LATE) read_rows();
-      bf16x8 fa[RA > 0 ? RA : 1];
-#pragma unroll
-      for (int n = 0; n < RA; ++n) fa[n] = acc_frag(stagec, n);
-      sched_fence();
-      float x[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) x[r] = __builtin_fmaf(s[r], p.c2, C::NORM == NORM_SOFTMAX ? nl4[r / 4][r % 4] : p.b2);
-      if constexpr (C::BIAS) {
-        // register r = 4 q4 + e is (query, key) = (own row, key 8 q4 + 4 half + e of the tile) on the query side,
-        // (query 8 q4 + 4 half + e of the tile, own key) on the key side
-        const uint32_t bt = lds0 + ST * C::STAGE_BYTES + C::Y1_BYTES + C::Y2_BYTES;
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          uint32_t lo, hi;
-          if constexpr (C::KV_SIDE) {
-            const int row = 8 * q4 + 4 * half + ((lane & 15) >> 2);               // the row this lane addresses
-            const int cl = 4 * w4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);    // chunk of its 4 columns
-            const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(
-                bt + row * 256 + ((cl ^ ((row & 3) << 2)) << 4) + (lane & 1) * 8));
-            const u32x2 w2 = __builtin_bit_cast(u32x2, v);
-            lo = w2[0];
-            hi = w2[1];
-          } else {
-            const int row = 32 * w4 + ln;
-            const u32x2 w2 = *reinterpret_cast<__attribute__((address_space(3))) const u32x2*>(
-                (lds_char*)(uintptr_t)(bt + row * 64 + ((q4 ^ ((row >> 2) & 3)) << 4) + 8 * half));
-            lo = w2[0];
-            hi = w2[1];
-          }
-          x[4 * q4 + 0] += __builtin_bit_cast(float, lo << 16) * p.bunit;
-          x[4 * q4 + 1] += __builtin_bit_cast(float, lo & 0xffff0000u) * p.bunit;
-          x[4 * q4 + 2] += __builtin_bit_cast(float, hi << 16) * p.bunit;
-          x[4 * q4 + 3] += __builtin_bit_cast(float, hi & 0xffff0000u) * p.bunit;
-        }
-      }
-      if (!full) {  // a hidden entry gets the exponent that makes its weight exactly 0
-        sched_fence();  // (keeps this a branch: most tiles skip it)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int oth = o0 + key_offset(r) + 4 * half;
-          bool vis = oth < L_oth;
-          if constexpr (C::CAUSAL)
-            vis = vis && (C::KV_SIDE ? own <= oth + off && oth + off - p.window < own : oth <= own + off && own + off - p.window < oth);
-          x[r] = vis ? x[r] : -INFINITY;
-        }
-        sched_fence();
-      }
-      // the weight w2 (dV), and the factor e that the partner turns dP into dS' with
-      const float dist0 = (float)(C::KV_SIDE ? o0 + off - own + 4 * half : own + off - o0 - 4 * half);
-      float w2[16];
-      uint32_t e[16];  // (as bits: with ReLU it is a mask)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if constexpr (C::NORM == NORM_SOFTMAX) {
-          w2[r] = fast_exp2(x[r]);
-          e[r] = __builtin_bit_cast(uint32_t, w2[r]);
-        } else if constexpr (C::NORM == NORM_SIGMOID) {
-          w2[r] = fast_rcp(1.f + fast_exp2(-x[r]));
-          e[r] = __builtin_bit_cast(uint32_t, w2[r] * (1.f - w2[r]));
-        } else if constexpr (C::LIN) {  // a hidden entry has x = -inf: weight and factor 0
-          const bool vis = x[r] != -INFINITY;
-          const float dist = dist0 + (C::KV_SIDE ? 1.f : -1.f) * (float)key_offset(r);
-          const float dec = fast_exp2(lg * fmaxf(dist, 0.f));  // (visible entries have dist >= 0; <= 1 keeps 0 * dec finite)
-          const float sp = (vis ? x[r] : 0.f) * dec;           // S'
-          const float inv = nl4[r / 4][r % 4];
-          w2[r] = sp * inv;
-          e[r] = __builtin_bit_cast(uint32_t, vis ? inv * dec : 0.f);
-          // abs-sum: the sign of S' travels in the (otherwise unused) sign of the factor
-          if constexpr (C::NORM == NORM_ABSSUM)
-            e[r] |= __builtin_bit_cast(uint32_t, sp) & 0x80000000u;
-        } else {  // no normalization with ReLU: P = max(x, 0)
-          w2[r] = fmaxf(x[r], 0.f);
-          e[r] = x[r] > 0.f ? 0xffffffffu : 0u;  // dS' = dP or 0
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        lds_store16(e_lane + q * 1024, u32x4{e[4 * q], e[4 * q + 1], e[4 * q + 2], e[4 * q + 3]});
-      if constexpr (C::KV_SIDE) {
-        bf16x8 wb[2] = {pack8(w2, 0), pack8(w2, 1)};
-        sched_fence();
-#pragma unroll
-        for (int n = 0; n < NF; ++n) {
-          acc[n % DBX] = mfma(fa[n % RA], wb[n / DBX], acc[n % DBX]);
-          if (n + RA < NF) fa[n % RA] = acc_frag(stagec, n + RA);
-          sched_fence();
-        }
-      }
-    };
-
-    // role 1: dP of the walk's tile in stage nextc, from row fragments through the ring f that holds the first of them
-    auto upstream = [&](auto nextc, bf16x8 (&f)[RING]) {
-      dp = zero16();
-      static_for<0, T>([&](auto tc) {
-        constexpr int t = decltype(tc)::value;
-        dp = mfma(f[(NF + t) % RING], xb[t], dp);
-        if constexpr (t + RING < T) f[(NF + t) % RING] = row_frag(nextc, t + RING);
-        sched_fence();
-      });
-    };
-    // role 1: dS' and the accumulation of tile n (stage stagec), then dP of the tile behind it (stage nextc)
-    auto gradients = [&](auto stagec, auto nextc, int o0) {
-      constexpr int ST = decltype(stagec)::value;
-      constexpr std::integral_constant<int, (ST + 1 + C::LOOK) % C::STAGES> copyc{};
-      bool any, full;
-      visibility(o0, any, full);
-      bf16x8 f[RING];
-      if (!any) {
-#pragma unroll
-        for (int t = 0; t < RING && t < T; ++t) f[(NF + t) % RING] = row_frag(nextc, t);
-        all_copies(copyc);
-        upstream(nextc, f);
-        return;
-      }
-      u32x4 e4[4];
-      f32x4 dl4[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) e4[q] = lds_read16u(e_lane + q * 1024);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        dl4[q] = f32x4{rq_own, rq_own, rq_own, rq_own};
-        if constexpr (C::ROWQ) dl4[q] = lds_read16(lds0 + C::ROWS0 + ST * C::ROW_BYTES + 256 + (8 * q + 4 * half) * 4);
-      }
-#pragma unroll
-      for (int n = 0; n < RING; ++n) f[n] = n < NF ? acc_frag(stagec, n) : row_frag(nextc, n - NF);
-      sched_fence();
-      float w[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const uint32_t ebits = e4[r / 4][r % 4];
-        const float e = __builtin_bit_cast(float, ebits), dl = dl4[r / 4][r % 4];
-        if constexpr (C::NORM == NORM_SOFTMAX) {
-          w[r] = e * (dp[r] - dl);
-        } else if constexpr (C::ABS) {
-          // g * delta: delta with its sign flipped where S' < 0 (abs-sum), or delta already signed by the row sum
-          const float corr = C::NORM == NORM_ABSSUM
-                                 ? __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, dl) ^ (ebits & 0x80000000u))
-                                 : dl;
-          w[r] = (dp[r] - corr) * fabsf(e);
-        } else if constexpr (C::NORM == BWD_NORM_NONE_RELU) {
-          const float d = dp[r];  // (a scalar first: the bit cast of a vector element came out as an undefined register)
-          w[r] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, d) & ebits);
-        } else {
-          w[r] = dp[r] * e;
-        }
-      }
-      if constexpr (C::LIN)
-        if (!full) {  // the factor of a hidden entry is 0: its gradient is 0 whatever dP is, where the product with an infinite one is NaN
-          sched_fence();
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            w[r] = __builtin_bit_cast(float, (e4[r / 4][r % 4] & 0x7fffffffu) != 0 ? __builtin_bit_cast(uint32_t, w[r]) : 0u);
-          sched_fence();
-        }
-      if constexpr (C::BIAS && !C::KV_SIDE) {
-        // the bias enters S' with slope 1: its gradient is dS' itself, 4 x 4 consecutive keys of the lane's own row
-        if (p.dbias != nullptr && own < p.L_q) {
-          __bf16* drow = p.dbias + (((int64_t)b * p.H_q + ho) * p.L_q + own) * p.dbias_ld + o0 + 4 * half;
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4)
-            if (o0 + 8 * q4 + 4 * half < p.L_k) {  // (a group across the last key writes into the row's padding)
-              bf16x4 v;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = (__bf16)w[4 * q4 + e];
-              *reinterpret_cast<bf16x4*>(drow + 8 * q4) = v;
-            }
-        }
-      }
-      bf16x8 wb[2] = {pack8(w, 0), pack8(w, 1)};
-      sched_fence();
-      static_for<0, NF>([&](auto nc) {
-        constexpr int n = decltype(nc)::value, m = n + RING, GAP = NF / (NC + 1) > 0 ? NF / (NC + 1) : 1;
-        acc[n % DBX] = mfma(f[n % RING], wb[n / DBX], acc[n % DBX]);
-        if constexpr (m < NF) f[n % RING] = acc_frag(stagec, m);
-        else if constexpr (m < NF + T) f[n % RING] = row_frag(nextc, m - NF);
-        sched_fence();
-        if constexpr (n % GAP == 0 && n / GAP < NC) issue(copyc, std::integral_constant<int, n / GAP>{});
-      });
-      upstream(nextc, f);
-    };
-
     auto convert_rows = [&](auto stagec) {  // the tile's statistics in LDS, as they arrived, into what the weights need
       if constexpr (C::ROWQ && ROLE == 0) {
         if (w4 == 0) {
@@ -1070,96 +845,377 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
         }
       }
     };
-    // Iteration i of the walk: tiles i and i + 1 have landed (of this wave's copies only the youngest LOOK - 2 tiles'
-    // may be in flight), the factors of tile i - 1 are written (of role 0's LDS operations only the reads of
-    // prefetch() may be in flight), and every wave is done with tile i - 2, whose stage takes tile i + LOOK.  Role 0
-    // works on tile i, role 1 on tile i - 1.
-    auto enter = [&](auto stagec, int i) {
+    auto enter = [&](auto stagec) {
       constexpr int ST = decltype(stagec)::value;
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::LOOK - 2) * NC) : "memory");
-      if constexpr (ROLE == 0) asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(RF) : "memory");
+      if constexpr (NC > 0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::LOOK - 2) * NC) : "memory");
+      if constexpr (ROLE == 0) asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(RING) : "memory");
       else asm volatile("s_barrier" ::: "memory");
       convert_rows(std::integral_constant<int, (ST + 1) % C::STAGES>{});
       issue_rows(std::integral_constant<int, (ST + C::LOOK) % C::STAGES>{});
     };
-    // role 0: iteration i on tile i = n; role 1: iteration n + 1 on tile n
-    auto step = [&](auto stagec, int n) {
-      constexpr int ST = decltype(stagec)::value;
-      constexpr std::integral_constant<int, (ST + 1) % C::STAGES> nextc{};
-      const int i = ROLE == 0 ? n : n + 1;
-      if constexpr (ROLE == 0) {
-        enter(stagec, i);
-        scores(stagec, here.t * C::TILE);
-      } else {
-        enter(nextc, i);
-        gradients(stagec, nextc, here.t * C::TILE);
-      }
+    auto next_tile = [&]() {
       advance_copies();
       advance(here);
       e_lane += e_flip;
       e_flip = 0u - e_flip;
-      if constexpr (ROLE == 0) {
-        sched_fence();
-        prefetch(nextc);
-        sched_fence();
-      }
-      if constexpr (ROLE == 0 && C::LIN && C::KV_SIDE)
-        if (here.t == t_first && n + 1 < N) lg = p.has_decay ? dt.log2_gamma[here.h] : 0.f;
     };
-    if (N > 0) {
-      static_for<0, C::LOOK>([&](auto nc) {
-        issue_rows(nc);
-        all_copies(nc);
-        advance_copies();
-      });
-    }
-    // The own operand, requested in front of the first copies, is consumed here once: the compiler must not wait for it inside
-    // the loop, where its count would wait for the copies too.  (In front of the copies the two latencies added up: 0.2 us of a
-    // pass of one to four tiles; and the abs-sum kernels of 128/256 spilled 25 to 30 registers instead of 9: 2 x 64/8 x 1024 causal
-    // 593 -> 544 us.)
-#pragma unroll
-    for (int t = 0; t < T; ++t) pin(xb[t]);
-    pin(rq_own);
-    if constexpr (OWN_ROW && ROLE == 0) rq_own = convert_stat(rq_own);
-    if (N > 0) {
+    auto first_copies = [&]() {
+      if (N > 0)
+        static_for<0, C::LOOK>([&](auto nc) {
+          issue_rows(nc);
+          all_copies(nc);
+          advance_copies();
+        });
+    };
+    constexpr std::integral_constant<int, 0> first{};
+    auto first_tiles_landed = [&]() {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      constexpr std::integral_constant<int, 0> first{};
       convert_rows(first);
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      if constexpr (ROLE == 0) {
-        prefetch(first);
-        sched_fence();
-      } else {  // iteration 0
-        enter(first, 0);
-        bf16x8 f[RING];
-#pragma unroll
-        for (int t = 0; t < RING && t < T; ++t) f[(NF + t) % RING] = row_frag(first, t);
-        all_copies(std::integral_constant<int, C::LOOK>{});
-        advance_copies();
-        upstream(first, f);
-      }
+    };
+    auto all_tiles = [&](auto step) {
 #pragma clang loop unroll(disable)
       for (int n = 0; n < N; n += C::STAGES)
         static_for<0, C::STAGES>([&](auto uc) {
           if (n + decltype(uc)::value < N) step(uc, n + decltype(uc)::value);
         });
-      if constexpr (ROLE == 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // iteration N
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no copy outlives the workgroup's LDS)
-    }
+    };
 
-    // ---- results: register r of block db is column own, row d = 32 db + 8 (r/4) + 4 half + r%4 ----
-    if (own < L_own) {
-      constexpr int D = ROLE == 0 ? C::DV : C::DQK;
-      float* o = nullptr;
-      if constexpr (ROLE == 0) o = p.dV + (((int64_t)b * p.H_kv + hk) * p.L_k + own) * D;
-      else o = (C::KV_SIDE ? p.dK + ((int64_t)b * p.H_kv + hk) * p.L_k * D : p.dQ + ((int64_t)b * p.H_q + ho) * p.L_q * D) + (int64_t)own * D;
-      const float f = ROLE == 0 ? 1.f : p.scale;
+    if constexpr (ROLE == 0) {
+      constexpr int T1 = C::T1, T2 = C::T2, M = T1 + T2;
+      // ---- own operands: B fragments, straight from global memory ----
+      const __bf16* x1 = C::KV_SIDE ? p.K + b * p.ks[0] + hk * p.ks[1] + (int64_t)own_c * p.ks[2]
+                                    : p.Q + b * p.qs[0] + ho * p.qs[1] + (int64_t)own_c * p.qs[2];
+      const __bf16* x2 = C::KV_SIDE ? p.V + b * p.vs[0] + hk * p.vs[1] + (int64_t)own_c * p.vs[2]
+                                    : p.dO + (((int64_t)b * p.H_q + ho) * p.L_q + own_c) * C::DV;
+      bf16x8 xb1[T1], xb2[T2];
 #pragma unroll
-      for (int db = 0; db < DBX; ++db)
+      for (int t = 0; t < T1; ++t) xb1[t] = *reinterpret_cast<const bf16x8*>(x1 + (2 * t + half) * 8);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<f32x4*>(o + 32 * db + 8 * q + 4 * half) =
-              f32x4{acc[db][4 * q] * f, acc[db][4 * q + 1] * f, acc[db][4 * q + 2] * f, acc[db][4 * q + 3] * f};
+      for (int t = 0; t < T2; ++t) xb2[t] = *reinterpret_cast<const bf16x8*>(x2 + (2 * t + half) * 8);
+      // query side: the row quantities of the lane's own row (the statistic is converted behind the first copies)
+      constexpr bool OWN_ROW = !C::KV_SIDE && C::ROWS;
+      float nl_own = OWN_ROW ? (C::ABS ? 0.f : -INFINITY) : C::LIN ? 1.f : -INFINITY, dl_own = 0.f;
+      if constexpr (OWN_ROW) {
+        if (own < p.L_q) {
+          nl_own = p.lse[((int64_t)b * p.H_q + ho) * p.L_q + own];
+          dl_own = p.delta[((int64_t)b * p.H_q + ho) * p.L_q + own];
+        }
+      }
+      // row fragments (stage 0): those of X1's product, then those of X2's
+      constexpr int NR1 = T1 < C::PR1 ? T1 : C::PR1, NR2 = T2 < C::PR2 ? T2 : C::PR2;
+      uint32_t ar1[NR1], ar2[NR2];
+#pragma unroll
+      for (int t = 0; t < NR1; ++t) ar1[t] = lds0 + ln * C::RB1 + (((2 * t + half) ^ bswz<C::CPR1>(ln)) << 4);
+#pragma unroll
+      for (int t = 0; t < NR2; ++t) ar2[t] = lds0 + C::Y1_BYTES + ln * C::RB2 + (((2 * t + half) ^ bswz<C::CPR2>(ln)) << 4);
+      auto row_frag = [&](auto stagec, int n) {
+        constexpr int o = decltype(stagec)::value * C::STAGE_BYTES;
+        if (n < T1) return read_k_frag(ar1[n % C::PR1] + o + (n / C::PR1) * (C::PR1 * 32));
+        const int t = n - T1;
+        return read_k_frag(ar2[t % C::PR2] + o + (t / C::PR2) * (C::PR2 * 32));
+      };
+      bf16x8 fr[RING];  // the ring: the next tile's first fragments are carried from one iteration to the next
+      auto prefetch = [&](auto stagec) {
+#pragma unroll
+        for (int n = 0; n < RING; ++n) fr[n] = row_frag(stagec, n);
+      };
+      // Decay factors of a tile whose entries are all visible: one exponential per lane, for the register with the shortest
+      // distance, times these (register r = 4 q + e is q * 8 + e rows further on the key side, nearer on the query side).
+      float lg = 0.f, dec_q[C::LIN ? 4 : 1], dec_e[C::LIN ? 4 : 1];
+      auto set_decay = [&](int h) {
+        if constexpr (C::LIN) {
+          lg = p.has_decay ? dt.log2_gamma[h] : 0.f;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            dec_q[k] = fast_exp2(lg * (C::KV_SIDE ? 8.f * k : 24.f - 8.f * k));
+            dec_e[k] = fast_exp2(lg * (C::KV_SIDE ? 1.f * k : 3.f - k));
+          }
+        }
+      };
+      set_decay(h_first);
+
+      auto scores = [&](auto stagec, int o0) {
+        constexpr int ST = decltype(stagec)::value;
+        constexpr std::integral_constant<int, (ST + C::LOOK) % C::STAGES> copyc{};
+        bool any, full;
+        visibility(o0, any, full);
+        if (!any) {
+          all_copies(copyc);
+          return;
+        }
+        f32x4 nl4[4], dl4[4];
+        auto read_rows = [&](f32x4 (&v)[4], float own_value, int o) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            v[q] = f32x4{own_value, own_value, own_value, own_value};
+            if constexpr (C::ROWQ) v[q] = lds_read16(lds0 + C::ROWS0 + ST * C::ROW_BYTES + o + (8 * q + 4 * half) * 4);
+          }
+        };
+        if constexpr (!C::LIN) read_rows(nl4, nl_own, 0);
+        sched_fence();
+        f32x16 s = zero16(), dp = zero16();
+        auto product = [&](auto nc) {
+          constexpr int n = decltype(nc)::value;
+          if constexpr (n < T1) s = mfma(fr[n % RING], xb1[n < T1 ? n : 0], s);
+          else dp = mfma(fr[n % RING], xb2[n < T1 ? 0 : n - T1], dp);
+          if constexpr (n + RING < M) fr[n % RING] = row_frag(stagec, n + RING);
+          sched_fence();
+          copies(copyc, nc, std::integral_constant<int, M>{});
+        };
+                constexpr int AHEAD = 2;  // products of dP in front of the first use of S: they cover its latency
+        static_for<0, T1 + AHEAD>(product);
+        if constexpr (C::LIN) read_rows(nl4, nl_own, 0);  // (here: 16 registers less during the products)
+        float x[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) x[r] = __builtin_fmaf(s[r], p.c2, C::NORM == NORM_SOFTMAX ? nl4[r / 4][r % 4] : p.b2);
+        if constexpr (C::BIAS) {
+          // register r = 4 q4 + e is (query, key) = (own row, key 8 q4 + 4 half + e of the tile) on the query side,
+          // (query 8 q4 + 4 half + e of the tile, own key) on the key side
+          const uint32_t bt = lds0 + ST * C::STAGE_BYTES + C::Y1_BYTES + C::Y2_BYTES;
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            uint32_t lo, hi;
+            if constexpr (C::KV_SIDE) {
+              const int row = 8 * q4 + 4 * half + ((lane & 15) >> 2);               // the row this lane addresses
+              const int cl = 4 * w4 + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);    // chunk of its 4 columns
+              const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(
+                  bt + row * 256 + ((cl ^ ((row & 3) << 2)) << 4) + (lane & 1) * 8));
+              const u32x2 w2 = __builtin_bit_cast(u32x2, v);
+              lo = w2[0];
+              hi = w2[1];
+            } else {
+              const int row = 32 * w4 + ln;
+              const u32x2 w2 = *reinterpret_cast<__attribute__((address_space(3))) const u32x2*>(
+                  (lds_char*)(uintptr_t)(bt + row * 64 + ((q4 ^ ((row >> 2) & 3)) << 4) + 8 * half));
+              lo = w2[0];
+              hi = w2[1];
+            }
+            x[4 * q4 + 0] += __builtin_bit_cast(float, lo << 16) * p.bunit;
+            x[4 * q4 + 1] += __builtin_bit_cast(float, lo & 0xffff0000u) * p.bunit;
+            x[4 * q4 + 2] += __builtin_bit_cast(float, hi << 16) * p.bunit;
+            x[4 * q4 + 3] += __builtin_bit_cast(float, hi & 0xffff0000u) * p.bunit;
+          }
+        }
+        // abs-sum family, no normalization: distance to the diagonal of register 0's entry, and what turns dP - delta into dS'
+        const float dist0 = (float)(C::KV_SIDE ? o0 + off - own + 4 * half : own + off - o0 - 4 * half);
+        float f[C::LIN ? 16 : 1];
+        if (!full) {  // a hidden entry gets the exponent (or the factors) that make its weight exactly 0
+          sched_fence();  // (keeps this a branch: most tiles skip it)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int oth = o0 + key_offset(r) + 4 * half;
+            bool vis = oth < L_oth;
+            if constexpr (C::CAUSAL)
+              vis = vis && (C::KV_SIDE ? own <= oth + off && oth + off - p.window < own : oth <= own + off && own + off - p.window < oth);
+            x[r] = vis ? x[r] : C::LIN ? 0.f : -INFINITY;
+            if constexpr (C::LIN) {  // (visible entries have a distance >= 0)
+              const float dist = dist0 + (C::KV_SIDE ? 1.f : -1.f) * (float)key_offset(r);
+              f[r] = vis ? fast_exp2(lg * fmaxf(dist, 0.f)) : 0.f;
+            }
+          }
+          sched_fence();
+        } else if constexpr (C::LIN) {
+          const float near = fast_exp2(lg * (C::KV_SIDE ? dist0 : dist0 - 27.f));
+#pragma unroll
+          for (int r = 0; r < 16; ++r) f[r] = near * dec_q[r / 4] * dec_e[r % 4];
+          sched_fence();
+        }
+        // the weights, a few of them between every two products of dP
+        float pv[16];
+        auto weight = [&](int r) {
+          if constexpr (C::NORM == NORM_SOFTMAX) {
+            pv[r] = fast_exp2(x[r]);
+          } else if constexpr (C::NORM == NORM_SIGMOID) {
+            pv[r] = fast_rcp(1.f + fast_exp2(-x[r]));
+          } else if constexpr (C::LIN) {
+            f[r] *= nl4[r / 4][r % 4];
+            pv[r] = x[r] * f[r];
+          } else {  // no normalization with ReLU
+            pv[r] = fmaxf(x[r], 0.f);
+          }
+        };
+        static_for<T1 + AHEAD, M>([&](auto nc) {
+          constexpr int k = decltype(nc)::value - T1 - AHEAD, K = T2 - AHEAD;
+#pragma unroll
+          for (int r = 16 * k / K; r < 16 * (k + 1) / K; ++r) weight(r);
+          sched_fence();
+          product(nc);
+        });
+        read_rows(dl4, dl_own, 256);
+        if constexpr (C::KV_SIDE) {
+#pragma unroll
+          for (int t = 0; t < 2; ++t) lds_store16(e_lane + 2048 + t * 1024, __builtin_bit_cast(u32x4, pack8(pv, t)));
+        }
+        sched_fence();
+        float w[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float dl = dl4[r / 4][r % 4], d = dp[r];
+          if constexpr (C::NORM == NORM_SOFTMAX) {
+            w[r] = pv[r] * (d - dl);
+          } else if constexpr (C::NORM == NORM_SIGMOID) {
+            w[r] = d * pv[r] * (1.f - pv[r]);
+          } else if constexpr (C::LIN) {
+            // g * delta: delta with its sign flipped where S' < 0 (abs-sum), or delta already signed by the row sum
+            const float corr =
+                C::NORM == NORM_ABSSUM
+                    ? __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, dl) ^ (__builtin_bit_cast(uint32_t, pv[r]) & 0x80000000u))
+                    : dl;
+            w[r] = (d - corr) * f[r];
+          } else {
+            w[r] = pv[r] > 0.f ? d : 0.f;
+          }
+        }
+        if constexpr (C::LIN)
+          if (!full) {  // a hidden entry's gradient is 0 whatever dP is, where the product of its factor 0 with an infinite one is NaN
+            sched_fence();
+#pragma unroll
+            for (int r = 0; r < 16; ++r) w[r] = f[r] != 0.f ? w[r] : 0.f;
+            sched_fence();
+          }
+        if constexpr (C::BIAS && !C::KV_SIDE) {
+          // the bias enters S' with slope 1: its gradient is dS' itself, 4 x 4 consecutive keys of the lane's own row
+          if (p.dbias != nullptr && own < p.L_q) {
+            __bf16* drow = p.dbias + (((int64_t)b * p.H_q + ho) * p.L_q + own) * p.dbias_ld + o0 + 4 * half;
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+              if (o0 + 8 * q4 + 4 * half < p.L_k) {  // (a group across the last key writes into the row's padding)
+                bf16x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (__bf16)w[4 * q4 + e];
+                *reinterpret_cast<bf16x4*>(drow + 8 * q4) = v;
+              }
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) lds_store16(e_lane + t * 1024, __builtin_bit_cast(u32x4, pack8(w, t)));
+      };
+
+      first_copies();
+      // The own operands, requested in front of the first copies, are consumed here once: the compiler must not wait for them
+      // inside the loop, where its count would wait for the copies too.
+#pragma unroll
+      for (int t = 0; t < T1; ++t) pin(xb1[t]);
+#pragma unroll
+      for (int t = 0; t < T2; ++t) pin(xb2[t]);
+      pin(nl_own);
+      pin(dl_own);
+      if constexpr (OWN_ROW) nl_own = convert_stat(nl_own);
+      if (N > 0) {
+        first_tiles_landed();
+        prefetch(first);
+        sched_fence();
+        all_tiles([&](auto stagec, int n) {  // iteration n on tile n
+          constexpr std::integral_constant<int, (decltype(stagec)::value + 1) % C::STAGES> nextc{};
+          enter(stagec);
+          scores(stagec, here.t * C::TILE);
+          next_tile();
+          sched_fence();
+          prefetch(nextc);
+          sched_fence();
+          if constexpr (C::LIN && C::KV_SIDE)
+            if (here.t == t_first && n + 1 < N) set_decay(here.h);
+        });
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // iteration N
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (no copy outlives the workgroup's LDS)
+      }
+    } else {
+      constexpr int DB = C::DB, DB2 = C::DB2, NB = DB + DB2, NF = 2 * NB;
+      static_assert(NF % RING == 0, "the ring runs on from tile to tile");
+      f32x16 acc[NB];
+#pragma unroll
+      for (int d = 0; d < NB; ++d) acc[d] = zero16();
+      // transposed fragments (stage 0): blocks of Y1 (dK, dQ), then (key side) of Y2 (dV)
+      constexpr int NK1 = DB < C::PK1 ? DB : C::PK1, NK2 = DB2 < C::PK2 ? DB2 : C::PK2;
+      uint32_t at1[NK1][2], at2[NK2 > 0 ? NK2 : 1][2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int k = 0; k < NK1; ++k)
+          at1[k][h] = lds0 + (li & 1) * 8 + (trow + 8 * h) * C::RB1 + (((4 * k + tcl) ^ bswz<C::CPR1>(trow + 8 * h)) << 4);
+#pragma unroll
+        for (int k = 0; k < NK2; ++k)
+          at2[k][h] = lds0 + C::Y1_BYTES + (li & 1) * 8 + (trow + 8 * h) * C::RB2 + (((4 * k + tcl) ^ bswz<C::CPR2>(trow + 8 * h)) << 4);
+      }
+      // fragment n of the sums: 16-row step n / NB, block n % NB
+      auto acc_frag = [&](auto stagec, int n) {
+        const int t = n / NB, k = n % NB;
+        const uint32_t st = decltype(stagec)::value * C::STAGE_BYTES;
+        if (k < DB) {
+          const uint32_t o = st + t * 16 * C::RB1 + (k / C::PK1) * (C::PK1 * 64);
+          return read_tr_frag(at1[k % C::PK1][0] + o, at1[k % C::PK1][1] + o);
+        }
+        const int k2 = k - DB;
+        const uint32_t o = st + t * 16 * C::RB2 + (k2 / C::PK2) * (C::PK2 * 64);
+        return read_tr_frag(at2[k2 % C::PK2][0] + o, at2[k2 % C::PK2][1] + o);
+      };
+      bf16x8 f[RING];  // the ring, carried from tile to tile
+      auto prefetch = [&](auto stagec) {
+#pragma unroll
+        for (int n = 0; n < RING; ++n) f[n] = acc_frag(stagec, n);
+      };
+      // the sums over tile n (stage stagec); the ring goes on with the tile behind it (stage nextc)
+      auto sums = [&](auto stagec, auto nextc, int o0) {
+        constexpr int ST = decltype(stagec)::value;
+        constexpr std::integral_constant<int, (ST + 1 + C::LOOK) % C::STAGES> copyc{};
+        bool any, full;
+        visibility(o0, any, full);
+        if (!any) {
+          all_copies(copyc);
+          prefetch(nextc);
+          return;
+        }
+        bf16x8 wb[2], pb[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          wb[t] = read_k_frag(e_lane + t * 1024);
+          if constexpr (C::KV_SIDE) pb[t] = read_k_frag(e_lane + 2048 + t * 1024);
+        }
+        sched_fence();
+        static_for<0, NF>([&](auto nc) {
+          constexpr int n = decltype(nc)::value, k = n % NB, t = n / NB;
+          acc[k] = mfma(f[n % RING], k < DB ? wb[t] : pb[t], acc[k]);
+          if constexpr (n + RING < NF) f[n % RING] = acc_frag(stagec, n + RING);
+          else f[n % RING] = acc_frag(nextc, n + RING - NF);
+          sched_fence();
+          copies(copyc, nc, std::integral_constant<int, NF>{});
+        });
+      };
+
+      first_copies();
+      if (N > 0) {
+        first_tiles_landed();
+        enter(first);  // iteration 0
+        prefetch(first);
+        all_copies(std::integral_constant<int, C::LOOK>{});
+        advance_copies();
+        all_tiles([&](auto stagec, int n) {  // iteration n + 1 on tile n
+          constexpr std::integral_constant<int, (decltype(stagec)::value + 1) % C::STAGES> nextc{};
+          enter(nextc);
+          sums(stagec, nextc, here.t * C::TILE);
+          next_tile();
+        });
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // (no copy outlives the workgroup's LDS)
+      }
+
+      // ---- results: register r of block db is column own, row d = 32 db + 8 (r/4) + 4 half + r%4 ----
+      if (own < L_own) {
+        auto store = [&](float* o, const f32x16& a, float f) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(o + 8 * q + 4 * half) = f32x4{a[4 * q] * f, a[4 * q + 1] * f, a[4 * q + 2] * f, a[4 * q + 3] * f};
+        };
+        float* o = (C::KV_SIDE ? p.dK + ((int64_t)b * p.H_kv + hk) * p.L_k * C::DQK : p.dQ + ((int64_t)b * p.H_q + ho) * p.L_q * C::DQK) +
+                   (int64_t)own * C::DQK;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) store(o + 32 * db, acc[db], p.scale);
+        if constexpr (C::KV_SIDE) {
+          float* o2 = p.dV + (((int64_t)b * p.H_kv + hk) * p.L_k + own) * C::DV;
+#pragma unroll
+          for (int db = 0; db < DB2; ++db) store(o2 + 32 * db, acc[DB + db], 1.f);
+        }
+      }
     }
   };
   if (wave < 4) walk(std::integral_constant<int, 0>{});

@@ -20,16 +20,15 @@ constexpr int64_t kLongBiasWalk = 384;
 // Where only one workgroup fits a CU, short walks stay with one wavefront too: the pair is a tile behind itself, has three tiles
 // to wait for at its start, and of a narrow window most waves skip most tiles.  Keys (queries) that a row may see, times the
 // q heads that a key-side workgroup walks one after the other.  4 x 24 heads x 4096, one wavefront / pair, us: 128/128 window
-// 64 429 / 461, 256 533 / 548, 512 671 / 672; 192/128 64 529 / 572, 256 677 / 686, 512 844 / 827; 128/256 64 635 / 665, 128
-// 698 / 705, 256 807 / 778.  Causal without a window: 128/128 64 rows 18.0 / 18.9, 128 28.3 / 28.7, 150 31.3 / 30.4; 192/128
-// 21.0 / 21.8, 33.0 / 33.7, 36.4 / 35.8; 128/256 64 rows 23.7 / 24.6, 100 35.0 / 33.8; 128/128 with a bias tensor 64 rows 19.1 / 20.6,
-// 100 28.2 / 29.3 (192/128 with one 21.9 / 22.3, 32.8 / 32.3: always pairs).
-constexpr int64_t short_window(int dv) { return dv == 256 ? 96 : 256; }
+// 64 418 / 447, 128 448 / 469, 200 518 / 511, 256 502 / 509; 192/128 64 491 / 536, 128 540 / 565, 200 642 / 613, 256 622 / 618;
+// 128/256 64 600 / 609, 96 662 / 631.  Causal without a window, 8 x 64 heads: 128/128 64 rows 36.4 / 38.6, 100 53.9 / 55.5, 128 60.5 /
+// 64.0; 192/128 45.6 / 47.8, 67.9 / 74.7, 75.5 / 87.6; 128/256 64 rows 51.1 / 53.0 (100 rows 4 x 24 heads 26.9 / 25.3).
+constexpr int64_t short_window(int dqk, int dv) { return dv == 256 ? 64 : dqk == 192 ? 160 : 256; }
 constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
 // Both sides go in one launch (the key side's workgroups first): two launches / one, us, causal unless said: 64/64 1 x 16 heads x
 // 1024 54 / 34, 1 x 16 x 4096 186 / 140, 4 x 32/8 x 2048 335 / 289, 8 x 16 x 2048 unmasked 506 / 510, with a bias tensor 2 x 12 x 1023 x 1201
 // 85 / 68; 192/128 1 x 16 x 500 53 / 33, 1 x 6 x 4096 259 / 172, 1 x 128 x 4096 2597 / 2607; 128/256 2 x 16 x 1024 100 / 74, 4 x 16 x
-// 2048 438 / 433.  Four exceptions:
+// 2048 438 / 433.  Three exceptions:
 //   * 64/64 without a bias tensor: alone, the query side has 134 registers, three workgroups per CU; beside the key side it has that
 //     one's 202, two.  What the shared launch saves is at its ends: calls of much work (the keys that the query workgroups of an XCD
 //     walk, see walked_keys), whose key side fills the device, go one behind the other.  Causal (thousands of walked keys): 1 x 16 x 8192 (524)
@@ -38,16 +37,13 @@ constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
 //     (131) 151 / 146, 1 x 16 x 4096 (262) 249 / 245, 1 x 32 x 4096 (524) 480 / 483, 8 x 64 x 1024 (524) 584 / 593, 8 x 16 x 4096 (2097) 1882 / 1930.
 //   * 128/128 without a bias tensor: beside the key side's workgroups those of the query side get a CU each, which they otherwise
 //     share by two.  It pays while the key side leaves compute units idle: few workgroups (of 32 compute units per XCD), or
-//     causal ones of unequal length.  Causal (workgroups of the key side per XCD): 1 x 16 x 1024 (16) 75 / 44, 1 x 32/8 x 4096 (32) 676 / 550,
-//     2 x 12 x 2048 (48) 139 / 127, but 8 x 24/6 x 1000 (48) 297 / 332, 8 x 12 x 700 (72) 104 / 109, 4 x 32/8 x 2048 (64) 552 / 597; unmasked
-//     1 x 32/8 x 2048 (16) 332 / 256, 2 x 32/8 x 1500 (24) 298 / 290, 1 x 16 x 2048 (32, 64 of both sides) 142 / 141, but 2 x 32/8 x 2048 (32)
-//     461 / 506, 2 x 12 x 2048 (48) 221 / 252.
-//   * 192/128, causal, much work: the two sides among each other cost more in the L2 than the ends save (thousands of walked keys; on a
-//     second card the long calls were alike either way): 1 x 128 heads x 2048 (262) 812 / 798, 8 x 128 x 1024 (524) 2077 / 2064, 1 x 64 x 4096 (524)
-//     1367 / 1366, 1 x 128 x 3500 (784) 2108 / 2122, 1 x 24 x 8192 (786) 1855 / 1883, 1 x 128 x 4096 (1049) 2731 / 2755, 1 x 128/16 x 4096 (1049) 2657 /
-//     2693, 1 x 64 x 6000 (1128) 2781 / 2828, 1 x 128 x 8192 (4194) 10216 / 10286.  Unmasked: 8 x 16 x 1024 397 / 383, 1 x 64 x 4096 2413 / 2432.
-//   * 128/256, abs-sum family: as one kernel it spills 20 to 22 registers instead of 4.  2 x 16 x 1024 (64 workgroups of both sides per XCD)
-//     117 / 91, 1 x 24/6 x 2048 (80) 480 / 422, 2 x 16 x 2048 (128) 254 / 263, 4 x 16 x 2048 (256) 511 / 533.
+//     causal ones of unequal length.  Causal (workgroups of the key side per XCD): 1 x 16 x 1024 (16) 72 / 43, 1 x 32/8 x 4096 (32) 627 / 529,
+//     2 x 12 x 2048 (48) 135 / 124, but 8 x 24/6 x 1000 (48) 287 / 323, 8 x 12 x 700 (72) 102 / 108, 4 x 32/8 x 2048 (64) 519 / 576; unmasked
+//     1 x 32/8 x 2048 (16) 305 / 251, 2 x 32/8 x 1500 (24) 282 / 288, 1 x 16 x 2048 (32, 64 of both sides) 136 / 134, but 2 x 32/8 x 2048 (32)
+//     441 / 495, 2 x 12 x 2048 (48) 213 / 242.
+//   * 192/128, causal, much work: the two sides among each other cost more in the L2 than the ends save (thousands of walked keys; on some
+//     cards the long calls are alike either way): 1 x 128 heads x 2048 (262) 766 / 746, 1 x 64 x 4096 (524) 1262 / 1256, 8 x 16 x 2048 (262)
+//     760 / 737, 1 x 24 x 8192 (786) 1683 / 1717.
 // The workgroups of a side: whole sets of `together` groups (or parts of groups) per XCD (the kernels' mapping): sets x together x
 // 8 XCDs x workgroups per group or part.
 inline int64_t side_rounds(const BwdParams& p) { return (((int64_t)p.B * p.H_kv << p.cut) + 7) / 8; }
@@ -117,7 +113,7 @@ hipError_t launch_kernels(const BwdParams& p, const DecayTable& dt, hipStream_t 
   } else {
     auto is_short = [&](int64_t rows, int64_t heads) {
       const int64_t window = p.window < rows ? p.window : 0;
-      return window ? window * heads <= short_window(DV) : rows * heads <= short_walk(DV);
+      return window ? window * heads <= short_window(DQK, DV) : rows * heads <= short_walk(DV);
     };
     if constexpr (DQK == 128 && DV == 128 && !BIAS) {
       const bool short_key = CAUSAL && is_short(p.L_q, p.g);
@@ -128,8 +124,7 @@ hipError_t launch_kernels(const BwdParams& p, const DecayTable& dt, hipStream_t 
     } else {
       if constexpr (CAUSAL && (!BIAS || DQK == 128))
         if (is_short(p.L_q, p.g) && is_short(p.L_k, 1)) return launch_both<K1, Q1>(p, dt, s);
-      if constexpr (K2::ABS && DV == 256) return launch_sides<K2, Q2>(p, dt, s, workgroups <= 96);
-      else if constexpr (DQK == 192 && CAUSAL) return launch_sides<K2, Q2>(p, dt, s, walked_keys<true>(p) < 700000 || key_wgs < 64);
+      if constexpr (DQK == 192 && CAUSAL) return launch_sides<K2, Q2>(p, dt, s, walked_keys<true>(p) < 700000 || key_wgs < 64);
       else return launch_both<K2, Q2>(p, dt, s);
     }
   }
