@@ -1083,10 +1083,11 @@ ae_status_t ae_recurrent_destroy(ae_recurrent_t* h) {
 // Value heads of a group that a workgroup of the backward pass takes in turn, its gradients of q and k summed on chip; 0: one
 // head per workgroup and the sums in a kernel of their own (where that walk is not built or cut into segments).  Few heads fill
 // the device, many leave fewer parts to sum; the time is estimated in units of a walk over one head (16 us at 768 tokens):
-// heads + 1 for a workgroup of the first two walks, 1.6 to 2.4 for one of the third (which takes one head or two), handed to 256
-// compute units in this order, and the sum kernel's bytes.  Measured (us for 1 / 2 / 3 heads, 768 tokens): Mamba2 128/64 1 x 80 heads 49 / 59
-// / 72, 2 x 80 88 / 63 / 75, 4 x 80 199 / 118 / 112, 8 x 64 297 / 197 / 163, 8 x 80 377 / 259 / 216, 8 x 32/8 x 600 126 / 92 / 102;
-// 64/64 4 x 32/8 66 / 54 / 67, 8 x 24/8 93 / 82 / 71, 8 x 64/1 200 / 137 / 131.
+// heads + 1.2 for a workgroup of the first two walks, 1.6 to 2.4 for one of the third (which takes one head or two), handed to 256
+// compute units in this order, and the sum kernel's bytes (none where one workgroup takes the whole group).  Measured (us for 1 / 2 / 3 / 4
+// heads, 768 tokens, the better of the third walk's two forms): Mamba2 128/64 1 x 80 heads 51 / 60 / 73 / 87, 2 x 80 89 / 65 / 76 / 89, 3 x 80 133 / 100 /
+// 84 / 93, 4 x 80 198 / 121 / 113 / 98, 5 x 80 236 / 151 / 149 / 131, 8 x 64 296 / 199 / 166 / 142, 8 x 80 375 / 259 / 217 / 196, 8 x 24 x 600 83 / 74 /
+// 67 / 78; 64/64 4 x 80 129 / 100 / 94 / 85, 8 x 64 202 / 139 / 134 / 118, 8 x 80 270 / 189 / 165 / 163.
 static double gated_walks_time(int64_t first_two, double cost, int64_t third, double cost3) {
   // all compute units are busy until `lo`, `n_hi` of them until `hi`; the third walk's workgroups go where one is free first
   double lo = (double)(first_two / 256) * cost, hi = lo + cost;
@@ -1111,8 +1112,9 @@ static int gated_group_heads(const ae_gated_desc_t* d, int bwd_nseg, int* third)
     for (int m = 1; m <= (size % 2 == 0 ? 2 : 1); ++m) {
       const int64_t parts = (size + n - 1) / n;
       const double cost3 = d->D_qk == 128 ? (m == 2 ? 2.4 : 2.1) : (m == 2 ? 2.0 : 1.6);
-      const double t = gated_walks_time(2 * groups * parts, n + 1, groups * size / m, cost3) + 1e-4 * groups * parts * d->D_qk;
-      if ((n == 1 && m == 1) || t < least) {
+      const double sum = parts == 1 ? 0.0 : 0.8e-4 * groups * parts * d->D_qk;
+      const double t = gated_walks_time(2 * groups * parts, n + 1.2, groups * size / m, cost3) + sum;
+      if (least == 0 || t < least) {
         least = t;
         heads = n;
         *third = m;
@@ -1356,13 +1358,14 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
   // (where a workgroup takes several heads of a group, (1) and (2) leave sums over these, dkey_gate, and the row products of
   // every head: those of (1) in dB, those of (2) where the gradient of the log-decays will stand)
   ae::GatedGroupParams gp[2];
+  const bool one_part = h->group_heads > 0 && gated_parts(h) == 1;  // (one workgroup takes the group: nothing is left to add)
   gp[0].Q = p.Q;
   gp[0].K = p.K;
   gp[0].V = p.V;
   gp[0].R = static_cast<const __bf16*>(Q);
   gp[0].log_decay = p.log_decay;
   gp[0].key_gate = p.key_gate;
-  gp[0].out = dQu;
+  gp[0].out = one_part ? static_cast<float*>(dQ) : dQu;
   gp[0].dots = dB;
   gp[0].dkey_gate = static_cast<float*>(dkey_gate);
   gp[0].B = d.B;
@@ -1377,15 +1380,16 @@ ae_status_t ae_gated_backward(const ae_gated_t* h, const void* Q, const void* K,
   gp[1] = gp[0];
   std::swap(gp[1].Q, gp[1].K);
   std::swap(gp[1].V, gp[1].R);
-  gp[1].out = dk_parts;
+  gp[1].out = one_part ? static_cast<float*>(dK) : dk_parts;
   gp[1].dots = static_cast<float*>(dlog_decay);
   gp[1].reverse = 1;
   const bool sums_inside = h->group_heads > 0;
   hipError_t e = launch_gated_backward_segmented(walk, sums_inside ? gp : nullptr, d.D_qk, d.D_v, h->bwd_nseg, h->bwd_seg_len,
                                                  static_cast<char*>(workspace) + seg_off, stream);
   if (e == hipSuccess && sums_inside) {
-    e = ae::launch_gated_group_sum(dQu, dk_parts, static_cast<float*>(dQ), static_cast<float*>(dK), gp[0].parts, (int64_t)d.L * d.D_qk,
-                                   (int64_t)d.B * d.H_qk * d.L * d.D_qk, stream);
+    if (!one_part)
+      e = ae::launch_gated_group_sum(dQu, dk_parts, static_cast<float*>(dQ), static_cast<float*>(dK), gp[0].parts, (int64_t)d.L * d.D_qk,
+                                     (int64_t)d.B * d.H_qk * d.L * d.D_qk, stream);
     if (e == hipSuccess) e = ae::launch_gated_suffix_sum(dB, static_cast<float*>(dlog_decay), static_cast<float*>(dlog_decay), d.B * d.H, d.L, stream);
   } else if (e == hipSuccess) {
     ae::GatedBwdEpilogueParams q;

@@ -68,7 +68,7 @@ hipError_t launch_gated_backward_epilogue(const GatedBwdEpilogueParams& p, int d
 // leaves its sum in out [B, H_qk, parts, L, D_qk].  Forwards (reverse = 0; Q = dO, K = V, V = K, R = Q): the gradient of q, the
 // key gate on the keys, dots[h, t] = q_t . (gradient of q by head h).  Backwards (Q = V, K = dO, V = Q, R = K): the gradient of
 // k, x_h being that of head h in front of its gate: the sum of g x_h, dkey_gate[h, t] = k_t . x_h, dots[h, t] = g k_t . x_h.
-constexpr int kGatedGroupHeads = 3;
+constexpr int kGatedGroupHeads = 4;
 struct GatedGroupParams {
   const __bf16* Q;         // [B, H, L, D_v]
   const __bf16* K;         // [B, H, L, D_v]

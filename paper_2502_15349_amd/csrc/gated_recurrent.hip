@@ -596,10 +596,16 @@ __global__ __launch_bounds__(C::BOUND_THREADS, C::WAVES_PER_SIMD) void gated_rec
 // kernel read 2 x 251 MB at 8 x 80 heads x 768 tokens: 379 us for the whole backward pass with a launch per walk, 257 this way; with the
 // walks in one launch see gated_group_heads.
 // DQK_, DV_: head dims of the walk, i.e. of dO and V, and of Q and K.
-template <int DQK_, int DV_>
+// HEADS_: at most, per workgroup: 32 registers of state each at head dim 64.  Four need 253 registers, with one address held for each
+// kind of fragment and everything else formed from the lane's number in every unit.  Three / four, 128/64: 8 x 80 heads x 768 217 / 196 us
+// (27 / 20 parts per gradient), 8 x 64 166 / 142.  Up to three heads have an instance of their own: 8 x 24 x 600 66.0, in that of four 67.7.
+template <int DQK_, int DV_, int HEADS_>
 struct GroupCfg : GCfg<DQK_, DV_> {
   using G = GCfg<DQK_, DV_>;
-  static constexpr int HEADS = kGatedGroupHeads;  // at most, per workgroup: 32 registers of state each at head dim 64
+  static constexpr int HEADS = HEADS_;
+  // what the lane's number gives is hidden from the optimiser, so that it is formed in every unit and not kept through the loop; the
+  // rows of the dot products are read one block at a time
+  static constexpr bool LEAN = HEADS > 3;
   static constexpr int UNIT_BYTES = 2 * G::Q_BYTES, SHARED_BYTES = 2 * G::V_BYTES;
   static constexpr int kShared = 3 * UNIT_BYTES, kP = kShared + 2 * SHARED_BYTES, kGates = kP + G::P_BYTES;
   static constexpr int kDots = kGates + G::GATE_BYTES, kOut = kDots + G::NB * 256, LDS_BYTES = kOut + G::NB * 4096;
@@ -627,17 +633,10 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
     for (int n = 0; n < C::HEADS; ++n)
 #pragma unroll
       for (int db = 0; db < C::DBQ; ++db) H[n][db] = zero16();
-    uint32_t kt0[C::DBQ][2], vt0[2], rr0[4];
-    const uint32_t rq0 = row_lane<C>(lane);
-#pragma unroll
-    for (int k = 0; k < C::DBQ; ++k)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) kt0[k][j] = C::Q_BYTES + tr_lane<C::CPRQ>(lane, k, j, swapped_piece(lane));
-#pragma unroll
-    for (int j = 0; j < 2; ++j) vt0[j] = tr_lane<C::CPRV>(lane, wave, j, lane & 3);
-    // the rows of the dot products as the outputs lie in registers: row ln, columns 32 wave + 8 a + 4 half + {0..3}
-#pragma unroll
-    for (int a = 0; a < 4; ++a) rr0[a] = C::V_BYTES + ln * C::RBV + (((4 * wave + a) ^ bswz<C::CPRV>(ln)) << 4) + 8 * half;
+    // (of each kind of fragment one address: block k of 32 columns is at ^ 64 k, the rows 8 further down at (^ 32) + 8 rows)
+    uint32_t rq0 = row_lane<C>(lane), kt0 = C::Q_BYTES + tr_lane<C::CPRQ>(lane, 0, 0, swapped_piece(lane)), vt0 = tr_lane<C::CPRV>(lane, wave, 0, lane & 3);
+    // the rows of the dot products as the outputs lie in registers: row ln, columns 32 wave + 8 a + 4 half + {0..3} (at ^ 16 a)
+    const uint32_t rr0 = C::V_BYTES + ln * C::RBV + (((4 * wave) ^ bswz<C::CPRV>(ln)) << 4) + 8 * half;
     const uint32_t out = lds0 + C::kOut + wave * 4096, dots = lds0 + C::kDots + wave * 256;
     chunk_barrier();
     chunk_barrier();
@@ -650,6 +649,9 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
         constexpr int n = decltype(nc)::value;
         if (n < nh) {
           const uint32_t sb = unit_stage(st);
+          int lane_now = lane;
+          if constexpr (C::LEAN) pin(lane_now);
+          const int ln = lane_now & 31, half = lane_now >> 5;
           const float dec = lds_read4(gate + (C::kDec + odd) * 4);
           const float f0 = p.scale * __expf(lds_read4(gate + (C::kB + ln) * 4));
           const float f1 = p.scale * __expf(lds_read4(gate + (C::kB + 32 + ln) * 4));
@@ -665,30 +667,39 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
           // (read anew for every head, and the fences keep the sums in front of the update: registers)
           bf16x8 vf[4];
 #pragma unroll
-          for (int s = 0; s < 4; ++s) vf[s] = read_tr_frag(sh + vt0[0] + 16 * s * C::RBV, sh + vt0[1] + 16 * s * C::RBV);
-          bf16x4 rows[2][4];
-#pragma unroll
-          for (int q = 0; q < 2; ++q)
+          for (int s = 0; s < 4; ++s) vf[s] = read_tr_frag(sh + vt0 + 16 * s * C::RBV, sh + (vt0 ^ 32u) + 8 * C::RBV + 16 * s * C::RBV);
+          bf16x4 rows[C::LEAN ? 1 : 2][4];
+          auto read_rows = [&](int q) {
+            uint32_t ra = sh + rr0;
+            if constexpr (C::LEAN) pin(ra);
 #pragma unroll
             for (int a = 0; a < 4; ++a)
-              rows[q][a] = *reinterpret_cast<__attribute__((address_space(3))) const bf16x4*>((lds_char*)(uintptr_t)(sh + rr0[a] + 32 * q * C::RBV));
-          add_pairs(vf, lds0 + C::kP + lane * 16, o0, o1);
+              rows[C::LEAN ? 0 : q][a] = *reinterpret_cast<__attribute__((address_space(3))) const bf16x4*>((lds_char*)(uintptr_t)((ra ^ (16u * a)) + 32 * q * C::RBV));
+          };
+          read_rows(0);
+          if constexpr (!C::LEAN) read_rows(1);
+          add_pairs(vf, lds0 + C::kP + lane_now * 16, o0, o1);
           sched_fence();
           float d0 = 0.f, d1 = 0.f;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             d0 = __builtin_fmaf(o0[r], (float)rows[0][r / 4][r % 4], d0);
-            d1 = __builtin_fmaf(o1[r], (float)rows[1][r / 4][r % 4], d1);
             sum0[r] = __builtin_fmaf(g0, o0[r], sum0[r]);
+          }
+          if constexpr (C::LEAN) {
+            sched_fence();
+            read_rows(1);
+          }
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
             sum1[r] = __builtin_fmaf(g1, o1[r], sum1[r]);
+            d1 = __builtin_fmaf(o1[r], (float)rows[C::LEAN ? 0 : 1][r / 4][r % 4], d1);
           }
           d0 = sum_halves(d0);
           d1 = sum_halves(d1);
-          lds_store4(dots + lane * 4, half ? d1 : d0);  // of token `lane` of the chunk
+          lds_store4(dots + lane_now * 4, half ? d1 : d0);  // of token `lane` of the chunk
           sched_fence();
           if (n == nh - 1) {
-            int lane_now = lane;  // (hidden from the optimiser: the addresses below are formed here, not kept through the loop)
-            pin(lane_now);
             auto store_block = [&](auto qc, const f32x16& o) {
               f32x4 v[4];
               turn_around(out, lane_now, o, v);
@@ -703,7 +714,14 @@ __device__ __forceinline__ void gated_group_walk(const GatedGroupParams& p, int 
             store_block(std::integral_constant<int, 1>{}, sum1);
           }
           sched_fence();
-          update_state<C>(H[n], vf, gate + (C::kW + odd * 64 + 4 * half) * 4, sb, kt0);
+          uint32_t kt[C::DBQ][2];
+          if constexpr (C::LEAN) pin(kt0);
+#pragma unroll
+          for (int k = 0; k < C::DBQ; ++k) {
+            kt[k][0] = kt0 ^ (64u * k);
+            kt[k][1] = (kt[k][0] ^ 32u) + 8 * C::RBQ;
+          }
+          update_state<C>(H[n], vf, gate + (C::kW + odd * 64 + 4 * half) * 4, sb, kt);
           chunk_barrier();
           st = next(st);
           odd ^= 1;
@@ -1155,8 +1173,13 @@ hipError_t launch_gated_backward(const GatedParams (&walk)[3], const GatedGroupP
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   }
   if (group) {
-    if (dqk == 64) return pairs ? launch_walks<GroupCfg<64, 64>, GCfg<64, 64, 2>, true>(w, blocks, s) : launch_walks<GroupCfg<64, 64>, GCfg<64, 64>, true>(w, blocks, s);
-    return pairs ? launch_walks<GroupCfg<64, 128>, GCfg<128, 64, 2>, true>(w, blocks, s) : launch_walks<GroupCfg<64, 128>, GCfg<128, 64>, true>(w, blocks, s);
+    auto launch_groups = [&](auto headsc) {
+      constexpr int N = decltype(headsc)::value;
+      if (dqk == 64) return pairs ? launch_walks<GroupCfg<64, 64, N>, GCfg<64, 64, 2>, true>(w, blocks, s) : launch_walks<GroupCfg<64, 64, N>, GCfg<64, 64>, true>(w, blocks, s);
+      return pairs ? launch_walks<GroupCfg<64, 128, N>, GCfg<128, 64, 2>, true>(w, blocks, s) : launch_walks<GroupCfg<64, 128, N>, GCfg<128, 64>, true>(w, blocks, s);
+    };
+    if (w.group[0].heads == kGatedGroupHeads) return launch_groups(std::integral_constant<int, kGatedGroupHeads>{});
+    return launch_groups(std::integral_constant<int, kGatedGroupHeads - 1>{});
   }
   if (pairs) return hipErrorInvalidValue;
   if (dqk == 64 && dv == 64) return launch_walks<GCfg<64, 64>, GCfg<64, 64>>(w, blocks, s);

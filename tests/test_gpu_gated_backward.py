@@ -210,6 +210,32 @@ def test_batch_entries_do_not_depend_on_the_launches(A, dqk, dv):
             assert np.array_equal(x[b:b + 1], y)
 
 
+@pytest.mark.parametrize("dqk", [64, 128])
+@pytest.mark.parametrize("H,H_qk,L", [(32, 8, 130), (80, 1, 130), (61, 1, 64), (62, 1, 65), (62, 2, 1), (62, 2, 129)])
+def test_four_heads_per_workgroup(A, dqk, H, H_qk, L):
+    # Groups of 4 (one workgroup each: no sums are left), 80, 61, 62 and 31 value heads, taken four at a time and, in
+    # the last part, four, one, two or three, against the same heads with a q/k head each: sums of n values x in 32 bits, each operation within 2^-24 of its
+    # result, so within 2^-23 n of the sum of |x|; the row products k . x have dqk terms.
+    B, n = 8, H // H_qk
+    Q, K, V, la, kg, dO = (t.cuda() for t in inputs(950, B, H, H_qk, L, dqk, 64, "mamba2"))
+    h = A.ae_gated_create(B=B, H=H, H_qk=H_qk, L=L, D_qk=dqk, D_v=64, scale=0.1)
+    rows = (B * H * L * 4 + 255) // 256 * 256
+    parts = (A.ae_gated_backward_workspace_bytes(h) - rows) // (2 * B * H_qk * L * dqk * 4)
+    A.ae_gated_destroy(h)
+    assert parts == (n + 3) // 4
+    dQ, dK, dV, dla, dkg = A.gated_recurrent_backward(Q, K, V, la, kg, dO, scale=0.1)
+    Qx, Kx = (t.repeat_interleave(n, dim=1) for t in (Q, K))
+    eQ, eK, eV, ela, ekg = A.gated_recurrent_backward(Qx, Kx, V, la, kg, dO, scale=0.1)
+    assert torch.equal(dV, eV)
+    for got, ref in ((dQ, eQ), (dK, eK)):
+        ref = ref.double().view(B, H_qk, n, L, dqk)
+        assert ((got.double() - ref.sum(dim=2)).abs() <= 2.0 ** -23 * n * ref.abs().sum(dim=2) + 1e-30).all()
+    terms = (Kx.double() * eK.double()).abs().sum(-1) / kg.double()  # of k . x, where eK = g x
+    assert ((dkg.double() - ekg.double()).abs() <= 2.0 ** -23 * dqk * terms + 1e-30).all()
+    later = ((Qx.double() * eQ.double()).abs().sum(-1) + (Kx.double() * eK.double()).abs().sum(-1)).flip(-1).cumsum(-1).flip(-1)
+    assert ((dla.double() - ela.double()).abs() <= 2.0 ** -23 * (dqk + 2) * later + 1e-30).all()
+
+
 @pytest.mark.parametrize("dqk,dv,H,H_qk", [(128, 128, 2, 2), (64, 64, 3, 3), (128, 64, 4, 1)])
 @pytest.mark.parametrize("kind", ["gated_retention", "mamba2"])
 @pytest.mark.parametrize("L", [1061, 2560])
