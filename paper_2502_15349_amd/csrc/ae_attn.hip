@@ -794,32 +794,62 @@ static size_t gated_segments_ws(size_t walks, int nseg, int dqk, int dv) {
   return slots * dqk * dv * 4 + ((slots * 4 + 255) & ~(size_t)255);
 }
 
-// The walk described by p (whole sequence, caller's h_in / h_out), cut into segments: every segment's final state
-// from a zero start and the sum of its log-decays; those chained into the state in front of every segment; the
+// A walk cut into segments is walked twice: for the segments' states and, behind the chaining of these, for the outputs.  The first launch
+// has room for a workgroup that walks in full: its segment, the lead, is not walked again, and nobody needs the last segment's state.  So
+// L = lead + nseg segments, which are shorter.  A lead of more than about a third of a segment takes longer than the others' state walks.  Not from six
+// segments on: a lead shortens them by 5 % and less, and walks that all started at one distance of 1280 or 1344 tokens were slower than
+// the longer ones of 1408 by as much.  Us, without / with a lead: 128 pairs x 4096 (128/128, two segments) 201 / 171, 128 x 1300 66.5 / 59.5, 96 x 2000
+// 72.9 / 66.0, 80 x 1500 (three) 52.7 / 49.9, 80 x 5000 160 / 137, 64 x 3000 (four) 75.9 / 70.5, 50 x 3000 (five) 58.8 / 56.6; 64/64 128 x 3000 68.0 / 61.5,
+// Mamba2 2 x 80 x 3000 (three) 76.5 / 70.3, 2 x 64 x 3000 (four) 61.8 / 59.4; with six or more: Mamba2 1 x 80 x 8192 94.9 / 91.5 to 104, 1 x 32 x 8192 128/128
+// 87.6 / 86.2 to 94, 2 x 24 x 3000 37.6 / 38.4.
+constexpr int kLeadBelow = 6;  // segments
+static int lead_of(int L, int nseg, int seg_len) { return std::max<int>(64, (int)((L - (int64_t)nseg * seg_len + 63) / 64 * 64)); }
+static int segments_behind_lead(int L, int nseg, int seg_len) {
+  while (seg_len > 128 && 100 * lead_of(L, nseg, seg_len - 64) <= 36 * (seg_len - 64)) seg_len -= 64;
+  return seg_len;
+}
+
+// The walk described by p (whole sequence, caller's h_in / h_out), cut into segments: the lead in full, or the state in front of the sequence,
+// and every segment's final state from a zero start and the sum of its log-decays; those chained into the state in front of every segment; the
 // segments walked again, side by side, for their outputs.
 static hipError_t launch_gated_segmented(const ae::GatedParams& p, const ae::DecayTable& dt, int dqk, int dv, int nseg, int seg_len,
                                          void* workspace, hipStream_t stream) {
   const size_t slots = (size_t)p.B * p.H * nseg;
   float* dec = static_cast<float*>(workspace);
   float* buf = reinterpret_cast<float*>(static_cast<char*>(workspace) + ((slots * 4 + 255) & ~(size_t)255));
-  ae::GatedParams s1 = p;
-  s1.nseg = nseg;
-  s1.seg_len = seg_len;
-  s1.state_only = 1;
-  s1.h_in = nullptr;
-  s1.h_out = buf;
-  s1.seg_decay = dec;
-  s1.O = nullptr;
-  hipError_t e = ae::launch_gated_recurrent(s1, dt, dqk, dv, stream);
-  if (e != hipSuccess) return e;
-  e = ae::launch_gated_combine_segments(buf, dec, p.h_in, p.B * p.H, nseg, dqk * dv, stream);
-  if (e != hipSuccess) return e;
-  ae::GatedParams s2 = p;
-  s2.nseg = nseg;
-  s2.seg_len = seg_len;
-  s2.h_in = buf;
-  s2.h_out_last_only = 1;
-  return ae::launch_gated_recurrent(s2, dt, dqk, dv, stream);
+  ae::GatedParams states = p;
+  states.state_only = 1;
+  states.h_in = nullptr;
+  states.h_out = buf;
+  states.seg_decay = dec;
+  states.O = nullptr;
+  ae::GatedParams out = p;
+  out.h_in = buf;
+  out.h_out_last_only = 1;
+  hipError_t e;
+  const int shorter = nseg < kLeadBelow ? segments_behind_lead(p.L, nseg, seg_len) : seg_len;
+  if (shorter < seg_len) {
+    seg_len = shorter;
+    ae::GatedParams lead = p;
+    lead.seg_len = lead.seg_to = out.seg_from = states.seg_from = lead_of(p.L, nseg, seg_len);
+    lead.part = out.part = states.part = 1;
+    out.seg_to = states.seg_to = p.L;
+    lead.h_out = buf;
+    lead.out_slots = states.out_slots = out.in_slots = nseg;
+    out.nseg = (p.L - lead.seg_len + seg_len - 1) / seg_len;  // (one less than nseg where the lead fills what the last one lacked)
+    states.nseg = out.nseg - 1;
+    states.h_out = buf + dqk * dv;
+    states.seg_decay = dec + 1;
+    out.seg_len = states.seg_len = seg_len;
+    e = states.nseg > 0 ? ae::launch_gated_lead(lead, states, dt, dqk, dv, stream) : ae::launch_gated_recurrent(lead, dt, dqk, dv, stream);
+    if (e == hipSuccess) e = ae::launch_gated_chain_segments(buf, dec, p.B * p.H, nseg, out.nseg, dqk * dv, stream);
+  } else {
+    states.nseg = out.nseg = nseg;
+    states.seg_len = out.seg_len = seg_len;
+    e = ae::launch_gated_recurrent(states, dt, dqk, dv, stream);
+    if (e == hipSuccess) e = ae::launch_gated_combine_segments(buf, dec, p.h_in, p.B * p.H, nseg, dqk * dv, stream);
+  }
+  return e != hipSuccess ? e : ae::launch_gated_recurrent(out, dt, dqk, dv, stream);
 }
 
 // The same for the three walks of the backward pass: their states (of D_qk x D_v elements each) stand one walk behind the other,

@@ -39,7 +39,19 @@ struct GatedParams {
   // number of value heads per q/k head, H_v = H; in launch_gated_backward beside several heads of the first two walks only)
   int heads_per_workgroup = 1;
   float* seg_decay = nullptr;
+  // part: only the tokens [seg_from, seg_to) of the walk, in nseg >= 1 segments; h_in holds in_slots states for a (batch, head), of which
+  // segment i starts from the i-th, h_out (and seg_decay) out_slots (the pointers may stand at another slot than the first).
+  // Kernels of their own: reading these fields cost the other launches 0.2 us each.
+  int part = 0;
+  int seg_from = 0, seg_to = 0, in_slots = 1, out_slots = 1;
 };
+// A walk's first segment in full (lead: whole rows of outputs, its final state) and the states of later ones (states: state_only),
+// side by side in one launch.  The same constant decays for both.
+hipError_t launch_gated_lead(const GatedParams& lead, const GatedParams& states, const DecayTable& dt, int dqk, int dv, hipStream_t s);
+// In place on buf [B, H, nseg, D_qk x D_v], the first `n` slots of every (batch, head): slot 0 holds the state in front of the first of
+// them, slot i > 0 what segment i - 1 adds to it (its final state from a zero start), seg_decay[i] that segment's decay; slot i becomes
+// the state in front of segment i.
+hipError_t launch_gated_chain_segments(float* buf, const float* seg_decay, int BH, int nseg, int n, int state_elems, hipStream_t s);
 // In place on buf [B, H, nseg, D_qk x D_v] (the segments' final states from a zero start, as a state_only walk
 // leaves them): slot s becomes the state in front of segment s, given the state in front of the sequence (h_in,
 // [B, H, D_qk x D_v], or null for zero) and the segments' decays.

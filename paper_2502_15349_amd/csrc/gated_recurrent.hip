@@ -315,7 +315,8 @@ struct TileCopy {
 // block: the workgroup's number among those of this walk; const_decay(h): the log-decay of head h where p.log_decay is null.
 // OUT_GATE: output rows have a factor of their own (1 without GatedParams::gate_on_output).  Not a run-time test: that took 117 us
 // for 113 at 8 x 16 heads x 4096, 64/64, where there is none.
-template <class C, bool STATE_ONLY, bool OUT_GATE, class F>
+// PART: see GatedParams::part.
+template <class C, bool STATE_ONLY, bool OUT_GATE, bool PART, class F>
 __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint32_t lds0, F&& const_decay) {
   using Y = GLayout<C, STATE_ONLY>;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -327,8 +328,9 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
   const bool rev = p.reverse != 0;
   // the tokens this workgroup walks: L of them from position `first` of the walk (the whole sequence unless it is
   // cut into segments); row_lo: the one with the lowest address, where all base pointers below stand
-  const int64_t Lt = p.L, first = (int64_t)seg * p.seg_len;
-  const int L = (int)(p.nseg > 1 ? min(Lt - first, (int64_t)p.seg_len) : Lt);
+  const int64_t Lt = p.L, first = (PART ? p.seg_from : 0) + (int64_t)seg * p.seg_len;
+  const int L = (int)(PART ? min(p.seg_to - first, (int64_t)p.seg_len) : p.nseg > 1 ? min(Lt - first, (int64_t)p.seg_len) : Lt);
+  const int in_slots = PART ? p.in_slots : p.nseg, out_slots = PART ? p.out_slots : p.nseg;  // states of a (batch, head)
   const int64_t row_lo = rev ? Lt - first - L : first;
   const int n_chunks = (L + C::CH - 1) / C::CH;
   auto stage_of = [&](int c) { return lds0 + (uint32_t)(c % Y::STAGES) * Y::STAGE_BYTES; };
@@ -337,14 +339,13 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
   if (wave < C::SW) {
     // ================= state wavefront: 32 value columns of one head =================
     const int hw = wave / C::NB, vblk = wave % C::NB, bh = bh0 + hw;
-    const int64_t slot = (int64_t)bh * p.nseg + seg;  // of this segment's states
     const uint32_t gate = gates_of(hw);
     f32x16 H[C::DBQ];  // register r of tile db: row d = 32 db + 16 (r / 8) + 8 half + r % 8 of the slab, column ln
     auto h_row = [&](int db, int r) { return (int64_t)(32 * db + 16 * (r >> 3) + 8 * half + (r & 7)) * C::DV; };
 #pragma unroll
     for (int db = 0; db < C::DBQ; ++db) {
       if (p.h_in) {
-        const float* src = p.h_in + slot * C::DQK * C::DV + 32 * vblk + ln;
+        const float* src = p.h_in + ((int64_t)bh * in_slots + seg) * C::DQK * C::DV + 32 * vblk + ln;
 #pragma unroll
         for (int r = 0; r < 16; ++r) H[db][r] = src[h_row(db, r)];
       } else {
@@ -452,7 +453,7 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
       }
     }
     if (p.h_out && (!p.h_out_last_only || seg == p.nseg - 1)) {
-      float* dst = p.h_out + (p.h_out_last_only ? (int64_t)bh : slot) * C::DQK * C::DV + 32 * vblk + ln;
+      float* dst = p.h_out + (p.h_out_last_only ? (int64_t)bh : (int64_t)bh * out_slots + seg) * C::DQK * C::DV + 32 * vblk + ln;
 #pragma unroll
       for (int db = 0; db < C::DBQ; ++db)
 #pragma unroll
@@ -513,7 +514,7 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
     }
     if (p.seg_decay && lane == 0) {
 #pragma unroll
-      for (int hh = 0; hh < C::HPW; ++hh) p.seg_decay[(int64_t)(bh0 + hh) * p.nseg + seg] = seg_b[hh];
+      for (int hh = 0; hh < C::HPW; ++hh) p.seg_decay[(int64_t)(bh0 + hh) * out_slots + seg] = seg_b[hh];
     }
     return;
   }
@@ -583,8 +584,27 @@ __device__ __forceinline__ void gated_walk(const GatedParams& p, int block, uint
 template <class C, bool STATE_ONLY>
 __global__ __launch_bounds__(C::BOUND_THREADS, C::WAVES_PER_SIMD) void gated_recurrent_kernel(const GatedParams p, const DecayTable dt, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[GLayout<C, STATE_ONLY>::LDS_BYTES];
-  gated_walk<C, STATE_ONLY, false>(p, first_block + (int)blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
+  gated_walk<C, STATE_ONLY, false, false>(p, first_block + (int)blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem),
                                    [&](int h) { return dt.log2_gamma[h] * 0.6931471805599453f; });  // ln gamma
+}
+
+// See launch_gated_lead.  The longer workgroups come first.
+template <class C>
+__global__ __launch_bounds__(C::BOUND_THREADS, C::WAVES_PER_SIMD) void gated_lead_kernel(const GatedParams lead, const GatedParams states, const DecayTable dt,
+                                                                                          int lead_blocks) {
+  constexpr int A = GLayout<C, false>::LDS_BYTES, B = GLayout<C, true>::LDS_BYTES;
+  __shared__ __attribute__((aligned(1024))) char smem[A > B ? A : B];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((lds_char*)smem);
+  const int block = (int)blockIdx.x;
+  const auto decay = [&](int h) { return dt.log2_gamma[h] * 0.6931471805599453f; };
+  if (block < lead_blocks) gated_walk<C, false, false, true>(lead, block, lds0, decay);
+  else gated_walk<C, true, false, true>(states, block - lead_blocks, lds0, decay);
+}
+// Segments of a part of the walk in full.
+template <class C>
+__global__ __launch_bounds__(C::BOUND_THREADS, C::WAVES_PER_SIMD) void gated_part_kernel(const GatedParams p, const DecayTable dt) {
+  __shared__ __attribute__((aligned(1024))) char smem[GLayout<C, false>::LDS_BYTES];
+  gated_walk<C, false, false, true>(p, (int)blockIdx.x, (uint32_t)(uintptr_t)((lds_char*)smem), [&](int h) { return dt.log2_gamma[h] * 0.6931471805599453f; });
 }
 
 // ---- backward pass where value heads share a q/k head: the gradients of q and k, summed over heads ----
@@ -906,15 +926,15 @@ void gated_backward_kernel(const GatedBackwardWalks w) {
   const auto no_const = [](int) { return 0.f; };
   constexpr int kE = GROUP ? 2 : 0;  // place of the walk for the gradient of v
   if constexpr (std::is_same<A, E>::value) {
-    gated_walk<E, STATE_ONLY, GATED>(w.walk[which], block, lds0, no_const);
+    gated_walk<E, STATE_ONLY, GATED, false>(w.walk[which], block, lds0, no_const);
   } else {
     // (wavefronts beyond those of the walk end here: a barrier counts those that are left)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (which == kE) {
-      if (wave < E::WAVES) gated_walk<E, STATE_ONLY, GATED>(w.walk[kE], block, lds0, no_const);
+      if (wave < E::WAVES) gated_walk<E, STATE_ONLY, GATED, false>(w.walk[kE], block, lds0, no_const);
     } else if (wave < A::WAVES) {
       if constexpr (GROUP) gated_group_walk<A>(w.group[which], block, lds0);
-      else gated_walk<A, STATE_ONLY, false>(w.walk[which], block, lds0, no_const);
+      else gated_walk<A, STATE_ONLY, false, false>(w.walk[which], block, lds0, no_const);
     }
   }
 }
@@ -952,6 +972,11 @@ hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
   typedef GCfg<DQK, DV, HPW> C;
   if (p.gate_on_output && !p.state_only) return hipErrorInvalidValue;
   const int64_t blocks = (int64_t)p.B * p.H / HPW * p.nseg;
+  if (p.part) {
+    if (p.state_only || !launch_fits(blocks, C::THREADS)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gated_part_kernel<C>, dim3((unsigned)blocks), dim3(C::THREADS), 0, s, p, dt);
+    return hipGetLastError();
+  }
   const int lds = lds_for_one_each(C::SHARES_CU && p.nseg == 1 && gated_one_each(blocks, p.L));
   return launch_in_parts(blocks, C::THREADS, [&](int first, dim3 grid) {
     if (p.state_only) hipLaunchKernelGGL((gated_recurrent_kernel<C, true>), grid, dim3(C::THREADS), 0, s, p, dt, first);
@@ -986,6 +1011,31 @@ __global__ __launch_bounds__(256) void gated_combine_segments_kernel(float* buf,
       if (s0 + u >= nseg) break;
       slot[(int64_t)(s0 + u) * state_elems] = x;
       x = __expf(d[u]) * x + local[u];
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void gated_chain_segments_kernel(float* buf, const float* seg_decay, int nseg, int n, int state_elems) {
+  constexpr int kAhead = 8;
+  const int64_t bh = blockIdx.y;
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= state_elems) return;
+  float* slot = buf + bh * nseg * state_elems + e;
+  const float* dec = seg_decay + bh * nseg;
+  float x = slot[0];
+  for (int s0 = 1; s0 < n; s0 += kAhead) {
+    float local[kAhead], d[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (s0 + u >= n) break;
+      local[u] = slot[(int64_t)(s0 + u) * state_elems];
+      d[u] = dec[s0 + u];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (s0 + u >= n) break;
+      x = __expf(d[u]) * x + local[u];
+      slot[(int64_t)(s0 + u) * state_elems] = x;
     }
   }
 }
@@ -1079,6 +1129,14 @@ hipError_t launch_gated_combine_segments(float* buf, const float* seg_decay, con
   return hipGetLastError();
 }
 
+hipError_t launch_gated_chain_segments(float* buf, const float* seg_decay, int BH, int nseg, int n, int state_elems, hipStream_t s) {
+  if (BH < 1 || BH > 65535 || n < 1 || n > nseg || state_elems < 1) return hipErrorInvalidValue;
+  if (n == 1) return hipSuccess;
+  hipLaunchKernelGGL(gated_chain_segments_kernel, dim3((unsigned)((state_elems + 255) / 256), (unsigned)BH), dim3(256), 0, s, buf, seg_decay, nseg, n,
+                     state_elems);
+  return hipGetLastError();
+}
+
 bool gated_group_supported(int dqk, int dv) { return (dqk == 64 || dqk == 128) && dv == 64; }
 
 hipError_t launch_gated_group_sum(const float* dq_parts, const float* dk_parts, float* dQ, float* dK, int parts, int64_t head_elems,
@@ -1110,11 +1168,37 @@ bool gated_supported(int dqk, int dv) { return (dqk == 64 || dqk == 128) && (dv 
 static hipError_t check_walk(GatedParams& p) {
   if (p.H_v == 0) p.H_v = p.H;
   if (p.H_qk < 1 || p.H % p.H_qk != 0 || p.H % p.H_v != 0) return hipErrorInvalidValue;
-  if (p.nseg < 1 || (p.nseg > 1 && (p.seg_len < 64 || p.seg_len % 64 != 0 || (int64_t)(p.nseg - 1) * p.seg_len >= p.L)))
+  const int64_t from = p.part ? p.seg_from : 0, to = p.part ? p.seg_to : p.L;
+  if (p.nseg < 1 || from < 0 || from % 64 != 0 || to > p.L ||
+      ((p.nseg > 1 || p.part) && (p.seg_len < 64 || p.seg_len % 64 != 0 || from + (int64_t)(p.nseg - 1) * p.seg_len >= to)))
     return hipErrorInvalidValue;
   // value heads that share their q/k head (Mamba2's groups) can share the Q and K tiles of a workgroup, two at a time
   if (p.heads_per_workgroup != 1 && (p.heads_per_workgroup != 2 || p.H / p.H_qk % 2 != 0 || p.H_v != p.H)) return hipErrorInvalidValue;
   return (int64_t)p.B * p.H * p.nseg > 0x7fffffffLL ? hipErrorInvalidValue : hipSuccess;
+}
+
+template <int DQK, int DV, int HPW = 1>
+static hipError_t launch_lead(const GatedParams& lead, const GatedParams& states, const DecayTable& dt, hipStream_t s) {
+  typedef GCfg<DQK, DV, HPW> C;
+  const int64_t first = (int64_t)lead.B * lead.H / HPW * lead.nseg, blocks = first + (int64_t)states.B * states.H / HPW * states.nseg;
+  if (!launch_fits(blocks, C::THREADS)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gated_lead_kernel<C>, dim3((unsigned)blocks), dim3(C::THREADS), 0, s, lead, states, dt, (int)first);
+  return hipGetLastError();
+}
+hipError_t launch_gated_lead(const GatedParams& lead_in, const GatedParams& states_in, const DecayTable& dt, int dqk, int dv, hipStream_t s) {
+  GatedParams lead = lead_in, states = states_in;
+  hipError_t e = check_walk(lead);
+  if (e == hipSuccess) e = check_walk(states);
+  if (e != hipSuccess) return e;
+  const bool pairs = lead.heads_per_workgroup == 2;
+  if ((pairs && dv != 64) || states.heads_per_workgroup != lead.heads_per_workgroup || !lead.part || !states.part || lead.state_only || !states.state_only || lead.gate_on_output ||
+      states.gate_on_output)
+    return hipErrorInvalidValue;
+  if (dqk == 64 && dv == 64) return pairs ? launch_lead<64, 64, 2>(lead, states, dt, s) : launch_lead<64, 64>(lead, states, dt, s);
+  if (dqk == 128 && dv == 64) return pairs ? launch_lead<128, 64, 2>(lead, states, dt, s) : launch_lead<128, 64>(lead, states, dt, s);
+  if (dqk == 64 && dv == 128) return launch_lead<64, 128>(lead, states, dt, s);
+  if (dqk == 128 && dv == 128) return launch_lead<128, 128>(lead, states, dt, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_gated_recurrent(const GatedParams& p_in, const DecayTable& dt, int dqk, int dv, hipStream_t s) {

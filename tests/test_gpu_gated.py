@@ -161,6 +161,25 @@ def test_segmented_walk(A, dqk, dv, H, H_qk, kind, L):
     assert (np.abs(hN.cpu().double().numpy() - ref_h) / hs).max() <= MAX_ABS
 
 
+@pytest.mark.parametrize("B,H,H_qk,L,dqk,dv,kind", [(2, 64, 64, 1300, 64, 64, "gated_retention"), (2, 64, 64, 1281, 128, 128, "mamba2"), (1, 85, 85, 1537, 64, 128, "mamba2"),
+                                                    (2, 32, 32, 1472, 128, 128, "gated_retention"), (1, 50, 50, 1999, 64, 64, "mamba2"),
+                                                    (2, 64, 1, 1500, 128, 64, "mamba2"), (2, 128, 2, 1700, 64, 64, "mamba2")])
+def test_walk_with_a_lead(A, B, H, H_qk, L, dqk, dv, kind):
+    # two to five segments behind a first one that is walked in full beside their state walks, whole and short last ones (1472 and 1281: none and one
+    # token), one and two heads per workgroup; the state in front of the sequence, the final one
+    Q, K, V, la, kg = inputs(870, B, H, H_qk, L, dqk, dv, kind)
+    h0 = torch.randn(B, H, dqk, dv, generator=torch.Generator().manual_seed(87))
+    scale = 1.0 / math.sqrt(dqk)
+    got, state = run(A, Q, K, V, la, kg, scale, h_in=h0, want_state=True, segmented=True)
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        hq = h // (H // H_qk)
+        ref, ref_h = oracle_gated(*(t[b:b + 1, i:i + 1].float().numpy() for t, i in ((Q, hq), (K, hq), (V, h))), la[b:b + 1, h:h + 1].numpy(),
+                                  None if kg is None else kg[b:b + 1, h:h + 1].numpy(), scale=scale, h0=h0[b:b + 1, h:h + 1].numpy(), return_state=True)
+        check(got[b:b + 1, h:h + 1].cpu().double().numpy(), ref, f"lead {kind} {dqk}/{dv} L={L} ({b},{h})")
+        hs = np.maximum(np.abs(ref_h).max(axis=-1, keepdims=True), 1.0)
+        assert (np.abs(state[b:b + 1, h:h + 1].cpu().double().numpy() - ref_h) / hs).max() <= MAX_ABS
+
+
 def test_segmented_entry_point_on_a_shape_that_is_not_cut(A):
     # many heads or a short sequence: no workspace, and the bits of ae_gated_forward
     Q, K, V, la, kg = inputs(830, 2, 3, 3, 300, 64, 64, "mamba2")
