@@ -547,3 +547,23 @@ def test_more_workgroups_than_one_launch_holds(A):
         es, ed = 0.1 * (q * k).abs().sum(-1, keepdim=True), 0.1 * (v * do).abs().sum(-1, keepdim=True)
         for name, got, w, e, x in (("dQ", dQ, d, ed, k), ("dK", dK, d, ed, q), ("dV", dV, s, es, do)):
             assert ((got[b0:b0 + n].double() - w * x).abs() <= (2.0 ** -8 * w.abs() + 2.0 ** -17 * e) * x.abs() + 1e-7).all(), (name, b0)
+
+
+@pytest.mark.parametrize("dims", DIMS, ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("norm", ["abssum", "abs_of_sum", "none"])
+def test_backward_decay_rates(A, dims, norm):
+    """Decay rates above one, of one, and so small that a factor vanishes within a tile: tiles that are visible as a whole form the factors
+    as products (one exponential per lane times constants), the others one by one."""
+    w = Workload("rates", 990, 2, 4, 2, 200, 330, *dims, score_mod="head_decay", norm=norm, mask="causal")
+    gam = [1.02, 1.0, 0.05, 1e-4]
+    Q, K, V = make_inputs(w)
+    dO = make_grad(w)
+    dev = torch.device("cuda:0")
+    args = dict(scale=w.scale_value, score_mod="head_decay", gamma=gam, norm=norm, mask="causal")
+    Qd, Kd, Vd = Q.to(dev), K.to(dev), V.to(dev)
+    stats = None if norm == "none" else torch.empty((2, 4, 200), dtype=torch.float32, device=dev)
+    O = A.attention_forward(Qd, Kd, Vd, stats=stats, **args)
+    got = A.attention_backward(Qd, Kd, Vd, O, dO.to(dev), stats, **args)
+    ref = attention_backward(Q, K, V, dO, **args)
+    for name, g, r in zip(("dQ", "dK", "dV"), got, ref):
+        check(g.cpu().double().numpy(), r, f"{norm} {dims} {name}")
