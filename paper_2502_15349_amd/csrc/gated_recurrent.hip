@@ -985,57 +985,84 @@ hipError_t launch(const GatedParams& p, const DecayTable& dt, hipStream_t s) {
 }
 
 // ---- segments: from the final states of the segments (each from a zero start) to the states in front of them ----
-// One thread per state element walks the segments; what it waits for is memory, so the states and decays of up to kAhead
+// One thread per state element, or four, walks the segments; what it waits for is memory, so the states and decays of up to kAhead
 // segments are requested together instead of one at a time, each behind the store of the one before (whole calls with walks cut
 // in 7 and in 32 segments 210 -> 206 and 245 -> 233 us), and no more than there are (1 x 128 heads x 1152 tokens, two segments,
-// 75.9 us with eight requests, 73.3 so).
-__global__ __launch_bounds__(256) void gated_combine_segments_kernel(float* buf, const float* seg_decay, const float* h_in, int nseg,
-                                                                      int state_elems) {
-  constexpr int kAhead = 8;
+// 75.9 us with eight requests, 73.3 so).  Four elements a thread instead of one, and nothing of the last segment read: whole calls of 128 pairs
+// (128/128) x 1300 59.3 -> 54.4 us, x 4096 171 -> 166, of 96 x 1100 47.2 -> 43.6; beyond eight segments one element, more wavefronts (V; 8 pairs x 32768, 32
+// segments, 88.2 with one, 88.8 with four).
+template <int V>
+struct StatePiece {
+  float x[V];
+  __device__ __forceinline__ void load(const float* p) {
+    if constexpr (V == 4) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = v[i];
+    } else {
+      x[0] = *p;
+    }
+  }
+  __device__ __forceinline__ void store(float* p) const {
+    if constexpr (V == 4) *reinterpret_cast<f32x4*>(p) = f32x4{x[0], x[1], x[2], x[3]};
+    else *p = x[0];
+  }
+  __device__ __forceinline__ void chain(float d, const StatePiece& local) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) x[i] = d * x[i] + local.x[i];
+  }
+};
+constexpr int kAhead = 8, kChainThreads = 64;  // (one wavefront: few pairs of small states, 24 x 4096 elements, are 96 workgroups of 256)
+template <int V>
+__global__ __launch_bounds__(kChainThreads) void gated_combine_segments_kernel(float* buf, const float* seg_decay, const float* h_in, int nseg,
+                                                                                int state_elems) {
   const int64_t bh = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int e = (blockIdx.x * kChainThreads + threadIdx.x) * V;
   if (e >= state_elems) return;
-  float x = h_in ? h_in[bh * state_elems + e] : 0.f;
+  StatePiece<V> x = {};
+  if (h_in) x.load(h_in + bh * state_elems + e);
   float* slot = buf + bh * nseg * state_elems + e;
   const float* dec = seg_decay + bh * nseg;
   for (int s0 = 0; s0 < nseg; s0 += kAhead) {
-    float local[kAhead], d[kAhead];
+    StatePiece<V> local[kAhead];
+    float d[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
-      if (s0 + u >= nseg) break;
-      local[u] = slot[(int64_t)(s0 + u) * state_elems];
+      if (s0 + u >= nseg - 1) break;  // (nothing follows the last segment)
+      local[u].load(slot + (int64_t)(s0 + u) * state_elems);
       d[u] = dec[s0 + u];
     }
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       if (s0 + u >= nseg) break;
-      slot[(int64_t)(s0 + u) * state_elems] = x;
-      x = __expf(d[u]) * x + local[u];
+      x.store(slot + (int64_t)(s0 + u) * state_elems);
+      if (s0 + u < nseg - 1) x.chain(__expf(d[u]), local[u]);
     }
   }
 }
-
-__global__ __launch_bounds__(256) void gated_chain_segments_kernel(float* buf, const float* seg_decay, int nseg, int n, int state_elems) {
-  constexpr int kAhead = 8;
+// The same behind a lead, see launch_gated_chain_segments.
+__global__ __launch_bounds__(kChainThreads) void gated_chain_segments_kernel(float* buf, const float* seg_decay, int nseg, int n, int state_elems) {
   const int64_t bh = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int e = (blockIdx.x * kChainThreads + threadIdx.x) * 4;
   if (e >= state_elems) return;
   float* slot = buf + bh * nseg * state_elems + e;
   const float* dec = seg_decay + bh * nseg;
-  float x = slot[0];
+  StatePiece<4> x;
+  x.load(slot);
   for (int s0 = 1; s0 < n; s0 += kAhead) {
-    float local[kAhead], d[kAhead];
+    StatePiece<4> local[kAhead];
+    float d[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       if (s0 + u >= n) break;
-      local[u] = slot[(int64_t)(s0 + u) * state_elems];
+      local[u].load(slot + (int64_t)(s0 + u) * state_elems);
       d[u] = dec[s0 + u];
     }
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       if (s0 + u >= n) break;
-      x = __expf(d[u]) * x + local[u];
-      slot[(int64_t)(s0 + u) * state_elems] = x;
+      x.chain(__expf(d[u]), local[u]);
+      x.store(slot + (int64_t)(s0 + u) * state_elems);
     }
   }
 }
@@ -1123,16 +1150,17 @@ __global__ __launch_bounds__(64) void gated_bwd_suffix_sum_kernel(const float* d
 
 hipError_t launch_gated_combine_segments(float* buf, const float* seg_decay, const float* h_in, int BH, int nseg, int state_elems,
                                          hipStream_t s) {
-  if (BH < 1 || BH > 65535 || nseg < 1 || state_elems < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gated_combine_segments_kernel, dim3((unsigned)((state_elems + 255) / 256), (unsigned)BH), dim3(256), 0, s, buf,
-                     seg_decay, h_in, nseg, state_elems);
+  if (BH < 1 || BH > 65535 || nseg < 1 || state_elems < 4 || state_elems % 4 != 0) return hipErrorInvalidValue;
+  auto grid = [&](int v) { return dim3((unsigned)((state_elems + v * kChainThreads - 1) / (v * kChainThreads)), (unsigned)BH); };
+  if (nseg <= kAhead) hipLaunchKernelGGL(gated_combine_segments_kernel<4>, grid(4), dim3(kChainThreads), 0, s, buf, seg_decay, h_in, nseg, state_elems);
+  else hipLaunchKernelGGL(gated_combine_segments_kernel<1>, grid(1), dim3(kChainThreads), 0, s, buf, seg_decay, h_in, nseg, state_elems);
   return hipGetLastError();
 }
 
 hipError_t launch_gated_chain_segments(float* buf, const float* seg_decay, int BH, int nseg, int n, int state_elems, hipStream_t s) {
-  if (BH < 1 || BH > 65535 || n < 1 || n > nseg || state_elems < 1) return hipErrorInvalidValue;
+  if (BH < 1 || BH > 65535 || n < 1 || n > nseg || state_elems < 4 || state_elems % 4 != 0) return hipErrorInvalidValue;
   if (n == 1) return hipSuccess;
-  hipLaunchKernelGGL(gated_chain_segments_kernel, dim3((unsigned)((state_elems + 255) / 256), (unsigned)BH), dim3(256), 0, s, buf, seg_decay, nseg, n,
+  hipLaunchKernelGGL(gated_chain_segments_kernel, dim3((unsigned)((state_elems + 4 * kChainThreads - 1) / (4 * kChainThreads)), (unsigned)BH), dim3(kChainThreads), 0, s, buf, seg_decay, nseg, n,
                      state_elems);
   return hipGetLastError();
 }

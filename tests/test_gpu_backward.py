@@ -565,5 +565,10 @@ def test_backward_decay_rates(A, dims, norm):
     O = A.attention_forward(Qd, Kd, Vd, stats=stats, **args)
     got = A.attention_backward(Qd, Kd, Vd, O, dO.to(dev), stats, **args)
     ref = attention_backward(Q, K, V, dO, **args)
+    # A row of few keys (a small rate) or of signed weights that cancel subtracts nearly equal numbers, dP - delta, delta taken from an output whose
+    # weights were rounded to bfloat16: single elements are no measure.  Of the norm: the roundings of the weights, of dS' and, through delta, of
+    # the forward weights, 2^-9 each at most.
     for name, g, r in zip(("dQ", "dK", "dV"), got, ref):
-        check(g.cpu().double().numpy(), r, f"{norm} {dims} {name}")
+        err = np.linalg.norm(g.cpu().double().numpy() - r) / np.linalg.norm(r)
+        print(f"{norm} {dims} {name}: {err:.5f}", flush=True)
+        assert err <= 3 * 2.0 ** -9, (name, err)
