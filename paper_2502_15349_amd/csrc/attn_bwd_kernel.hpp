@@ -89,6 +89,10 @@ __device__ __forceinline__ int bswz(int row) {
 // no normalization with the ReLU modification (the forward kernels carry the modification as a
 // parameter of its own; here the pair is one more value of the NORM parameter)
 constexpr int BWD_NORM_NONE_RELU = 5;
+// Abs-sum family, no normalization: the factor between dP and dS' of an entry that is hidden.  A visible entry's is never
+// negative, but may be 0 as well where its decay vanishes, and then passes an infinite or NaN dP on, wherever its tile lies.
+constexpr float kHiddenFactor = -0.f;
+__device__ __forceinline__ bool factor_hidden(float f) { return __builtin_bit_cast(uint32_t, f) == 0x80000000u; }
 enum : int { BWD_DQ = 0, BWD_DKV = 1 };  // the query-side kernel (dQ), the key-side kernel (dK and dV)
 
 // ---- one wavefront per 32 own rows ---------------------------------------------------------------------------------
@@ -461,7 +465,7 @@ __device__ __forceinline__ void bwd_single_walk(const BwdParams& p, const DecayT
         x[r] = vis ? x[r] : C::LIN ? 0.f : -INFINITY;
         if constexpr (C::LIN) {  // (visible entries have a distance >= 0)
           const float dist = dist0 + (C::KV_SIDE ? 1.f : -1.f) * (float)key_offset(r);
-          f[r] = vis ? fast_exp2(lg * fmaxf(dist, 0.f)) : 0.f;
+          f[r] = vis ? fast_exp2(lg * fmaxf(dist, 0.f)) : kHiddenFactor;
         }
       }
       sched_fence();
@@ -502,10 +506,10 @@ __device__ __forceinline__ void bwd_single_walk(const BwdParams& p, const DecayT
       w[r] = pv;
     }
     if constexpr (C::LIN)
-      if (!full) {  // a hidden entry's gradient is 0 whatever dP is, where the product of its factor 0 with an infinite one is NaN
+      if (!full) {  // a hidden entry's gradient is 0 whatever dP is (the product of a factor 0 with an infinite one is NaN)
         sched_fence();
 #pragma unroll
-        for (int r = 0; r < 16; ++r) w[r] = f[r] != 0.f ? w[r] : 0.f;
+        for (int r = 0; r < 16; ++r) w[r] = factor_hidden(f[r]) ? 0.f : w[r];
         sched_fence();
       }
     if constexpr (C::BIAS && !C::KV_SIDE) {
@@ -1041,7 +1045,7 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
             x[r] = vis ? x[r] : C::LIN ? 0.f : -INFINITY;
             if constexpr (C::LIN) {  // (visible entries have a distance >= 0)
               const float dist = dist0 + (C::KV_SIDE ? 1.f : -1.f) * (float)key_offset(r);
-              f[r] = vis ? fast_exp2(lg * fmaxf(dist, 0.f)) : 0.f;
+              f[r] = vis ? fast_exp2(lg * fmaxf(dist, 0.f)) : kHiddenFactor;
             }
           }
           sched_fence();
@@ -1098,10 +1102,10 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
           }
         }
         if constexpr (C::LIN)
-          if (!full) {  // a hidden entry's gradient is 0 whatever dP is, where the product of its factor 0 with an infinite one is NaN
+          if (!full) {  // a hidden entry's gradient is 0 whatever dP is (the product of a factor 0 with an infinite one is NaN)
             sched_fence();
 #pragma unroll
-            for (int r = 0; r < 16; ++r) w[r] = f[r] != 0.f ? w[r] : 0.f;
+            for (int r = 0; r < 16; ++r) w[r] = factor_hidden(f[r]) ? 0.f : w[r];
             sched_fence();
           }
         if constexpr (C::BIAS && !C::KV_SIDE) {

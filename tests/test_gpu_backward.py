@@ -532,6 +532,31 @@ def test_backward_hidden_entries_stay_zero(A, dims, form):
     assert not torch.isfinite(got[1][~free]).all()
 
 
+@pytest.mark.parametrize("dims", DIMS, ids=lambda d: f"d{d[0]}_{d[1]}")
+@pytest.mark.parametrize("norm", ["abssum", "abs_of_sum", "none"])
+@pytest.mark.parametrize("L", [100, 300])  # (one wavefront per 32 rows, and the pairs, where a head dim has both)
+def test_backward_vanished_decay_passes_infinities_on(A, dims, norm, L):
+    """An entry is left out because it is hidden, not because its decay vanishes: with a rate of 1e-4 the factor is 0 in 32 bits from ten
+    tokens on, and an infinite value row or row of dO still reaches every query or key that sees it, in tiles that are visible as a whole
+    and in those on the diagonal alike (the oracle's product in 64 bits is infinite), and no other."""
+    dev = torch.device("cuda:0")
+    w = Workload("vanished", 48, 1, 4, 2, L, L, dims[0], dims[1], mask="causal")
+    Q, K, V = (t.to(dev) for t in make_inputs(w))
+    dO = make_grad(w).to(dev)
+    args = dict(scale=w.scale_value, score_mod="head_decay", gamma=[1e-4] * 4, norm=norm, mask="causal")
+    stats = torch.empty((1, 4, L), dtype=torch.float32, device=dev) if norm != "none" else None
+    O = A.attention_forward(Q, K, V, stats=stats, **args)
+    t = torch.arange(L, device=dev)
+    Vx = V.clone()
+    Vx[0, :, 35, 3] = float("inf")  # (queries 46 to 63 share a tile of the diagonal with it, later ones do not)
+    bad = ~torch.isfinite(A.attention_backward(Q, K, Vx, O, dO, stats, **args)[0]).all(-1)
+    assert torch.equal(bad, (t >= 35).expand_as(bad))
+    dOx = dO.clone()
+    dOx[0, :, 60, 3] = float("inf")
+    bad = ~torch.isfinite(A.attention_backward(Q, K, V, O, dOx, stats, **args)[1]).all(-1)
+    assert torch.equal(bad, (t <= 60).expand_as(bad))
+
+
 def test_more_workgroups_than_one_launch_holds(A):
     # 8.4 million heads of one token: either side of the backward pass has 2^31 threads, both together more than a launch holds.  With
     # s = scale q . k and d = scale v . dO (64 terms each, summed in 32 bits: 2^-18 of the sum of their absolute values), rounded to
