@@ -643,6 +643,7 @@ struct BwdPairCfg {
   static constexpr int STAGES = 5 * (STAGE_BYTES + ROW_BYTES) + 2 * 4 * 4096 <= 160 * 1024 ? 5 : 4, LOOK = STAGES - 2;
   static constexpr int ROWS0 = STAGES * STAGE_BYTES, E0 = ROWS0 + STAGES * ROW_BYTES, E_PAIR = KV_SIDE ? 4096 : 2048, E_BYTES = 4 * E_PAIR;
   static constexpr int LDS_BYTES = E0 + 2 * E_BYTES;
+  static_assert(E_PAIR >= 2048, "a block of results takes 2 KB of either buffer");
   // copies: groups of four 1 KB blocks, group q by the wavefronts of role q % 2, or all by one role
   static constexpr int G1 = DQK / 64, G2 = DV / 64, GB = BIAS_ ? 2 : 0, GROUPS = G1 + G2 + GB;
   static constexpr int COPIER = KV_SIDE ? (DV == 256 && !LIN ? 0 : 2) : 1;  // 0, 1: that role; 2: both in turn
@@ -1234,22 +1235,33 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
       }
 
       // ---- results: register r of block db is column own, row d = 32 db + 8 (r/4) + 4 half + r%4 ----
-      if (own < L_own) {
-        auto store = [&](float* o, const f32x16& a, float f) {
+      // A block of 32 x 32 is turned around in the pair's hand-over buffers, which nobody reads any more (16-byte chunk k of row r at
+      // k ^ (r % 8), the upper 16 rows in the second buffer): eight lanes then store 128 bytes of a row.  These stores are the end of a
+      // workgroup, with nothing beside them.  Pieces of 16 bytes from 32 rows each instead, us: 8 x 64 heads causal, 192/128, x 200 142 -> 132,
+      // x 256 190 -> 160, x 512 412 -> 355, window 256 409 -> 353, unmasked x 128 84 -> 68; 128/128 x 256 140 -> 125;
+      // 1 x 128 x 4096 192/128 2439 -> 2398.
+      const int row = lane >> 3, rows = L_own - ow0 - row;
+      const uint32_t buf = lds0 + C::E0 + w4 * C::E_PAIR;
+      const uint32_t put = buf + (ln >> 4) * C::E_BYTES + (ln & 15) * 128 + ((half ^ (ln & 7)) << 4);
+      const uint32_t get = buf + row * 128 + (((lane & 7) ^ row) << 4);
+      const int64_t row0 = (C::KV_SIDE ? ((int64_t)b * p.H_kv + hk) * p.L_k : ((int64_t)b * p.H_q + ho) * p.L_q) + ow0 + row;
+      float* const o1 = (C::KV_SIDE ? p.dK : p.dQ) + row0 * C::DQK + 4 * (lane & 7);
+      float* const o2 = p.dV + row0 * C::DV + 4 * (lane & 7);  // (key side)
+      static_for<0, NB>([&](auto dbc) {
+        constexpr int db = decltype(dbc)::value;
+        const float f = db < DB ? p.scale : 1.f;
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<f32x4*>(o + 8 * q + 4 * half) = f32x4{a[4 * q] * f, a[4 * q + 1] * f, a[4 * q + 2] * f, a[4 * q + 3] * f};
-        };
-        float* o = (C::KV_SIDE ? p.dK + ((int64_t)b * p.H_kv + hk) * p.L_k * C::DQK : p.dQ + ((int64_t)b * p.H_q + ho) * p.L_q * C::DQK) +
-                   (int64_t)own * C::DQK;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) store(o + 32 * db, acc[db], p.scale);
-        if constexpr (C::KV_SIDE) {
-          float* o2 = p.dV + (((int64_t)b * p.H_kv + hk) * p.L_k + own) * C::DV;
-#pragma unroll
-          for (int db = 0; db < DB2; ++db) store(o2 + 32 * db, acc[DB + db], 1.f);
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 v = {acc[db][4 * q] * f, acc[db][4 * q + 1] * f, acc[db][4 * q + 2] * f, acc[db][4 * q + 3] * f};
+          lds_store16(put ^ (32 * q), __builtin_bit_cast(u32x4, v));
         }
-      }
+        f32x4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = lds_read16(get + (k & 1) * 1024 + (k >> 1) * C::E_BYTES);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (8 * k < rows) *reinterpret_cast<f32x4*>(db < DB ? o1 + 8 * k * C::DQK + 32 * db : o2 + 8 * k * C::DV + 32 * (db - DB)) = v[k];
+      });
     }
   };
   if (wave < 4) walk(std::integral_constant<int, 0>{});
