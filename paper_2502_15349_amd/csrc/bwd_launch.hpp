@@ -10,21 +10,27 @@ namespace {
 
 // One wavefront per 32 own rows where two workgroups of it fit a CU (64/64, and the query side of 128/128 without a bias
 // tensor), a pair of wavefronts elsewhere (the measurements stand at bwd_pair_walk).  64/64 with a bias tensor has
-// both: the pair pays on long walks while an XCD holds no more than one workgroup per CU.  Whole backward pass, one wavefront /
-// pair, us: 1 x 6 heads x 1023 x 1060 (8 and 9 workgroups per XCD) 73 / 68, 2 x 12 x 1023 x 1060 (24 and 27) 83 / 80;
-// 1 x 6 x 4096 x 4133 (32 and 33) 342 / 398, 8 x 16 x 512 x 549 (64 and 80) 96 / 113, 8 x 16 x 2048 causal (256) 744 / 919,
-// without the bias's gradient 364 / 514; 4 x 24 x 100 causal 20.0 / 22.4, 2 x 12 x 512 causal 39.3 / 40.5, unmasked 38.9 / 38.1.
-// Causal workgroups are half as long on the average: up to 48 of them (2 x 12 x 2048, 48 and 48, 116 / 109; 4096, 96, 262 / 368).
-constexpr int64_t units_per_xcd(bool causal) { return causal ? 48 : 32; }
+// both: the pair pays on long walks while an XCD holds no more than one workgroup per CU.  Whole backward pass with the bias's gradient, one
+// wavefront / pair, us (workgroups per XCD): unmasked 1 x 6 heads x 1023 (16) 40.4 / 34.8, x 2048 (32) 69 / 59, x 3000 (48) 120 / 144, 1 x 16 x 1300 (44) 60 /
+// 71, 2 x 12 x 1023 (48) 52 / 62, 8 x 16 x 600 (160) 95 / 115.  Causal workgroups are half as long on the average: 2 x 12 x 768 (36) 41.1 / 38.2, 1 x 6 x 3000 (48)
+// 110 / 102, 1 x 16 x 1600 (52) 75.5 / 65.4, x 2048 (64) 108 / 96, 1 x 6 x 4096 (64) 169 / 150, 2 x 12 x 1300 (66) 72.9 / 70.5, x 1600 (78) 86.8 / 95.5, 1 x 16 x 3000
+// (96) 229 / 234, 8 x 16 x 768 (192) 114 / 133.
+constexpr int64_t units_per_xcd(bool causal) { return causal ? 64 : 32; }
 constexpr int64_t kLongBiasWalk = 384;
-// Where only one workgroup fits a CU, short walks stay with one wavefront too: the pair is a tile behind itself, has three tiles
-// to wait for at its start, and of a narrow window most waves skip most tiles.  Keys (queries) that a row may see, times the
-// q heads that a key-side workgroup walks one after the other.  4 x 24 heads x 4096, one wavefront / pair, us: 128/128 window
-// 64 418 / 447, 128 448 / 469, 200 518 / 511, 256 502 / 509; 192/128 64 491 / 536, 128 540 / 565, 200 642 / 613, 256 622 / 618;
-// 128/256 64 600 / 609, 96 662 / 631.  Causal without a window, 8 x 64 heads: 128/128 64 rows 36.4 / 38.6, 100 53.9 / 55.5, 128 60.5 /
-// 64.0; 192/128 45.6 / 47.8, 67.9 / 74.7, 75.5 / 87.6; 128/256 64 rows 51.1 / 53.0 (100 rows 4 x 24 heads 26.9 / 25.3).
-constexpr int64_t short_window(int dqk, int dv) { return dv == 256 ? 64 : dqk == 192 ? 160 : 256; }
-constexpr int64_t short_walk(int dv) { return dv == 256 ? 64 : 128; }
+// Where only one workgroup fits a CU, short causal walks stay with one wavefront too: the pair is a tile behind itself and has three
+// tiles to wait for at its start.  Keys (queries) that a row may see, times the q heads that a key-side workgroup walks one after the
+// other; the pair's lead over one wavefront is smaller in the abs-sum family and without normalization, and at 128/128 with a bias
+// tensor.  8 x 64 heads, one wavefront / pair, us: 192/128 48 rows 40.2 / 41.9, 64 45.7 / 46.4, 80 58.9 / 55.9, 128 75.8 / 73.2, abs-sum 64
+// 50.1 / 51.9, 128 80.7 / 83.8, bias tensor 48 46.0 / 47.7, 64 51.3 / 52.0, 100 76.5 / 72.1; 128/256 64 51.4 / 51.3, 80 69.0 / 63.0, abs-sum 64 55.5 / 57.0,
+// 128 100.2 / 103.8; 128/128 64 36.3 / 37.7, 80 46.3 / 44.7, 128 60.4 / 59.4, abs-sum 64 40.1 / 41.3, 128 64.4 / 65.0, bias tensor 100 65.3 / 67.8,
+// 128 70.0 / 73.6.
+template <int DQK, int NORM, bool BIAS>
+constexpr int64_t short_walk() { return NORM == NORM_ABSSUM || NORM == NORM_ABS_OF_SUM || NORM == NORM_NONE || (BIAS && DQK == 128) ? 128 : 64; }
+// Narrow windows, of which most waves of a pair skip most tiles, count as short at 128/128 only.  4 x 24 heads x 4096, one wavefront / pair:
+// 192/128 window 32 498 / 454, 64 488 / 479, 128 541 / 514, 256 624 / 569; 128/256 64 601 / 563, 128 665 / 604; 128/128 64 419 / 427, 128 447 / 450,
+// 200 518 / 492, 256 503 / 493.
+template <int DQK, int DV>
+constexpr int64_t short_window() { return DQK == 128 && DV == 128 ? 128 : 0; }
 // Both sides go in one launch (the key side's workgroups first): two launches / one, us, causal unless said: 64/64 1 x 16 heads x
 // 1024 54 / 34, 1 x 16 x 4096 186 / 140, 4 x 32/8 x 2048 335 / 289, 8 x 16 x 2048 unmasked 506 / 510, with a bias tensor 2 x 12 x 1023 x 1201
 // 85 / 68; 192/128 1 x 16 x 500 53 / 33, 1 x 6 x 4096 259 / 172, 1 x 128 x 4096 2597 / 2607; 128/256 2 x 16 x 1024 100 / 74, 4 x 16 x
@@ -113,7 +119,7 @@ hipError_t launch_kernels(const BwdParams& p, const DecayTable& dt, hipStream_t 
   } else {
     auto is_short = [&](int64_t rows, int64_t heads) {
       const int64_t window = p.window < rows ? p.window : 0;
-      return window ? window * heads <= short_window(DQK, DV) : rows * heads <= short_walk(DV);
+      return window ? window * heads <= short_window<DQK, DV>() : rows * heads <= short_walk<DQK, NORM, BIAS>();
     };
     if constexpr (DQK == 128 && DV == 128 && !BIAS) {
       const bool short_key = CAUSAL && is_short(p.L_q, p.g);
@@ -122,7 +128,7 @@ hipError_t launch_kernels(const BwdParams& p, const DecayTable& dt, hipStream_t 
         if (short_key) return launch_sides<K1, Q1>(p, dt, s, both);
       return launch_sides<K2, Q1>(p, dt, s, both);
     } else {
-      if constexpr (CAUSAL && (!BIAS || DQK == 128))
+      if constexpr (CAUSAL)
         if (is_short(p.L_q, p.g) && is_short(p.L_k, 1)) return launch_both<K1, Q1>(p, dt, s);
       if constexpr (DQK == 192 && CAUSAL) return launch_sides<K2, Q2>(p, dt, s, walked_keys<true>(p) < 700000 || key_wgs < 64);
       else return launch_both<K2, Q2>(p, dt, s);

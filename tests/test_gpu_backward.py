@@ -143,10 +143,10 @@ def test_backward_pairs_of_wavefronts(A, dims, Lq, Lk):
 @pytest.mark.parametrize("dims", [(128, 128), (128, 256), (192, 128)], ids=lambda d: f"d{d[0]}_{d[1]}")
 @pytest.mark.parametrize("Lq,Lk,window,g", [(64, 65, 500, 1), (65, 64, 500, 1), (128, 128, 500, 1), (129, 128, 500, 1), (128, 129, 500, 1), (400, 333, 7, 1), (333, 400, 33, 2),
                                             (400, 420, 96, 1), (420, 400, 97, 1), (520, 540, 256, 1), (540, 520, 257, 1), (300, 333, 128, 2),
-                                            (333, 300, 129, 2), (300, 310, 299, 1)])
+                                            (333, 300, 129, 2), (300, 310, 299, 1), (400, 420, 128, 1), (420, 400, 129, 1), (64, 64, 500, 2), (32, 33, 500, 2)])
 def test_backward_short_walks(A, dims, Lq, Lk, window, g):
-    """Head dims whose registers leave room for one workgroup per CU: windows of up to 256 rows (128/256: 96), times the q
-    heads of a group on the key side, and causal walks of up to 128 (64) rows run on single wavefronts, longer ones on pairs.  Both
+    """Head dims whose registers leave room for one workgroup per CU: causal walks of up to 64 rows (128 without normalization), times
+    the q heads of a group on the key side, and at 128/128 windows of up to 128 run on single wavefronts, longer ones on pairs.  Both
     sides of each limit, windows that hide whole tiles from some waves and not from others, L_q and L_k either way."""
     for kw in (dict(), dict(norm="sigmoid", score_mod="bias", bias=-3.0), dict(norm="none", scale=0.01)):
         run_case(A, Workload(f"short{window}", 48, 1, g, 1, Lq, Lk, dims[0], dims[1], mask="sliding_window", window=window, **kw))
