@@ -1113,11 +1113,13 @@ ae_status_t ae_recurrent_destroy(ae_recurrent_t* h) {
 // Value heads of a group that a workgroup of the backward pass takes in turn, its gradients of q and k summed on chip; 0: one
 // head per workgroup and the sums in a kernel of their own (where that walk is not built or cut into segments).  Few heads fill
 // the device, many leave fewer parts to sum; the time is estimated in units of a walk over one head (16 us at 768 tokens):
-// heads + 1.2 for a workgroup of the first two walks, 1.6 to 2.4 for one of the third (which takes one head or two), handed to 256
-// compute units in this order, and the sum kernel's bytes (none where one workgroup takes the whole group).  Measured (us for 1 / 2 / 3 / 4
+// heads + 1.2 for a workgroup of the first two walks at 128/64, + 0.4 at 64/64, 1.6 to 2.4 for one of the third (which takes one head or
+// two), handed to 256 compute units in this order, and the sum kernel's bytes (none where one workgroup takes the whole group).  Of 90 calls
+// the heads so chosen were at most 4 % behind the best, 0.5 % on the mean; with + 1.2 at 64/64 up to 39 % (7 x 24 x 768).  Measured (us for 1 / 2 / 3 / 4
 // heads, 768 tokens, the better of the third walk's two forms): Mamba2 128/64 1 x 80 heads 51 / 60 / 73 / 87, 2 x 80 89 / 65 / 76 / 89, 3 x 80 133 / 100 /
 // 84 / 93, 4 x 80 198 / 121 / 113 / 98, 5 x 80 236 / 151 / 149 / 131, 8 x 64 296 / 199 / 166 / 142, 8 x 80 375 / 259 / 217 / 196, 8 x 24 x 600 83 / 74 /
-// 67 / 78; 64/64 4 x 80 129 / 100 / 94 / 85, 8 x 64 202 / 139 / 134 / 118, 8 x 80 270 / 189 / 165 / 163.
+// 67 / 78, 3 x 32/8 59 / 60 / 74 / 82, 4 x 24 56 / 58 / 69 / 87; 64/64 2 x 80 x 700 66 / 50 / 60 / 75, 4 x 80 125 / 96 / 91 / 85, 5 x 80 x 700 132 / 109 / 112 / 106,
+// 8 x 64 199 / 136 / 132 / 118, 8 x 80 265 / 181 / 160 / 161, 6 x 24 69 / 53 / 63 / 80, 7 x 24 71 / 55 / 64 / 81, 8 x 24 76 / 72 / 64 / 81, 6 x 32/8 78 / 74 / 74 / 76.
 static double gated_walks_time(int64_t first_two, double cost, int64_t third, double cost3) {
   // all compute units are busy until `lo`, `n_hi` of them until `hi`; the third walk's workgroups go where one is free first
   double lo = (double)(first_two / 256) * cost, hi = lo + cost;
@@ -1141,9 +1143,9 @@ static int gated_group_heads(const ae_gated_desc_t* d, int bwd_nseg, int* third)
   for (int n = 1; n <= std::min<int64_t>(size, ae::kGatedGroupHeads); ++n)
     for (int m = 1; m <= (size % 2 == 0 ? 2 : 1); ++m) {
       const int64_t parts = (size + n - 1) / n;
-      const double cost3 = d->D_qk == 128 ? (m == 2 ? 2.4 : 2.1) : (m == 2 ? 2.0 : 1.6);
-      const double sum = parts == 1 ? 0.0 : 0.8e-4 * groups * parts * d->D_qk;
-      const double t = gated_walks_time(2 * groups * parts, n + 1.2, groups * size / m, cost3) + sum;
+      const double cost = n + (d->D_qk == 128 ? 1.2 : 0.4), cost3 = d->D_qk == 128 ? (m == 2 ? 2.4 : 2.1) : (m == 2 ? 1.9 : 1.6);
+      const double sum = parts == 1 ? 0.0 : (d->D_qk == 128 ? 0.8e-4 : 1.2e-4) * groups * parts * d->D_qk;
+      const double t = gated_walks_time(2 * groups * parts, cost, groups * size / m, cost3) + sum;
       if (least == 0 || t < least) {
         least = t;
         heads = n;
