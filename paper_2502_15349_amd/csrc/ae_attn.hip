@@ -782,6 +782,7 @@ static void cut_segments(int64_t n, int L, int* nseg, int* seg_len) {  // nseg =
 // (us, cut / uncut): 40 workgroups x 512 tokens 30.4 / 33.2; 64 x 512 34.9 / 33.6, 64 x 600 40.8 / 40.5 (64/64 22.9 / 24.9); 85 x 700
 // 48.0 / 44.2, 85 x 900 53.6 / 58.1; 86 x 1152 68.3 / 69.0, 110 x 1152 71.6 / 69.5, 128 x 1280 79.7 / 76.7, 128 x 1408 85.4 / 84.1
 // (128/128; 64/64 and Mamba2 alike, 128 workgroups of Mamba2 x 1280 78.3 / 79.4).
+// (Measured without the lead of segments_behind_lead, which makes the cut side faster where there are two to five segments.)
 static void gated_segments(int64_t workgroups, int L, int* nseg, int* seg_len) {
   const int64_t n = most_segments(workgroups, L), room = 256 / workgroups;
   const int from = room >= 6 ? 512 : room >= 4 ? 576 : room == 3 ? 832 : workgroups <= 100 ? 1152 : 1280;
@@ -836,13 +837,13 @@ static hipError_t launch_gated_segmented(const ae::GatedParams& p, const ae::Dec
     out.seg_to = states.seg_to = p.L;
     lead.h_out = buf;
     lead.out_slots = states.out_slots = out.in_slots = nseg;
-    out.nseg = (p.L - lead.seg_len + seg_len - 1) / seg_len;  // (one less than nseg where the lead fills what the last one lacked)
-    states.nseg = out.nseg - 1;
+    out.nseg = nseg;
+    states.nseg = nseg - 1;
     states.h_out = buf + dqk * dv;
     states.seg_decay = dec + 1;
     out.seg_len = states.seg_len = seg_len;
-    e = states.nseg > 0 ? ae::launch_gated_lead(lead, states, dt, dqk, dv, stream) : ae::launch_gated_recurrent(lead, dt, dqk, dv, stream);
-    if (e == hipSuccess) e = ae::launch_gated_chain_segments(buf, dec, p.B * p.H, nseg, out.nseg, dqk * dv, stream);
+    e = ae::launch_gated_lead(lead, states, dt, dqk, dv, stream);
+    if (e == hipSuccess) e = ae::launch_gated_chain_segments(buf, dec, p.B * p.H, nseg, dqk * dv, stream);
   } else {
     states.nseg = out.nseg = nseg;
     states.seg_len = out.seg_len = seg_len;

@@ -678,9 +678,6 @@ __device__ __forceinline__ void lds_store4(uint32_t addr, float v) {
 __device__ __forceinline__ void lds_store16(uint32_t addr, u32x4 v) {
   *reinterpret_cast<__attribute__((address_space(3))) u32x4*>((lds_char*)(uintptr_t)addr) = v;
 }
-__device__ __forceinline__ u32x4 lds_read16u(uint32_t addr) {
-  return *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>((lds_char*)(uintptr_t)addr);
-}
 
 template <class C>
 __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTable& dt, int block, uint32_t lds0) {
@@ -841,7 +838,8 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
     // hold up every wavefront at the compute unit's memory pipe (64 bytes per clock).
     auto copies = [&](auto copyc, auto nc, auto mc) {
       if constexpr (NC == 0) return;
-      constexpr int n = decltype(nc)::value, GAP = decltype(mc)::value / (NC + 1) > 0 ? decltype(mc)::value / (NC + 1) : 1;
+      constexpr int n = decltype(nc)::value, M = decltype(mc)::value, GAP = M / (NC + 1) > 0 ? M / (NC + 1) : 1;
+      static_assert((NC - 1) * GAP < M, "a product for every copy");
       if constexpr (n % GAP == 0 && n / GAP < NC) issue(copyc, std::integral_constant<int, n / GAP>{});
     };
 
@@ -998,7 +996,7 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
           sched_fence();
           copies(copyc, nc, std::integral_constant<int, M>{});
         };
-                constexpr int AHEAD = 2;  // products of dP in front of the first use of S: they cover its latency
+        constexpr int AHEAD = 2;  // products of dP in front of the first use of S: they cover its latency
         static_for<0, T1 + AHEAD>(product);
         if constexpr (C::LIN) read_rows(nl4, nl_own, 0);  // (here: 16 registers less during the products)
         float x[16];

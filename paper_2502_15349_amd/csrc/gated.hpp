@@ -48,10 +48,9 @@ struct GatedParams {
 // A walk's first segment in full (lead: whole rows of outputs, its final state) and the states of later ones (states: state_only),
 // side by side in one launch.  The same constant decays for both.
 hipError_t launch_gated_lead(const GatedParams& lead, const GatedParams& states, const DecayTable& dt, int dqk, int dv, hipStream_t s);
-// In place on buf [B, H, nseg, D_qk x D_v], the first `n` slots of every (batch, head): slot 0 holds the state in front of the first of
-// them, slot i > 0 what segment i - 1 adds to it (its final state from a zero start), seg_decay[i] that segment's decay; slot i becomes
-// the state in front of segment i.
-hipError_t launch_gated_chain_segments(float* buf, const float* seg_decay, int BH, int nseg, int n, int state_elems, hipStream_t s);
+// In place on buf [B, H, nseg, D_qk x D_v]: slot 0 holds the state in front of the first segment, slot i > 0 what segment i - 1 adds to
+// it (its final state from a zero start), seg_decay[i] that segment's decay; slot i becomes the state in front of segment i.
+hipError_t launch_gated_chain_segments(float* buf, const float* seg_decay, int BH, int nseg, int state_elems, hipStream_t s);
 // In place on buf [B, H, nseg, D_qk x D_v] (the segments' final states from a zero start, as a state_only walk
 // leaves them): slot s becomes the state in front of segment s, given the state in front of the sequence (h_in,
 // [B, H, D_qk x D_v], or null for zero) and the segments' decays.

@@ -1041,7 +1041,7 @@ __global__ __launch_bounds__(kChainThreads) void gated_combine_segments_kernel(f
   }
 }
 // The same behind a lead, see launch_gated_chain_segments.
-__global__ __launch_bounds__(kChainThreads) void gated_chain_segments_kernel(float* buf, const float* seg_decay, int nseg, int n, int state_elems) {
+__global__ __launch_bounds__(kChainThreads) void gated_chain_segments_kernel(float* buf, const float* seg_decay, int nseg, int state_elems) {
   const int64_t bh = blockIdx.y;
   const int e = (blockIdx.x * kChainThreads + threadIdx.x) * 4;
   if (e >= state_elems) return;
@@ -1049,18 +1049,18 @@ __global__ __launch_bounds__(kChainThreads) void gated_chain_segments_kernel(flo
   const float* dec = seg_decay + bh * nseg;
   StatePiece<4> x;
   x.load(slot);
-  for (int s0 = 1; s0 < n; s0 += kAhead) {
+  for (int s0 = 1; s0 < nseg; s0 += kAhead) {
     StatePiece<4> local[kAhead];
     float d[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
-      if (s0 + u >= n) break;
+      if (s0 + u >= nseg) break;
       local[u].load(slot + (int64_t)(s0 + u) * state_elems);
       d[u] = dec[s0 + u];
     }
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
-      if (s0 + u >= n) break;
+      if (s0 + u >= nseg) break;
       x.chain(__expf(d[u]), local[u]);
       x.store(slot + (int64_t)(s0 + u) * state_elems);
     }
@@ -1157,11 +1157,10 @@ hipError_t launch_gated_combine_segments(float* buf, const float* seg_decay, con
   return hipGetLastError();
 }
 
-hipError_t launch_gated_chain_segments(float* buf, const float* seg_decay, int BH, int nseg, int n, int state_elems, hipStream_t s) {
-  if (BH < 1 || BH > 65535 || n < 1 || n > nseg || state_elems < 4 || state_elems % 4 != 0) return hipErrorInvalidValue;
-  if (n == 1) return hipSuccess;
-  hipLaunchKernelGGL(gated_chain_segments_kernel, dim3((unsigned)((state_elems + 4 * kChainThreads - 1) / (4 * kChainThreads)), (unsigned)BH), dim3(kChainThreads), 0, s, buf, seg_decay, nseg, n,
-                     state_elems);
+hipError_t launch_gated_chain_segments(float* buf, const float* seg_decay, int BH, int nseg, int state_elems, hipStream_t s) {
+  if (BH < 1 || BH > 65535 || nseg < 2 || state_elems < 4 || state_elems % 4 != 0) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((state_elems + 4 * kChainThreads - 1) / (4 * kChainThreads)), (unsigned)BH);
+  hipLaunchKernelGGL(gated_chain_segments_kernel, grid, dim3(kChainThreads), 0, s, buf, seg_decay, nseg, state_elems);
   return hipGetLastError();
 }
 
