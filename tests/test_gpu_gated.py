@@ -161,13 +161,28 @@ def test_segmented_walk(A, dqk, dv, H, H_qk, kind, L):
     assert (np.abs(hN.cpu().double().numpy() - ref_h) / hs).max() <= MAX_ABS
 
 
-@pytest.mark.parametrize("B,H,H_qk,L,dqk,dv,kind", [(2, 64, 64, 1300, 64, 64, "gated_retention"), (2, 64, 64, 1281, 128, 128, "mamba2"), (1, 85, 85, 1537, 64, 128, "mamba2"),
-                                                    (2, 32, 32, 1472, 128, 128, "gated_retention"), (1, 50, 50, 1999, 64, 64, "mamba2"),
-                                                    (2, 64, 1, 1500, 128, 64, "mamba2"), (2, 128, 2, 1700, 64, 64, "mamba2")])
-def test_walk_with_a_lead(A, B, H, H_qk, L, dqk, dv, kind):
-    # two to five segments behind a first one that is walked in full beside their state walks, whole and short last ones (1472 and 1281: none and one
-    # token), one and two heads per workgroup; the state in front of the sequence, the final one
+LEADS = [  # B, H, H_qk, L, D_qk, D_v, gates, lead, segment: two to five segments
+    (2, 64, 64, 1344, 64, 64, "gated_retention", 192, 576),   # two; a whole last one
+    (2, 64, 64, 1281, 128, 128, "mamba2", 192, 576),          # two; the last one ends a token into a chunk, and so do the next two
+    (1, 85, 85, 1537, 64, 128, "mamba2", 64, 512),            # three
+    (1, 81, 27, 1537, 128, 64, "mamba2", 64, 512),            # three, groups of three heads: one head per workgroup
+    (1, 60, 60, 1320, 64, 128, "gated_retention", 64, 320),   # four
+    (1, 50, 50, 1999, 64, 64, "mamba2", 128, 384),            # five
+    (2, 80, 1, 1280, 64, 64, "mamba2", 128, 384),             # two heads per workgroup: three
+    (2, 80, 1, 3000, 128, 64, "mamba2", 320, 896),
+    (2, 64, 1, 3000, 128, 64, "mamba2", 192, 704),            # four
+    (1, 96, 1, 1344, 64, 64, "mamba2", 64, 256),              # five
+    (2, 32, 32, 1472, 128, 128, "gated_retention", 0, 384),   # no lead: four segments as they are
+    (2, 64, 1, 1500, 128, 64, "mamba2", 0, 384),
+]
+
+
+@pytest.mark.parametrize("B,H,H_qk,L,dqk,dv,kind,lead,seg", LEADS)
+def test_walk_with_a_lead(A, B, H, H_qk, L, dqk, dv, kind, lead, seg):
+    # segments behind a first one that is walked in full beside their state walks; the state in front of the sequence, the final
+    # one.  Slow gates: what a segment hands on is most of the next one's state
     Q, K, V, la, kg = inputs(870, B, H, H_qk, L, dqk, dv, kind)
+    la = la * 0.02
     h0 = torch.randn(B, H, dqk, dv, generator=torch.Generator().manual_seed(87))
     scale = 1.0 / math.sqrt(dqk)
     got, state = run(A, Q, K, V, la, kg, scale, h_in=h0, want_state=True, segmented=True)
@@ -178,6 +193,11 @@ def test_walk_with_a_lead(A, B, H, H_qk, L, dqk, dv, kind):
         check(got[b:b + 1, h:h + 1].cpu().double().numpy(), ref, f"lead {kind} {dqk}/{dv} L={L} ({b},{h})")
         hs = np.maximum(np.abs(ref_h).max(axis=-1, keepdims=True), 1.0)
         assert (np.abs(state[b:b + 1, h:h + 1].cpu().double().numpy() - ref_h) / hs).max() <= MAX_ABS
+    # Which form ran: the first segment starts from the given state and the one behind a lead from the lead's own, so both have the bits
+    # of a walk that is not cut; the next one starts from a chained state, of other roundings
+    whole = run(A, Q, K, V, la, kg, scale, h_in=h0)
+    first = (got != whole).any(dim=-1).any(dim=1).any(dim=0).nonzero()[0].item()
+    assert lead + seg <= first < lead + seg + 64, (first, lead, seg)
 
 
 def test_segmented_entry_point_on_a_shape_that_is_not_cut(A):
