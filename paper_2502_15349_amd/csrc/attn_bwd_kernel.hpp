@@ -29,7 +29,7 @@
 // What bounds it is how well a SIMD's vector and matrix work overlap, and that takes two wavefronts per SIMD of at most
 // 256 registers.  Where accumulators, resident operands and score tiles of 32 own rows fit that (64/64; 128/128, query
 // side), a wavefront does all of the above and two workgroups share a CU: bwd_single_walk.  Where they do not, the 32
-// rows go to a pair of wavefronts: bwd_pair_walk (its key side at 128/256 spills up to 6 registers), but for
+// rows go to a pair of wavefronts: bwd_pair_walk (its key side at 128/256 spills up to 4 registers), but for
 // short walks, which the first form takes with one workgroup per CU and up to 472 registers.  The lines between the two
 // stand in bwd_launch.hpp.
 #pragma once
@@ -1245,7 +1245,7 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
       const int64_t row0 = (C::KV_SIDE ? ((int64_t)b * p.H_kv + hk) * p.L_k : ((int64_t)b * p.H_q + ho) * p.L_q) + ow0 + row;
       float* const o1 = (C::KV_SIDE ? p.dK : p.dQ) + row0 * C::DQK + 4 * (lane & 7);
       float* const o2 = p.dV + row0 * C::DV + 4 * (lane & 7);  // (key side)
-      static_for<0, NB>([&](auto dbc) {
+      auto put_block = [&](auto dbc) {
         constexpr int db = decltype(dbc)::value;
         const float f = db < DB ? p.scale : 1.f;
 #pragma unroll
@@ -1253,12 +1253,28 @@ __device__ __forceinline__ void bwd_pair_walk(const BwdParams& p, const DecayTab
           const f32x4 v = {acc[db][4 * q] * f, acc[db][4 * q + 1] * f, acc[db][4 * q + 2] * f, acc[db][4 * q + 3] * f};
           lds_store16(put ^ (32 * q), __builtin_bit_cast(u32x4, v));
         }
-        f32x4 v[4];
+      };
+      f32x4 v[2][4];
+      auto get_block = [&](f32x4 (&v)[4]) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = lds_read16(get + (k & 1) * 1024 + (k >> 1) * C::E_BYTES);
+        sched_fence();
+      };
+      put_block(first);
+      get_block(v[0]);
+      static_for<0, NB>([&](auto dbc) {  // (LDS works in order: block db + 1 goes in behind the reads of block db, while these are on their way)
+        constexpr int db = decltype(dbc)::value;
+        if constexpr (db + 1 < NB) {
+          put_block(std::integral_constant<int, db + 1>{});
+          sched_fence();
+          get_block(v[(db + 1) % 2]);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pin(v[db % 2][k]);  // (the compiler would read each piece where it is stored, one behind the other)
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          if (8 * k < rows) *reinterpret_cast<f32x4*>(db < DB ? o1 + 8 * k * C::DQK + 32 * db : o2 + 8 * k * C::DV + 32 * (db - DB)) = v[k];
+          if (8 * k < rows)
+            *reinterpret_cast<f32x4*>(db < DB ? o1 + 8 * k * C::DQK + 32 * db : o2 + 8 * k * C::DV + 32 * (db - DB)) = v[db % 2][k];
       });
     }
   };
