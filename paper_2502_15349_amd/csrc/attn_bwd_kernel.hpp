@@ -618,8 +618,8 @@ __device__ __forceinline__ void bwd_single_walk(const BwdParams& p, const DecayT
 // 4096 128/256 1265 + 850 -> 1200 + 795, abs-sum with decay 192/128 1215 + 990 -> 1120 + 857; key side of 128/128
 // 4 x 32/8 x 2048 300 -> 285.  There role 1 waited for eight LDS reads behind every barrier and then ran its vector work, both
 // in front of its products: 2430 clocks per tile of 1280 clocks of products, now 2020.  What bounds it now is power: the
-// same kernels on inputs of zeros take 4030 + 3015 us (the first split 4500 + 3575), the clock falls from 2.05 to 1.89 GHz as the
-// matrix units' share of the cycles goes from 0.48 to 0.54.  Left out for timing, of the 192/128 time: the copies 6-9 %,
+// same kernels on inputs of zeros take 4030 + 3015 us (the first split 4500 + 3575), the clock falls from 2.06 to 1.91 GHz as the
+// matrix units' share of the cycles goes from 0.48 and 0.49 to 0.54 and 0.59.  Left out for timing, of the 192/128 time: the copies 6-9 %,
 // the row fragments 3 %, the transposed ones 5 %, the row quantities 1-2 %, the hand-over 3 %, the exponentials 5 %, all of them 22 %.
 // Deeper rings, more products in front of the weights, raised wave priority: no difference.  The query side's copies all
 // go with role 1, which has less to do there (role 0 or both: 2 % more).  Against two workgroups per CU where those
